@@ -158,7 +158,8 @@ def work(case):
 def tolerance(case):
     # about four times the largest error of each kind of case against the same computed in 64 bits: weights and softmax
     # rows are rounded once at the store (bf16: 1.7e-3 and 3.9e-3), the attention output also rounds its weights (bf16:
-    # 2.3e-3 and 1.1e-2; fp32: 1.2e-6 and 1e-5), the unfused pipeline its scores, twice (bf16: 5.4e-3 and 2.2e-2)
+    # 2.3e-3 and 1.1e-2), the unfused pipeline its scores, twice (bf16: 5.4e-3 and 2.2e-2); fp32 with sharp rows and wide
+    # heads 2.1e-6 and 5.3e-5
     if case.get("out_dtype", case["dtype"]) == "bf16":
         return {"weights": {"rel": 7e-3, "max": 1.6e-2}, "softmax": {"rel": 7e-3, "max": 1.6e-2},
                 "attention": {"rel": 1e-2, "max": 4e-2}, "unfused": {"rel": 2e-2, "max": 9e-2}}[case["call"]]
