@@ -1,5 +1,5 @@
-// Attention output  O = softmax(scale * Q K^T) V  for the element types and head sizes that the tiled
-// bf16 kernel does not take: fp32 (d a multiple of 4 up to 256) and bf16 with 128 < d <= 256.
+// Attention output  O = softmax(scale * Q K^T) V  for the head sizes that the tiled bf16 kernel does not take:
+// bf16 with 128 < d <= 256.
 //
 // (Paper: Multi-Head Self-Attention section, Attention(Q, K, V) = softmax(Q K^T / sqrt(d_k)) V; the product
 // with V is what the section "Limitations and future Directions" names as the next thing to fuse.  The
@@ -9,16 +9,10 @@
 // memory, no barriers, nothing crosses waves.  Operands come straight from global memory (K and V of a
 // head are read by all the waves of the head: they live in the caches), which makes every row clamp and
 // every padding a matter of the load's address or of a zero in its place.
-//   S^T = K_sub * Q^T      on the matrix instruction of the element type (fp32: v_mfma_f32_32x32x2_f32, so
-//                          the scores have fp32 products and sums; bf16: v_mfma_f32_32x32x16_bf16);
-//                          lane (query l32, half h) holds keys 8i + 4h + j of its query.
+//   S^T = K_sub * Q^T      lane (query l32, half h) holds keys 8i + 4h + j of its query.
 //   p = 2^(c s - ref), running sum, reference exponent that follows the running maximum lazily.
-//   O^T += V_sub^T * P^T   fp32: one v_mfma_f32_32x32x2_f32 per accumulator r -- it contracts the key pair
-//                          (8(r/4) + r%4, 8(r/4) + 4 + r%4), whose weights ARE accumulator r of the two
-//                          half-waves, against one float of V per lane (row = the key of the lane's half,
-//                          column = 32b + l32): fp32 weights, fp32 products, no rounding before the store.
-//                          bf16: as in the tiled kernel (weights rounded to bf16, 16 keys per instruction,
-//                          the lane's 8 weights are its operand), the 8 values of V gathered by 2-byte loads.
+//   O^T += V_sub^T * P^T   as in the tiled kernel (weights rounded to bf16, 16 keys per instruction, the lane's
+//                          8 weights are its operand), the 8 values of V gathered by 2-byte loads.
 #include "launchers.h"
 #include "qk_common.h"
 
@@ -156,49 +150,27 @@ void attention_general_kernel(const T* __restrict__ Q, const T* __restrict__ K, 
         for (int r = 1; r < 16; ++r) sum += p[r];
         l_run += sum;
         // ---- output accumulators -----------------------------------------------------------------------------------
-        if constexpr (E == 4) {
-            // accumulator r is the weight of key 8 (r / 4) + 4 half + r % 4: four keys (one r / 4) per batch
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                float vv[4][DVB];
+        for (int m = 0; m < 2; ++m) {
+            u32x4 pw;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const char* vrow = Vh + (int64_t)row_in(key0 + 8 * r4 + 4 * half + j) * rb;
+            for (int i = 0; i < 4; ++i) pw[i] = pack_bf16x2(p[8 * m + 2 * i], p[8 * m + 2 * i + 1]);
+            // operand slot e of the lane <-> key 16m + 8 (e / 4) + 4 half + e % 4 (the key of accumulator 8m + e)
+            u32x4 vf[DVB];
 #pragma unroll
-                    for (int b = 0; b < DVB; ++b) {
-                        const float v = *reinterpret_cast<const float*>(vrow + vcol[b]);
-                        vv[j][b] = b * 32 + l32 < d ? v : 0.0f;
-                    }
+            for (int i = 0; i < 4; ++i) {
+                const int e = 2 * i;
+                const char* vlo = Vh + (int64_t)row_in(key0 + 16 * m + 8 * (e / 4) + 4 * half + (e % 4)) * rb;
+                const char* vhi = Vh + (int64_t)row_in(key0 + 16 * m + 8 * (e / 4) + 4 * half + (e % 4) + 1) * rb;
+#pragma unroll
+                for (int b = 0; b < DVB; ++b) {
+                    const uint32_t lo = *reinterpret_cast<const uint16_t*>(vlo + vcol[b]);
+                    const uint32_t hi = *reinterpret_cast<const uint16_t*>(vhi + vcol[b]);
+                    vf[b][i] = b * 32 + l32 < d ? (lo | (hi << 16)) : 0u;
                 }
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int b = 0; b < DVB; ++b)
-                        oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[j][b], p[4 * r4 + j], oacc[b], 0, 0, 0);
             }
-        } else {
 #pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                u32x4 pw;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) pw[i] = pack_bf16x2(p[8 * m + 2 * i], p[8 * m + 2 * i + 1]);
-                // operand slot e of the lane <-> key 16m + 8 (e / 4) + 4 half + e % 4 (the key of accumulator 8m + e)
-                u32x4 vf[DVB];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = 2 * i;
-                    const char* vlo = Vh + (int64_t)row_in(key0 + 16 * m + 8 * (e / 4) + 4 * half + (e % 4)) * rb;
-                    const char* vhi = Vh + (int64_t)row_in(key0 + 16 * m + 8 * (e / 4) + 4 * half + (e % 4) + 1) * rb;
-#pragma unroll
-                    for (int b = 0; b < DVB; ++b) {
-                        const uint32_t lo = *reinterpret_cast<const uint16_t*>(vlo + vcol[b]);
-                        const uint32_t hi = *reinterpret_cast<const uint16_t*>(vhi + vcol[b]);
-                        vf[b][i] = b * 32 + l32 < d ? (lo | (hi << 16)) : 0u;
-                    }
-                }
-#pragma unroll
-                for (int b = 0; b < DVB; ++b) Mma<uint16_t>::run(oacc[b], vf[b], pw);
-            }
+            for (int b = 0; b < DVB; ++b) Mma<uint16_t>::run(oacc[b], vf[b], pw);
         }
     }
 
@@ -212,14 +184,9 @@ void attention_general_kernel(const T* __restrict__ Q, const T* __restrict__ K, 
         for (int i = 0; i < 4; ++i) {
             const int col = b * 32 + 8 * i + 4 * half;   // d is a multiple of 4: the run lies inside the row or past it
             if (col < d) {
-                if constexpr (E == 4) {
-                    f32x4 w = {oacc[b][4 * i] * inv, oacc[b][4 * i + 1] * inv, oacc[b][4 * i + 2] * inv, oacc[b][4 * i + 3] * inv};
-                    *reinterpret_cast<f32x4*>(orow + col * 4) = w;
-                } else {
-                    u32x2 w = {pack_bf16x2(oacc[b][4 * i] * inv, oacc[b][4 * i + 1] * inv),
-                               pack_bf16x2(oacc[b][4 * i + 2] * inv, oacc[b][4 * i + 3] * inv)};
-                    *reinterpret_cast<u32x2*>(orow + col * 2) = w;
-                }
+                u32x2 w = {pack_bf16x2(oacc[b][4 * i] * inv, oacc[b][4 * i + 1] * inv),
+                           pack_bf16x2(oacc[b][4 * i + 2] * inv, oacc[b][4 * i + 3] * inv)};
+                *reinterpret_cast<u32x2*>(orow + col * 2) = w;
             }
         }
 }
@@ -239,39 +206,25 @@ hipError_t launch_general_t(const void* Q, const void* K, const void* V, void* O
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_general_blocks(int blocks, const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, int d,
-                                 float scale, hipStream_t stream)
-{
-    switch (blocks) {
-    case 1: return launch_general_t<T, 1>(Q, K, V, O, BH, N, d, scale, stream);
-    case 2: return launch_general_t<T, 2>(Q, K, V, O, BH, N, d, scale, stream);
-    case 3: return launch_general_t<T, 3>(Q, K, V, O, BH, N, d, scale, stream);
-    case 4: return launch_general_t<T, 4>(Q, K, V, O, BH, N, d, scale, stream);
-    case 5: return launch_general_t<T, 5>(Q, K, V, O, BH, N, d, scale, stream);
-    case 6: return launch_general_t<T, 6>(Q, K, V, O, BH, N, d, scale, stream);
-    case 7: return launch_general_t<T, 7>(Q, K, V, O, BH, N, d, scale, stream);
-    case 8: return launch_general_t<T, 8>(Q, K, V, O, BH, N, d, scale, stream);
-    default: return hipErrorInvalidValue;
-    }
-}
-
 }  // namespace
 
-bool attention_general_supported(DType dt, int64_t BH, int64_t N, int64_t d)
+bool attention_general_supported(int64_t BH, int64_t N, int64_t d)
 {
-    const int64_t step = dt == DType::F32 ? 4 : 16;
-    if (d < step || d > 256 || (d % step) != 0) return false;
+    if (d <= 128 || d > 256 || (d % 16) != 0) return false;
     if (N < 1 || N > ((int64_t)1 << 24)) return false;
     return BH * ((N + 31) / 32) <= (int64_t)0x7ffffff0;
 }
 
-hipError_t launch_attention_general(DType dt, const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N,
-                                    int64_t d, float scale, hipStream_t stream)
+hipError_t launch_attention_general(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
+                                    float scale, hipStream_t stream)
 {
-    const int blocks = (int)((d + 31) / 32);
-    if (dt == DType::F32) return launch_general_blocks<float>(blocks, Q, K, V, O, BH, (int)N, (int)d, scale, stream);
-    return launch_general_blocks<uint16_t>(blocks, Q, K, V, O, BH, (int)N, (int)d, scale, stream);
+    switch ((int)((d + 31) / 32)) {
+    case 5: return launch_general_t<uint16_t, 5>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
+    case 6: return launch_general_t<uint16_t, 6>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
+    case 7: return launch_general_t<uint16_t, 7>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
+    case 8: return launch_general_t<uint16_t, 8>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace attnw

@@ -89,22 +89,24 @@ int attnw_attention(const void* Q, const void* K, const void* V, void* O, int64_
     if (mul_overflows(B, H, &BH) || mul_overflows(BH, N, &elems) || mul_overflows(elems, d, &elems) ||
         mul_overflows(elems, elem_size(dtype), &bytes))
         return ATTNW_ERR_SHAPE;
-    const attnw::DType dt = dtype == ATTNW_F32 ? attnw::DType::F32 : attnw::DType::BF16;
-    const bool tiled = dtype == ATTNW_BF16 && attnw::attention_supported(BH, N, d);
-    if (!tiled && !attnw::attention_general_supported(dt, BH, N, d)) return ATTNW_ERR_UNSUPPORTED;
+    const bool f32 = dtype == ATTNW_F32;
+    const bool tiled = !f32 && attnw::attention_supported(BH, N, d);
+    if (!(f32 ? attnw::attention_f32_supported(BH, N, d) : tiled || attnw::attention_general_supported(BH, N, d)))
+        return ATTNW_ERR_UNSUPPORTED;
     if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O)) return ATTNW_ERR_ALIGN;
     if (overlaps(O, bytes, Q, bytes) || overlaps(O, bytes, K, bytes) || overlaps(O, bytes, V, bytes))
         return ATTNW_ERR_ALIAS;
     hipStream_t st = static_cast<hipStream_t>(stream);
     // many short sequences: the kernel in which a wave works alone on a (head, 32 queries) pair
     // (ATTNW_ATTENTION_KERNEL=tiny puts every shape it takes on it, =tiled none: tests and measurements compare them)
-    if (dtype == ATTNW_BF16 && attnw::attention_tiny_supported(BH, N, d)) {
+    if (f32) return attnw::launch_attention_f32(Q, K, V, O, BH, N, d, scale, st) == hipSuccess ? ATTNW_OK : ATTNW_ERR_LAUNCH;
+    if (attnw::attention_tiny_supported(BH, N, d)) {
         const char* force = getenv("ATTNW_ATTENTION_KERNEL");
         const bool want = force ? strcmp(force, "tiny") == 0 : attnw::prefers_attention_tiny(BH, N, d);
         if (want) return attnw::launch_attention_tiny(Q, K, V, O, BH, N, d, scale, st) == hipSuccess ? ATTNW_OK : ATTNW_ERR_LAUNCH;
     }
     const hipError_t e = tiled ? attnw::launch_attention(Q, K, V, O, BH, N, d, scale, st)
-                               : attnw::launch_attention_general(dt, Q, K, V, O, BH, N, d, scale, st);
+                               : attnw::launch_attention_general(Q, K, V, O, BH, N, d, scale, st);
     return e == hipSuccess ? ATTNW_OK : ATTNW_ERR_LAUNCH;
 }
 

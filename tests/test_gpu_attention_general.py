@@ -140,3 +140,17 @@ def test_attention_general_is_deterministic():
     V = wl.value_inputs(x, seed=7)
     a, b = _run(x, V, guard=64), _run(x, V, guard=64)
     assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+@pytest.mark.parametrize("d", [4, 36, 64, 96, 128, 256])
+@pytest.mark.parametrize("N", [1, 100, 129])
+def test_attention_f32_many_heads(N, d):
+    """Enough heads that a workgroup takes 128 queries and every wave all keys (fewer heads share the keys of a query
+    block between the waves of a workgroup): strips with waves past the end, one key, one key past a tile."""
+    heads = 512
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=3900 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=3901 + N)
+    O = gu.to_f64(_run(x, V))
+    assert np.isfinite(O).all()
+    for h in (0, 1, heads // 2 + 1, heads - 1):
+        _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention {heads} heads N={N} d={d} head {h}")
