@@ -91,7 +91,7 @@ int attnw_attention(const void* Q, const void* K, const void* V, void* O, int64_
         return ATTNW_ERR_SHAPE;
     const bool f32 = dtype == ATTNW_F32;
     const bool tiled = !f32 && attnw::attention_supported(BH, N, d);
-    if (!(f32 ? attnw::attention_f32_supported(BH, N, d) : tiled || attnw::attention_general_supported(BH, N, d)))
+    if (!(f32 ? attnw::attention_f32_supported(BH, N, d) : tiled || attnw::attention_wide_supported(BH, N, d)))
         return ATTNW_ERR_UNSUPPORTED;
     if (!aligned16(Q) || !aligned16(K) || !aligned16(V) || !aligned16(O)) return ATTNW_ERR_ALIGN;
     if (overlaps(O, bytes, Q, bytes) || overlaps(O, bytes, K, bytes) || overlaps(O, bytes, V, bytes))
@@ -106,7 +106,7 @@ int attnw_attention(const void* Q, const void* K, const void* V, void* O, int64_
         if (want) return attnw::launch_attention_tiny(Q, K, V, O, BH, N, d, scale, st) == hipSuccess ? ATTNW_OK : ATTNW_ERR_LAUNCH;
     }
     const hipError_t e = tiled ? attnw::launch_attention(Q, K, V, O, BH, N, d, scale, st)
-                               : attnw::launch_attention_general(Q, K, V, O, BH, N, d, scale, st);
+                               : attnw::launch_attention_wide(Q, K, V, O, BH, N, d, scale, st);
     return e == hipSuccess ? ATTNW_OK : ATTNW_ERR_LAUNCH;
 }
 

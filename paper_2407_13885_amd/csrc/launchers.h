@@ -66,9 +66,9 @@ bool attention_f32_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_attention_f32(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                 float scale, hipStream_t stream);
 
-// The same for bf16 head sizes above 128, up to 256: one wave per 32 queries, operands straight from global memory.
-bool attention_general_supported(int64_t BH, int64_t N, int64_t d);
-hipError_t launch_attention_general(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
+// The same for bf16 head sizes above 128, up to 256 (multiples of 16): tiled through LDS, V turned by the transposing LDS read.
+bool attention_wide_supported(int64_t BH, int64_t N, int64_t d);
+hipError_t launch_attention_wide(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                     float scale, hipStream_t stream);
 
 // The same for many short sequences (bf16, d = 64 with N <= 128, d = 32 with N <= 224): a wave per (head, 32 queries), operands

@@ -63,10 +63,33 @@ __device__ __forceinline__ void dma16_untracked(const char* src, uint32_t lds_ba
 #endif
 }
 
+// The same from a wave-uniform base and a byte offset per lane.
+__device__ __forceinline__ void dma16_untracked(const char* base, uint32_t offset, uint32_t lds_base)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(offset), "s"(base) : "memory", "m0");
+#endif
+}
+
 __device__ __forceinline__ uint32_t lds_offset_of(const void* p)
 {
     return (uint32_t)(uintptr_t)(lds_ptr)(p);
 }
+
+// Transposing LDS read (ds_read_b64_tr_b16): each group of 16 lanes reads four runs of 16 elements of 2 bytes, lanes
+// 4j .. 4j + 3 run j (8 bytes a lane), and lane i of the group gets element i of the four runs.
+__device__ __forceinline__ u32x2 lds_read_tr16(const char* p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef s16x4 __attribute__((address_space(3)))* tr_ptr;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(p)));
+#else
+    (void)p;
+    return u32x2{0u, 0u};
+#endif
+}
+__device__ __forceinline__ u32x4 u32x4_of(u32x2 lo, u32x2 hi) { return u32x4{lo[0], lo[1], hi[0], hi[1]}; }
 
 template <int I> struct IC { static constexpr int value = I; };
 

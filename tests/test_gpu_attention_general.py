@@ -154,3 +154,17 @@ def test_attention_f32_many_heads(N, d):
     assert np.isfinite(O).all()
     for h in (0, 1, heads // 2 + 1, heads - 1):
         _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention {heads} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("d", [144, 160, 176, 192, 208, 224, 240, 256])
+@pytest.mark.parametrize("N", [65, 129, 256, 257])
+def test_attention_bf16_large_heads_many(N, d):
+    """Enough heads that a wave takes all keys (fewer share the keys of a query block between four waves): every padding of
+    a row, a last tile of one key, waves and strips past the end."""
+    heads = 300
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=4100 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=4101 + N)
+    O = gu.to_f64(_run(x, V))
+    assert np.isfinite(O).all()
+    for h in (0, 1, heads // 2 + 1, heads - 1):
+        _check(O[0, h], x, V, 0, h, (0, N), f"bf16 attention {heads} heads N={N} d={d} head {h}")
