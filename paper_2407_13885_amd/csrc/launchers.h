@@ -71,6 +71,12 @@ bool attention_wide_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_attention_wide(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                     float scale, hipStream_t stream);
 
+// The same for a few heads (bf16, d a multiple of 16 up to 256), queries q_base .. N - 1 of every head: the keys of a query
+// block shared between the waves of a workgroup.
+bool prefers_attention_ranges(int64_t BH, int64_t N, int64_t d);
+hipError_t launch_attention_ranges(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
+                                   float scale, int q_base, hipStream_t stream);
+
 // The same for many short sequences (bf16, d = 64 with N <= 128, d = 32 with N <= 224): a wave per (head, 32 queries), operands
 // straight from global memory, the exponentials as they stand the operand of the second contraction.
 bool attention_tiny_supported(int64_t BH, int64_t N, int64_t d);

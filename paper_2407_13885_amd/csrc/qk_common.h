@@ -37,6 +37,8 @@ template <> struct Mma<float> {
 
 // vmcnt(0) with the other counters left alone (gfx9 encoding of s_waitcnt)
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+// lgkmcnt(0): the LDS reads issued so far have returned their data
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 // vmcnt(N): wait until at most the N youngest vector-memory operations are outstanding
 template <int N> __device__ __forceinline__ void wait_vmem_le()
 {

@@ -92,7 +92,7 @@ def test_attention_head_sizes_between_the_powers_of_two(N, d):
 @pytest.mark.parametrize("d", [32, 48, 64, 80, 112, 128])
 @pytest.mark.parametrize("N", [1, 33, 129, 257, 600])
 def test_attention_many_heads_take_the_wide_strips(N, d):
-    """Few heads run on 64-query strips whose keys are spread over four waves (the tests above); with more than two
+    """Few heads run on blocks of 32 queries whose keys are shared between the waves of a workgroup (the tests above); with more than two
     such strips per compute unit the library takes 256-query strips, every wave walking all keys.  Enough heads for
     that, first, middle and last head checked."""
     H = 512 // ((N + 63) // 64) + 1
@@ -106,7 +106,7 @@ def test_attention_many_heads_take_the_wide_strips(N, d):
 
 @pytest.mark.parametrize("B,H,N,d", [(1, 1, 4096, 128), (1, 4, 4096, 128), (2, 4, 4096, 64), (1, 1, 16384, 128), (1, 2, 16384, 32)])
 def test_attention_few_heads_of_many_keys(B, H, N, d):
-    """The sizes the paper measures are single heads: the four partial results of a query block (one per key range,
+    """The sizes the paper measures are single heads: the partial results of a query block (one per wave,
     each with its own reference exponent and sum) are merged at the end.  Sampled rows of every head."""
     x = wl.fused_inputs("t", "bf16", B, H, N, d, seed=2500 + H + N + d, row_factor=(0.5, 2.0))
     V = wl.value_inputs(x, seed=2501 + N)
@@ -215,3 +215,16 @@ def test_attention_is_deterministic():
     V = wl.value_inputs(x, seed=7)
     a, b = _run(x, V, guard=0 + 64), _run(x, V, guard=0 + 64)
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("d", [16, 32, 48, 64, 80, 96, 112, 128, 144, 256])
+@pytest.mark.parametrize("H,N", [(1, 1), (2, 64), (2, 65), (2, 256), (2, 257), (1, 513), (1, 1025), (300, 20), (150, 65), (30, 512)])
+def test_attention_keys_shared_between_waves(H, N, d):
+    """Blocks of 32 queries whose waves take the keys in turn: two, four and eight waves, waves without a sub-tile, a last
+    sub-tile of one key, a last block of one query, every padding of a row, more blocks than compute units."""
+    x = wl.fused_inputs("t", "bf16", 1, H, N, d, seed=5200 + H + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=5201 + N)
+    O = gu.to_f64(_run(x, V))
+    assert np.isfinite(O).all()
+    for h in sorted({0, H // 2, H - 1}):
+        _check_rows(O[0, h], x, V, 0, h, (0, N), f"{H} heads N={N} d={d} head {h}")
