@@ -51,15 +51,12 @@ struct AttnCfg {
 
 // TAIL: N is not a whole number of tiles / strips.  Rows past the end are read as row N-1 (every load
 // stays inside the arrays), their weights are forced to 0 and their queries are not stored.
-// PAD:  rows of Q, K, V and O are `rb` < DB bytes long (head sizes that are not 32, 64 or 128); on chip they are
-// padded to DB: Q fragments and V columns past the end are zeros, K chunks past the end hold a copy of the row's
-// first chunk (finite, and it meets the zero Q fragments), output columns past the end are not stored.
-template <int DB, int QB, bool TAIL, bool PAD = false>
+template <int DB, int QB, bool TAIL>
 __global__ __launch_bounds__(512)
 void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
-                      uint16_t* __restrict__ O, int N, int rb_arg, float c, uint32_t sign_flip, uint32_t strips, uint32_t total)
+                      uint16_t* __restrict__ O, int N, float c, uint32_t sign_flip, uint32_t strips, uint32_t total)
 {
-    const int rb = PAD ? rb_arg : DB;             // bytes of a row in memory
+    constexpr int rb = DB;                        // bytes of a row
     using C = AttnCfg<DB, QB>;
     constexpr int NW = C::NW, QW = C::QW, BM = C::BM, BN = C::BN, G = C::G, CPR = C::CPR, DVB = C::DVB;
     constexpr int K_TILE_BYTES = C::K_TILE_BYTES, K_LOADS = C::K_LOADS, V_LOADS = C::V_LOADS;
@@ -96,10 +93,7 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (!PAD || (2 * g + half) * 16 < rb)
-                v = *reinterpret_cast<const u32x4*>(Qh + (int64_t)row_in(q0 + qb * 32 + l32) * rb + (2 * g + half) * 16) ^ sign_flip;
-            qf[qb][g] = v;
+            qf[qb][g] = *reinterpret_cast<const u32x4*>(Qh + (int64_t)row_in(q0 + qb * 32 + l32) * rb + (2 * g + half) * 16) ^ sign_flip;
         }
 
     // ---- per-lane constants ----------------------------------------------------------------------------
@@ -113,8 +107,7 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
     int k_off0;
     {
         const int s = wave * 64 + lane;
-        int ch = (s % CPR) ^ ((k_key(0) / C::RPL) & C::SWZ_MASK);
-        if (PAD && ch * 16 >= rb) ch = 0;         // a padding chunk: any finite data of the row
+        const int ch = (s % CPR) ^ ((k_key(0) / C::RPL) & C::SWZ_MASK);
         k_off0 = k_key(0) * rb + ch * 16;
     }
     auto k_off = [&](int j) __attribute__((always_inline)) { return k_off0 + j * KSTEP * rb; };
@@ -164,8 +157,7 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
         for (int j = 0; j < V_LOADS; ++j) {
             const char* src = tile_base + v_off(j);
             if (clamp) src -= (int64_t)(tile * BN + v_key(j) - row_in(tile * BN + v_key(j))) * rb;
-            if (PAD && (int)(((wave + NW * j) >> 1) * 16) >= rb) vreg[j] = u32x4{0u, 0u, 0u, 0u};   // columns past the end
-            else vreg[j] = *reinterpret_cast<const u32x4*>(src);
+            vreg[j] = *reinterpret_cast<const u32x4*>(src);
         }
     };
     auto v_scatter = [&](int buf) __attribute__((always_inline)) {
@@ -283,7 +275,7 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
         v_load(nxt);
         // (a wave whose queries all lie past the end -- the last strip of a ragged length -- only moves tiles and meets
         // the barriers: the waves that share its SIMD get the issue slots; measured on 192 heads of N = 577, d = 64:
-        // 47.4 -> 43.0 us, 16 heads of N = 4097, d = 128: 249 -> 209 us.  The test stays outside compute_tile -- inside,
+        // 47.4 -> 43.0 us.  The test stays outside compute_tile -- inside,
         // per query block, it cost the full strips 3-5 %)
         if (!TAIL || q0 < N) compute_tile(bufc, t, maskc);
         v_scatter(BUF ^ 1);
@@ -313,16 +305,15 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
             for (int i = 0; i < 4; ++i) {
                 u32x2 w = {pack_bf16x2(oacc[qb][b][4 * i] * inv, oacc[qb][b][4 * i + 1] * inv),
                            pack_bf16x2(oacc[qb][b][4 * i + 2] * inv, oacc[qb][b][4 * i + 3] * inv)};
-                // (d is a multiple of 16: a run of four columns lies inside the row or past it)
-                if (!PAD || (b * 32 + 8 * i) * 2 + half * 8 < rb) *reinterpret_cast<u32x2*>(orow + (b * 32 + 8 * i) * 2) = w;
+                *reinterpret_cast<u32x2*>(orow + (b * 32 + 8 * i) * 2) = w;
             }
     }
 }
 
 // Queries 0 .. q_end - 1 of every head (q_end < 0: all).
-template <int DB, int QB, bool TAIL, bool PAD = false>
+template <int DB, int QB, bool TAIL>
 hipError_t launch_attention_t(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, float scale,
-                              hipStream_t stream, int d = DB / 2, int q_end = -1)
+                              hipStream_t stream, int q_end = -1)
 {
     using C = AttnCfg<DB, QB>;
     const uint32_t strips = (uint32_t)(((q_end < 0 ? N : q_end) + C::BM - 1) / C::BM);
@@ -330,8 +321,8 @@ hipError_t launch_attention_t(const void* Q, const void* K, const void* V, void*
     const uint32_t grid = (uint32_t)((total + 7) / 8 * 8);
     const float c = fabsf(scale) * kLog2e;
     const uint32_t flip = scale < 0.0f ? Mma<uint16_t>::kSignMask : 0u;
-    hipLaunchKernelGGL((attention_kernel<DB, QB, TAIL, PAD>), dim3(grid), dim3(512), 0, stream, static_cast<const uint16_t*>(Q),
-                       static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), static_cast<uint16_t*>(O), N, 2 * d,
+    hipLaunchKernelGGL((attention_kernel<DB, QB, TAIL>), dim3(grid), dim3(512), 0, stream, static_cast<const uint16_t*>(Q),
+                       static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), static_cast<uint16_t*>(O), N,
                        c, flip, strips, (uint32_t)total);
     return hipGetLastError();
 }
@@ -340,7 +331,7 @@ hipError_t launch_attention_t(const void* Q, const void* K, const void* V, void*
 // of workgroups on the chip: such a workgroup spends what ONE of its waves spends on a full strip -- the whole sweep
 // over the keys -- on a few rows.  The partial strips are left out of the launch and follow as a second one of the kernel
 // for few heads, whose waves share the keys of 32 queries.  Measured: 64 heads of N = 2049, d = 64: 146 -> 96 us; 128 heads of
-// N = 1025: 74 -> 62 us; 16 heads of N = 4097, d = 128: 209 -> 170 us.
+// N = 1025: 74 -> 62 us.
 template <int DB, int QB = 1>
 hipError_t launch_attention_own_tail(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, float scale,
                                      hipStream_t stream, bool* taken)
@@ -351,7 +342,7 @@ hipError_t launch_attention_own_tail(const void* Q, const void* K, const void* V
     *taken = full >= 1 && tail_rows >= 1 && tail_rows <= 64 &&
              (BH * full + slots - 1) / slots < (BH * (full + 1) + slots - 1) / slots;
     if (!*taken) return hipSuccess;
-    const hipError_t e = launch_attention_t<DB, QB, true>(Q, K, V, O, BH, N, scale, stream, DB / 2, (int)(full * BM));
+    const hipError_t e = launch_attention_t<DB, QB, true>(Q, K, V, O, BH, N, scale, stream, (int)(full * BM));
     if (e != hipSuccess) return e;
     return launch_attention_ranges(Q, K, V, O, BH, N, DB / 2, scale, (int)(full * BM), stream);
 }
@@ -360,7 +351,7 @@ hipError_t launch_attention_own_tail(const void* Q, const void* K, const void* V
 
 bool attention_supported(int64_t BH, int64_t N, int64_t d)
 {
-    if (d < 16 || d > 128 || (d % 16) != 0) return false;
+    if (d != 32 && d != 64) return false;
     if (N < 1 || N > ((int64_t)1 << 24)) return false;
     return BH * ((N + 255) / 256) <= (int64_t)0x7ffffff0;
 }
@@ -369,12 +360,6 @@ hipError_t launch_attention(const void* Q, const void* K, const void* V, void* O
                             float scale, hipStream_t stream)
 {
     if (prefers_attention_ranges(BH, N, d)) return launch_attention_ranges(Q, K, V, O, BH, N, d, scale, 0, stream);
-    // head sizes between the powers of two: rows padded on chip, in the instantiation that also takes any length
-    if (d != 32 && d != 64 && d != 128) {
-        if (d <= 32) return launch_attention_t<64, 1, true, true>(Q, K, V, O, BH, (int)N, scale, stream, (int)d);
-        if (d <= 64) return launch_attention_t<128, 1, true, true>(Q, K, V, O, BH, (int)N, scale, stream, (int)d);
-        return launch_attention_t<256, 1, true, true>(Q, K, V, O, BH, (int)N, scale, stream, (int)d);
-    }
     if (d == 32) {          // short rows: two query blocks per wave whenever that leaves enough workgroups
         const bool wide = N >= 2048 && BH * ((N + 511) / 512) >= 200;
         if ((N % 256) != 0) {
@@ -391,10 +376,6 @@ hipError_t launch_attention(const void* Q, const void* K, const void* V, void* O
     }
     if ((N % 256) != 0) {   // any length: rows past the end are clamped and masked
         bool taken;
-        if (d == 128) {
-            const hipError_t e = launch_attention_own_tail<256>(Q, K, V, O, BH, (int)N, scale, stream, &taken);
-            return taken ? e : launch_attention_t<256, 1, true>(Q, K, V, O, BH, (int)N, scale, stream);
-        }
         // (512-query strips only where the rows a last strip leaves unused are a small share)
         if (N >= 2048 && BH * ((N + 511) / 512) >= 200) {
             const hipError_t e = launch_attention_own_tail<128, 2>(Q, K, V, O, BH, (int)N, scale, stream, &taken);
@@ -403,7 +384,6 @@ hipError_t launch_attention(const void* Q, const void* K, const void* V, void* O
         const hipError_t e = launch_attention_own_tail<128>(Q, K, V, O, BH, (int)N, scale, stream, &taken);
         return taken ? e : launch_attention_t<128, 1, true>(Q, K, V, O, BH, (int)N, scale, stream);
     }
-    if (d == 128) return launch_attention_t<256, 1, false>(Q, K, V, O, BH, (int)N, scale, stream);
     // two query blocks per wave (512-query strips) when that still gives every compute unit a workgroup
     if ((N % 512) == 0 && BH * (N / 512) >= 200) return launch_attention_t<128, 2, false>(Q, K, V, O, BH, (int)N, scale, stream);
     return launch_attention_t<128, 1, false>(Q, K, V, O, BH, (int)N, scale, stream);

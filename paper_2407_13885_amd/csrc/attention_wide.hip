@@ -1,29 +1,30 @@
-// Attention output  O = softmax(scale * Q K^T) V  for wide bf16 heads: d a multiple of 16, 128 < d <= 256, any N.
+// Attention output  O = softmax(scale * Q K^T) V  in bf16: d a multiple of 16 up to 256 but 32 and 64, any N.
 //
 // (Paper: Multi-Head Self-Attention section, Attention(Q, K, V) = softmax(Q K^T / sqrt(d_k)) V; the product
 // with V is what the section "Limitations and future Directions" names as the next thing to fuse.  The
-// max-subtracted softmax of the Softmax section, Eq. 1, is applied incrementally as in the kernel for d <= 128.)
+// max-subtracted softmax of the Softmax section, Eq. 1, is applied incrementally as in attention_kernels.hip.)
 //
-// What bounds it: the LDS port, as in the kernel for d <= 128 (every matrix instruction takes one 1 KiB operand fragment
-// from LDS), with half as much softmax per matrix instruction.  A wave owns 32 queries: 128 accumulators and up to 64
-// registers of Q fragments leave no room for a second query block at two waves per SIMD.
+// What bounds it: the LDS port (every matrix instruction takes one 1 KiB operand fragment from LDS) and, up to d = 128, the
+// softmax between the two contractions of a wave, under the board's power cap.  A wave owns 32 queries: at d = 256 its 128
+// accumulators and 64 registers of Q fragments leave no room for a second query block at two waves per SIMD.
 //
-// A workgroup is WQ query blocks of 32; a tile is 32 keys.  K and V lie in LDS as they lie in memory, chunks swizzled: V is
-// turned by the transposing LDS read (ds_read_b64_tr_b16: 4 keys x 16 columns, a lane gets the four keys of its column), so
-// both tiles travel global -> LDS directly, without registers or a scatter.  Double buffered (4 x 16 KiB: what the direct
-// transfers can address), one barrier per tile.  (Problems of a few heads: attention_ranges.hip.)
-// Measured, 16 heads of N = 4096, against one wave per workgroup with operands straight from the caches: d = 256 928 ->
-// 238 us (1157 TFLOP/s), 192 700 -> 185, 144 633 -> 157.
+// A workgroup is WQ query blocks of 32; a tile is SUBS x 32 keys.  K and V lie in LDS as they lie in memory, chunks
+// swizzled: V is turned by the transposing LDS read (ds_read_b64_tr_b16: 4 keys x 16 columns, a lane gets the four keys of
+// its column), so both tiles travel global -> LDS directly, without registers or a scatter.  Double buffered (4 tiles in
+// the 64 KiB that the direct transfers can address), one barrier per tile.  (Problems of a few heads:
+// attention_ranges.hip.)  Measured, 16 heads of N = 4096: d = 256 928 -> 238 us (1157 TFLOP/s), 192 700 -> 185, 144 633 -> 157
+// against one wave per workgroup with operands straight from the caches; d = 96 132 -> 106, d = 128 134 -> 130.5, forty
+// heads of N = 600, d = 128 26.7 -> 23.6 against 128-key tiles, V scattered transposed and rows padded to 128 columns.
 #include "launchers.h"
 #include "attention_common.h"
 
 namespace attnw {
 namespace {
 
-template <int DVB, int WQ>
+template <int DVB, int WQ, int SUBS>
 struct WideCfg {
     static constexpr int BM = 32 * WQ;
-    static constexpr int BN = 32;
+    static constexpr int BN = 32 * SUBS;
     static constexpr int DB = DVB * 64;           // bytes of a row on chip
     static constexpr int CPR = DVB * 4;           // 16-byte chunks of it
     static constexpr int TILE = BN * DB;
@@ -33,12 +34,12 @@ struct WideCfg {
 // DVB: 32-column blocks of a row, ceil(d / 32).  HALF: d is an odd multiple of 16 -- the last 16 columns on chip are
 // copies of the row's first chunks, left out of the first contraction and not stored by the second.  rb: bytes of a row
 // in memory.  Rows past N are read as row N - 1, weigh nothing and are not stored.
-template <int DVB, bool HALF, int WQ>
+template <int DVB, bool HALF, int WQ, int SUBS>
 __global__ __launch_bounds__(64 * WQ)
 void attention_wide_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                            uint16_t* __restrict__ O, int N, float c, uint32_t sign_flip, uint32_t strips, uint32_t total)
 {
-    using C = WideCfg<DVB, WQ>;
+    using C = WideCfg<DVB, WQ, SUBS>;
     using L = RowLayout<DVB>;
     constexpr int NW = WQ, DB = C::DB, CPR = C::CPR, BN = C::BN, TILE = C::TILE, XFERS = C::XFERS;
     constexpr int rb = DB - (HALF ? 32 : 0);
@@ -105,8 +106,8 @@ void attention_wide_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
     int voff[VPERIOD];
 #pragma unroll
     for (int b = 0; b < VPERIOD; ++b) voff[b] = (b ^ L::v_block(vkey)) * 64;
-    auto v_frag = [&](int buf, int b, int m) __attribute__((always_inline)) {
-        const char* p = vrow + buf * TILE + 16 * m * DB + (b / VPERIOD) * VPERIOD * 64 + voff[b % VPERIOD];
+    auto v_frag = [&](int buf, int u, int b, int m) __attribute__((always_inline)) {
+        const char* p = vrow + buf * TILE + (32 * u + 16 * m) * DB + (b / VPERIOD) * VPERIOD * 64 + voff[b % VPERIOD];
         return u32x4_of(lds_read_tr16(p), lds_read_tr16(p + 8 * DB));
     };
 
@@ -118,15 +119,14 @@ void attention_wide_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
     float mb_run = kNegBig, l_run = 0.0f;
     constexpr float kLazy = 8.0f;                 // binades the maximum may run ahead of the reference exponent
 
-    // the lane's 16 weights of a sub-tile as the operand of the second contraction
-    u32x4 pw[2];
-    auto weights = [&](int buf, int key0) __attribute__((always_inline)) {
+    // sub-tile u of the tile in buffer buf
+    auto sub_tile = [&](int buf, int u, int key0) __attribute__((always_inline)) {
         f32x16 s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.0f;
 #pragma unroll
         for (int g = 0; g < G; ++g)
-            Mma<uint16_t>::run(s, *reinterpret_cast<const u32x4*>(krow + buf * TILE + (g / KPERIOD) * KPERIOD * 32 + koff[g % KPERIOD]), qf[g]);
+            Mma<uint16_t>::run(s, *reinterpret_cast<const u32x4*>(krow + buf * TILE + u * 32 * DB + (g / KPERIOD) * KPERIOD * 32 + koff[g % KPERIOD]), qf[g]);
         float tm = max3(s[0], s[1], s[2]);
 #pragma unroll
         for (int r = 3; r < 15; r += 2) tm = max3(tm, s[r], s[r + 1]);
@@ -153,16 +153,15 @@ void attention_wide_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
 #pragma unroll
         for (int r = 1; r < 16; ++r) sum += p[r];
         l_run += sum;
+        u32x4 pw[2];                              // the lane's 16 weights as the operand of the second contraction
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int i = 0; i < 4; ++i) pw[m][i] = pack_bf16x2(p[8 * m + 2 * i], p[8 * m + 2 * i + 1]);
-    };
-    auto values = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int b = 0; b < DVB; ++b) Mma<uint16_t>::run(oacc[b], v_frag(buf, b, m), pw[m]);
+            for (int b = 0; b < DVB; ++b) Mma<uint16_t>::run(oacc[b], v_frag(buf, u, b, m), pw[m]);
     };
 
     const int n_tiles = (N + BN - 1) / BN;
@@ -176,37 +175,38 @@ void attention_wide_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
             k_issue(t + 1, BUF ^ 1);
             v_issue(t + 1, BUF ^ 1);
         }
-        if (q0 < N) {                         // (a wave without queries only moves tiles)
-            weights(BUF, t * BN);
-            values(BUF);
+        if (q0 < N) {                             // (a wave without queries only moves tiles)
+#pragma unroll
+            for (int u = 0; u < SUBS; ++u)
+                if (SUBS == 1 || t * BN + u * 32 < N) sub_tile(BUF, u, t * BN + u * 32);
         }
         wait_vmem();
         __syncthreads();
     });
 
     // ---- normalise, round once, store: a lane owns runs of 4 consecutive output columns of its query ----------------------
+    const float inv = 1.0f / half_wave_sum(l_run);
+    if (q0 + l32 >= N) return;
     char* const orow = Oh + (int64_t)(q0 + l32) * rb + half * 8;
-    auto store_run = [&](int b, int i, float o0, float o1, float o2, float o3) __attribute__((always_inline)) {
-        const u32x2 w = {pack_bf16x2(o0, o1), pack_bf16x2(o2, o3)};
-        if (!HALF || b * 64 + i * 16 < rb) *reinterpret_cast<u32x2*>(orow + b * 64 + i * 16) = w;
-    };
-            const float inv = 1.0f / half_wave_sum(l_run);
-            if (q0 + l32 >= N) return;
-    #pragma unroll
-            for (int b = 0; b < DVB; ++b)
-    #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    store_run(b, i, oacc[b][4 * i] * inv, oacc[b][4 * i + 1] * inv, oacc[b][4 * i + 2] * inv, oacc[b][4 * i + 3] * inv);
+#pragma unroll
+    for (int b = 0; b < DVB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const u32x2 w = {pack_bf16x2(oacc[b][4 * i] * inv, oacc[b][4 * i + 1] * inv),
+                             pack_bf16x2(oacc[b][4 * i + 2] * inv, oacc[b][4 * i + 3] * inv)};
+            if (!HALF || b * 64 + i * 16 < rb) *reinterpret_cast<u32x2*>(orow + b * 64 + i * 16) = w;
+        }
 }
 
-template <int DVB, bool HALF, int WQ>
-hipError_t launch_wide_t(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, float scale, hipStream_t stream)
+// Queries 0 .. q_end - 1 of every head.
+template <int DVB, bool HALF, int WQ, int SUBS>
+hipError_t launch_wide_t(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, float scale, hipStream_t stream, int q_end)
 {
-    using C = WideCfg<DVB, WQ>;
-    const uint32_t strips = (uint32_t)((N + C::BM - 1) / C::BM);
+    using C = WideCfg<DVB, WQ, SUBS>;
+    const uint32_t strips = (uint32_t)((q_end + C::BM - 1) / C::BM);
     const uint64_t total = (uint64_t)BH * strips;
     const uint32_t grid = (uint32_t)((total + 7) / 8 * 8);
-    hipLaunchKernelGGL((attention_wide_kernel<DVB, HALF, WQ>), dim3(grid), dim3(64 * WQ), 0, stream,
+    hipLaunchKernelGGL((attention_wide_kernel<DVB, HALF, WQ, SUBS>), dim3(grid), dim3(64 * WQ), 0, stream,
                        static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V),
                        static_cast<uint16_t*>(O), N, fabsf(scale) * kLog2e, scale < 0.0f ? Mma<uint16_t>::kSignMask : 0u, strips,
                        (uint32_t)total);
@@ -216,26 +216,42 @@ hipError_t launch_wide_t(const void* Q, const void* K, const void* V, void* O, i
 template <int DVB, bool HALF>
 hipError_t launch_wide(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, float scale, hipStream_t stream)
 {
-    if (prefers_attention_ranges(BH, N, DVB * 32)) return launch_attention_ranges(Q, K, V, O, BH, N, DVB * 32 - (HALF ? 16 : 0), scale, 0, stream);
     // at most two query blocks per head: workgroups of two waves (2000 heads of N = 64, d = 192: 57.5 -> 51 us; 4000 of
     // N = 32: 75 -> 50)
-    if (N <= 64) return launch_wide_t<DVB, HALF, 2>(Q, K, V, O, BH, N, scale, stream);
-    return launch_wide_t<DVB, HALF, 8>(Q, K, V, O, BH, N, scale, stream);
+    if (N <= 64) return launch_wide_t<DVB, HALF, 2, 1>(Q, K, V, O, BH, N, scale, stream, N);
+    // short rows: a tile of four sub-tiles per barrier (16 heads of N = 4096, d = 64: 85 -> 78 us; d = 128 with two: 130.5 -> 132.7)
+    constexpr int SUBS = DVB <= 2 ? 4 : 1;
+    // A last strip of at most 64 queries that would start another round of workgroups spends what ONE of its waves spends on
+    // a full strip: it follows as a launch of the kernel for few heads (16 heads of N = 4097, d = 128: 209 -> 170 us).
+    const int64_t full = N / 256, tail_rows = N - full * 256, slots = compute_units();
+    if (full >= 1 && tail_rows >= 1 && tail_rows <= 64 && (BH * full + slots - 1) / slots < (BH * (full + 1) + slots - 1) / slots) {
+        const hipError_t e = launch_wide_t<DVB, HALF, 8, SUBS>(Q, K, V, O, BH, N, scale, stream, (int)full * 256);
+        return e != hipSuccess ? e : launch_attention_ranges(Q, K, V, O, BH, N, DVB * 32 - (HALF ? 16 : 0), scale, (int)full * 256, stream);
+    }
+    return launch_wide_t<DVB, HALF, 8, SUBS>(Q, K, V, O, BH, N, scale, stream, N);
 }
 
 }  // namespace
 
+// (d = 32 and 64 have a kernel of their own, whose waves own up to two query blocks)
 bool attention_wide_supported(int64_t BH, int64_t N, int64_t d)
 {
-    if (d <= 128 || d > 256 || (d % 16) != 0) return false;
+    if (d < 16 || d > 256 || (d % 16) != 0 || d == 32 || d == 64) return false;
     if (N < 1 || N > ((int64_t)1 << 24)) return false;
-    return BH * ((N + 31) / 32) <= (int64_t)0x7ffffff0;
+    return BH * (d <= 128 ? (N + 255) / 256 : (N + 31) / 32) <= (int64_t)0x7ffffff0;
 }
 
 hipError_t launch_attention_wide(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                  float scale, hipStream_t stream)
 {
+    if (prefers_attention_ranges(BH, N, d)) return launch_attention_ranges(Q, K, V, O, BH, N, d, scale, 0, stream);
     switch ((int)(d / 16)) {
+    case 1: return launch_wide<1, true>(Q, K, V, O, BH, (int)N, scale, stream);
+    case 3: return launch_wide<2, true>(Q, K, V, O, BH, (int)N, scale, stream);
+    case 5: return launch_wide<3, true>(Q, K, V, O, BH, (int)N, scale, stream);
+    case 6: return launch_wide<3, false>(Q, K, V, O, BH, (int)N, scale, stream);
+    case 7: return launch_wide<4, true>(Q, K, V, O, BH, (int)N, scale, stream);
+    case 8: return launch_wide<4, false>(Q, K, V, O, BH, (int)N, scale, stream);
     case 9: return launch_wide<5, true>(Q, K, V, O, BH, (int)N, scale, stream);
     case 10: return launch_wide<5, false>(Q, K, V, O, BH, (int)N, scale, stream);
     case 11: return launch_wide<6, true>(Q, K, V, O, BH, (int)N, scale, stream);

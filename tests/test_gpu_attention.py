@@ -228,3 +228,17 @@ def test_attention_keys_shared_between_waves(H, N, d):
     assert np.isfinite(O).all()
     for h in sorted({0, H // 2, H - 1}):
         _check_rows(O[0, h], x, V, 0, h, (0, N), f"{H} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("d", [16, 32, 48, 64, 80, 96, 112, 128])
+@pytest.mark.parametrize("N", [513, 600])
+def test_attention_every_wave_all_keys(N, d):
+    """Enough heads that 256-query strips are taken at every head size: a last strip of one query as a launch of its own, a
+    last strip with waves past the end, a last tile and sub-tile that are not whole."""
+    H = 127
+    x = wl.fused_inputs("t", "bf16", 1, H, N, d, seed=5400 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=5401 + N)
+    O = gu.to_f64(_run(x, V))
+    assert np.isfinite(O).all()
+    for h in (0, 64, H - 1):
+        _check_rows(O[0, h], x, V, 0, h, (0, N), f"attention {H} heads N={N} d={d} head {h}")
