@@ -287,6 +287,13 @@ hipError_t launch_f32_ranges(const void* Q, const void* K, const void* V, void* 
     // (d > 128: the K and V tiles of four ranges do not fit the LDS)
     constexpr int most = DVB <= 4 ? 4 : 2;
     const int wk = key_ranges_f32(BH, N, most);
+    // No keys to share, and 256-query strips whose waves are more than half busy: the bf16 instruction on operands in three
+    // parts (16 heads of N = 4096, d = 128: 998 -> 609 us, eight, exactly half: 519 either way; 300 heads of N = 197, d = 64
+    // 52 -> 42; forty of 700, d = 32, 43 % busy: 31 -> 32).
+    if constexpr (DVB <= 4) {
+        const int64_t cus = compute_units(), rounds = (BH * ((N + 255) / 256) + cus - 1) / cus;
+        if (wk == 1 && BH * ((N + 31) / 32) * 2 > rounds * cus * 8) return launch_attention_f32_split(Q, K, V, O, BH, N, d, scale, stream);
+    }
     if constexpr (most == 4)
         if (wk == 4) return launch_f32_t<DVB, 1, 4>(Q, K, V, O, BH, N, d, scale, stream);
     if (wk == 2) return launch_f32_t<DVB, 2, 2>(Q, K, V, O, BH, N, d, scale, stream);

@@ -1,0 +1,286 @@
+// Attention output  O = softmax(scale * Q K^T) V  in fp32 for many heads (d a multiple of 4 up to 128, any N): both
+// contractions on the bf16 matrix instruction, every operand as three bf16 parts (split_f32.h).
+//
+// (Paper: Multi-Head Self-Attention section, Attention(Q, K, V) = softmax(Q K^T / sqrt(d_k)) V; the product
+// with V is what the section "Limitations and future Directions" names as the next thing to fuse.  The
+// max-subtracted softmax of the Softmax section, Eq. 1, is applied incrementally as in the other kernels.)
+//
+// What bounds it: the matrix instruction (12 x 32 cycles per 32 queries, 32 keys and 16 columns of d, where the fp32
+// instruction takes 16 x 64), under the board's power cap.  Eight waves of 32 queries share a tile of 32 keys: splitting a
+// K or V element costs six vector instructions, spread over 256 queries.  A thread loads 8 elements of a row, splits them
+// and writes a 16-byte chunk to each of the three planes of the tile; planes lie as rows in memory do, chunks
+// swizzled, and V is turned by the transposing LDS read.  Double buffered, one barrier per tile.
+// Measured, 16 heads of N = 4096, against the fp32 instruction: d = 32 / 64 / 96 / 128 290 / 523 / 761 / 998 -> 188 / 312 / 457 /
+// 609 us (1.35 PFLOP/s of bf16 products); error of the output against 64 bits 1.24e-6 -> 1.05e-6 (d = 128).
+#include "attention_common.h"
+#include "launchers.h"
+#include "split_f32.h"
+
+namespace attnw {
+namespace {
+
+// DVB: 32-column blocks of a row, ceil(d / 32); columns past d are zeros on chip.  Rows past N are read as row N - 1, weigh
+// nothing and are not stored.
+template <int DVB>
+__global__ __launch_bounds__(512)
+void attention_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+                                float* __restrict__ O, int N, int d, float c, float q_sign, uint32_t strips, uint32_t total)
+{
+    using L = RowLayout<DVB>;
+    constexpr int NW = 8, BN = 32;
+    constexpr int DB = DVB * 64;                  // bytes of a row of a plane
+    constexpr int CPR = DVB * 4;                  // 16-byte chunks of it
+    constexpr int PLANE = BN * DB;
+    constexpr int BUF_BYTES = 6 * PLANE;          // K hi, mid, lo, V hi, mid, lo
+    constexpr int G = DVB * 2;                    // 16-column contraction groups
+    constexpr int CHUNKS = BN * CPR;              // chunks of a plane: the first CHUNKS slots are K's, as many follow of V
+    constexpr int SLOTS = (2 * CHUNKS + NW * 64 - 1) / (NW * 64);
+    static_assert(CHUNKS % 64 == 0, "a wave's slots are of one tensor");
+
+    __shared__ __align__(1024) char lds[2 * BUF_BYTES];
+
+    const uint32_t logical = xcd_contiguous_block_id(blockIdx.x, gridDim.x);
+    if (logical >= total) return;
+    const uint32_t bh = logical / strips;
+    const uint32_t strip = logical - bh * strips;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int l32 = lane & 31;
+    const int half = lane >> 5;
+    const float* Qh = Q + (int64_t)bh * N * d;
+    const float* Kh = K + (int64_t)bh * N * d;
+    const float* Vh = V + (int64_t)bh * N * d;
+    float* Oh = O + (int64_t)bh * N * d;
+    const int q0 = strip * 32 * NW + wave * 32;
+
+    // (q_sign: a negative scale negates Q)
+    // 8 elements of a row from column col on, zeros past its end (d is a multiple of 4: halves are inside or outside)
+    auto row8 = [&](const float* row, int col, f32x4& a, f32x4& b) __attribute__((always_inline)) {
+        a = *reinterpret_cast<const f32x4*>(row + (col < d ? col : 0));
+        b = *reinterpret_cast<const f32x4*>(row + (col + 4 < d ? col + 4 : 0));
+    };
+    auto split_row8 = [&](int col, f32x4 a, f32x4 b) __attribute__((always_inline)) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            x[e] = col < d ? a[e] : 0.0f;
+            x[4 + e] = col + 4 < d ? b[e] : 0.0f;
+        }
+        return split8(x);
+    };
+
+    Split8 qf[G];
+    {
+        const float* qrow = Qh + (int64_t)min(q0 + l32, N - 1) * d;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            f32x4 a, b;
+            row8(qrow, g * 16 + half * 8, a, b);
+            qf[g] = split_row8(g * 16 + half * 8, a * q_sign, b * q_sign);
+        }
+    }
+
+    // ---- tiles: slot s of a tile is chunk s of K or chunk s - CHUNKS of V --------------------------------------------------
+    f32x4 rega[SLOTS], regb[SLOTS];
+    auto load = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < SLOTS; ++j) {
+            const int w = wave + NW * j;          // (wave-uniform: which tensor, and whether there is such a slot)
+            if ((SLOTS * NW * 64 == 2 * CHUNKS || w * 64 < 2 * CHUNKS)) {
+                const bool v = w * 64 >= CHUNKS;
+                const int s = (v ? w * 64 - CHUNKS : w * 64) + lane;
+                const int key = s / CPR;
+                row8((v ? Vh : Kh) + (int64_t)min(t * BN + key, N - 1) * d, (s - key * CPR) * 8, rega[j], regb[j]);
+            }
+        }
+    };
+    auto store = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < SLOTS; ++j) {
+            const int w = wave + NW * j;
+            if ((SLOTS * NW * 64 == 2 * CHUNKS || w * 64 < 2 * CHUNKS)) {
+                const bool v = w * 64 >= CHUNKS;
+                const int s = (v ? w * 64 - CHUNKS : w * 64) + lane;
+                const int key = s / CPR, ch = s - key * CPR;
+                const Split8 x = split_row8(ch * 8, rega[j], regb[j]);
+                char* to = lds + buf * BUF_BYTES + (v ? 3 * PLANE : 0) + key * DB + (ch ^ (v ? L::v_block(key) * 4 : L::k_chunk(key))) * 16;
+                *reinterpret_cast<u32x4*>(to) = x.hi;
+                *reinterpret_cast<u32x4*>(to + PLANE) = x.mid;
+                *reinterpret_cast<u32x4*>(to + 2 * PLANE) = x.lo;
+            }
+        }
+    };
+
+    // ---- per-lane places of the operand fragments ------------------------------------------------------------------------
+    const char* const krow = lds + l32 * DB;
+    constexpr int KPERIOD = L::KPERIOD, VPERIOD = L::VPERIOD;
+    int koff[KPERIOD];
+#pragma unroll
+    for (int g = 0; g < KPERIOD; ++g) koff[g] = ((2 * g + half) ^ L::k_chunk(l32)) * 16;
+    const int vkey = 4 * half + ((lane & 15) >> 2);            // a lane's row of the 8-key group that it reads
+    const char* const vrow = lds + 3 * PLANE + vkey * DB + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    int voff[VPERIOD];
+#pragma unroll
+    for (int b = 0; b < VPERIOD; ++b) voff[b] = (b ^ L::v_block(vkey)) * 64;
+
+    f32x16 oacc[DVB];
+    float mb_run, l_run;
+    auto reset = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < DVB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[b][r] = 0.0f;
+        mb_run = kNegBig;
+        l_run = 0.0f;
+    };
+    constexpr float kLazy = 8.0f;                 // binades the maximum may run ahead of the reference exponent
+
+    // weights of 32 keys from their scores; the reference exponent follows the maximum lazily
+    auto weights = [&](const f32x16& s, int key0, float (&p)[16]) __attribute__((always_inline)) {
+        float tm = max3(s[0], s[1], s[2]);
+#pragma unroll
+        for (int r = 3; r < 15; r += 2) tm = max3(tm, s[r], s[r + 1]);
+        const float mbn = half_wave_max(fmaxf(tm, s[15])) * c;   // (keys past the end are copies of key N-1: no new maximum)
+        if (__builtin_amdgcn_ballot_w64(mbn > mb_run + kLazy) != 0) {
+            const float mb_new = fmaxf(mb_run, mbn);
+            const float alpha = fast_exp2(mb_run - mb_new);    // exactly 1 for lanes whose exponent stands
+            l_run *= alpha;
+#pragma unroll
+            for (int b = 0; b < DVB; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[b][r] *= alpha;
+            mb_run = mb_new;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[r], c, -mb_run));
+        if (key0 + 32 > N) {                      // keys past the end weigh nothing
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (key0 + 4 * half + 8 * (r / 4) + (r % 4) >= N) p[r] = 0.0f;
+        }
+        float sum = p[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) sum += p[r];
+        l_run += sum;
+    };
+
+    auto compute = [&](int t, int buf) __attribute__((always_inline)) {
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const char* k = krow + buf * BUF_BYTES + (g / KPERIOD) * KPERIOD * 32 + koff[g % KPERIOD];
+            const Split8 kf = {*reinterpret_cast<const u32x4*>(k), *reinterpret_cast<const u32x4*>(k + PLANE),
+                               *reinterpret_cast<const u32x4*>(k + 2 * PLANE)};
+            mma_split(s, kf, qf[g]);
+        }
+        float p[16];
+        weights(s, t * BN, p);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = p[8 * m + e];
+            const Split8 pw = split8(x);          // a lane's weights of group m are its operand of the second contraction
+#pragma unroll
+            for (int b = 0; b < DVB; ++b) {
+                const char* v = vrow + buf * BUF_BYTES + 16 * m * DB + (b / VPERIOD) * VPERIOD * 64 + voff[b % VPERIOD];
+                const Split8 vf = {u32x4_of(lds_read_tr16(v), lds_read_tr16(v + 8 * DB)),
+                                   u32x4_of(lds_read_tr16(v + PLANE), lds_read_tr16(v + PLANE + 8 * DB)),
+                                   u32x4_of(lds_read_tr16(v + 2 * PLANE), lds_read_tr16(v + 2 * PLANE + 8 * DB))};
+                mma_split(oacc[b], vf, pw);
+            }
+        }
+    };
+
+    // ---- the sweep: while tile t is computed, tile t + 1 is split into the other buffer and tile t + 2 is under way ----------
+    reset();
+    const int n_tiles = (N + BN - 1) / BN;
+    load(0);
+    store(0);
+    if (n_tiles > 1) load(1);
+    __syncthreads();
+    for_tiles(0, 0, n_tiles, [&](int t, auto bufc) __attribute__((always_inline)) {
+        constexpr int BUF = decltype(bufc)::value;
+        if (t + 1 < n_tiles) {
+            store(BUF ^ 1);
+            if (t + 2 < n_tiles) load(t + 2);
+        }
+        if (q0 < N) compute(t, BUF);              // (a wave without queries only moves tiles)
+        __syncthreads();
+    });
+    if (q0 >= N) return;
+
+    // ---- infinities, NaN and overflows (rare): what the parts make of them is not what fp32 does.  The wave starts again on
+    // the fp32 instruction, operands straight from memory ---------------------------------------------------------------------
+    float worst = l_run;
+#pragma unroll
+    for (int b = 0; b < DVB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) worst = __builtin_fmaf(oacc[b][r], 0.0f, worst);   // NaN if any accumulator is not finite
+    if (__builtin_amdgcn_ballot_w64(!(fabsf(worst) < __builtin_inff())) != 0) {
+        reset();
+        const float* qrow = Qh + (int64_t)min(q0 + l32, N - 1) * d;
+        for (int key0 = 0; key0 < N; key0 += 32) {
+            const float* kr = Kh + (int64_t)min(key0 + l32, N - 1) * d;
+            f32x16 s;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+            for (int col = 0; col < d; col += 4) {             // columns col, col + 1, then col + 2, col + 3
+                const f32x4 a = *reinterpret_cast<const f32x4*>(kr + col), b = *reinterpret_cast<const f32x4*>(qrow + col) * q_sign;
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(half ? a[1] : a[0], half ? b[1] : b[0], s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(half ? a[3] : a[2], half ? b[3] : b[2], s, 0, 0, 0);
+            }
+            float p[16];
+            weights(s, key0, p);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float* vr = Vh + (int64_t)min(key0 + 4 * half + 8 * (r / 4) + (r % 4), N - 1) * d;
+#pragma unroll
+                for (int b = 0; b < DVB; ++b)
+                    oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[min(b * 32 + l32, d - 1)], p[r], oacc[b], 0, 0, 0);
+            }
+        }
+    }
+
+    // ---- normalise and store: a lane owns runs of 4 consecutive output columns of its query ----------------------
+    const float inv = 1.0f / half_wave_sum(l_run);
+    if (q0 + l32 >= N) return;
+    float* const orow = Oh + (int64_t)(q0 + l32) * d + half * 4;
+#pragma unroll
+    for (int b = 0; b < DVB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x4 o = {oacc[b][4 * i], oacc[b][4 * i + 1], oacc[b][4 * i + 2], oacc[b][4 * i + 3]};
+            if (b * 32 + 8 * i + 4 * half < d) *reinterpret_cast<f32x4*>(orow + b * 32 + 8 * i) = o * inv;
+        }
+}
+
+template <int DVB>
+hipError_t launch_split_t(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, int d, float scale, hipStream_t stream)
+{
+    const uint32_t strips = (uint32_t)((N + 255) / 256);
+    const uint64_t total = (uint64_t)BH * strips;
+    const uint32_t grid = (uint32_t)((total + 7) / 8 * 8);
+    hipLaunchKernelGGL((attention_f32_split_kernel<DVB>), dim3(grid), dim3(512), 0, stream, static_cast<const float*>(Q),
+                       static_cast<const float*>(K), static_cast<const float*>(V), static_cast<float*>(O), N, d, fabsf(scale) * kLog2e,
+                       scale < 0.0f ? -1.0f : 1.0f, strips, (uint32_t)total);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_attention_f32_split(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
+                                      float scale, hipStream_t stream)
+{
+    switch ((int)((d + 31) / 32)) {
+    case 1: return launch_split_t<1>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
+    case 2: return launch_split_t<2>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
+    case 3: return launch_split_t<3>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
+    case 4: return launch_split_t<4>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace attnw

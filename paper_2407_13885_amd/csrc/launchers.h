@@ -66,6 +66,10 @@ bool attention_f32_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_attention_f32(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                 float scale, hipStream_t stream);
 
+// The same for many heads (d a multiple of 4 up to 128): both contractions on the bf16 instruction, operands in three parts.
+hipError_t launch_attention_f32_split(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
+                                      float scale, hipStream_t stream);
+
 // The same for the other multiples of 16 up to 256: tiled through LDS, V turned by the transposing LDS read.
 bool attention_wide_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_attention_wide(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,

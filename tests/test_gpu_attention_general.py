@@ -168,3 +168,41 @@ def test_attention_bf16_large_heads_many(N, d):
     assert np.isfinite(O).all()
     for h in (0, 1, heads // 2 + 1, heads - 1):
         _check(O[0, h], x, V, 0, h, (0, N), f"bf16 attention {heads} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("d", [4, 32, 36, 64, 100, 128])
+@pytest.mark.parametrize("N", [257, 600])
+def test_attention_f32_in_three_parts(N, d):
+    """Enough heads for the kernel that multiplies operands in three bf16 parts: every padding of a row, last tiles of one
+    key and of 24, waves past the end; rows of scores of both signs of the scale."""
+    heads = 256
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=4300 + N + d, row_factor=(0.5, 2.0),
+                        **({"scale": -1.0 / math.sqrt(d)} if d == 36 else {}))
+    V = wl.value_inputs(x, seed=4301 + N)
+    O = gu.to_f64(_run(x, V))
+    assert np.isfinite(O).all()
+    for h in (0, 1, heads // 2 + 1, heads - 1):
+        _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention in parts {heads} heads N={N} d={d} head {h}")
+
+
+def test_attention_f32_in_three_parts_not_finite():
+    """Infinities, NaN and values that bf16 rounds to infinity give what fp32 arithmetic gives."""
+    heads, N, d = 256, 257, 32
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=4400)
+    V = wl.value_inputs(x, seed=4401)
+    x.Q[0, 0, :, 0] = np.where(np.arange(N) % 2 == 0, 1.0, -1.0)
+    x.K[0, 0, 5, 0] = -np.inf                     # weight 0 for even queries, NaN rows for odd ones
+    V[0, 1, 3, 2] = np.inf                        # a column of infinities
+    x.Q[0, 2, 7, 1] = np.nan                      # one NaN row
+    V[0, 3, 9, 4] = 3.4e38                        # finite, and above the largest bf16
+    O = gu.to_f64(_run(x, V))
+    for h in range(5):
+        with np.errstate(all="ignore"):
+            S = float(x.scale) * (x.Q[0, h].astype(np.float64) @ x.K[0, h].astype(np.float64).T)
+            E = np.exp(S - S.max(axis=1, keepdims=True))
+            ref = (E / E.sum(axis=1, keepdims=True)) @ V[0, h].astype(np.float64)
+        assert (np.isnan(O[0, h]) == np.isnan(ref)).all() and (np.isinf(O[0, h]) == np.isinf(ref)).all(), f"head {h}"
+        ok = np.isfinite(ref)
+        size = np.abs(V[0, h][np.isfinite(V[0, h])]).max()
+        # (weights and sums good to a few 2^-24 of sum_j P_ij |V_jt| <= the largest value; scores below 10)
+        assert np.abs(O[0, h] - ref)[ok].max() <= 2.0 ** -16 * size, f"head {h}"
