@@ -53,6 +53,10 @@ bool qk_gang_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_qk_gang(const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d, float scale,
                           hipStream_t stream);
 
+// Fused attention weights, fp32, d a multiple of 4 up to 128, N a multiple of 4: the contraction on the bf16 instruction,
+// operands in three parts.
+hipError_t launch_qk_f32_split(const void* Q, const void* K, void* P, int64_t BH, int64_t N, int64_t d, float scale, hipStream_t stream);
+
 // Y = scale * X over count elements, rounded once to the storage type; X == Y allowed.
 hipError_t launch_scale(DType dt, const void* X, void* Y, int64_t count, float scale, hipStream_t stream);
 

@@ -1,0 +1,52 @@
+"""GPU parity of the fp32 attention weights on enough strips for the kernel that multiplies operands in three bf16 parts."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2407_13885_amd import workloads as wl
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    gu.require_gpu()
+
+
+@pytest.mark.parametrize("d", [4, 32, 36, 64, 100, 128])
+@pytest.mark.parametrize("N", [64, 100, 132, 260, 512])
+def test_weights_f32_in_three_parts(N, d):
+    """Every padding of a row; strips with waves past the end, last tiles of 4 keys, sub-tiles without keys, whole tiles."""
+    heads = 128
+    scale = {"scale": -1.0 / math.sqrt(d)} if d == 36 else {}
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=6100 + N + d, **scale)
+    P = gu.to_f64(gu.run_fused(x, guard=4096))
+    assert np.abs(P.sum(axis=-1) - 1.0).max() <= 1e-5
+    for h in (0, 1, heads // 2 + 1, heads - 1):
+        ref = oracle.attention_weights(x.Q[0, h], x.K[0, h], "f32", x.scale)
+        gu.check_weights(P[0, h], ref, "f32", f"fused f32 in parts {heads} heads N={N} d={d} head {h}")
+
+
+def test_weights_f32_in_three_parts_not_finite():
+    """Infinities, NaN and values that bf16 rounds to infinity give what fp32 arithmetic gives."""
+    heads, N, d = 128, 132, 32
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=6200)
+    x.Q[0, 0, :, 0] = np.where(np.arange(N) % 2 == 0, 1.0, -1.0)
+    x.K[0, 0, 5, 0] = -np.inf                     # weight 0 for even queries, NaN rows for odd ones
+    x.Q[0, 1, 7, 1] = np.nan                      # one NaN row
+    x.Q[0, 2, :, 3] = 0.0
+    x.K[0, 2, 9, 3] = 3.4e38                      # finite, above the largest bf16, and multiplied by zero
+    P = gu.to_f64(gu.run_fused(x, guard=4096))
+    for h in range(4):
+        with np.errstate(all="ignore"):
+            S = float(x.scale) * (x.Q[0, h].astype(np.float64) @ x.K[0, h].astype(np.float64).T)
+            E = np.exp(S - S.max(axis=1, keepdims=True))
+            ref = E / E.sum(axis=1, keepdims=True)
+        assert (np.isnan(P[0, h]) == np.isnan(ref)).all(), f"head {h}"
+        ok = np.isfinite(ref)
+        assert np.abs(P[0, h] - ref)[ok].max() <= gu.ABS_F32, f"head {h}"
