@@ -250,12 +250,14 @@ hipError_t launch_f32_t(const void* Q, const void* K, const void* V, void* O, in
 {
     using C = F32Cfg<DVB, WQ, WK>;
     const uint32_t strips = (uint32_t)((N + C::BM - 1) / C::BM);
-    const uint64_t total = (uint64_t)BH * strips;
-    const uint32_t grid = (uint32_t)((total + 7) / 8 * 8);
-    hipLaunchKernelGGL((attention_f32_kernel<DVB, WQ, WK>), dim3(grid), dim3(64 * C::NW), 0, stream, static_cast<const float*>(Q),
-                       static_cast<const float*>(K), static_cast<const float*>(V), static_cast<float*>(O), N, d * 4,
-                       fabsf(scale) * kLog2e, scale < 0.0f ? Mma<float>::kSignMask : 0u, strips, (uint32_t)total);
-    return hipGetLastError();
+    return launch_by_heads(BH, strips, 64 * C::NW, [&](int64_t first, int64_t heads) {
+        const int64_t at = first * N * d;
+        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
+        hipLaunchKernelGGL((attention_f32_kernel<DVB, WQ, WK>), dim3(grid), dim3(64 * C::NW), 0, stream, static_cast<const float*>(Q) + at,
+                           static_cast<const float*>(K) + at, static_cast<const float*>(V) + at, static_cast<float*>(O) + at, N, d * 4,
+                           fabsf(scale) * kLog2e, scale < 0.0f ? Mma<float>::kSignMask : 0u, strips, total);
+        return hipGetLastError();
+    });
 }
 
 // Key ranges per workgroup.  The time of a launch goes as (waves that the fullest SIMD gets) x (32-key sub-tiles of such

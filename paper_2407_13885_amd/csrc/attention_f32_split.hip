@@ -261,12 +261,14 @@ template <int DVB>
 hipError_t launch_split_t(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, int d, float scale, hipStream_t stream)
 {
     const uint32_t strips = (uint32_t)((N + 255) / 256);
-    const uint64_t total = (uint64_t)BH * strips;
-    const uint32_t grid = (uint32_t)((total + 7) / 8 * 8);
-    hipLaunchKernelGGL((attention_f32_split_kernel<DVB>), dim3(grid), dim3(512), 0, stream, static_cast<const float*>(Q),
-                       static_cast<const float*>(K), static_cast<const float*>(V), static_cast<float*>(O), N, d, fabsf(scale) * kLog2e,
-                       scale < 0.0f ? -1.0f : 1.0f, strips, (uint32_t)total);
-    return hipGetLastError();
+    return launch_by_heads(BH, strips, 512, [&](int64_t first, int64_t heads) {
+        const int64_t at = first * N * d;
+        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
+        hipLaunchKernelGGL((attention_f32_split_kernel<DVB>), dim3(grid), dim3(512), 0, stream, static_cast<const float*>(Q) + at,
+                           static_cast<const float*>(K) + at, static_cast<const float*>(V) + at, static_cast<float*>(O) + at, N, d,
+                           fabsf(scale) * kLog2e, scale < 0.0f ? -1.0f : 1.0f, strips, total);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace

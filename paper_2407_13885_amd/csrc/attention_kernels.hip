@@ -317,14 +317,16 @@ hipError_t launch_attention_t(const void* Q, const void* K, const void* V, void*
 {
     using C = AttnCfg<DB, QB>;
     const uint32_t strips = (uint32_t)(((q_end < 0 ? N : q_end) + C::BM - 1) / C::BM);
-    const uint64_t total = (uint64_t)BH * strips;
-    const uint32_t grid = (uint32_t)((total + 7) / 8 * 8);
     const float c = fabsf(scale) * kLog2e;
     const uint32_t flip = scale < 0.0f ? Mma<uint16_t>::kSignMask : 0u;
-    hipLaunchKernelGGL((attention_kernel<DB, QB, TAIL>), dim3(grid), dim3(512), 0, stream, static_cast<const uint16_t*>(Q),
-                       static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), static_cast<uint16_t*>(O), N,
-                       c, flip, strips, (uint32_t)total);
-    return hipGetLastError();
+    return launch_by_heads(BH, strips, 512, [&](int64_t first, int64_t heads) {
+        const int64_t at = first * N * C::D;
+        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
+        hipLaunchKernelGGL((attention_kernel<DB, QB, TAIL>), dim3(grid), dim3(512), 0, stream, static_cast<const uint16_t*>(Q) + at,
+                           static_cast<const uint16_t*>(K) + at, static_cast<const uint16_t*>(V) + at, static_cast<uint16_t*>(O) + at, N,
+                           c, flip, strips, total);
+        return hipGetLastError();
+    });
 }
 
 // A ragged length whose last strip (256 queries, 512 with two query blocks per wave) holds at most 64 queries, and whose partial strips start another round

@@ -204,13 +204,15 @@ hipError_t launch_wide_t(const void* Q, const void* K, const void* V, void* O, i
 {
     using C = WideCfg<DVB, WQ, SUBS>;
     const uint32_t strips = (uint32_t)((q_end + C::BM - 1) / C::BM);
-    const uint64_t total = (uint64_t)BH * strips;
-    const uint32_t grid = (uint32_t)((total + 7) / 8 * 8);
-    hipLaunchKernelGGL((attention_wide_kernel<DVB, HALF, WQ, SUBS>), dim3(grid), dim3(64 * WQ), 0, stream,
-                       static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V),
-                       static_cast<uint16_t*>(O), N, fabsf(scale) * kLog2e, scale < 0.0f ? Mma<uint16_t>::kSignMask : 0u, strips,
-                       (uint32_t)total);
-    return hipGetLastError();
+    return launch_by_heads(BH, strips, 64 * WQ, [&](int64_t first, int64_t heads) {
+        const int64_t at = first * N * (DVB * 32 - (HALF ? 16 : 0));
+        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
+        hipLaunchKernelGGL((attention_wide_kernel<DVB, HALF, WQ, SUBS>), dim3(grid), dim3(64 * WQ), 0, stream,
+                           static_cast<const uint16_t*>(Q) + at, static_cast<const uint16_t*>(K) + at, static_cast<const uint16_t*>(V) + at,
+                           static_cast<uint16_t*>(O) + at, N, fabsf(scale) * kLog2e, scale < 0.0f ? Mma<uint16_t>::kSignMask : 0u, strips,
+                           total);
+        return hipGetLastError();
+    });
 }
 
 template <int DVB, bool HALF>

@@ -18,6 +18,23 @@ hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, v
 // Compute units of the current device (256 if the query fails).
 int compute_units();
 
+// A launch may hold less than 2^32 threads; a larger one starts what is left of its size modulo 2^32 and reports no error (seen
+// with 2^24 + 64 heads of 256 threads: the first 64 heads had results).  Calls of so many heads go out as several launches:
+// part(first head, heads) starts one, its grid at most seven workgroups more than the heads need.  (Heads by multiples of
+// eight: an output of 2-byte elements and any N starts on a 16-byte boundary in each of them.)
+template <typename Part>
+hipError_t launch_by_heads(int64_t BH, uint32_t workgroups_per_head, uint32_t threads, Part&& part)
+{
+    int64_t most = ((((int64_t)1 << 32) - 1) / threads - 7) / workgroups_per_head;
+    if (most >= 8) most &= ~(int64_t)7;
+    if (most < 1) return hipErrorInvalidValue;
+    for (int64_t first = 0; first < BH; first += most) {
+        const hipError_t e = part(first, BH - first < most ? BH - first : most);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // bf16, by the round-based kernel: fused attention weights (statistics of one strip gathered while the
 // weights of the previous one are written) or, with scores_only, the scaled scores (one sweep per
 // strip through the same staging and store path; d = 64 only).  Only for the shapes

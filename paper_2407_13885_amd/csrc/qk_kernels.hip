@@ -639,15 +639,17 @@ hipError_t launch_variant(bool scores_only, const void* Q, const void* K, void* 
             return hipGetLastError();
         }
     }
-    const uint64_t total = (uint64_t)BH * strips;
-    const uint32_t grid = (uint32_t)((total + 7) / 8 * 8);
-    if (scores_only)
-        hipLaunchKernelGGL((qk_kernel<T, DB, QB, WQ, WK, SUBS, true, FAST>), dim3(grid), dim3(threads), 0, stream, q, k,
-                           o, N, d, c, flip, strips, (uint32_t)total, 1, 0);
-    else
-        hipLaunchKernelGGL((qk_kernel<T, DB, QB, WQ, WK, SUBS, false, FAST>), dim3(grid), dim3(threads), 0, stream, q,
-                           k, o, N, d, c, flip, strips, (uint32_t)total, 1, 0);
-    return hipGetLastError();
+    return launch_by_heads(BH, strips, threads, [&](int64_t first, int64_t heads) {
+        const int64_t in = first * N * d, to = first * N * N;
+        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
+        if (scores_only)
+            hipLaunchKernelGGL((qk_kernel<T, DB, QB, WQ, WK, SUBS, true, FAST>), dim3(grid), dim3(threads), 0, stream, q + in,
+                               k + in, o + to, N, d, c, flip, strips, total, 1, 0);
+        else
+            hipLaunchKernelGGL((qk_kernel<T, DB, QB, WQ, WK, SUBS, false, FAST>), dim3(grid), dim3(threads), 0, stream, q + in,
+                               k + in, o + to, N, d, c, flip, strips, total, 1, 0);
+        return hipGetLastError();
+    });
 }
 
 template <typename T, int DB, int QB, int WQ, int WK, int SUBS, bool SPLITTABLE = false>

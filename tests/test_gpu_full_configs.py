@@ -221,3 +221,30 @@ def test_more_than_two_to_the_31_elements_of_short_sequences_and_rows():
     for r0 in (0, rows // 2, 43826196 - 500, rows - 1000):         # (43826196 * 49 crosses 2^31 elements)
         ref = oracle.softmax(_bits(S[r0:r0 + 1000]), "bf16")
         gu.check_weights(gu.to_f64(W[r0:r0 + 1000]), ref, "bf16", f"softmax rows {r0}..")
+
+
+@pytest.mark.parametrize("call,dtype,heads,N,d", [("attention", "f32", (1 << 24) + 64, 65, 4), ("attention", "f32", (1 << 23) + 64, 200, 4),
+                                                  ("attention", "bf16", (1 << 25) + 64, 1, 144), ("fused", "f32", (1 << 23) + 64, 3, 4)])
+def test_more_heads_than_one_launch_holds(call, dtype, heads, N, d):
+    """A launch holds less than 2^32 threads: with 256, 512, 128 and 512 threads a head these calls go out as two.  The first
+    heads, those at the end of the first launch and the last ones; every output written."""
+    import paper_2407_13885_amd as attnw
+    torch.manual_seed(78)
+    X = torch.randn(heads, N, d, device="cuda", dtype=gu.TORCH_DT[dtype])     # Q, K and V
+    out = torch.full((heads, N, d if call == "attention" else N), -700.0, device="cuda", dtype=gu.TORCH_DT[dtype])
+    if call == "attention":
+        attnw.attnw_attention(X, X, X, out, 1, heads, N, d, 0.5, gu.DT[dtype])
+    else:
+        attnw.attnw_fused(X, X, out, 1, heads, N, d, 0.5, gu.DT[dtype])
+    torch.cuda.synchronize()
+    step = 1 << 20
+    assert all(bool((out[i:i + step] > -600).all().item()) for i in range(0, heads, step)), "outputs that were not written"
+    for h0 in (0, heads // 2 - 16, heads - 128, heads - 16):
+        x = X[h0:h0 + 16].double().cpu()
+        P = torch.softmax(0.5 * (x @ x.transpose(1, 2)), dim=-1)
+        ref = P @ x if call == "attention" else P
+        size = P @ x.abs() if call == "attention" else P
+        # one rounding each of weights and output (bf16); sums of at most 200 fp32 products, scores below 32 (fp32): 2^-12
+        tol = 2.0 ** -7 if dtype == "bf16" else 2.0 ** -12
+        err = (out[h0:h0 + 16].double().cpu() - ref).abs()
+        assert bool((err <= tol * (size + ref.abs())).all()), f"heads {h0}..: worst {float(err.max()):.3e}"
