@@ -294,7 +294,8 @@ hipError_t launch_f32_ranges(const void* Q, const void* K, const void* V, void* 
     // 52 -> 42; forty of 700, d = 32, 43 % busy: 31 -> 32).
     if constexpr (DVB <= 4) {
         const int64_t cus = compute_units(), rounds = (BH * ((N + 255) / 256) + cus - 1) / cus;
-        if (wk == 1 && BH * ((N + 31) / 32) * 2 > rounds * cus * 8) return launch_attention_f32_split(Q, K, V, O, BH, N, d, scale, stream);
+        if (wk == 1 && BH * ((N + 31) / 32) * 2 > rounds * cus * 8 && split_takes_scale(scale))
+            return launch_attention_f32_split(Q, K, V, O, BH, N, d, scale, stream);
     }
     if constexpr (most == 4)
         if (wk == 4) return launch_f32_t<DVB, 1, 4>(Q, K, V, O, BH, N, d, scale, stream);

@@ -10,8 +10,9 @@
 // K or V element costs six vector instructions, spread over 256 queries.  A thread loads 8 elements of a row, splits them
 // and writes a 16-byte chunk to each of the three planes of the tile; planes lie as rows in memory do, chunks
 // swizzled, and V is turned by the transposing LDS read.  Double buffered, one barrier per tile.
-// Measured, 16 heads of N = 4096, against the fp32 instruction: d = 32 / 64 / 96 / 128 290 / 523 / 761 / 998 -> 188 / 312 / 457 /
-// 609 us (1.35 PFLOP/s of bf16 products); error of the output against 64 bits 1.24e-6 -> 1.05e-6 (d = 128).
+// Measured, 16 heads of N = 4096, against the fp32 instruction: d = 32 / 64 / 96 / 128 290 / 523 / 761 / 998 -> 192 / 328 / 473 /
+// 632 us (1.30 PFLOP/s of bf16 products; the weights' factor of 2^24 costs 1 to 2 % of it); error of the output against 64 bits
+// 1.24e-6 -> 1.05e-6 (d = 128).
 #include "attention_common.h"
 #include "launchers.h"
 #include "split_f32.h"
@@ -53,35 +54,18 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
     float* Oh = O + (int64_t)bh * N * d;
     const int q0 = strip * 32 * NW + wave * 32;
 
-    // (q_sign: a negative scale negates Q)
-    // 8 elements of a row from column col on, zeros past its end (d is a multiple of 4: halves are inside or outside)
-    auto row8 = [&](const float* row, int col, f32x4& a, f32x4& b) __attribute__((always_inline)) {
-        a = *reinterpret_cast<const f32x4*>(row + (col < d ? col : 0));
-        b = *reinterpret_cast<const f32x4*>(row + (col + 4 < d ? col + 4 : 0));
-    };
-    auto split_row8 = [&](int col, f32x4 a, f32x4 b) __attribute__((always_inline)) {
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            x[e] = col < d ? a[e] : 0.0f;
-            x[4 + e] = col + 4 < d ? b[e] : 0.0f;
-        }
-        return split8(x);
-    };
-
-    Split8 qf[G];
+    Split8 qf[G];                                 // (q_sign: a negative scale negates Q)
     {
         const float* qrow = Qh + (int64_t)min(q0 + l32, N - 1) * d;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            f32x4 a, b;
-            row8(qrow, g * 16 + half * 8, a, b);
-            qf[g] = split_row8(g * 16 + half * 8, a * q_sign, b * q_sign);
+            const int col = g * 16 + half * 8;
+            qf[g] = split_row8(load_row8(qrow, col, d), col, d, q_sign * kSplitUp);
         }
     }
 
     // ---- tiles: slot s of a tile is chunk s of K or chunk s - CHUNKS of V --------------------------------------------------
-    f32x4 rega[SLOTS], regb[SLOTS];
+    Row8 reg[SLOTS];
     auto load = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < SLOTS; ++j) {
@@ -90,7 +74,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
                 const bool v = w * 64 >= CHUNKS;
                 const int s = (v ? w * 64 - CHUNKS : w * 64) + lane;
                 const int key = s / CPR;
-                row8((v ? Vh : Kh) + (int64_t)min(t * BN + key, N - 1) * d, (s - key * CPR) * 8, rega[j], regb[j]);
+                reg[j] = load_row8((v ? Vh : Kh) + (int64_t)min(t * BN + key, N - 1) * d, (s - key * CPR) * 8, d);
             }
         }
     };
@@ -102,7 +86,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
                 const bool v = w * 64 >= CHUNKS;
                 const int s = (v ? w * 64 - CHUNKS : w * 64) + lane;
                 const int key = s / CPR, ch = s - key * CPR;
-                const Split8 x = split_row8(ch * 8, rega[j], regb[j]);
+                const Split8 x = split_row8(reg[j], ch * 8, d);
                 char* to = lds + buf * BUF_BYTES + (v ? 3 * PLANE : 0) + key * DB + (ch ^ (v ? L::v_block(key) * 4 : L::k_chunk(key))) * 16;
                 *reinterpret_cast<u32x4*>(to) = x.hi;
                 *reinterpret_cast<u32x4*>(to + PLANE) = x.mid;
@@ -136,7 +120,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
     constexpr float kLazy = 8.0f;                 // binades the maximum may run ahead of the reference exponent
 
     // weights of 32 keys from their scores; the reference exponent follows the maximum lazily
-    auto weights = [&](const f32x16& s, int key0, float (&p)[16]) __attribute__((always_inline)) {
+    auto weights = [&](const f32x16& s, float c, int key0, float (&p)[16]) __attribute__((always_inline)) {
         float tm = max3(s[0], s[1], s[2]);
 #pragma unroll
         for (int r = 3; r < 15; r += 2) tm = max3(tm, s[r], s[r + 1]);
@@ -176,12 +160,12 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
             mma_split(s, kf, qf[g]);
         }
         float p[16];
-        weights(s, t * BN, p);
+        weights(s, c * kSplitDown, t * BN, p);
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             float x[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = p[8 * m + e];
+            for (int e = 0; e < 8; ++e) x[e] = p[8 * m + e] * kSplitUp;
             const Split8 pw = split8(x);          // a lane's weights of group m are its operand of the second contraction
 #pragma unroll
             for (int b = 0; b < DVB; ++b) {
@@ -214,13 +198,14 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
 
     // ---- infinities, NaN and overflows (rare): what the parts make of them is not what fp32 does.  The wave starts again on
     // the fp32 instruction, operands straight from memory ---------------------------------------------------------------------
-    float worst = l_run;
+    float worst = l_run, down = kSplitDown;
 #pragma unroll
     for (int b = 0; b < DVB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) worst = __builtin_fmaf(oacc[b][r], 0.0f, worst);   // NaN if any accumulator is not finite
     if (__builtin_amdgcn_ballot_w64(!(fabsf(worst) < __builtin_inff())) != 0) {
         reset();
+        down = 1.0f;
         const float* qrow = Qh + (int64_t)min(q0 + l32, N - 1) * d;
         for (int key0 = 0; key0 < N; key0 += 32) {
             const float* kr = Kh + (int64_t)min(key0 + l32, N - 1) * d;
@@ -233,7 +218,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
                 s = __builtin_amdgcn_mfma_f32_32x32x2f32(half ? a[3] : a[2], half ? b[3] : b[2], s, 0, 0, 0);
             }
             float p[16];
-            weights(s, key0, p);
+            weights(s, c, key0, p);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const float* vr = Vh + (int64_t)min(key0 + 4 * half + 8 * (r / 4) + (r % 4), N - 1) * d;
@@ -245,7 +230,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
     }
 
     // ---- normalise and store: a lane owns runs of 4 consecutive output columns of its query ----------------------
-    const float inv = 1.0f / half_wave_sum(l_run);
+    const float inv = 1.0f / half_wave_sum(l_run) * down;
     if (q0 + l32 >= N) return;
     float* const orow = Oh + (int64_t)(q0 + l32) * d + half * 4;
 #pragma unroll

@@ -72,6 +72,8 @@ hipError_t launch_qk_gang(const void* Q, const void* K, void* out, int64_t BH, i
 
 // Fused attention weights, fp32, d a multiple of 4 up to 128, N a multiple of 4: the contraction on the bf16 instruction,
 // operands in three parts.
+// (Scores of operands in parts carry a factor of 2^48 that leaves with the scale, which stays a normal number only from here on.)
+inline bool split_takes_scale(float scale) { return scale == 0.0f || scale >= 0x1p-78f || scale <= -0x1p-78f; }
 hipError_t launch_qk_f32_split(const void* Q, const void* K, void* P, int64_t BH, int64_t N, int64_t d, float scale, hipStream_t stream);
 
 // Y = scale * X over count elements, rounded once to the storage type; X == Y allowed.

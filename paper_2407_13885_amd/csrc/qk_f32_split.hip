@@ -58,29 +58,13 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
     const int q0 = strip * 128 + wq * 32;
     char* const stage = lds + 2 * BUF_BYTES + wave * ST_BYTES;
 
-    // 8 elements of a row from column col on, zeros past its end (d is a multiple of 4: halves are inside or outside)
-    auto row8 = [&](const float* row, int col, f32x4& a, f32x4& b) __attribute__((always_inline)) {
-        a = *reinterpret_cast<const f32x4*>(row + (col < d ? col : 0));
-        b = *reinterpret_cast<const f32x4*>(row + (col + 4 < d ? col + 4 : 0));
-    };
-    auto split_row8 = [&](int col, f32x4 a, f32x4 b) __attribute__((always_inline)) {
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            x[e] = col < d ? a[e] : 0.0f;
-            x[4 + e] = col + 4 < d ? b[e] : 0.0f;
-        }
-        return split8(x);
-    };
-
     // (q_sign: a negative scale negates Q)
     const float* const qrow = Qh + (int64_t)min(q0 + l32, N - 1) * d;
     Split8 qf[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        f32x4 a, b;
-        row8(qrow, g * 16 + half * 8, a, b);
-        qf[g] = split_row8(g * 16 + half * 8, a * q_sign, b * q_sign);
+        const int col = g * 16 + half * 8;
+        qf[g] = split_row8(load_row8(qrow, col, d), col, d, q_sign * kSplitUp);
     }
 
     // ---- K tiles: slot s of a tile is its chunk s ---------------------------------------------------------------------------
@@ -92,14 +76,14 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
         int t = (j >= n_tiles ? j - n_tiles : j) + rot;
         return t >= n_tiles ? t - n_tiles : t;
     };
-    f32x4 rega[SLOTS], regb[SLOTS];
+    Row8 reg[SLOTS];
     auto load = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < SLOTS; ++j)
             if (CHUNKS % (NW * 64) == 0 || (wave + NW * j) * 64 < CHUNKS) {   // (wave-uniform)
                 const int s = (wave + NW * j) * 64 + lane;
                 const int key = s / CPR;
-                row8(Kh + (int64_t)min(t * BN + key, N - 1) * d, (s - key * CPR) * 8, rega[j], regb[j]);
+                reg[j] = load_row8(Kh + (int64_t)min(t * BN + key, N - 1) * d, (s - key * CPR) * 8, d);
             }
     };
     auto store = [&](int buf) __attribute__((always_inline)) {
@@ -108,7 +92,7 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
             if (CHUNKS % (NW * 64) == 0 || (wave + NW * j) * 64 < CHUNKS) {
                 const int s = (wave + NW * j) * 64 + lane;
                 const int key = s / CPR, ch = s - key * CPR;
-                const Split8 x = split_row8(ch * 8, rega[j], regb[j]);
+                const Split8 x = split_row8(reg[j], ch * 8, d);
                 char* to = lds + buf * BUF_BYTES + key * DB + (ch ^ L::k_chunk(key)) * 16;
                 *reinterpret_cast<u32x4*>(to) = x.hi;
                 *reinterpret_cast<u32x4*>(to + PLANE) = x.mid;
@@ -134,9 +118,10 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
         return s + rest;
     };
 
+    const float c_parts = c * kSplitDown;         // for scores of operands in parts
     // running maximum and sum of exponentials over the lane's keys (accumulator r is key key0 + 4 half + 8 (r / 4) + r % 4)
     float m_run = kNegBig, l_run = 0.0f;
-    auto fold = [&](const f32x16& s, int key0) __attribute__((always_inline)) {
+    auto fold = [&](const f32x16& s, float c, int key0) __attribute__((always_inline)) {
         float tm = max3(s[0], s[1], s[2]);
 #pragma unroll
         for (int r = 3; r < 15; r += 2) tm = max3(tm, s[r], s[r + 1]);
@@ -155,7 +140,7 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
         l_run = l_run * fast_exp2((m_run - mn) * c) + sum;
         m_run = mn;
     };
-    auto merge = [&](float m, float l) __attribute__((always_inline)) {   // statistics of other keys of the same query
+    auto merge = [&](float m, float l, float c) __attribute__((always_inline)) {   // statistics of other keys of the same query
         const float mn = fmaxf(m_run, m);
         l_run = l_run * fast_exp2((m_run - mn) * c) + l * fast_exp2((m - mn) * c);
         m_run = mn;
@@ -178,17 +163,17 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
 #pragma unroll
         for (int u = 0; u < SUBS; ++u) {
             const int key0 = tile_at(j) * BN + (u * WK + wk) * 32;
-            if (q0 < N && key0 < N) fold(scores(BUF, u), key0);
+            if (q0 < N && key0 < N) fold(scores(BUF, u), c_parts, key0);
         }
         __syncthreads();
     });
-    merge(__shfl_xor(m_run, 32, 64), __shfl_xor(l_run, 32, 64));
+    merge(__shfl_xor(m_run, 32, 64), __shfl_xor(l_run, 32, 64), c_parts);
     if (half == 0) {
         stat_lds[wave * 64 + l32] = m_run;
         stat_lds[wave * 64 + 32 + l32] = l_run;
     }
     __syncthreads();
-    merge(stat_lds[(wave ^ 1) * 64 + l32], stat_lds[(wave ^ 1) * 64 + 32 + l32]);
+    merge(stat_lds[(wave ^ 1) * 64 + l32], stat_lds[(wave ^ 1) * 64 + 32 + l32], c_parts);
     // infinities, NaN and overflows: what the parts make of them is not what fp32 does (the end of the kernel deals with them)
     const bool exact = __builtin_amdgcn_ballot_w64(!(l_run > 0.0f && l_run < __builtin_inff())) == 0;
 
@@ -208,7 +193,7 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
             for (int r4 = 0; r4 < 4; ++r4) {
                 f32x4 p;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) p[i] = fast_exp2(__builtin_fmaf(s[4 * r4 + i] - m_run, c, -bias));
+                for (int i = 0; i < 4; ++i) p[i] = fast_exp2(__builtin_fmaf(s[4 * r4 + i] - m_run, c_parts, -bias));
                 *reinterpret_cast<f32x4*>(stage + l32 * ST_PITCH + (8 * r4 + 4 * half) * 4) = p;
             }
             const bool full = rows_full && key0 + 32 <= N;
@@ -240,8 +225,8 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
     };
     m_run = kNegBig;
     l_run = 0.0f;
-    for (int key0 = 0; key0 < N; key0 += 32) fold(scores_f32(key0), key0);
-    merge(__shfl_xor(m_run, 32, 64), __shfl_xor(l_run, 32, 64));
+    for (int key0 = 0; key0 < N; key0 += 32) fold(scores_f32(key0), c, key0);
+    merge(__shfl_xor(m_run, 32, 64), __shfl_xor(l_run, 32, 64), c);
     const float bias_f32 = fast_log2(l_run);
     for (int key0 = wk * 32; key0 < N; key0 += WK * 32) {
         const f32x16 s = scores_f32(key0);

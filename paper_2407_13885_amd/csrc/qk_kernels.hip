@@ -820,7 +820,8 @@ hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, v
     // heads of N = 2048, d = 64 65 us against 98), rows on 16-byte boundaries, d <= 128: the bf16 instruction on operands in
     // three parts.  Measured, us: eight heads of N = 2048, d = 64 168 -> 91, 300 of 196 83 -> 49, 600 of 100 51 -> 32, 1000 of 64
     // 45 -> 26, 100 of 512, d = 128 154 -> 106.
-    if (dt == DType::F32 && !scores_only && d <= 128 && N % 4 == 0 && N >= 64 && 2 * BH * ((N + 127) / 128) >= compute_units())
+    if (dt == DType::F32 && !scores_only && d <= 128 && N % 4 == 0 && N >= 64 && 2 * BH * ((N + 127) / 128) >= compute_units() &&
+        split_takes_scale(scale))
         return launch_qk_f32_split(Q, K, out, BH, N, d, scale, stream);
     if (dt == DType::F32) return launch_qk_t<float>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream, true);
     // ATTNW_FUSED_KERNEL=twopass keeps bf16 problems on the two-pass kernel above, =rounds keeps short sequences

@@ -43,7 +43,7 @@ def _run(x, V, guard=4096):
     return O
 
 
-def _check(got, x, V, b, h, rows, what):
+def _check(got, x, V, b, h, rows, what, floor=0.0):
     r0, r1 = rows
     ref, P = oracle.attention_output(x.Q[b, h], x.K[b, h], V[b, h], x.dtype, x.scale, rows=rows, return_weights=True)
     A = P @ np.abs(wl.widen(V[b, h], x.dtype))
@@ -52,7 +52,7 @@ def _check(got, x, V, b, h, rows, what):
     else:
         u = 2.0 ** -24
         Bi = abs(float(np.float32(x.scale))) * (np.abs(wl.widen(x.Q[b, h, r0:r1], "f32")) @ np.abs(wl.widen(x.K[b, h], "f32")).T).max(axis=1)
-        tol = ((2 * x.d + 4) * u * Bi[:, None] + 2.0 ** -20 + 2 * x.N * u) * (A + np.abs(ref))
+        tol = ((2 * x.d + 4) * u * Bi[:, None] + 2.0 ** -20 + 2 * x.N * u) * (A + np.abs(ref)) + floor
     err = np.abs(got[r0:r1] - ref)
     assert np.isfinite(got[r0:r1]).all(), f"{what}: non-finite output"
     if (err > tol).any():
@@ -183,6 +183,40 @@ def test_attention_f32_in_three_parts(N, d):
     assert np.isfinite(O).all()
     for h in (0, 1, heads // 2 + 1, heads - 1):
         _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention in parts {heads} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("heads", [2, 256])
+@pytest.mark.parametrize("what", ["V", "V columns", "V rows", "Q and K columns", "tiny weights", "scale 2^-70", "scale 2^-90"])
+def test_attention_f32_over_the_range_of_fp32(what, heads):
+    """Operands of every magnitude that fp32 holds, on the fp32 instruction (two heads) and in three bf16 parts (256): the same
+    bound, relative to sum_j P_ij |V_jt|, with the spacing of fp32's smallest numbers per product as a floor."""
+    N, d = 257, 4 if what == "tiny weights" else 64
+    scale = {"Q and K columns": 2.0 ** 20, "scale 2^-70": 2.0 ** -70, "scale 2^-90": 2.0 ** -90}.get(what, 1.0)
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=4500 + len(what), scale=scale / math.sqrt(d))
+    V = wl.value_inputs(x, seed=4501)
+    if what == "V":
+        V *= np.float32(2.0 ** -124)
+    elif what == "V columns":
+        V *= (2.0 ** -np.linspace(0, 125, d)).astype(np.float32)
+    elif what == "V rows":
+        V *= (2.0 ** -(np.arange(N) % 125.0)).astype(np.float32)[:, None]
+    elif what == "Q and K columns":               # (products of 2^-20: the scale brings them back)
+        e = np.linspace(-100, 100, d)
+        x.Q[...] *= (2.0 ** e).astype(np.float32)
+        x.K[...] *= (2.0 ** (-e - 20)).astype(np.float32)
+    elif what == "tiny weights":                  # the only key with a value weighs 2^-124: scores -86, the others near 0
+        x.Q[...] *= np.float32(0.01)
+        x.Q[..., 0] = 2.0
+        x.K[..., 0] = 0.0
+        x.K[..., 100, 0] = -86.0
+        V[...] = 0.0
+        V[..., 100, :] = 256.0 + np.arange(d) / 7.0
+    else:
+        x.Q[...] *= np.float32(scale ** -0.5)
+        x.K[...] *= np.float32(scale ** -0.5)
+    O = gu.to_f64(_run(x, V))
+    for h in sorted({0, heads // 2, heads - 1}):
+        _check(O[0, h], x, V, 0, h, (0, N), f"{what}, {heads} heads, head {h}", floor=N * 2.0 ** -149)
 
 
 def test_attention_f32_in_three_parts_not_finite():

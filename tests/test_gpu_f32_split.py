@@ -32,6 +32,27 @@ def test_weights_f32_in_three_parts(N, d):
         gu.check_weights(P[0, h], ref, "f32", f"fused f32 in parts {heads} heads N={N} d={d} head {h}")
 
 
+@pytest.mark.parametrize("heads", [2, 128])
+@pytest.mark.parametrize("what", ["Q and K columns", "scale 2^-70", "scale 2^-90"])
+def test_weights_f32_over_the_range_of_fp32(what, heads):
+    """Operands of every magnitude that fp32 holds, on the fp32 instruction (two heads) and in three bf16 parts (128): as exact as
+    ordinary ones."""
+    N, d = 132, 64
+    scale = {"Q and K columns": 2.0 ** 20, "scale 2^-70": 2.0 ** -70, "scale 2^-90": 2.0 ** -90}[what]
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=6300 + len(what), scale=scale / math.sqrt(d))
+    if what == "Q and K columns":                 # (products of 2^-20: the scale brings them back)
+        e = np.linspace(-100, 100, d)
+        x.Q[...] *= (2.0 ** e).astype(np.float32)
+        x.K[...] *= (2.0 ** (-e - 20)).astype(np.float32)
+    else:
+        x.Q[...] *= np.float32(scale ** -0.5)
+        x.K[...] *= np.float32(scale ** -0.5)
+    P = gu.to_f64(gu.run_fused(x, guard=4096))
+    for h in sorted({0, heads // 2, heads - 1}):
+        ref = oracle.attention_weights(x.Q[0, h], x.K[0, h], "f32", x.scale)
+        gu.check_weights(P[0, h], ref, "f32", f"{what}, {heads} heads, head {h}")
+
+
 def test_weights_f32_in_three_parts_not_finite():
     """Infinities, NaN and values that bf16 rounds to infinity give what fp32 arithmetic gives."""
     heads, N, d = 128, 132, 32
