@@ -47,6 +47,8 @@ __device__ __forceinline__ float half_sum_f(float x)
 #endif
 }
 
+__device__ const u32x4 kZeros = {0u, 0u, 0u, 0u};
+
 template <int DVB, int WQ, int WK>
 struct F32Cfg {
     static constexpr int NW = WQ * WK;            // waves per workgroup
@@ -62,8 +64,8 @@ struct F32Cfg {
 };
 
 // DVB: 32-column blocks of an output row, ceil(d / 32); rows are padded to 32 DVB elements on chip (rb: bytes of a row
-// in memory).  Padding chunks hold a copy of the row's first chunk: finite, and in the first contraction it meets zero
-// Q fragments; in the second it makes output columns that are not stored.  Rows past N are read as row N - 1.
+// in memory).  Padding chunks are transferred from an array of zeros (any of the caller's numbers could be infinite, and NaN
+// against the zeros of the padded Q fragments).  Rows past N are read as row N - 1.
 template <int DVB, int WQ, int WK>
 __global__ __launch_bounds__(64 * WQ * WK, DVB <= 4 ? 2 : 1)
 void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
@@ -115,8 +117,9 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
             const int key = s / CPR;
             int ch = s - key * CPR;
             if constexpr (decltype(swzc)::value != 0) ch ^= key & 7;
-            if (ch >= row_chunks) ch = 0;
-            dma16_untracked(head + (int64_t)min(key0 + key, N - 1) * rb + ch * 16, dst + (wave + NW * j) * 1024);
+            const char* src = head + (int64_t)min(key0 + key, N - 1) * rb + ch * 16;
+            if (ch >= row_chunks) src = reinterpret_cast<const char*>(&kZeros);
+            dma16_untracked(src, dst + (wave + NW * j) * 1024);
         }
     };
     auto k_issue = [&](int t) __attribute__((always_inline)) { issue(Kh, k_base, t * BN, IC<1>{}); };

@@ -240,3 +240,26 @@ def test_attention_f32_in_three_parts_not_finite():
         size = np.abs(V[0, h][np.isfinite(V[0, h])]).max()
         # (weights and sums good to a few 2^-24 of sum_j P_ij |V_jt| <= the largest value; scores below 10)
         assert np.abs(O[0, h] - ref)[ok].max() <= 2.0 ** -16 * size, f"head {h}"
+
+
+@pytest.mark.parametrize("heads,N,d", [(2, 100, 36), (2, 600, 36), (2, 600, 200), (300, 20, 20), (300, 50, 132), (512, 100, 100), (256, 257, 36)])
+def test_attention_f32_infinite_key(heads, N, d):
+    """A key with -inf in the first chunk of a row that is padded on chip: weight 0 for the queries that meet it with a positive
+    number, NaN rows for those with a negative one, as in fp32 arithmetic.  On every shape of workgroup."""
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=4600 + N + d)
+    V = wl.value_inputs(x, seed=4601)
+    h = heads - 1
+    x.Q[0, h, :, 0] = np.where(np.arange(N) % 2 == 0, 1.0, -1.0)
+    x.K[0, h, 5, 0] = -np.inf
+    O = gu.to_f64(_run(x, V))
+    assert np.isfinite(O[0, :h]).all()
+    assert np.isnan(O[0, h, 1::2]).all()
+    Q, K = x.Q[0, h, ::2].astype(np.float64), np.delete(x.K[0, h].astype(np.float64), 5, axis=0)
+    W = np.delete(V[0, h].astype(np.float64), 5, axis=0)
+    S = float(x.scale) * (Q @ K.T)
+    E = np.exp(S - S.max(axis=1, keepdims=True))
+    P = E / E.sum(axis=1, keepdims=True)
+    ref, u = P @ W, 2.0 ** -24
+    B = abs(float(x.scale)) * (np.abs(Q) @ np.abs(K).T).max(axis=1)
+    tol = ((2 * d + 4) * u * B[:, None] + 2.0 ** -20 + 2 * N * u) * (P @ np.abs(W) + np.abs(ref))
+    assert (np.abs(O[0, h, ::2] - ref) <= tol).all()
