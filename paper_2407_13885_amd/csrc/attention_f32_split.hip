@@ -221,10 +221,13 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
             weights(s, c, key0, p);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const float* vr = Vh + (int64_t)min(key0 + 4 * half + 8 * (r / 4) + (r % 4), N - 1) * d;
+                const int key = key0 + 4 * half + 8 * (r / 4) + (r % 4);
+                const float* vr = Vh + (int64_t)min(key, N - 1) * d;
 #pragma unroll
-                for (int b = 0; b < DVB; ++b)
-                    oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[min(b * 32 + l32, d - 1)], p[r], oacc[b], 0, 0, 0);
+                for (int b = 0; b < DVB; ++b) {
+                    const float v = vr[min(b * 32 + l32, d - 1)];
+                    oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(key < N ? v : 0.0f, p[r], oacc[b], 0, 0, 0);
+                }
             }
         }
     }

@@ -263,3 +263,21 @@ def test_attention_f32_infinite_key(heads, N, d):
     B = abs(float(x.scale)) * (np.abs(Q) @ np.abs(K).T).max(axis=1)
     tol = ((2 * d + 4) * u * B[:, None] + 2.0 ** -20 + 2 * N * u) * (P @ np.abs(W) + np.abs(ref))
     assert (np.abs(O[0, h, ::2] - ref) <= tol).all()
+
+
+@pytest.mark.parametrize("heads,N,d", [(256, 257, 36), (256, 257, 64), (256, 600, 32)])
+def test_attention_f32_in_three_parts_infinite_last_value(heads, N, d):
+    """An infinity in the last row of V, which the rows past the end of a last tile are read as: that column is infinite in every
+    row of the head, nothing else changes."""
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=4700 + N + d)
+    V = wl.value_inputs(x, seed=4701)
+    h = heads - 1
+    V[0, h, N - 1, 2] = np.inf
+    O = gu.to_f64(_run(x, V))
+    assert (O[0, h, :, 2] == np.inf).all()
+    V[0, h, N - 1, 2] = O[0, h, :, 2] = 0.0
+    ref = oracle.attention_output(x.Q[0, h], x.K[0, h], V[0, h], "f32", x.scale, rows=(0, N))
+    ref[:, 2] = 0.0
+    # (as in the bound above: d and N enough for B below 16)
+    assert np.abs(O[0, h] - ref).max() <= ((2 * d + 4) * 16 + 2 * N + 16) * 2.0 ** -24 * 2 * np.abs(V[0, h]).max()
+    assert np.isfinite(O[0, :h]).all()
