@@ -286,8 +286,13 @@ hipError_t launch_f32_ranges(const void* Q, const void* K, const void* V, void* 
                              hipStream_t stream)
 {
     // at most two query blocks per head: workgroups of as many waves (4096 heads of N = 49, d = 32 with four, two of them
-    // idle: 36 -> 30.5 us; of N = 20, d = 16: 22.5 -> 9.0)
-    if (N <= 32) return launch_f32_t<DVB, 1, 1>(Q, K, V, O, BH, N, d, scale, stream);
+    // idle: 36 -> 30.5 us; of N = 20, d = 16: 22.5 -> 9.0).  d > 128: K and V of 32 keys would leave room for two workgroups on a compute
+    // unit, and nothing shares them.
+    if constexpr (DVB > 4) {
+        if (N <= 32) return launch_attention_short(DType::F32, Q, K, V, O, BH, N, d, scale, stream);
+    } else {
+        if (N <= 32) return launch_f32_t<DVB, 1, 1>(Q, K, V, O, BH, N, d, scale, stream);
+    }
     if (N <= 64) return launch_f32_t<DVB, 2, 1>(Q, K, V, O, BH, N, d, scale, stream);
     // (d > 128: the K and V tiles of four ranges do not fit the LDS)
     constexpr int most = DVB <= 4 ? 4 : 2;

@@ -218,9 +218,10 @@ hipError_t launch_wide_t(const void* Q, const void* K, const void* V, void* O, i
 template <int DVB, bool HALF>
 hipError_t launch_wide(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, float scale, hipStream_t stream)
 {
-    // at most two query blocks per head: workgroups of two waves (2000 heads of N = 64, d = 192: 57.5 -> 51 us; 4000 of
-    // N = 32: 75 -> 50)
-    if (N <= 64) return launch_wide_t<DVB, HALF, 2, 1>(Q, K, V, O, BH, N, scale, stream, N);
+    // At most two query blocks per head: workgroups of two waves (2000 heads of N = 64, d = 192: 57.5 -> 51 us).  (Up to d = 128 such
+    // lengths are the other kernels'.)
+    if constexpr (DVB > 4)
+        if (N <= 64) return launch_wide_t<DVB, HALF, 2, 1>(Q, K, V, O, BH, N, scale, stream, N);
     // short rows: a tile of four sub-tiles per barrier (16 heads of N = 4096, d = 64: 85 -> 78 us; d = 128 with two: 130.5 -> 132.7)
     constexpr int SUBS = DVB <= 2 ? 4 : 1;
     // A last strip of at most 64 queries that would start another round of workgroups spends what ONE of its waves spends on
@@ -246,6 +247,8 @@ bool attention_wide_supported(int64_t BH, int64_t N, int64_t d)
 hipError_t launch_attention_wide(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                  float scale, hipStream_t stream)
 {
+    // one query block per head, nothing that waves could share
+    if (d > 128 && N <= 32) return launch_attention_short(DType::BF16, Q, K, V, O, BH, N, d, scale, stream);
     if (prefers_attention_ranges(BH, N, d)) return launch_attention_ranges(Q, K, V, O, BH, N, d, scale, 0, stream);
     switch ((int)(d / 16)) {
     case 1: return launch_wide<1, true>(Q, K, V, O, BH, (int)N, scale, stream);

@@ -104,6 +104,11 @@ bool prefers_attention_ranges(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_attention_ranges(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                    float scale, int q_base, hipStream_t stream);
 
+// The same for sequences of at most 32 tokens with 128 < d <= 256 (bf16: a multiple of 16, fp32: of 4): a wave per head, operands
+// straight from global memory.
+hipError_t launch_attention_short(DType dt, const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
+                                  float scale, hipStream_t stream);
+
 // The same for many short sequences (bf16, d = 64 with N <= 128, d = 32 with N <= 224): a wave per (head, 32 queries), operands
 // straight from global memory, the exponentials as they stand the operand of the second contraction.
 bool attention_tiny_supported(int64_t BH, int64_t N, int64_t d);

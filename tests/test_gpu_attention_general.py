@@ -281,3 +281,26 @@ def test_attention_f32_in_three_parts_infinite_last_value(heads, N, d):
     # (as in the bound above: d and N enough for B below 16)
     assert np.abs(O[0, h] - ref).max() <= ((2 * d + 4) * 16 + 2 * N + 16) * 2.0 ** -24 * 2 * np.abs(V[0, h]).max()
     assert np.isfinite(O[0, :h]).all()
+
+
+@pytest.mark.parametrize("d", [144, 160, 176, 192, 208, 224, 240, 256])
+@pytest.mark.parametrize("heads,N", [(3, 1), (3, 17), (3, 31), (600, 32), (300, 33), (300, 49), (300, 64)])
+def test_attention_bf16_large_heads_of_one_or_two_query_blocks(heads, N, d):
+    """One query block per head: a wave without LDS.  Two query blocks and enough heads: workgroups of two waves."""
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=4800 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=4801 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, 1, heads // 2 + 1, heads - 1):
+        _check(O[0, h], x, V, 0, h, (0, N), f"bf16 attention {heads} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("d", [132, 160, 164, 196, 224, 228, 256])
+@pytest.mark.parametrize("heads,N", [(1, 1), (5, 17), (5, 31), (600, 32)])
+def test_attention_f32_large_heads_of_one_query_block(heads, N, d):
+    """A wave per head without LDS: every padding of a row, rows past the end; both signs of the scale."""
+    scale = {"scale": -1.0 / math.sqrt(d)} if N == 17 else {}
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=4900 + N + d, row_factor=(0.5, 2.0), **scale)
+    V = wl.value_inputs(x, seed=4901 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in sorted({0, heads // 2, heads - 1}):
+        _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention {heads} heads N={N} d={d} head {h}")

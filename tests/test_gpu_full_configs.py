@@ -224,9 +224,9 @@ def test_more_than_two_to_the_31_elements_of_short_sequences_and_rows():
 
 
 @pytest.mark.parametrize("call,dtype,heads,N,d", [("attention", "f32", (1 << 24) + 64, 65, 4), ("attention", "f32", (1 << 23) + 64, 200, 4),
-                                                  ("attention", "bf16", (1 << 25) + 64, 1, 144), ("fused", "f32", (1 << 23) + 64, 3, 4)])
+                                                  ("attention", "bf16", (1 << 26) + 64, 1, 144), ("fused", "f32", (1 << 23) + 64, 3, 4)])
 def test_more_heads_than_one_launch_holds(call, dtype, heads, N, d):
-    """A launch holds less than 2^32 threads: with 256, 512, 128 and 512 threads a head these calls go out as two.  The first
+    """A launch holds less than 2^32 threads: with 256, 512, 64 and 512 threads a head these calls go out as two.  The first
     heads, those at the end of the first launch and the last ones; every output written."""
     import paper_2407_13885_amd as attnw
     torch.manual_seed(78)
