@@ -293,6 +293,17 @@ hipError_t launch_f32_ranges(const void* Q, const void* K, const void* V, void* 
     } else {
         if (N <= 32) return launch_f32_t<DVB, 1, 1>(Q, K, V, O, BH, N, d, scale, stream);
     }
+    // Two, three or (d <= 64) five query blocks per head, more heads than compute units, about one block per SIMD (d <= 64 with
+    // three or five: two): workgroups of several waves, not all with queries, come to unequal numbers on the compute units; one-wave
+    // workgroups do not.  Measured, us, several waves / one: 270 heads of N = 64, d = 32 7.5 / 5.6, 293 of N = 64, d = 128 23.0 / 16.0, 304
+    // of N = 68, d = 128 31 / 21, 450 of N = 40, d = 64 12.1 / 9.1, 539 of N = 96, d = 32 14.0 / 11.0, 300 of N = 140, d = 64 38 / 28; beyond:
+    // 1000 of N = 40, d = 64 14.9 / 16.4, 600 of N = 64, d = 128 26 / 36, 400 of N = 128, d = 64 24.1 / 24.7; below: 200 of N = 64, d = 128
+    // 13.9 / 14.5.
+    if constexpr (DVB <= 4) {
+        const int64_t blocks = (N + 31) / 32, most = (DVB <= 2 && blocks > 2 ? 8 : 4) * (int64_t)compute_units();
+        if ((blocks <= 3 || (DVB <= 2 && blocks == 5)) && BH > compute_units() && BH * blocks <= most)
+            return launch_f32_t<DVB, 1, 1>(Q, K, V, O, BH, N, d, scale, stream);
+    }
     if (N <= 64) return launch_f32_t<DVB, 2, 1>(Q, K, V, O, BH, N, d, scale, stream);
     // (d > 128: the K and V tiles of four ranges do not fit the LDS)
     constexpr int most = DVB <= 4 ? 4 : 2;

@@ -304,3 +304,14 @@ def test_attention_f32_large_heads_of_one_query_block(heads, N, d):
     O = gu.to_f64(_run(x, V))
     for h in sorted({0, heads // 2, heads - 1}):
         _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention {heads} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("d", [4, 36, 64, 100, 128])
+@pytest.mark.parametrize("heads,N", [(300, 33), (300, 64), (300, 65), (300, 96), (300, 129), (300, 160)])
+def test_attention_f32_one_wave_workgroups_of_a_few_blocks(heads, N, d):
+    """More heads than compute units, each of two, three or five query blocks: a workgroup per block, the last of one query or full."""
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5000 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=5001 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads // 2 + 1, heads - 1):
+        _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention {heads} heads N={N} d={d} head {h}")
