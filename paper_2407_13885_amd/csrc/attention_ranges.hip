@@ -264,14 +264,15 @@ hipError_t launch_ranges(const void* Q, const void* K, const void* V, void* O, i
 
 // A round of 32-query workgroups (one per compute unit) against a round of the 256-query workgroups of the kernels that
 // give every wave all keys.  N = 4096, us: d = 128 30 a round (one head 27) against 110; d = 64 15 against 75; d = 256
-// 80 against 190.  Two exceptions: 48 heads of N = 512, d = 128 (three rounds) 24 against 21.6; 100 heads of N = 65, d = 160
-// (two) 7.9 against 7.0.
+// 80 against 190.  Below 1024 keys a round of the larger workgroups is worth fewer: three rounds, d = 128: 226 heads of N = 85 11.5
+// against 6.8, 150 of N = 150 14.0 against 10.2, 100 of N = 200 15.9 against 12.7, 48 of N = 512 24 against 21.6 (d = 80 up to 256
+// keys: 6.0 / 5.3, 7.2 / 7.6, 8.1 / 9.0); 100 heads of N = 65, d = 160 (two) 7.9 against 7.0.
 bool prefers_attention_ranges(int64_t BH, int64_t N, int64_t d)
 {
     const int64_t cus = compute_units();
     const int64_t blocks = (BH * ((N + 31) / 32) + cus - 1) / cus, strips = (BH * ((N + 255) / 256) + cus - 1) / cus;
     if (d <= 64) return blocks <= 4 * strips;
-    if (d <= 128) return blocks <= (N > 256 && N < 1024 ? 2 : 3) * strips;
+    if (d <= 128) return blocks <= (N >= 1024 || (N <= 256 && d <= 96) ? 3 : 2) * strips;
     return blocks <= (N <= 128 ? 1 : 2) * strips;
 }
 

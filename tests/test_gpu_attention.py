@@ -242,3 +242,14 @@ def test_attention_every_wave_all_keys(N, d):
     assert np.isfinite(O).all()
     for h in (0, 64, H - 1):
         _check_rows(O[0, h], x, V, 0, h, (0, N), f"attention {H} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("d", [112, 128])
+@pytest.mark.parametrize("H,N", [(200, 65), (226, 85), (150, 150), (100, 200)])
+def test_attention_one_round_of_wide_strips(H, N, d):
+    """A workgroup of eight waves per head although most of its waves have no queries."""
+    x = wl.fused_inputs("t", "bf16", 1, H, N, d, seed=5500 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=5501 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, H // 2, H - 1):
+        _check_rows(O[0, h], x, V, 0, h, (0, N), f"attention {H} heads N={N} d={d} head {h}")
