@@ -253,9 +253,13 @@ hipError_t launch_ranges(const void* Q, const void* K, const void* V, void* O, i
     // where there are not as many sub-tiles (32 heads of N = 256, d = 128: eight 7.6 us, four 7.1).  More workgroups than
     // that, and a short sweep: two waves, so that the beginning and the merge of one workgroup are covered by the sweep
     // of another (d = 128: 32 heads of N = 512 16.7 -> 13.7, 64 of 256 14.1 -> 9.5, 250 of 80 11.9 -> 7.0; sixteen of
-    // 1024 no different, twelve of 2048 50 -> 74).
-    const bool rounds = BH * ((N - q_base + 31) / 32) > compute_units();
-    if (N <= 64 || (rounds && N <= 512)) return launch_ranges_t<DVB, HALF, 2>(Q, K, V, O, BH, N, scale, q_base, stream);
+    // 1024 no different, twelve of 2048 50 -> 74).  Four waves up to twice as many workgroups where a compute unit holds two such
+    // (d <= 96: 20 heads of N = 512, us, two / four waves: d = 32 7.2 / 5.2, 64 10.0 / 7.8, 96 11.7 / 9.1; 40 of 357, d = 64 8.5 / 7.1; 128
+    // of 128 alike; beyond twice: 100 heads of N = 300, d = 64 8.9 / 10.4).
+    const int64_t blocks = BH * ((N - q_base + 31) / 32), cus = compute_units();
+    if (DVB <= 3 && N > 64 && N <= 512 && blocks > cus && blocks <= 2 * cus)
+        return launch_ranges_t<DVB, HALF, 4>(Q, K, V, O, BH, N, scale, q_base, stream);
+    if (N <= 64 || (blocks > cus && N <= 512)) return launch_ranges_t<DVB, HALF, 2>(Q, K, V, O, BH, N, scale, q_base, stream);
     if (DVB > 4 || N <= 256) return launch_ranges_t<DVB, HALF, 4>(Q, K, V, O, BH, N, scale, q_base, stream);
     return launch_ranges_t<DVB, HALF, DVB <= 4 ? 8 : 4>(Q, K, V, O, BH, N, scale, q_base, stream);
 }

@@ -253,3 +253,14 @@ def test_attention_one_round_of_wide_strips(H, N, d):
     O = gu.to_f64(_run(x, V))
     for h in (0, H // 2, H - 1):
         _check_rows(O[0, h], x, V, 0, h, (0, N), f"attention {H} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("d", [16, 32, 48, 64, 80, 96])
+@pytest.mark.parametrize("H,N", [(128, 65), (100, 129), (40, 225), (20, 512)])
+def test_attention_two_small_workgroups_per_compute_unit(H, N, d):
+    """Up to twice as many blocks of 32 queries as compute units: four waves share the keys of a block, some without a sub-tile."""
+    x = wl.fused_inputs("t", "bf16", 1, H, N, d, seed=5600 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=5601 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, H // 2, H - 1):
+        _check_rows(O[0, h], x, V, 0, h, (0, N), f"attention {H} heads N={N} d={d} head {h}")
