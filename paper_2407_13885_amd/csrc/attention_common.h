@@ -1,5 +1,5 @@
-// Shared by the attention kernels that keep K and V in LDS as they lie in memory: chunk swizzles, the exchange between
-// the two half-waves of a query, the weights of a 32-key sub-tile.
+// Shared by the attention kernels: the exchange between the two half-waves of a query, and the chunk swizzles of those that keep
+// K and V in LDS as they lie in memory.
 #pragma once
 
 #include "qk_common.h"

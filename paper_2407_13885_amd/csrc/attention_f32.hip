@@ -8,9 +8,9 @@
 // either contraction needs 256 bytes from LDS, a fraction of what the LDS delivers in that time, so all that
 // counts is that a SIMD always has a matrix instruction to issue: K and V are staged in LDS by transfers that run
 // while the other contraction of the tile is under way, and the softmax of one wave is covered by the matrix
-// instructions of the other wave on its SIMD (two workgroups per compute unit up to d = 128).  Measured, 16 heads of
-// N = 4096, against one wave per workgroup with operands straight from the caches: d = 64 0.73 -> 0.52 ms, 128 2.09 -> 1.01
-// (136 TFLOP/s), 256 3.97 -> 2.11; one head, d = 128 1.03 -> 0.16 ms.
+// instructions of the other wave on its SIMD (two workgroups per compute unit up to d = 128).  Measured, N = 4096, against
+// one wave per workgroup with operands straight from the caches: 16 heads of d = 256 3.97 -> 2.11 ms (130 TFLOP/s), one head of
+// d = 128 1.03 -> 0.16.  (Many heads with d <= 128: attention_f32_split.hip; at most 32 keys with d > 128: attention_short.hip.)
 //
 // A workgroup of (usually) four waves: WQ query blocks of 32 x WK key ranges.  A tile is 32 keys per key range; K and V have one
 // buffer each, and every tile has two phases:
@@ -22,30 +22,11 @@
 // as in memory.
 // WK > 1 (problems of a few heads): a wave takes one 32-key sub-tile of every tile and the partial results of a query
 // block, each with its own reference exponent and sum, are merged through LDS at the end.
+#include "attention_common.h"
 #include "launchers.h"
-#include "qk_common.h"
 
 namespace attnw {
 namespace {
-
-__device__ __forceinline__ float half_max_f(float x)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-#else
-    return x;
-#endif
-}
-__device__ __forceinline__ float half_sum_f(float x)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-#else
-    return x;
-#endif
-}
 
 __device__ const u32x4 kZeros = {0u, 0u, 0u, 0u};
 
@@ -61,6 +42,7 @@ struct F32Cfg {
     static constexpr int SLOTS = 2 + DVB * 16;    // merge: reference exponent, sum, output accumulators
     static constexpr int MERGE = WK > 1 ? NW * SLOTS * 256 : 0;
     static constexpr int LDS = 2 * TILE > MERGE ? 2 * TILE : MERGE;
+    static_assert(2 * TILE <= kDirectLds, "reach of direct transfers");
 };
 
 // DVB: 32-column blocks of an output row, ceil(d / 32); rows are padded to 32 DVB elements on chip (rb: bytes of a row
@@ -159,7 +141,7 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
             float tm = max3(s[0], s[1], s[2]);
 #pragma unroll
             for (int r = 3; r < 15; r += 2) tm = max3(tm, s[r], s[r + 1]);
-            const float mbn = half_max_f(fmaxf(tm, s[15])) * c;   // (keys past the end are copies of key N-1: no new maximum)
+            const float mbn = half_wave_max(fmaxf(tm, s[15])) * c;   // (keys past the end are copies of key N-1: no new maximum)
             if (__builtin_amdgcn_ballot_w64(mbn > mb_run + kLazy) != 0) {
                 const float mb_new = fmaxf(mb_run, mbn);
                 const float alpha = fast_exp2(mb_run - mb_new);   // exactly 1 for lanes whose exponent stands
@@ -220,7 +202,7 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
             f[j] = fast_exp2(grp[j * SLOTS * 64] - M);
             L = __builtin_fmaf(f[j], grp[j * SLOTS * 64 + 64], L);
         }
-        const float inv = 1.0f / half_sum_f(L);
+        const float inv = 1.0f / half_wave_sum(L);
         if (q0 + l32 >= N) return;
         for (int b = wk; b < DVB; b += WK)
 #pragma unroll
@@ -235,7 +217,7 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
                     *reinterpret_cast<f32x4*>(orow + (b * 32 + 8 * i) * 4) = o * inv;
             }
     } else {
-        const float inv = 1.0f / half_sum_f(l_run);
+        const float inv = 1.0f / half_wave_sum(l_run);
         if (q0 + l32 >= N) return;
 #pragma unroll
         for (int b = 0; b < DVB; ++b)

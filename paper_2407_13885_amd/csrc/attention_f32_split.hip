@@ -6,7 +6,8 @@
 // max-subtracted softmax of the Softmax section, Eq. 1, is applied incrementally as in the other kernels.)
 //
 // What bounds it: the matrix instruction (12 x 32 cycles per 32 queries, 32 keys and 16 columns of d, where the fp32
-// instruction takes 16 x 64), under the board's power cap.  Eight waves of 32 queries share a tile of 32 keys: splitting a
+// instruction takes 16 x 64), under the board's power cap: busy 63 % of SIMD cycles at d = 128, vector ALU 34 %, both 8 % (14 registers
+// spilled there: 4 of them are read back twice per tile, the others belong to the restart).  Eight waves of 32 queries share a tile of 32 keys: splitting a
 // K or V element costs six vector instructions, spread over 256 queries.  A thread loads 8 elements of a row, splits them
 // and writes a 16-byte chunk to each of the three planes of the tile; planes lie as rows in memory do, chunks
 // swizzled, and V is turned by the transposing LDS read.  Double buffered, one barrier per tile.

@@ -44,8 +44,8 @@ struct AttnCfg {
     static constexpr int V_LOADS = 2 * CPR / NW;  // wave-wide loads of 64 keys x one chunk, per wave and tile
     static constexpr int VT_PITCH = BN * 2 + 16;  // bytes of one Vt row (one output column, 128 keys)
     static constexpr int VT_BYTES = D * VT_PITCH;
-    static constexpr int RPL = CPR >= 16 ? 1 : 16 / CPR;
-    static constexpr int SWZ_MASK = (CPR >= 16 ? 16 : CPR) - 1;
+    static constexpr int RPL = 16 / CPR;          // (4 or 8 chunks per row)
+    static constexpr int SWZ_MASK = CPR - 1;
     static constexpr int LDS_TOTAL = 2 * K_TILE_BYTES + 2 * VT_BYTES;
 };
 
@@ -61,7 +61,7 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
     constexpr int NW = C::NW, QW = C::QW, BM = C::BM, BN = C::BN, G = C::G, CPR = C::CPR, DVB = C::DVB;
     constexpr int K_TILE_BYTES = C::K_TILE_BYTES, K_LOADS = C::K_LOADS, V_LOADS = C::V_LOADS;
     constexpr int VT_PITCH = C::VT_PITCH, VT_BYTES = C::VT_BYTES;
-    static_assert(2 * K_TILE_BYTES <= 65536, "the K buffers sit in the first 64 KiB of LDS (transfer base register)");
+    static_assert(2 * K_TILE_BYTES <= kDirectLds, "reach of direct transfers");
     static_assert((2 * CPR) % NW == 0, "V tile load shape");
 
     __shared__ __align__(1024) char lds[C::LDS_TOTAL];

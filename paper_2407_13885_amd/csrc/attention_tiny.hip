@@ -43,7 +43,7 @@ void attention_tiny_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
     constexpr int NST = 32 * CPR / 64;            // store instructions per unit
     constexpr int NV = NKB * 32 * ROW_B / 1024;   // 1-KiB wave transfers that bring the V of a head
     constexpr int NQK = (NKB + 1) * G;            // 16-byte loads per lane that bring K and the Q rows of a unit
-    __shared__ __align__(1024) char v_lds[kWaves][NV * 1024];   // (first in LDS: the transfers address the first 64 KiB)
+    __shared__ __align__(1024) char v_lds[kWaves][NV * 1024];
     __shared__ __align__(16) uint16_t o_lds[kWaves][32 * PITCH];
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -4,15 +4,16 @@
 // with V is what the section "Limitations and future Directions" names as the next thing to fuse.  The
 // max-subtracted softmax of the Softmax section, Eq. 1, is applied incrementally as in attention_kernels.hip.)
 //
-// What bounds it: the LDS port (every matrix instruction takes one 1 KiB operand fragment from LDS) and, up to d = 128, the
-// softmax between the two contractions of a wave, under the board's power cap.  A wave owns 32 queries: at d = 256 its 128
-// accumulators and 64 registers of Q fragments leave no room for a second query block at two waves per SIMD.
+// What bounds it: the order inside a wave (scores, softmax, output), with the two waves of a SIMD brought into step by the barrier
+// of every tile, under the board's power cap.  Counters at d = 128 / 256, of SIMD cycles: matrix pipe 51 / 59 %, vector ALU 46 / 34 %,
+// both at once 13 / 8 %; the 1 KiB fragments of the matrix instructions fill about half of what the LDS can deliver.  A wave owns 32
+// queries: at d = 256 its 128 accumulators and 64 registers of Q fragments leave no room for a second query block at two
+// waves per SIMD.
 //
 // A workgroup is WQ query blocks of 32; a tile is SUBS x 32 keys.  K and V lie in LDS as they lie in memory, chunks
 // swizzled: V is turned by the transposing LDS read (ds_read_b64_tr_b16: 4 keys x 16 columns, a lane gets the four keys of
-// its column), so both tiles travel global -> LDS directly, without registers or a scatter.  Double buffered (4 tiles in
-// the 64 KiB that the direct transfers can address), one barrier per tile.  (Problems of a few heads:
-// attention_ranges.hip.)  Measured, 16 heads of N = 4096: d = 256 928 -> 238 us (1157 TFLOP/s), 192 700 -> 185, 144 633 -> 157
+// its column), so both tiles travel global -> LDS directly, without registers or a scatter.  Double buffered (4 tiles, 64 KiB at
+// d = 256), one barrier per tile.  (Problems of a few heads: attention_ranges.hip; of at most 32 keys, d > 128: attention_short.hip.)  Measured, 16 heads of N = 4096: d = 256 928 -> 238 us (1157 TFLOP/s), 192 700 -> 185, 144 633 -> 157
 // against one wave per workgroup with operands straight from the caches; d = 96 132 -> 106, d = 128 134 -> 130.5, forty
 // heads of N = 600, d = 128 26.7 -> 23.6 against 128-key tiles, V scattered transposed and rows padded to 128 columns.
 #include "launchers.h"
@@ -44,7 +45,7 @@ void attention_wide_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
     constexpr int NW = WQ, DB = C::DB, CPR = C::CPR, BN = C::BN, TILE = C::TILE, XFERS = C::XFERS;
     constexpr int rb = DB - (HALF ? 32 : 0);
     constexpr int G = rb / 32;                    // 32-byte contraction groups of a row
-    static_assert(4 * TILE <= 65536, "direct transfers address the first 64 KiB of LDS");
+    static_assert(4 * TILE <= kDirectLds, "reach of direct transfers");
 
     __shared__ __align__(1024) char lds[4 * TILE];
     char* const k_lds = lds;
@@ -222,7 +223,8 @@ hipError_t launch_wide(const void* Q, const void* K, const void* V, void* O, int
     // lengths are the other kernels'.)
     if constexpr (DVB > 4)
         if (N <= 64) return launch_wide_t<DVB, HALF, 2, 1>(Q, K, V, O, BH, N, scale, stream, N);
-    // short rows: a tile of four sub-tiles per barrier (16 heads of N = 4096, d = 64: 85 -> 78 us; d = 128 with two: 130.5 -> 132.7)
+    // short rows: a tile of four sub-tiles per barrier (16 heads of N = 4096: d = 16 65.5 -> 57 us, 48 79.9 -> 75.0; d = 128 with two:
+    // 130.5 -> 132.7)
     constexpr int SUBS = DVB <= 2 ? 4 : 1;
     // A last strip of at most 64 queries that would start another round of workgroups spends what ONE of its waves spends on
     // a full strip: it follows as a launch of the kernel for few heads (16 heads of N = 4097, d = 128: 209 -> 170 us).

@@ -98,7 +98,8 @@ int attnw_attention(const void* Q, const void* K, const void* V, void* O, int64_
         return ATTNW_ERR_ALIAS;
     hipStream_t st = static_cast<hipStream_t>(stream);
     // many short sequences: the kernel in which a wave works alone on a (head, 32 queries) pair
-    // (ATTNW_ATTENTION_KERNEL=tiny puts every shape it takes on it, =tiled none: tests and measurements compare them)
+    // (ATTNW_ATTENTION_KERNEL=tiny puts every shape it takes on it, =tiled none, whichever kernel then takes it: tests and
+    // measurements compare them)
     if (f32) return attnw::launch_attention_f32(Q, K, V, O, BH, N, d, scale, st) == hipSuccess ? ATTNW_OK : ATTNW_ERR_LAUNCH;
     if (attnw::attention_tiny_supported(BH, N, d)) {
         const char* force = getenv("ATTNW_ATTENTION_KERNEL");

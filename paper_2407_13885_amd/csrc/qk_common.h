@@ -57,7 +57,9 @@ __device__ __forceinline__ void dma16(const char* __restrict__ src, char* __rest
 
 // The same transfer issued from inline assembly, which the compiler's wait-count pass does not see: the
 // only waits on it are the explicit vmcnt waits of the caller (vector-memory operations retire in order).
-// lds_base = byte offset in LDS, wave-uniform, below 64 KiB (it travels in M0).
+// lds_base = byte offset in LDS, wave-uniform (it travels in M0), the transfer inside the first kDirectLds bytes.
+// (More than 64 KiB: attention_f32.hip stages V from there up to 128 KiB, and its results there agree with the oracle.)
+constexpr int kDirectLds = 128 * 1024;
 __device__ __forceinline__ void dma16_untracked(const char* src, uint32_t lds_base)
 {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -88,7 +88,7 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
     constexpr int K_TILE_BYTES = C::K_TILE_BYTES, LOADS = C::LOADS, ST_PITCH = C::ST_PITCH;
     constexpr int ST_BYTES = C::ST_BYTES, CPS = C::CPS, RPI = C::RPI, NF = C::NF, NCH = C::NCH;
     static_assert(SUBS == 2 && NBUF == 2, "accumulator sets, fragment prefetch and buffers alternate per step / tile");
-    static_assert(C::LDS_K <= 65536, "the K buffers sit in the first 64 KiB of LDS (transfer base register)");
+    static_assert(C::LDS_K <= kDirectLds, "reach of direct transfers");
     static_assert(NCH >= NF + 2 && 16 % NCH == 0, "chunk layout of a step");
     static_assert((BN * CPR) % (64 * NW) == 0, "tile transfer shape");
 

@@ -92,12 +92,25 @@ def test_attention_head_sizes_between_the_powers_of_two(N, d):
 @pytest.mark.parametrize("d", [32, 48, 64, 80, 112, 128])
 @pytest.mark.parametrize("N", [1, 33, 129, 257, 600])
 def test_attention_many_heads_take_the_wide_strips(N, d):
-    """Few heads run on blocks of 32 queries whose keys are shared between the waves of a workgroup (the tests above); with more than two
-    such strips per compute unit the library takes 256-query strips, every wave walking all keys.  Enough heads for
-    that, first, middle and last head checked."""
+    """Two rounds of 64-query strips on the chip: with d >= 80 and N >= 129 the library takes 256-query strips, every wave walking all
+    keys, otherwise blocks of 32 queries whose keys the waves share (d <= 64 on 256-query strips: the next test).  First, middle
+    and last head checked."""
     H = 512 // ((N + 63) // 64) + 1
     x = wl.fused_inputs("t", "bf16", 1, H, N, d, seed=2300 + N + d, row_factor=(0.5, 2.0))
     V = wl.value_inputs(x, seed=2301 + N)
+    O = gu.to_f64(_run(x, V))
+    assert np.isfinite(O).all()
+    for h in (0, H // 2, H - 1):
+        _check_rows(O[0, h], x, V, 0, h, (0, N), f"attention wide strips N={N} d={d} head {h} of {H}")
+
+
+@pytest.mark.parametrize("N,d", [(129, 64), (257, 64), (161, 32), (257, 32), (384, 32)])
+def test_attention_very_many_heads_of_one_to_three_tiles(N, d):
+    """Enough heads for 256-query strips at d = 32 and 64: one to three tiles of 128 keys, the last of one key, of 33 or whole, waves
+    past the end, a last strip of one query as a launch of its own."""
+    H = 1300
+    x = wl.fused_inputs("t", "bf16", 1, H, N, d, seed=2400 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=2401 + N)
     O = gu.to_f64(_run(x, V))
     assert np.isfinite(O).all()
     for h in (0, H // 2, H - 1):

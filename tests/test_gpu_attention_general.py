@@ -145,14 +145,28 @@ def test_attention_general_is_deterministic():
 @pytest.mark.parametrize("d", [4, 36, 64, 96, 128, 256])
 @pytest.mark.parametrize("N", [1, 100, 129])
 def test_attention_f32_many_heads(N, d):
-    """Enough heads that a workgroup takes 128 queries and every wave all keys (fewer heads share the keys of a query
-    block between the waves of a workgroup): strips with waves past the end, one key, one key past a tile."""
+    """Enough heads that every wave takes all keys (fewer heads share the keys of a query block between the waves of a
+    workgroup): one key, 128-query workgroups with a wave that is not full (N = 100, and 129 with d = 256), operands in three bf16
+    parts (N = 129 up to d = 128)."""
     heads = 512
     x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=3900 + N + d, row_factor=(0.5, 2.0))
     V = wl.value_inputs(x, seed=3901 + N)
     O = gu.to_f64(_run(x, V))
     assert np.isfinite(O).all()
     for h in (0, 1, heads // 2 + 1, heads - 1):
+        _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention {heads} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("d", [4, 32, 36, 64, 100, 128])
+def test_attention_f32_several_strips_of_all_keys(d):
+    """Forty heads of 700 keys: several 128-query workgroups per head on the fp32 instruction (too few 256-query strips for operands in
+    parts), the last with a wave of 28 queries and waves past the end."""
+    heads, N = 40, 700
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=4000 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=4001 + N)
+    O = gu.to_f64(_run(x, V))
+    assert np.isfinite(O).all()
+    for h in (0, heads // 2 + 1, heads - 1):
         _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention {heads} heads N={N} d={d} head {h}")
 
 

@@ -90,6 +90,7 @@ def test_scale_values_and_constant_values(N, d, monkeypatch):
 
 
 def test_agrees_with_the_tiled_kernel_and_is_deterministic(monkeypatch):
+    """Against the kernel that takes the shape otherwise: blocks of 32 queries whose waves share the keys."""
     x = wl.fused_inputs("t", "bf16", 2, 40, 49, 32, seed=5)
     V = wl.value_inputs(x, seed=6)
     monkeypatch.setenv("ATTNW_ATTENTION_KERNEL", "tiny")
