@@ -16,9 +16,14 @@
  *     are [B][H][N][N] (key index fastest) or [rows][cols] (cols fastest).
  *   - `dtype` selects ONE element type for inputs and output: ATTNW_F32
  *     (IEEE binary32) or ATTNW_BF16 (upper 16 bits of a binary32).  All
- *     arithmetic between load and store is fp32 (bf16 inputs are multiplied on
- *     the matrix cores with fp32 accumulation); bf16 results are rounded once,
- *     to nearest even, at the store.
+ *     arithmetic between load and store is fp32 or no less exact: bf16 inputs
+ *     are multiplied on the matrix cores with fp32 accumulation; fp32 inputs
+ *     with d <= 128 and enough heads (attnw_fused, attnw_attention) go to the
+ *     bf16 matrix instruction as three bf16 parts each, which hold all 24 bits
+ *     of every fp32 number, six of the nine products kept (those above 2^-24
+ *     of the whole), fp32 accumulation: errors measured at or below those of
+ *     the fp32 instruction over the whole range of fp32 magnitudes.  bf16
+ *     results are rounded once, to nearest even, at the store.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued on it and the call returns without waiting.  A call is
  *     one kernel launch (two for a softmax of few rows too long for the
@@ -26,8 +31,9 @@
  *     the keys of a strip are split over workgroups -- the first launch then
  *     uses parts of P as scratch --, or whose last few queries of a ragged
  *     length get one or two launches of their own; two for an attention output
- *     whose last few queries of a ragged length get a launch of their own) and
- *     nothing else on the stream, so it can be
+ *     whose last few queries of a ragged length get a launch of their own; as
+ *     many as are needed for so many heads -- millions -- that one launch would
+ *     hold 2^32 threads) and nothing else on the stream, so it can be
  *     recorded by stream capture and replayed as part of a graph.
  *   - Return value: ATTNW_OK (0) or a negative attnw_status.  Nothing throws or
  *     aborts.  Arguments are validated before any HIP call, in this order:
@@ -179,15 +185,17 @@ int attnw_scale(const void *X, void *Y, int64_t count, float scale,
  * row maximum and sum (Eq. 1 applied incrementally).
  * ATTNW_BF16: d a multiple of 16 up to 256, any N >= 1.  The weights are rounded
  * to bf16 before they multiply V on the matrix cores, the output once more at the
- * store.  (d up to 128 runs tiled through on-chip memory -- d = 32, 64, 128 with N
- * a multiple of 256 on the fast path, other head sizes padded on chip, other
- * lengths with the rows past the end clamped and masked; few heads are spread over
- * the chip by key ranges; sequences of up to 128 tokens with d = 64, or 160 with
- * d = 32, run a wave per head and 32 queries without on-chip tiles.  Larger d reads its
- * operands straight from device memory.  ATTNW_ATTENTION_KERNEL=tiny / =tiled in the
- * environment puts every shape that the wave-per-head kernel takes on it / none.)
- * ATTNW_F32: d a multiple of 4 up to 256, any N >= 1.  Both contractions on the
- * fp32 matrix instruction: fp32 products, sums and weights, no rounding but fp32's.
+ * store.  (Many heads: 256-query strips, K and V tiled through on-chip memory; few
+ * heads: blocks of 32 queries whose keys are shared between the waves of a
+ * workgroup; sequences of up to 128 tokens with d = 64, or 160 with d = 32, a wave
+ * per head and 32 queries, and of up to 32 tokens with d above 128 a wave per head,
+ * both without on-chip tiles.  ATTNW_ATTENTION_KERNEL=tiny / =tiled in the
+ * environment puts every shape that the wave-per-head kernel for d = 32 and 64
+ * takes on it / none.)
+ * ATTNW_F32: d a multiple of 4 up to 256, any N >= 1.  fp32 products, sums and
+ * weights, no rounding but fp32's, on the fp32 matrix instruction; many heads with
+ * d <= 128 on the bf16 one with operands (weights among them) in three parts, see
+ * above.
  * Anything else: ATTNW_ERR_UNSUPPORTED.  O must not overlap Q, K or V.
  * Validation order as for attnw_fused.
  */
