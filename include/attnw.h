@@ -32,8 +32,8 @@
  *     uses parts of P as scratch --, or whose last few queries of a ragged
  *     length get one or two launches of their own; two for an attention output
  *     whose last few queries of a ragged length get a launch of their own; as
- *     many as are needed for so many heads -- millions -- that one launch would
- *     hold 2^32 threads) and nothing else on the stream, so it can be
+ *     many as are needed for so many heads or softmax rows -- millions -- that
+ *     one launch would hold 2^32 threads) and nothing else on the stream, so it can be
  *     recorded by stream capture and replayed as part of a graph.
  *   - Return value: ATTNW_OK (0) or a negative attnw_status.  Nothing throws or
  *     aborts.  Arguments are validated before any HIP call, in this order:

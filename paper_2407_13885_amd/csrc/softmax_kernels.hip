@@ -607,24 +607,36 @@ void softmax_long_kernel(const TI* S, TO* P, int64_t rows, int64_t cols, int chu
         Elem<TO>::store1(dst + tail0 + tid, fast_exp2((Elem<TI>::load1(src + tail0 + tid) - m) * kLog2e) * inv);
 }
 
+// Rows of a part of a launch: all that remain or `blocks` whole blocks of them.
+int64_t rows_of(int64_t remaining, int64_t blocks, int64_t per_block)
+{
+    return remaining < blocks * per_block ? remaining : blocks * per_block;
+}
+
 template <typename TI, typename TO, int R, int TPR>
 hipError_t launch_rows(const void* S, void* P, int64_t rows, int groups, hipStream_t stream)
 {
     constexpr int RPB = (TPR <= 64) ? 256 / TPR : 1;
-    const int64_t blocks = (rows + RPB - 1) / RPB;
-    const int threads = (TPR <= 64) ? 256 : TPR;
-    hipLaunchKernelGGL((softmax_rows_kernel<TI, TO, R, TPR>), dim3((uint32_t)blocks), dim3(threads), 0, stream,
-                       static_cast<const TI*>(S), static_cast<TO*>(P), rows, groups);
-    return hipGetLastError();
+    constexpr int threads = (TPR <= 64) ? 256 : TPR;
+    const int64_t cols = (int64_t)groups * (Elem<TI>::VEC > Elem<TO>::VEC ? Elem<TI>::VEC : Elem<TO>::VEC);
+    return launch_by_heads((rows + RPB - 1) / RPB, 1, threads, [&](int64_t first, int64_t blocks) {   // (parts of whole blocks of rows)
+        const int64_t row = first * RPB;
+        hipLaunchKernelGGL((softmax_rows_kernel<TI, TO, R, TPR>), dim3((uint32_t)blocks), dim3(threads), 0, stream,
+                           static_cast<const TI*>(S) + row * cols, static_cast<TO*>(P) + row * cols, rows_of(rows - row, blocks, RPB), groups);
+        return hipGetLastError();
+    });
 }
 
 template <typename TI, typename TO, int R, int TPR, int EG>
 hipError_t launch_elem(const void* S, void* P, int64_t rows, int cols, hipStream_t stream)
 {
     constexpr int RPB = 256 / TPR;
-    hipLaunchKernelGGL((softmax_elem_kernel<TI, TO, R, TPR, EG>), dim3((uint32_t)((rows + RPB - 1) / RPB)), dim3(256), 0,
-                       stream, static_cast<const TI*>(S), static_cast<TO*>(P), rows, cols);
-    return hipGetLastError();
+    return launch_by_heads((rows + RPB - 1) / RPB, 1, 256, [&](int64_t first, int64_t blocks) {
+        const int64_t row = first * RPB;
+        hipLaunchKernelGGL((softmax_elem_kernel<TI, TO, R, TPR, EG>), dim3((uint32_t)blocks), dim3(256), 0, stream,
+                           static_cast<const TI*>(S) + row * cols, static_cast<TO*>(P) + row * cols, rows_of(rows - row, blocks, RPB), cols);
+        return hipGetLastError();
+    });
 }
 
 // cols <= 1024 with cols % EG == 0: lanes per row and groups per lane by the number of groups
@@ -671,24 +683,29 @@ hipError_t launch_packed(const void* S, void* P, int64_t rows, int cols, int RW,
 {
     const int64_t its = (rows + RW - 1) / RW;
     if ((its + 3) / 4 > (int64_t)0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid((uint32_t)((its + 3) / 4));
-    const T* s_ = static_cast<const T*>(S);
-    T* p_ = static_cast<T*>(P);
-    if (EPL <= 2) hipLaunchKernelGGL((softmax_packed_kernel<T, 2>), grid, dim3(256), 0, stream, s_, p_, rows, cols, RW, CW, LPR);
-    else if (EPL <= 4) hipLaunchKernelGGL((softmax_packed_kernel<T, 4>), grid, dim3(256), 0, stream, s_, p_, rows, cols, RW, CW, LPR);
-    else hipLaunchKernelGGL((softmax_packed_kernel<T, 8>), grid, dim3(256), 0, stream, s_, p_, rows, cols, RW, CW, LPR);
-    return hipGetLastError();
+    return launch_by_heads((its + 3) / 4, 1, 256, [&](int64_t first, int64_t blocks) {   // (RW rows are whole chunks)
+        const int64_t row = first * 4 * RW, n = rows_of(rows - row, blocks, 4 * RW);
+        const dim3 grid((uint32_t)blocks);
+        const T* s_ = static_cast<const T*>(S) + row * cols;
+        T* p_ = static_cast<T*>(P) + row * cols;
+        if (EPL <= 2) hipLaunchKernelGGL((softmax_packed_kernel<T, 2>), grid, dim3(256), 0, stream, s_, p_, n, cols, RW, CW, LPR);
+        else if (EPL <= 4) hipLaunchKernelGGL((softmax_packed_kernel<T, 4>), grid, dim3(256), 0, stream, s_, p_, n, cols, RW, CW, LPR);
+        else hipLaunchKernelGGL((softmax_packed_kernel<T, 8>), grid, dim3(256), 0, stream, s_, p_, n, cols, RW, CW, LPR);
+        return hipGetLastError();
+    });
 }
 
 template <typename T, int R, int TPR>
 hipError_t launch_rows_shifted(const void* S, void* P, int64_t rows, int64_t cols, hipStream_t stream)
 {
     constexpr int RPB = (TPR <= 64) ? 256 / TPR : 1;
-    const int64_t blocks = (rows + RPB - 1) / RPB;
-    const int threads = (TPR <= 64) ? 256 : TPR;
-    hipLaunchKernelGGL((softmax_rows_shifted_kernel<T, R, TPR>), dim3((uint32_t)blocks), dim3(threads), 0, stream,
-                       static_cast<const T*>(S), static_cast<T*>(P), rows, (int)cols);
-    return hipGetLastError();
+    constexpr int threads = (TPR <= 64) ? 256 : TPR;
+    return launch_by_heads((rows + RPB - 1) / RPB, 1, threads, [&](int64_t first, int64_t blocks) {
+        const int64_t row = first * RPB;
+        hipLaunchKernelGGL((softmax_rows_shifted_kernel<T, R, TPR>), dim3((uint32_t)blocks), dim3(threads), 0, stream,
+                           static_cast<const T*>(S) + row * cols, static_cast<T*>(P) + row * cols, rows_of(rows - row, blocks, RPB), (int)cols);
+        return hipGetLastError();
+    });
 }
 
 template <typename TI, typename TO>

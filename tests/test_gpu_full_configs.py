@@ -248,3 +248,23 @@ def test_more_heads_than_one_launch_holds(call, dtype, heads, N, d):
         tol = 2.0 ** -7 if dtype == "bf16" else 2.0 ** -12
         err = (out[h0:h0 + 16].double().cpu() - ref).abs()
         assert bool((err <= tol * (size + ref.abs())).all()), f"heads {h0}..: worst {float(err.max()):.3e}"
+
+
+@pytest.mark.parametrize("rows,cols", [((1 << 26) + 100, 264), ((1 << 28) + 100, 65)])
+def test_more_softmax_rows_than_one_launch_holds(rows, cols):
+    """2^24 and some workgroups of 256 threads: two launches, rows on and off the 16-byte boundaries.  In place; every row sum, the
+    first rows, those around the end of the first launch and the last ones."""
+    import paper_2407_13885_amd as attnw
+    torch.manual_seed(79)
+    S = torch.empty(rows, cols, device="cuda", dtype=torch.bfloat16)
+    step = 1 << 22
+    for i in range(0, rows, step):
+        S[i:i + step] = torch.randn(min(step, rows - i), cols, device="cuda") * 2
+    picks = [(r, r + 64) for r in (0, rows // 2, rows - 600, rows - 300, rows - 64)]
+    before = [S[a:b].clone() for a, b in picks]
+    attnw.attnw_softmax(S, S, rows, cols, attnw.ATTNW_BF16)
+    torch.cuda.synchronize()
+    worst = max(float((S[i:i + step].float().sum(-1) - 1).abs().max().item()) for i in range(0, rows, step))
+    assert worst <= gu.ROWSUM_BF16, f"row sum off by {worst:.3e}"
+    for (a, b), x in zip(picks, before):
+        gu.check_weights(gu.to_f64(S[a:b]), oracle.softmax(_bits(x), "bf16"), "bf16", f"softmax rows {a}..")
