@@ -76,6 +76,11 @@ hipError_t launch_qk_gang(const void* Q, const void* K, void* out, int64_t BH, i
 inline bool split_takes_scale(float scale) { return scale == 0.0f || scale >= 0x1p-78f || scale <= -0x1p-78f; }
 hipError_t launch_qk_f32_split(const void* Q, const void* K, void* P, int64_t BH, int64_t N, int64_t d, float scale, hipStream_t stream);
 
+// Fused attention weights or scaled scores, fp32, any N with N d < 2^28, d a multiple of 4 up to 256: the same with 32-query strips whose
+// scores stay in the registers of a workgroup (up to 2048 keys; the rest computed twice).
+hipError_t launch_qk_f32_strip(bool scores_only, const void* Q, const void* K, void* P, int64_t BH, int64_t N, int64_t d, float scale,
+                               hipStream_t stream);
+
 // Y = scale * X over count elements, rounded once to the storage type; X == Y allowed.
 hipError_t launch_scale(DType dt, const void* X, void* Y, int64_t count, float scale, hipStream_t stream);
 

@@ -811,18 +811,49 @@ bool prefers_gang(int64_t BH, int64_t N, int64_t d)
     return BH * (N / 128) < (int64_t)compute_units();
 }
 
+// fp32 weights on the two-sweep kernel that splits K once per 128 queries: rows on 16-byte boundaries, d <= 128, strips for at
+// least half of the compute units, and where it beats the 32-query strips of the next rule, which need four rounds of workgroups
+// for one of these.  Measured, this -> those, us: short sequences (1280 heads of N = 100, d = 64 49 -> 79; 150 of 128 10.5 -> 12.4;
+// 375 of 128, d = 32 13.7 -> 17.8) and rows past the 2048 keys that stay in registers (ten heads of 3000, d = 64 167 -> 185, seven
+// of 4096, d = 128 376 -> 416) stay; not 15 heads of 2048, d = 64 100 -> 95, 125 of 1024 235 -> 207, 31 of 1024, d = 128 99 -> 87, 160 of
+// 200 51 -> 37, and wherever the last round of the larger strips is not full (18 of 1024, d = 64 48 -> 36, 75 of 256 16.8 -> 15.6, four of
+// 4096 171 -> 117).
+bool prefers_f32_split(int64_t BH, int64_t N, int64_t d)
+{
+    const int64_t cus = compute_units(), large = BH * ((N + 127) / 128), small = BH * ((N + 31) / 32);
+    if (d > 128 || N % 4 != 0 || N < 64 || 2 * large < cus) return false;
+    const int64_t rounds = (large + cus - 1) / cus, small_rounds = (small + cus - 1) / cus;
+    if (small_rounds < 4 * rounds) return N < (d > 64 ? 192 : d > 32 ? 256 : 512);
+    return N > 2048 || N < (d > 64 ? 192 : 512) || d <= 32;
+}
+
+// fp32 on 32-query strips whose scores stay in registers: weights of everything that the rule above leaves but very short rows of
+// short sequences (1969 heads of N = 65, d = 8 62 -> 73 us); measured against the general kernel: two heads of 2976, d = 84 416 -> 60, one of
+// 128, d = 64 8.9 -> 5.3, one of 416, d = 128 69 -> 11.5, nine of 2743, d = 128 417 -> 242, 25 of 730, d = 228 221 -> 86, 182 of 700, d = 256
+// 1094 -> 497, 1969 of 65, d = 64 128 -> 89.  Scores: four of 996, d = 256 152 -> 33, 93 of 1025, d = 64 241 -> 184; not taken where the
+// general kernel streams whole tiles as fast (93 of 1024: d = 32 81 -> 98, d = 256 451 -> 487) or splits the keys of a few long rows
+// over workgroups (one of 2048, d = 64 16.5 -> 20).
+bool prefers_f32_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
+{
+    if (N * d >= (int64_t)1 << 28) return false;
+    const int64_t cus = compute_units(), strips = BH * ((N + 31) / 32);
+    if (!scores_only) return d > 16 || N >= 128 || strips <= cus;
+    if (N % 4 != 0) return true;
+    if (d > 128) return N % 128 != 0 || strips <= 4 * cus;
+    if (d > 64) return true;
+    if (N >= 2048 && 2 * strips < cus) return false;
+    return d > 32 || N < 128 || strips <= 2 * cus;
+}
+
 }  // namespace
 
 hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, void* out,
                      int64_t BH, int64_t N, int64_t d, float scale, hipStream_t stream)
 {
-    // fp32 weights with 128-query strips for at least half of the compute units (the rest splits its keys over workgroups: four
-    // heads of N = 2048, d = 64 65 us against 98), rows on 16-byte boundaries, d <= 128: the bf16 instruction on operands in
-    // three parts.  Measured, us: eight heads of N = 2048, d = 64 168 -> 91, 300 of 196 83 -> 49, 600 of 100 51 -> 32, 1000 of 64
-    // 45 -> 26, 100 of 512, d = 128 154 -> 106.
-    if (dt == DType::F32 && !scores_only && d <= 128 && N % 4 == 0 && N >= 64 && 2 * BH * ((N + 127) / 128) >= compute_units() &&
-        split_takes_scale(scale))
+    if (dt == DType::F32 && !scores_only && prefers_f32_split(BH, N, d) && split_takes_scale(scale))
         return launch_qk_f32_split(Q, K, out, BH, N, d, scale, stream);
+    if (dt == DType::F32 && prefers_f32_strip(scores_only, BH, N, d) && split_takes_scale(scale))
+        return launch_qk_f32_strip(scores_only, Q, K, out, BH, N, d, scale, stream);
     if (dt == DType::F32) return launch_qk_t<float>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream, true);
     // ATTNW_FUSED_KERNEL=twopass keeps bf16 problems on the two-pass kernel above, =rounds keeps short sequences
     // off the resident kernel (tests and measurements compare the three)
