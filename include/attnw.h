@@ -50,9 +50,9 @@
  *   - Environment: ATTNW_FUSED_KERNEL selects among the kernels behind
  *     attnw_fused / attnw_gemm_scores for bf16 shapes that several of them
  *     serve (read at every call; tests and measurements compare them):
- *       unset    N from 8 to 128 (d up to 128; not N above 96 with d above 96)
- *                or to 192 (d up to 64): a wave per head and 32 queries, scores
- *                in its registers;
+ *       unset    N from 65 to 384 (K of a head up to 80 KiB): a wave per head
+ *                and 32 queries, scores in its registers, K in LDS; N from 8 to
+ *                64 (some scores: 128): the same, a wave alone;
  *                d = 64 and N = 512 or 1024, or d = 32 or 64 and N up to 608
  *                and not a multiple of 32: scores of a strip held in registers,
  *                one sweep; one
@@ -62,7 +62,8 @@
  *       rounds   never the register-resident kernels
  *       twopass  always the general two-pass kernel
  *       gang     the gang kernel wherever it takes the shape
- *       tiny     the wave-per-head kernel wherever it takes the shape
+ *       tiny     the kernel of N up to 64 wherever it takes the shape (N up to 128)
+ *       heads    the kernel of 65 to 384 tokens wherever it takes the shape
  *     Weights of all of them agree to rounding of the row sum, scores bit for bit.
  *     The workgroups of the gang kernel wait for each other's row statistics
  *     inside one launch, so all of a gang must be running at once: the grid is

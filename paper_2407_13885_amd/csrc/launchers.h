@@ -63,6 +63,12 @@ bool qk_tiny_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_qk_tiny(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d,
                           float scale, hipStream_t stream);
 
+// Fused attention weights or scaled scores, bf16, 64 < N <= 384, d a multiple of 16 up to 256, K of a head at most 80 KiB: a
+// wave per (head, 32 queries), the K of the head in LDS for the waves of a workgroup.
+bool qk_heads_supported(int64_t BH, int64_t N, int64_t d);
+hipError_t launch_qk_heads(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d, float scale,
+                           hipStream_t stream);
+
 // Fused attention weights, bf16, d = 64 or 128, N a multiple of 512 from 1024 to 16384: the scores of a strip stay
 // in the registers of the N / 512 workgroups that share its rows (one sweep over the keys; the workgroups exchange
 // their row statistics through tables parked in P).  Two launches: table slots zeroed, then the kernel.

@@ -863,32 +863,33 @@ hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, v
     const bool rounds = force && strcmp(force, "rounds") == 0;
     const bool gang = force && strcmp(force, "gang") == 0;
     const bool tiny = force && strcmp(force, "tiny") == 0;
-    // Sequences of up to 128 tokens: the kernel in which a wave works alone on a (head, 32 queries) pair.  Measured
+    const bool heads = force && strcmp(force, "heads") == 0;
+    // 65 to 384 tokens: whole rows of scores in the registers of a wave, K of the head in LDS.  Measured against the kernels below, fused /
+    // scores in us, 1000 heads: N = 65, d = 64 9.6 -> 8.5, 100 16.5 -> 10.4, 128, d = 128 35 -> 17, d = 256 49 -> 37, 129, d = 64 25 / 24
+    // -> 20 / 16, 160 27 / 30 -> 19 / 17, 197 44 / 40 -> 28 / 26 (d = 128 98 / 75 -> 49 / 44), 256 52 -> 41, 257 114 / 93 -> 52 / 43, 304 113 / 82
+    // -> 54 / 46; 200 heads of 371 39 -> 29, of 384 31 -> 23; one head of 197 10.8 -> 6.1, of 320, d = 128 18 -> 8.5.  Not taken: scores in
+    // whole tiles of the kernels below (N = 256: 2048 heads of d = 32 50 against 56, d = 128 107 against 114) and where d is padded to 96
+    // against none in the next kernel (500 of N = 128, d = 80: 7.5 against 8.3).
+    if (qk_heads_supported(BH, N, d)) {
+        const bool take = !scores_only || (N != 256 && !(d > 64 && d <= 96 && N > 96 && N <= 128));
+        if (heads || (!force && take)) return launch_qk_heads(scores_only, Q, K, out, BH, N, d, scale, stream);
+    }
+    // Sequences of up to 64 tokens (scores: 128): the kernel in which a wave works alone on a (head, 32 queries) pair.  Measured
     // against the kernels below, fused / scores in us: 12288 heads of N = 49, d = 32 320 / 219 -> 27 / 26; 4096 heads of
-    // N = 64, d = 32 69 / 35 -> 10 / 10; 1024 heads of d = 64: N = 33 14 / 11 -> 6 / 5.5, 64 20 / 12 -> 6 / 6, 100 22 / 17 -> 16 / 15,
-    // 128 25 / 17 -> 18 / 17; 16 heads: N = 49, d = 32 8.9 / 6.3 -> 4.3 / 4.2, N = 127, d = 96 12.6 / 9.3 -> 6.8 / 6.1.  Not taken:
-    // N = 128 with fewer than 512 (head, 32 queries) pairs (64 heads of d = 64: 5.4 / 3.8 against 5.7 / 5.1), scores of
-    // lengths that are multiples of 32 with few pairs (256 heads of N = 128: 5.4 against 6.0; 192 heads of N = 128, d = 64:
-    // 5.2 against 5.6; N = 64, d = 32, 384 pairs: 4.6 against 4.8 -- taken from 1024 pairs on, from 384 up to 96 tokens, and
+    // N = 64, d = 32 69 / 35 -> 10 / 10; 1024 heads of N = 33, d = 64 14 / 11 -> 6 / 5.5, 64 20 / 12 -> 6 / 6.  Not taken:
+    // scores of lengths that are multiples of 32 with few (head, 32 queries) pairs (192 heads of N = 128, d = 64: 5.2
+    // against 5.6; N = 64, d = 32, 384 pairs: 4.6 against 4.8 -- taken from 1024 pairs on, from 384 up to 96 tokens, and
     // for every head size above 64, whose rows the kernels below pad: 1536 heads of N = 32, d = 64 16.3 -> 4.7 us, 768
-    // heads of N = 64, d = 64 9.2 -> 5.6, 384 heads of N = 128, d = 64 8.7 -> 7.8, 192 heads of N = 96, d = 128 12.5 -> 6.6).
+    // heads of N = 64, d = 64 9.2 -> 5.6).
     if (qk_tiny_supported(BH, N, d)) {
         const int64_t units = BH * ((N + 31) / 32);
-        // 128 < N <= 256 (d <= 64; the operands of the next unit are requested later in a unit, two waves per SIMD), 1024 heads,
-        // fused / scores against the kernels below: N = 129, d = 64 27 / 23 against 35 / 29; 160 30 / 25 against 45 / 25; 192
-        // 38 / 33 against 49 / 27; 197 48 / 43 against 52 / 41; 223 50 / 47 against 51 / 43; 224 51 / 44 against 55 / 32; d = 32:
-        // N = 144 12 / 12 against 22 / 19, 197 28 / 27 against 42 / 30, 256 31 / 28 against 42 / 27 (4096 heads: 159 / 157 against 141 / 96)
-        const bool take = N <= 128 ? (scores_only ? ((N % 32) != 0 || units >= 1024 || (N <= 96 && units >= 384) || d > 64) : !(N == 128 && units < 512))
-                                   : (scores_only ? ((N % 32) != 0 && (N <= 160 || (d <= 32 && (N & 1) && N <= 224)))
-                                                  : (N <= 192 || ((d <= 32 || (N & 1)) && N <= 224)));
+        const bool take = !scores_only || (N % 32) != 0 || units >= 1024 || (N <= 96 && units >= 384) || d > 64;
         if (tiny || (!force && take)) return launch_qk_tiny(scores_only, Q, K, out, BH, N, d, scale, stream);
     }
-    // Short sequences whose length is not a multiple of 32 (d = 64; 197, 257, 577 ...): the kernel that stages a strip
-    // as the contiguous block of P that it is.  Measured against the general kernel, us: B64 H16 N = 33 31 -> 14,
-    // 65 34 -> 20, 100 26 -> 21, 161 66 -> 40, 197 74 -> 50, 200 50 -> 41; B32 H12 N = 257 75 -> 46, 300 52 -> 43; B16 H12
-    // N = 400 40 -> 29, 520 58 -> 44, 577 84 -> 70, 578 78 -> 56, 600 60 -> 52, 607 84 -> 71; one head of N = 197 16 -> 5.5, 577
-    // 34 -> 18.  Multiples of 32 stay where they were (128: 25 against 27, 256: 20 against 25, 320: 47 against 50, 576: 58
-    // against 64).
+    // Up to 608 tokens, a length that is not a multiple of 32 (d = 32 or 64; 577 ...): the kernel that stages a strip
+    // as the contiguous block of P that it is.  Measured against the general kernel, us: B16 H12 N = 400 40 -> 29, 520
+    // 58 -> 44, 577 84 -> 70, 578 78 -> 56, 600 60 -> 52, 607 84 -> 71; one head of N = 577 34 -> 18.  Multiples of 32 stay
+    // where they were (576: 58 against 64).
     // (scores of even lengths leave the general kernel as fast: its 4-byte stores pair up; measured 100 <= N <= 584)
     if (!force && (N % 32) != 0 && (!scores_only || (N & 1)) && qk_flat_supported(BH, N, d))
         return launch_qk_flat(scores_only, Q, K, out, BH, N, d, scale, stream);

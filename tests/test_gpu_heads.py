@@ -1,0 +1,65 @@
+"""GPU parity of attnw_fused / attnw_gemm_scores on 65 to 384 tokens (bf16: the kernel that keeps whole rows of scores in the
+registers of a wave and the K of a head in LDS) against the fp64 oracle: every element of sampled heads at the bf16 bar, the
+guard bands around the output, scores bit for bit against the general kernel."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2407_13885_amd import workloads as wl
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    gu.require_gpu()
+
+
+def _check(BH, N, d, monkeypatch, scale=None):
+    x = wl.fused_inputs("t", "bf16", 1, BH, N, d, seed=6100 + N + d, scale=scale, row_factor=(0.5, 2.0))
+    monkeypatch.setenv("ATTNW_FUSED_KERNEL", "heads")
+    got = gu.to_f64(gu.run_fused(x, guard=8192))[0]
+    S = gu.run_scores(x, guard=8192)
+    for h in sorted({0, BH // 2, BH - 1}):
+        ref = oracle.attention_weights(x.Q[0, h], x.K[0, h], "bf16", x.scale)
+        gu.check_weights(got[h], ref, "bf16", f"{BH} heads of {N} x {d}, head {h}")
+    assert np.isfinite(got).all()
+    assert np.abs(got.sum(-1) - 1.0).max() <= gu.ROWSUM_BF16
+    monkeypatch.setenv("ATTNW_FUSED_KERNEL", "twopass")
+    S2 = gu.run_scores(x, guard=8192)
+    assert torch.equal(S.view(torch.int16), S2.view(torch.int16))
+
+
+# every number of key blocks, last blocks of one key, of 31 and whole; rows on and off the 16-byte boundaries (multiples of 16
+# with padded staging, of 8, of 4, even, odd); workgroups of two to four waves, the last of a head with idle ones
+@pytest.mark.parametrize("N", [65, 72, 95, 96, 97, 100, 127, 128, 129, 130, 144, 160, 161, 191, 192, 197, 223, 224, 225, 256, 257,
+                               260, 287, 288, 289, 304, 320, 321, 326, 351, 352, 353, 383, 384])
+@pytest.mark.parametrize("d", [32, 64])
+def test_every_block_count(N, d, monkeypatch):
+    _check(3, N, d, monkeypatch)
+
+
+# head sizes that fill the steps of the contraction and that are padded to them (80, 112, 144, 208), up to the K that fits
+@pytest.mark.parametrize("N,d", [(65, 16), (383, 16), (200, 48), (384, 80), (353, 96), (129, 112), (320, 128), (197, 128), (192, 144),
+                                 (161, 192), (160, 208), (129, 256), (97, 256)])
+def test_head_sizes(N, d, monkeypatch):
+    _check(5, N, d, monkeypatch)
+
+
+@pytest.mark.parametrize("BH,N,d,scale", [(700, 197, 64, None), (1, 257, 64, -0.25), (2, 129, 32, 0.0), (400, 100, 128, None)])
+def test_many_heads_and_scales(BH, N, d, scale, monkeypatch):
+    _check(BH, N, d, monkeypatch, scale)
+
+
+def test_a_nan_poisons_its_own_row_only(monkeypatch):
+    x = wl.fused_inputs("t", "bf16", 1, 2, 197, 80, seed=6001)
+    x.Q[0, 1, 40, 3] = 0x7fc0
+    monkeypatch.setenv("ATTNW_FUSED_KERNEL", "heads")
+    got = gu.to_f64(gu.run_fused(x))[0]
+    bad = np.isnan(got)
+    assert bad[1, 40].all()
+    bad[1, 40] = False
+    assert not bad.any()
