@@ -50,11 +50,12 @@
  *   - Environment: ATTNW_FUSED_KERNEL selects among the kernels behind
  *     attnw_fused / attnw_gemm_scores for bf16 shapes that several of them
  *     serve (read at every call; tests and measurements compare them):
- *       unset    N from 65 to 384 (K of a head up to 80 KiB): a wave per head
- *                and 32 queries, scores in its registers, K in LDS; N from 8 to
- *                64 (some scores: 128): the same, a wave alone;
- *                d = 64 and N = 512 or 1024, or d = 32 or 64 and N up to 608
- *                and not a multiple of 32: scores of a strip held in registers,
+ *       unset    N up to 384 (K of a head up to 80 KiB): a wave per head and 32
+ *                queries, scores in its registers, K in LDS (windows of up to 64
+ *                tokens with d = 16 or 32 in great number: the same, a wave
+ *                alone); N up to 1280, d up to 128, lengths off the tiles or few
+ *                heads: a workgroup per 32 queries, scores in its registers;
+ *                d = 64 and N = 512 or 1024: scores of a strip held in registers,
  *                one sweep; one
  *                to a few heads of 1024 to 8192 keys: scores held across a
  *                gang of workgroups; else N a multiple of 256 and d = 64 or
@@ -62,8 +63,9 @@
  *       rounds   never the register-resident kernels
  *       twopass  always the general two-pass kernel
  *       gang     the gang kernel wherever it takes the shape
- *       tiny     the kernel of N up to 64 wherever it takes the shape (N up to 128)
- *       heads    the kernel of 65 to 384 tokens wherever it takes the shape
+ *       tiny     the kernel of a wave alone wherever it takes the shape
+ *       heads    the kernel of a wave per head and 32 queries wherever it takes it
+ *       strip    the kernel of a workgroup per 32 queries wherever it takes it
  *     Weights of all of them agree to rounding of the row sum, scores bit for bit.
  *     The workgroups of the gang kernel wait for each other's row statistics
  *     inside one launch, so all of a gang must be running at once: the grid is

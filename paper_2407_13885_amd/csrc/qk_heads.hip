@@ -1,4 +1,4 @@
-// Fused attention weights  P = softmax(scale * Q K^T)  and scaled scores, bf16, 64 < N <= 384, d a multiple of 16 up to 256: a wave per
+// Fused attention weights  P = softmax(scale * Q K^T)  and scaled scores, bf16, N <= 384, d a multiple of 16 up to 256: a wave per
 // (head, 32 queries) whose whole row of scores stays in its registers, the K of the head in LDS for the waves of a workgroup.
 //
 // (Paper: the fused kernel of the section "Fused Matrix Multiply + Scaling + Softmax" holds a block of scores in a core's SRAM from
@@ -233,8 +233,8 @@ void qk_heads_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict_
         for (int ch = first + lane; ch < n_whole; ch += 64)
             __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(blk + ch * 8), reinterpret_cast<u32x4*>(gbase + ch * 8));
         // the chunks shared with the neighbouring blocks, element by element
-        if (first && lane >= o && lane < 8) gbase[lane] = blk[lane];
-        if (lane >= 8 && lane < 8 + (staged & 7)) gbase[n_whole * 8 + lane - 8] = blk[n_whole * 8 + lane - 8];
+        if (first && lane >= o && lane < min(8, staged)) gbase[lane] = blk[lane];
+        if (lane >= 8 && lane < 8 + (staged & 7) && n_whole >= first) gbase[n_whole * 8 + lane - 8] = blk[n_whole * 8 + lane - 8];
     }
 }
 
@@ -302,7 +302,7 @@ hipError_t launch_heads(bool scores_only, const void* Q, const void* K, void* ou
 // (K of a head, rows padded as above, at most 80 KiB: two workgroups on a compute unit)
 bool qk_heads_supported(int64_t BH, int64_t N, int64_t d)
 {
-    if (N <= 64 || N > 384 || d < 16 || d > 256 || d % 16 != 0 || BH > (int64_t)0x0fffffff) return false;
+    if (N < 1 || N > 384 || d < 16 || d > 256 || d % 16 != 0 || BH > (int64_t)0x0fffffff) return false;
     const int64_t steps = d <= 64 ? d / 16 : d <= 96 ? 6 : d <= 128 ? 8 : d <= 192 ? 12 : 16;
     return (N + 31) / 32 * steps <= 80;
 }
@@ -311,6 +311,8 @@ hipError_t launch_qk_heads(bool scores_only, const void* Q, const void* K, void*
                            hipStream_t stream)
 {
     switch ((N + 31) / 32) {
+    case 1: return launch_heads<1>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream);
+    case 2: return launch_heads<2>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream);
     case 3: return launch_heads<3>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream);
     case 4: return launch_heads<4>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream);
     case 5: return launch_heads<5>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream);

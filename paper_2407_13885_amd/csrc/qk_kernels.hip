@@ -665,11 +665,11 @@ hipError_t launch_shape(bool scores_only, const void* Q, const void* K, void* ou
 
 // bf16, ragged lengths: 256-query strips, a wave per 32 queries that walks whole 128-key tiles and stores whole
 // memory lines out of a ring laid out as the rows lie in memory (RING in qk_kernel).
-template <int DB, int GRAN, int WQ>
+template <int DB, int GRAN>
 hipError_t launch_ring_t(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, int d, float scale,
                          hipStream_t stream)
 {
-    constexpr int BM = 32 * WQ;
+    constexpr int WQ = 8, BM = 32 * WQ;
     uint32_t strips = (uint32_t)((N + BM - 1) / BM);
     const uint16_t* q = static_cast<const uint16_t*>(Q);
     const uint16_t* k = static_cast<const uint16_t*>(K);
@@ -685,7 +685,7 @@ hipError_t launch_ring_t(bool scores_only, const void* Q, const void* K, void* o
     // 294 / 175 -> 222 / 139, 8200 929 -> 830 (4072, 16 full strips and nothing else: 203 - 210 / 131); 128 heads of N = 513,
     // d = 32: 53 -> 39.
     const int tail_rows = N % BM;
-    const int64_t slots = (int64_t)compute_units() * (WQ == 8 ? 1 : 2);
+    const int64_t slots = compute_units();
     const int64_t full = BH * (int64_t)(N / BM);
     const bool own_tail = tail_rows != 0 && tail_rows <= 96 && full > 0 &&
                           (full + slots - 1) / slots < (full + BH + slots - 1) / slots;
@@ -726,14 +726,14 @@ hipError_t launch_ring_t(bool scores_only, const void* Q, const void* K, void* o
     }
     return hipGetLastError();
 }
-template <int DB, int WQ = 8>
+template <int DB>
 hipError_t launch_ring(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, int d, float scale,
                        hipStream_t stream)
 {
     // staging writes as wide as the rows' positions in memory allow (rows start on multiples of 2 N bytes)
-    if (N % 4 == 0) return launch_ring_t<DB, 8, WQ>(scores_only, Q, K, out, BH, N, d, scale, stream);
-    if (N % 2 == 0) return launch_ring_t<DB, 4, WQ>(scores_only, Q, K, out, BH, N, d, scale, stream);
-    return launch_ring_t<DB, 2, WQ>(scores_only, Q, K, out, BH, N, d, scale, stream);
+    if (N % 4 == 0) return launch_ring_t<DB, 8>(scores_only, Q, K, out, BH, N, d, scale, stream);
+    if (N % 2 == 0) return launch_ring_t<DB, 4>(scores_only, Q, K, out, BH, N, d, scale, stream);
+    return launch_ring_t<DB, 2>(scores_only, Q, K, out, BH, N, d, scale, stream);
 }
 
 template <typename T>
@@ -758,14 +758,6 @@ hipError_t launch_qk_t(bool scores_only, const void* Q, const void* K, void* out
         // 1544 283 / 230 -> 259 / 169, 1284 209 / 157 -> 181 / 119; 1025 193 / 139 -> 182 / 126, B16 H16 N = 785 208 / 152 ->
         // 179 / 126; not taken: 1032 121 / 78 -> 163 / 104, 1030 144 / 93 -> 164 / 120, B16 H12 N = 577 105 / 77 -> 111 / 84,
         // B64 H16 N = 197 74 / 53 -> 95 / 77.  Odd lengths gain earlier: their alternative is 2-byte stores.
-        // Odd lengths of a few hundred to a thousand (a class token in front of 24 x 24 or 32 x 32 patches) with d <= 64:
-        // the same with 128-query strips (4 waves, two workgroups per compute unit).  B16 H12 N = 577: d = 64 107 / 77 ->
-        // 98 / 66, d = 32 99 / 72 -> 78 / 58; B8 H16 N = 1025 193 / 139 -> 156 / 110 (182 / 126 with 256-query strips);
-        // B32 H12 N = 257 75 / 53 both; B64 H16 N = 197 74 / 53 -> 91 / 72 (not taken); even lengths lose (578: 79 / 51 -> 84 / 59).
-        if ((N & 1) && N >= 320 && N < 1152 && row_bytes <= 128 && BH * ((N + 127) / 128) >= 200) {
-            if (row_bytes <= 64) return launch_ring<64, 4>(scores_only, Q, K, out, BH, N, d, scale, stream);
-            return launch_ring<128, 4>(scores_only, Q, K, out, BH, N, d, scale, stream);
-        }
         if (N >= ((N & 1) ? 704 : 1280) && (N % 256) != 0 && row_bytes <= 256 && BH * ((N + 255) / 256) >= 100) {
             if (row_bytes <= 64) return launch_ring<64>(scores_only, Q, K, out, BH, N, d, scale, stream);
             if (row_bytes <= 128) return launch_ring<128>(scores_only, Q, K, out, BH, N, d, scale, stream);
@@ -845,6 +837,33 @@ bool prefers_f32_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
     return d > 32 || N < 128 || strips <= 2 * cus;
 }
 
+// bf16 on 32-query strips, a workgroup each, 129 to 1280 tokens.  Measured, the kernel that would take it otherwise -> this one, fused /
+// scores in us:
+//   few strips: one head of N = 256, d = 64 5.9 -> 4.5, 384 7.7 -> 5.1, 577 16.3 / 12.5 -> 7.5 / 6.5, 1024 10.2 / 7.3 -> 7.5 / 6.2, d = 128 15.3 /
+//     9.8 -> 9.3 / 8.2; 64 heads of 197 6.5 -> 6.4, of 160 4.8 -> 5.2, of 320 8.9 -> 7.7, d = 128 9.4 -> 10.4; 24 of 1024, d = 64 24 -> 18; 12 of 512 5.9
+//     -> 6.4, 24 of 512 8.4 -> 7.8; 24 of 1280 30 / 20 -> 33 / 28; 12 of 1024 scores 8.2 -> 9.5
+//   many: 192 of 577, d = 64 64 -> 41; 390 of 577, d = 32 108 / 81 -> 66 / 62, d = 64 123 / 102 -> 78 / 71, d = 96 219 / 154 -> 97 / 88, d = 128
+//     228 / 165 -> 148 / 132; 130 of 1000, d = 64 151 / 112 -> 77 / 68; 128 of 1025 140 / 110 -> 86 / 82; 97 of 1152 85 / 58 -> 72 / 64; 495 of 512
+//     76 / 54 -> 68 / 58; 317 of 640 95 / 67 -> 69 / 62, d = 128 131 / 87 -> 142 / 121; 48 of 1024 26 -> 32, d = 128 97 / 60 -> 101 / 90; 647 of 448,
+//     d = 128 169 / 104 -> 125 / 124; 79 of 1279, d = 128 152 / 109 -> 151 / 129
+bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
+{
+    const int64_t cus = compute_units(), strips = BH * ((N + 31) / 32);
+    if (qk_heads_supported(BH, N, d))             // (against whole rows in a wave: short sequences)
+        return strips <= cus || (N > 192 && 2 * strips <= (d > 64 ? 2 : 5) * cus);
+    if (scores_only) {
+        if (d > 96 && N > 1216) return false;     // (one workgroup to a compute unit)
+        if (strips <= cus || (N % 32) != 0) return true;
+        return d <= 64 && (N % 256) != 0 && (d <= 32 || N < 704);
+    }
+    if (N % 256 != 0) return !(d > 96 && N == 640 && strips > 2 * cus);   // (640: a fifth of 128-query strips is all that the tiles waste)
+    if (d != 64 && d != 128) return N < 1280 || d > 64;
+    // whole tiles of the two-sweep, resident and gang kernels
+    if (d == 64 && N == 512) return strips > cus;
+    if (d == 64 && N == 768) return true;
+    return strips <= (N == 1024 ? 3 : 2) * cus;
+}
+
 }  // namespace
 
 hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, void* out,
@@ -864,35 +883,21 @@ hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, v
     const bool gang = force && strcmp(force, "gang") == 0;
     const bool tiny = force && strcmp(force, "tiny") == 0;
     const bool heads = force && strcmp(force, "heads") == 0;
-    // 65 to 384 tokens: whole rows of scores in the registers of a wave, K of the head in LDS.  Measured against the kernels below, fused /
-    // scores in us, 1000 heads: N = 65, d = 64 9.6 -> 8.5, 100 16.5 -> 10.4, 128, d = 128 35 -> 17, d = 256 49 -> 37, 129, d = 64 25 / 24
-    // -> 20 / 16, 160 27 / 30 -> 19 / 17, 197 44 / 40 -> 28 / 26 (d = 128 98 / 75 -> 49 / 44), 256 52 -> 41, 257 114 / 93 -> 52 / 43, 304 113 / 82
-    // -> 54 / 46; 200 heads of 371 39 -> 29, of 384 31 -> 23; one head of 197 10.8 -> 6.1, of 320, d = 128 18 -> 8.5.  Not taken: scores in
-    // whole tiles of the kernels below (N = 256: 2048 heads of d = 32 50 against 56, d = 128 107 against 114) and where d is padded to 96
-    // against none in the next kernel (500 of N = 128, d = 80: 7.5 against 8.3).
-    if (qk_heads_supported(BH, N, d)) {
-        const bool take = !scores_only || (N != 256 && !(d > 64 && d <= 96 && N > 96 && N <= 128));
-        if (heads || (!force && take)) return launch_qk_heads(scores_only, Q, K, out, BH, N, d, scale, stream);
-    }
-    // Sequences of up to 64 tokens (scores: 128): the kernel in which a wave works alone on a (head, 32 queries) pair.  Measured
-    // against the kernels below, fused / scores in us: 12288 heads of N = 49, d = 32 320 / 219 -> 27 / 26; 4096 heads of
-    // N = 64, d = 32 69 / 35 -> 10 / 10; 1024 heads of N = 33, d = 64 14 / 11 -> 6 / 5.5, 64 20 / 12 -> 6 / 6.  Not taken:
-    // scores of lengths that are multiples of 32 with few (head, 32 queries) pairs (192 heads of N = 128, d = 64: 5.2
-    // against 5.6; N = 64, d = 32, 384 pairs: 4.6 against 4.8 -- taken from 1024 pairs on, from 384 up to 96 tokens, and
-    // for every head size above 64, whose rows the kernels below pad: 1536 heads of N = 32, d = 64 16.3 -> 4.7 us, 768
-    // heads of N = 64, d = 64 9.2 -> 5.6).
-    if (qk_tiny_supported(BH, N, d)) {
-        const int64_t units = BH * ((N + 31) / 32);
-        const bool take = !scores_only || (N % 32) != 0 || units >= 1024 || (N <= 96 && units >= 384) || d > 64;
-        if (tiny || (!force && take)) return launch_qk_tiny(scores_only, Q, K, out, BH, N, d, scale, stream);
-    }
-    // Up to 608 tokens, a length that is not a multiple of 32 (d = 32 or 64; 577 ...): the kernel that stages a strip
-    // as the contiguous block of P that it is.  Measured against the general kernel, us: B16 H12 N = 400 40 -> 29, 520
-    // 58 -> 44, 577 84 -> 70, 578 78 -> 56, 600 60 -> 52, 607 84 -> 71; one head of N = 577 34 -> 18.  Multiples of 32 stay
-    // where they were (576: 58 against 64).
-    // (scores of even lengths leave the general kernel as fast: its 4-byte stores pair up; measured 100 <= N <= 584)
-    if (!force && (N % 32) != 0 && (!scores_only || (N & 1)) && qk_flat_supported(BH, N, d))
-        return launch_qk_flat(scores_only, Q, K, out, BH, N, d, scale, stream);
+    const bool strip = force && strcmp(force, "strip") == 0;
+    // Many windows of up to 64 tokens with heads of 16 or 32, off the 16-byte boundaries: waves that work alone on a stream of (head, 32
+    // queries) pairs (12288 heads of N = 49, d = 32: 26.7 us against 30.6 of the next kernel; 4096 of N = 64 12.5 against 11.3; scores 24.3
+    // against 23.6; d = 64 50.4 against 49.8).
+    if (qk_tiny_supported(BH, N, d) && (tiny || (!force && !scores_only && N % 8 != 0 && BH * ((N + 31) / 32) >= 8192)))
+        return launch_qk_tiny(scores_only, Q, K, out, BH, N, d, scale, stream);
+    if (qk_strip_supported(BH, N, d) && (strip || (!force && prefers_strip(scores_only, BH, N, d))))
+        return launch_qk_strip(scores_only, Q, K, out, BH, N, d, scale, stream);
+    // Up to 384 tokens: whole rows of scores in the registers of a wave, K of the head in LDS.  Measured against the kernels below and
+    // those that it replaced, fused / scores in us, 1000 heads: N = 33, d = 64 6.3 / 5.8 -> 5.0 / 4.7, 65 9.6 -> 8.5, 100 16.5 -> 10.4, 128, d = 128
+    // 35 -> 17, d = 256 49 -> 37, 129, d = 64 25 / 24 -> 20 / 16, 160 27 / 30 -> 19 / 17, 197 44 / 40 -> 28 / 26 (d = 128 98 / 75 -> 49 / 44),
+    // 256 52 -> 41, 257 114 / 93 -> 52 / 43, 304 113 / 82 -> 54 / 46; 200 heads of 371 39 -> 29, of 384 31 -> 23; 20000 of one token 88 -> 15.
+    // Not taken: scores in whole tiles of the kernels below (N = 256: 2048 heads of d = 32 50 against 56, d = 128 107 against 114).
+    if (qk_heads_supported(BH, N, d) && (heads || (!force && !(scores_only && N == 256))))
+        return launch_qk_heads(scores_only, Q, K, out, BH, N, d, scale, stream);
     if (!scores_only && qk_gang_supported(BH, N, d) && (gang || (!force && prefers_gang(BH, N, d))))
         return launch_qk_gang(Q, K, out, BH, N, d, scale, stream);
     if (!twopass && !(!rounds && prefers_key_split(BH, N, d))) {

@@ -1,6 +1,5 @@
-// Fused attention weights  P = softmax(scale * Q K^T)  and scaled scores for MANY SHORT sequences (bf16, N <= 128 with
-// d a multiple of 16 up to 128): windows of 49 or 64 tokens with three to thirty-two heads each and thousands of
-// windows per call, sentences of up to 128 tokens.  One head is a few matrix instructions of work; a workgroup
+// Fused attention weights  P = softmax(scale * Q K^T)  and scaled scores for MANY SHORT sequences (bf16, N <= 64,
+// d = 16 or 32): windows of 49 tokens with three to thirty-two heads each and thousands of windows per call.  One head is a few matrix instructions of work; a workgroup
 // per (head, strip) spends its time in prologue and barriers, and of eight waves that split 256 keys only two
 // have any.
 //
@@ -310,40 +309,21 @@ hipError_t launch_tiny_t(bool scores_only, const void* Q, const void* K, void* o
     return hipGetLastError();
 }
 
-template <int NKB>
-hipError_t launch_tiny(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, int d, float scale,
-                       hipStream_t stream)
-{
-    switch (d / 16) {
-    case 1: return launch_tiny_t<NKB, 1>(scores_only, Q, K, out, BH, N, scale, stream);
-    case 2: return launch_tiny_t<NKB, 2>(scores_only, Q, K, out, BH, N, scale, stream);
-    case 3: return launch_tiny_t<NKB, 3>(scores_only, Q, K, out, BH, N, scale, stream);
-    case 4: return launch_tiny_t<NKB, 4>(scores_only, Q, K, out, BH, N, scale, stream);
-    case 5: return launch_tiny_t<NKB, 5>(scores_only, Q, K, out, BH, N, scale, stream);
-    case 6: return launch_tiny_t<NKB, 6>(scores_only, Q, K, out, BH, N, scale, stream);
-    case 7: if constexpr (NKB < 4) return launch_tiny_t<NKB, 7>(scores_only, Q, K, out, BH, N, scale, stream); else break;
-    case 8: if constexpr (NKB < 4) return launch_tiny_t<NKB, 8>(scores_only, Q, K, out, BH, N, scale, stream); else break;
-    default: break;
-    }
-    return hipErrorInvalidValue;
-}
-
 }  // namespace
 
 bool qk_tiny_supported(int64_t BH, int64_t N, int64_t d)
 {
-    if (N < 8 || N > 128 || d < 16 || d > 128 || (d % 16) != 0) return false;   // (N >= 8: see the stores of a unit)
-    if (N > 96 && d > 96) return false;           // (operands and scores of a unit would not fit the registers)
+    if (N < 8 || N > 64 || (d != 16 && d != 32)) return false;   // (N >= 8: see the stores of a unit)
     return BH * ((N + 31) / 32) <= (int64_t)0x7ffffff0;
 }
 
 hipError_t launch_qk_tiny(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d,
                           float scale, hipStream_t stream)
 {
-    if (N <= 32) return launch_tiny<1>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream);
-    if (N <= 64) return launch_tiny<2>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream);
-    if (N <= 96) return launch_tiny<3>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream);
-    return launch_tiny<4>(scores_only, Q, K, out, BH, (int)N, (int)d, scale, stream);
+    if (N <= 32) return d == 16 ? launch_tiny_t<1, 1>(scores_only, Q, K, out, BH, (int)N, scale, stream)
+                                : launch_tiny_t<1, 2>(scores_only, Q, K, out, BH, (int)N, scale, stream);
+    return d == 16 ? launch_tiny_t<2, 1>(scores_only, Q, K, out, BH, (int)N, scale, stream)
+                   : launch_tiny_t<2, 2>(scores_only, Q, K, out, BH, (int)N, scale, stream);
 }
 
 }  // namespace attnw
