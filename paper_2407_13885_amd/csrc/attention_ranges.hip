@@ -10,7 +10,8 @@
 // output accumulators of its own, and the partial results are merged through LDS at the end.
 //
 // What bounds it: every compute unit reads the whole K and V of its head from the caches, 64 bytes per cycle at best (15 us for
-// 2 MiB; 35 bytes per cycle counted, matrix pipe 26 %, waves waiting 33 % of their life), with little arithmetic per byte.  No byte is used by two waves, so a wave stages its own sub-tiles in an LDS area
+// 2 MiB; 35 bytes per cycle counted, matrix pipe 26 %, waves waiting 33 % of their life), with little arithmetic per byte
+// (and where the blocks leave compute units idle, several of them share a block's columns: CS below).  No byte is used by two waves, so a wave stages its own sub-tiles in an LDS area
 // of its own and no barrier ties the waves together: while one requests and stores, the others compute.  K and V lie in
 // LDS as they lie in memory; V is turned by the transposing LDS read.
 #include "attention_common.h"
@@ -19,15 +20,19 @@
 namespace attnw {
 namespace {
 
-template <int DVB, int WK>
+// CS: workgroups that share the columns of V and O of a query block
+template <int DVB, int WK, int CS>
 struct RangesCfg {
     static constexpr int DB = DVB * 64;           // bytes of a row on chip
     static constexpr int CPR = DVB * 4;           // 16-byte chunks of it
     static constexpr int TILE = 32 * DB;          // a wave's sub-tile of K, and of V
     static constexpr int XFERS = TILE / 1024;     // wave-wide transfers of it
-    static constexpr int SLOTS = 2 + DVB * 16;    // merge: reference exponent, sum, output accumulators
+    static constexpr int OB = DVB / CS;           // 32-column blocks of V and O
+    static constexpr int V_TILE = TILE / CS;
+    static constexpr int SLOTS = 2 + OB * 16;     // merge: reference exponent, sum, output accumulators
     static constexpr int MERGE = WK * SLOTS * 256;
-    static constexpr int LDS = 2 * WK * TILE > MERGE ? 2 * WK * TILE : MERGE;
+    static constexpr int LDS = WK * (TILE + V_TILE) > MERGE ? WK * (TILE + V_TILE) : MERGE;
+    static_assert(DVB % CS == 0, "whole column blocks");
     static_assert(LDS <= 160 * 1024, "sub-tiles of all waves");
 };
 
@@ -37,13 +42,19 @@ struct RangesCfg {
 // V waits in registers for its place in LDS; K, whose place is free as soon as the scores are made, goes there directly (one head of
 // N = 4096, d = 128 27.4 us, K through registers too 29.5; four waves instead of eight 38).
 // q_base: the launch covers the queries from that one on.
-template <int DVB, bool HALF, int WK>
+// Where 32-query workgroups leave half of the compute units idle, CS of them share a block: each makes all scores, but reads and
+// multiplies its share of the columns of V only -- the larger part of what a compute unit's port has to carry.  No exchange, the
+// sums are those of one workgroup.
+template <int DVB, bool HALF, int WK, int CS>
 __global__ __launch_bounds__(64 * WK)
 void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                              uint16_t* __restrict__ O, int N, float c, uint32_t sign_flip, uint32_t strips, uint32_t total, int q_base)
 {
-    using C = RangesCfg<DVB, WK>;
+    using C = RangesCfg<DVB, WK, CS>;
     using L = RowLayout<DVB>;
+    using LV = RowLayout<DVB / CS>;
+    constexpr int OB = C::OB, DBV = OB * 64, CPRV = OB * 4, V_TILE = C::V_TILE, V_XFERS = V_TILE / 1024;
+    static_assert(CS == 1 || !HALF, "columns are shared in whole blocks");
     constexpr int DB = C::DB, CPR = C::CPR, TILE = C::TILE, XFERS = C::XFERS;
     constexpr int rb = DB - (HALF ? 32 : 0);
     constexpr int G = rb / 32;                    // 32-byte contraction groups of a row
@@ -53,14 +64,16 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
 
     const uint32_t logical = xcd_contiguous_block_id(blockIdx.x, gridDim.x);
     if (logical >= total) return;
-    const uint32_t bh = logical / strips;
-    const uint32_t strip = logical - bh * strips;
+    const uint32_t block = logical / CS;
+    const int col0 = (int)(logical % CS) * DBV;   // this workgroup's first byte of a row of V and O
+    const uint32_t bh = block / strips;
+    const uint32_t strip = block - bh * strips;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int l32 = lane & 31;
     const int half = lane >> 5;
     char* const k_lds = lds + wave * TILE;
-    char* const v_lds = lds + (WK + wave) * TILE;
+    char* const v_lds = lds + WK * TILE + wave * V_TILE;
 
     const char* Qh = reinterpret_cast<const char*>(Q) + (int64_t)bh * N * rb;
     const char* Kh = reinterpret_cast<const char*>(K) + (int64_t)bh * N * rb;
@@ -72,18 +85,17 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
     // (a lane's chunk number is its place in LDS; which chunk of the row it reads follows from the swizzle)
     auto offset = [&](int j, int rows, bool v) __attribute__((always_inline)) {   // rows: last valid row of the sub-tile
         const int s = j * 64 + lane;
-        const int key = s / CPR;
-        int ch = (s - key * CPR) ^ (v ? L::v_block(key) * 4 : L::k_chunk(key));
+        const int key = v ? s / CPRV : s / CPR;
+        int ch = v ? (s - key * CPRV) ^ (LV::v_block(key) * 4) : (s - key * CPR) ^ L::k_chunk(key);
         if (HALF && ch * 16 >= rb) ch -= rb / 16;
         return (uint32_t)(min(key, rows) * rb + ch * 16);
     };
-    uint32_t k_off[XFERS], v_off[XFERS];
+    uint32_t k_off[XFERS], v_off[V_XFERS];
 #pragma unroll
-    for (int j = 0; j < XFERS; ++j) {
-        k_off[j] = offset(j, 31, false);
-        v_off[j] = offset(j, 31, true);
-    }
-    u32x4 vreg[XFERS];
+    for (int j = 0; j < XFERS; ++j) k_off[j] = offset(j, 31, false);
+#pragma unroll
+    for (int j = 0; j < V_XFERS; ++j) v_off[j] = offset(j, 31, true);
+    u32x4 vreg[V_XFERS];
     const uint32_t k_base = lds_offset_of(k_lds);
     auto k_load = [&](int t) __attribute__((always_inline)) {
         const char* base = Kh + (int64_t)t * 32 * rb;
@@ -93,10 +105,10 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
             dma16_untracked(base, rows >= 31 ? k_off[j] : offset(j, rows, false), k_base + j * 1024);
     };
     auto v_load = [&](int t) __attribute__((always_inline)) {
-        const char* base = Vh + (int64_t)t * 32 * rb;
+        const char* base = Vh + (int64_t)t * 32 * rb + col0;
         const int rows = N - 1 - t * 32;
 #pragma unroll
-        for (int j = 0; j < XFERS; ++j)
+        for (int j = 0; j < V_XFERS; ++j)
             vreg[j] = *reinterpret_cast<const u32x4*>(base + (rows >= 31 ? v_off[j] : offset(j, rows, true)));
     };
     const int n_tiles = (N + 31) / 32;
@@ -114,20 +126,20 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
     }
 
     // ---- per-lane places of the operand fragments ------------------------------------------------------------------------
-    constexpr int KPERIOD = L::KPERIOD, VPERIOD = L::VPERIOD;
+    constexpr int KPERIOD = L::KPERIOD, VPERIOD = LV::VPERIOD;
     const char* const krow = k_lds + l32 * DB;
     int koff[KPERIOD];
 #pragma unroll
     for (int g = 0; g < KPERIOD; ++g) koff[g] = ((2 * g + half) ^ L::k_chunk(l32)) * 16;
     const int vkey = 4 * half + ((lane & 15) >> 2);            // a lane's row of the 8-key group that it reads
-    const char* const vrow = v_lds + vkey * DB + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    const char* const vrow = v_lds + vkey * DBV + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
     int voff[VPERIOD];
 #pragma unroll
-    for (int b = 0; b < VPERIOD; ++b) voff[b] = (b ^ L::v_block(vkey)) * 64;
+    for (int b = 0; b < VPERIOD; ++b) voff[b] = (b ^ LV::v_block(vkey)) * 64;
 
-    f32x16 oacc[DVB];
+    f32x16 oacc[OB];
 #pragma unroll
-    for (int b = 0; b < DVB; ++b)
+    for (int b = 0; b < OB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[b][r] = 0.0f;
     float mb_run = kNegBig, l_run = 0.0f;
@@ -137,7 +149,7 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
         const bool more = t + WK < n_tiles;
         wait_vmem();                              // K and V of this sub-tile have arrived
 #pragma unroll
-        for (int j = 0; j < XFERS; ++j) *reinterpret_cast<u32x4*>(v_lds + j * 1024 + lane * 16) = vreg[j];
+        for (int j = 0; j < V_XFERS; ++j) *reinterpret_cast<u32x4*>(v_lds + j * 1024 + lane * 16) = vreg[j];
         if (more) v_load(t + WK);
         f32x16 s;
 #pragma unroll
@@ -158,7 +170,7 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
             const float alpha = fast_exp2(mb_run - mb_new);    // exactly 1 for lanes whose exponent stands
             l_run *= alpha;
 #pragma unroll
-            for (int b = 0; b < DVB; ++b)
+            for (int b = 0; b < OB; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) oacc[b][r] *= alpha;
             mb_run = mb_new;
@@ -181,9 +193,9 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
 #pragma unroll
             for (int i = 0; i < 4; ++i) pw[i] = pack_bf16x2(p[8 * m + 2 * i], p[8 * m + 2 * i + 1]);
 #pragma unroll
-            for (int b = 0; b < DVB; ++b) {
-                const char* v = vrow + 16 * m * DB + (b / VPERIOD) * VPERIOD * 64 + voff[b % VPERIOD];
-                Mma<uint16_t>::run(oacc[b], u32x4_of(lds_read_tr16(v), lds_read_tr16(v + 8 * DB)), pw);
+            for (int b = 0; b < OB; ++b) {
+                const char* v = vrow + 16 * m * DBV + (b / VPERIOD) * VPERIOD * 64 + voff[b % VPERIOD];
+                Mma<uint16_t>::run(oacc[b], u32x4_of(lds_read_tr16(v), lds_read_tr16(v + 8 * DBV)), pw);
             }
         }
     }
@@ -198,7 +210,7 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
     mine[0] = mb_run;
     mine[64] = l_run;
 #pragma unroll
-    for (int b = 0; b < DVB; ++b)
+    for (int b = 0; b < OB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mine[(2 + b * 16 + r) * 64] = oacc[b][r];
     __syncthreads();
@@ -214,11 +226,11 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
     const float inv = 1.0f / half_wave_sum(l_sum);
     if (q0 + l32 >= N) return;
     // a run is 4 consecutive output columns of the lane's query; wave w takes runs w, w + WK, ..
-    char* const orow = Oh + (int64_t)(q0 + l32) * rb + half * 8;
+    char* const orow = Oh + (int64_t)(q0 + l32) * rb + col0 + half * 8;
 #pragma unroll
-    for (int i = 0; i < DVB * 4 / WK + (DVB * 4 % WK != 0); ++i) {
+    for (int i = 0; i < OB * 4 / WK + (OB * 4 % WK != 0); ++i) {
         const int run = wave + i * WK;
-        if (run * 16 >= rb) break;
+        if (run * 16 >= (CS == 1 ? rb : DBV)) break;
         float o[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -231,14 +243,14 @@ void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __r
     }
 }
 
-template <int DVB, bool HALF, int WK>
+template <int DVB, bool HALF, int WK, int CS = 1>
 hipError_t launch_ranges_t(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, float scale, int q_base, hipStream_t stream)
 {
     const uint32_t strips = (uint32_t)((N - q_base + 31) / 32);
-    return launch_by_heads(BH, strips, 64 * WK, [&](int64_t first, int64_t heads) {
+    return launch_by_heads(BH, strips * CS, 64 * WK, [&](int64_t first, int64_t heads) {
         const int64_t at = first * N * (DVB * 32 - (HALF ? 16 : 0));
-        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
-        hipLaunchKernelGGL((attention_ranges_kernel<DVB, HALF, WK>), dim3(grid), dim3(64 * WK), 0, stream,
+        const uint32_t total = (uint32_t)heads * strips * CS, grid = (total + 7) / 8 * 8;
+        hipLaunchKernelGGL((attention_ranges_kernel<DVB, HALF, WK, CS>), dim3(grid), dim3(64 * WK), 0, stream,
                            static_cast<const uint16_t*>(Q) + at, static_cast<const uint16_t*>(K) + at, static_cast<const uint16_t*>(V) + at,
                            static_cast<uint16_t*>(O) + at, N, fabsf(scale) * kLog2e, scale < 0.0f ? Mma<uint16_t>::kSignMask : 0u, strips,
                            total, q_base);
@@ -257,6 +269,26 @@ hipError_t launch_ranges(const void* Q, const void* K, const void* V, void* O, i
     // (d <= 96: 20 heads of N = 512, us, two / four waves: d = 32 7.2 / 5.2, 64 10.0 / 7.8, 96 11.7 / 9.1; 40 of 357, d = 64 8.5 / 7.1; 128
     // of 128 alike; beyond twice: 100 heads of N = 300, d = 64 8.9 / 10.4).
     const int64_t blocks = BH * ((N - q_base + 31) / 32), cus = compute_units();
+    // Workgroups per block (CS): what a round of workgroups costs against one of undivided columns, in per cent, times the rounds.  One head
+    // of N = 4096, us: d = 64 16.9 -> 15.2, 128 27.7 -> 24.4, 192 57.7 -> 35.1, 256 80 -> 45.7 (their smaller tiles also leave room for eight and six
+    // waves instead of four); of 1024: d = 96 8.8 -> 6.9, 128 11.0 -> 8.4, 256 25.0 -> 13.4; of 300: d = 256 13.4 -> 8.5.
+    if constexpr (!HALF && (DVB % 2 == 0 || DVB == 3)) {
+        auto cost = [&](int cs, int percent) { return (cs * blocks + cus - 1) / cus * percent; };
+        if (N > (blocks <= cus ? 256 : 512)) {
+            const int64_t whole = cost(1, 100);
+            if constexpr (DVB == 8) {
+                if (cost(4, 52) < whole && cost(4, 52) <= cost(2, 57)) return launch_ranges_t<DVB, HALF, 8, 4>(Q, K, V, O, BH, N, scale, q_base, stream);
+                if (cost(2, 57) < whole) return launch_ranges_t<DVB, HALF, 6, 2>(Q, K, V, O, BH, N, scale, q_base, stream);
+            } else if constexpr (DVB == 6) {
+                if (cost(2, 61) < whole) return launch_ranges_t<DVB, HALF, 8, 2>(Q, K, V, O, BH, N, scale, q_base, stream);
+            } else if constexpr (DVB == 4) {
+                if (cost(4, 78) < whole) return launch_ranges_t<DVB, HALF, 8, 4>(Q, K, V, O, BH, N, scale, q_base, stream);
+                if (cost(2, 86) < whole) return launch_ranges_t<DVB, HALF, 8, 2>(Q, K, V, O, BH, N, scale, q_base, stream);
+            } else {
+                if (cost(DVB, 88) < whole) return launch_ranges_t<DVB, HALF, 8, DVB>(Q, K, V, O, BH, N, scale, q_base, stream);
+            }
+        }
+    }
     if (DVB <= 3 && N > 64 && N <= 512 && blocks > cus && blocks <= 2 * cus)
         return launch_ranges_t<DVB, HALF, 4>(Q, K, V, O, BH, N, scale, q_base, stream);
     if (N <= 64 || (blocks > cus && N <= 512)) return launch_ranges_t<DVB, HALF, 2>(Q, K, V, O, BH, N, scale, q_base, stream);
