@@ -192,9 +192,11 @@ int attnw_scale(const void *X, void *Y, int64_t count, float scale,
  * heads: blocks of 32 queries whose keys are shared between the waves of a
  * workgroup; sequences of up to 128 tokens with d = 64, or 160 with d = 32, a wave
  * per head and 32 queries, and of up to 32 tokens with d above 128 a wave per head,
- * both without on-chip tiles.  ATTNW_ATTENTION_KERNEL=tiny / =tiled in the
- * environment puts every shape that the wave-per-head kernel for d = 32 and 64
- * takes on it / none.)
+ * both without on-chip tiles; many heads of up to some hundred tokens, d <= 128:
+ * K and V of a head in LDS, a wave per 32 queries.  ATTNW_ATTENTION_KERNEL=tiny
+ * / =heads / =tiled in the environment puts every shape that the wave-per-head
+ * kernel for d = 32 and 64 or the kernel with K and V in LDS takes on it / none
+ * on either.)
  * ATTNW_F32: d a multiple of 4 up to 256, any N >= 1.  fp32 products, sums and
  * weights, no rounding but fp32's, on the fp32 matrix instruction; many heads with
  * d <= 128 on the bf16 one with operands (weights among them) in three parts, see

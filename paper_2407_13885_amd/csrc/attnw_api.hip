@@ -97,12 +97,15 @@ int attnw_attention(const void* Q, const void* K, const void* V, void* O, int64_
     if (overlaps(O, bytes, Q, bytes) || overlaps(O, bytes, K, bytes) || overlaps(O, bytes, V, bytes))
         return ATTNW_ERR_ALIAS;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // many short sequences: the kernel in which a wave works alone on a (head, 32 queries) pair
-    // (ATTNW_ATTENTION_KERNEL=tiny puts every shape it takes on it, =tiled none, whichever kernel then takes it: tests and
-    // measurements compare them)
     if (f32) return attnw::launch_attention_f32(Q, K, V, O, BH, N, d, scale, st) == hipSuccess ? ATTNW_OK : ATTNW_ERR_LAUNCH;
+    // short sequences: the kernel that keeps K and V of a head in LDS, the one in which a wave works alone on a (head, 32 queries) pair
+    // (ATTNW_ATTENTION_KERNEL=heads, =tiny put every shape that they take on them, =tiled none, whichever kernel then takes it: tests
+    // and measurements compare them)
+    const char* force = getenv("ATTNW_ATTENTION_KERNEL");
+    if (attnw::attention_heads_supported(BH, N, d) &&
+        (force ? strcmp(force, "heads") == 0 : attnw::prefers_attention_heads(BH, N, d)))
+        return attnw::launch_attention_heads(Q, K, V, O, BH, N, d, scale, st) == hipSuccess ? ATTNW_OK : ATTNW_ERR_LAUNCH;
     if (attnw::attention_tiny_supported(BH, N, d)) {
-        const char* force = getenv("ATTNW_ATTENTION_KERNEL");
         const bool want = force ? strcmp(force, "tiny") == 0 : attnw::prefers_attention_tiny(BH, N, d);
         if (want) return attnw::launch_attention_tiny(Q, K, V, O, BH, N, d, scale, st) == hipSuccess ? ATTNW_OK : ATTNW_ERR_LAUNCH;
     }

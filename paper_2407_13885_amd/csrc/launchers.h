@@ -118,6 +118,13 @@ hipError_t launch_attention_ranges(const void* Q, const void* K, const void* V, 
 hipError_t launch_attention_short(DType dt, const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                   float scale, hipStream_t stream);
 
+// The same for sequences whose K and V fit the LDS (bf16, d a multiple of 16 up to 128): a wave per (head, 32 queries), K and V of the head
+// shared by the waves of a workgroup.
+bool attention_heads_supported(int64_t BH, int64_t N, int64_t d);
+bool prefers_attention_heads(int64_t BH, int64_t N, int64_t d);
+hipError_t launch_attention_heads(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d, float scale,
+                                  hipStream_t stream);
+
 // The same for many short sequences (bf16, d = 64 with N <= 128, d = 32 with N <= 224): a wave per (head, 32 queries), operands
 // straight from global memory, the exponentials as they stand the operand of the second contraction.
 bool attention_tiny_supported(int64_t BH, int64_t N, int64_t d);
