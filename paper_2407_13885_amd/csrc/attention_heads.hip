@@ -9,7 +9,7 @@
 //
 // Measured, 7267 heads of N = 129, d = 64: 122 us (238 MB a pass, 3.9 TB/s; 255 with tiles shared by 256-query workgroups), 7324 of 128 105
 // (163 with operands gathered by every wave for itself), 1953 of 400 166 (227).  What bounds it: short of N = 128 the traffic of Q, K, V
-// and O, beyond the vector ALU between the two matrix instructions of a wave (softmax of 32 x 32 scores: about 110 instructions against
+// and O, beyond the vector ALU between the two matrix instructions of a wave (softmax of 32 x 32 scores: about 150 instructions against
 // 4 + 4 of the matrix at d = 64), and the time that a workgroup alone on its compute unit waits for K and V.
 #include "attention_common.h"
 #include "launchers.h"
