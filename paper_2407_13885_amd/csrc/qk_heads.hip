@@ -30,14 +30,15 @@ constexpr int kDumpElems = 48;                    // where a wave's keys past N 
 inline __host__ __device__ int staged_pitch(int N) { return N % 16 == 0 ? N + 8 : N; }
 inline __host__ __device__ int area_bytes(int N) { return ((32 * staged_pitch(N) + 8) * 2 + 15) / 16 * 16 + 2 * kDumpElems; }
 
-// NKB: 32-key blocks of a head (32 (NKB - 1) < N <= 32 NKB); G: 16-element steps of the contraction (d = 16 G)
+// NKB: 32-key blocks of a head (32 (NKB - 1) < N <= 32 NKB); G: 16-element steps of the contraction (d = 16 G: a row padded to fewer
+// instantiations would bring an infinity in K to zeros of Q, NaN for a key that weighs nothing)
 // SCORES: write scale * Q K^T instead of the weights; c is then the scale itself
 template <int NKB, int G, bool SCORES>
 __global__ __launch_bounds__(64 * kHeadsWaves, (NKB <= 7 && G <= 8) ? 3 : 2)
-void qk_heads_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, uint16_t* __restrict__ out, int N, int d,
-                     float c, uint32_t sign_flip, uint32_t groups, uint32_t total_groups)
+void qk_heads_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, uint16_t* __restrict__ out, int N, float c,
+                     uint32_t sign_flip, uint32_t groups, uint32_t total_groups)
 {
-    constexpr int DB = 32 * G, CPR = 2 * G;       // bytes and 16-byte chunks of a row of K in LDS
+    constexpr int DB = 32 * G, CPR = 2 * G;       // bytes and 16-byte chunks of a row
     // chunk XOR row / RPL stays inside the row and puts the 16 rows that a fragment read serves at a time on different banks
     constexpr int P2 = G % 8 == 0 ? 16 : G % 4 == 0 ? 8 : G % 2 == 0 ? 4 : 2;
     constexpr int RPL = 16 / P2, SWZ_MASK = P2 - 1;
@@ -55,27 +56,27 @@ void qk_heads_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict_
     const uint32_t h = id / groups;
     const int q0 = (int)((id - h * groups) * nw + wave) * 32;
 
-    // ---- K of the head -> LDS (16-byte chunks XOR-swizzled by the row; rows past N are row N - 1 again, chunks past d the last
-    // one), Q -> registers (zeros past d) ----
-    const int row_bytes = 2 * d, row_chunks = d / 8;
+    // ---- K of the head -> LDS (16-byte chunks XOR-swizzled by the row; rows past N are row N - 1 again), Q -> registers ----
     {
-        const char* const Kh = reinterpret_cast<const char*>(K) + (int64_t)h * N * row_bytes;
+        const char* const Kh = reinterpret_cast<const char*>(K) + (int64_t)h * N * DB;
         for (int j = wave; j < NKB * G; j += nw) {
             const int s = j * 64 + lane;
             const int row = s / CPR;
             const int chunk = (s % CPR) ^ ((row / RPL) & SWZ_MASK);
-            dma16(Kh + min(row, N - 1) * row_bytes + min(chunk, row_chunks - 1) * 16, lds + j * 1024);
+            dma16(Kh + min(row, N - 1) * DB + chunk * 16, lds + j * 1024);
         }
     }
     u32x4 qf[G];
     {
-        const char* const p = reinterpret_cast<const char*>(Q) + ((int64_t)h * N + min(q0 + l32, N - 1)) * row_bytes + half * 16;
+        const char* const p = reinterpret_cast<const char*>(Q) + ((int64_t)h * N + min(q0 + l32, N - 1)) * DB + half * 16;
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const bool in = 16 * g < d;           // (uniform)
-            qf[g] = *reinterpret_cast<const u32x4*>(in ? p + g * 32 : p) ^ sign_flip;
-            if (!in) qf[g] = u32x4{0u, 0u, 0u, 0u};
-        }
+        for (int g = 0; g < G; ++g) qf[g] = *reinterpret_cast<const u32x4*>(p + g * 32) ^ sign_flip;
+#if defined(__HIP_DEVICE_COMPILE__)
+        // in registers before the barrier, under the transfers of K (the compiler sinks these loads behind it, one by one between the
+        // matrix instructions: 2048 heads of N = 64, d = 192 23.0 -> 19.5 us, 800 of 129, d = 64 16.9 -> 14.6)
+#pragma unroll
+        for (int g = 0; g < G; ++g) asm volatile("" : "+v"(qf[g]));
+#endif
     }
     wait_vmem();
     __syncthreads();                              // K is in place
@@ -258,10 +259,13 @@ inline int heads_waves(int blocks, int N, int k_bytes, int waves_per_simd, int& 
     return best;
 }
 
+// K rows of G steps count as so many in the limit of 80 KiB of K
+constexpr int counted_steps(int G) { return G <= 4 ? G : G <= 6 ? 6 : G <= 8 ? 8 : G <= 12 ? 12 : 16; }
+
 template <int NKB, int G>
-hipError_t launch_heads_t(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, int d, float scale, hipStream_t stream)
+hipError_t launch_heads_t(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, float scale, hipStream_t stream)
 {
-    if constexpr (NKB * G > 80) {
+    if constexpr (NKB * counted_steps(G) > 80) {
         return hipErrorInvalidValue;              // (not supported: see qk_heads_supported)
     } else {
         int lds = 0;
@@ -272,13 +276,13 @@ hipError_t launch_heads_t(bool scores_only, const void* Q, const void* K, void* 
         return launch_by_heads(BH, groups, (uint32_t)(64 * nw), [&](int64_t first, int64_t heads) {
             const uint32_t total = (uint32_t)heads * groups;
             const uint32_t grid = (total + 7) / 8 * 8;
-            const uint16_t* const q = static_cast<const uint16_t*>(Q) + first * N * d;
-            const uint16_t* const k = static_cast<const uint16_t*>(K) + first * N * d;
+            const uint16_t* const q = static_cast<const uint16_t*>(Q) + first * N * 16 * G;
+            const uint16_t* const k = static_cast<const uint16_t*>(K) + first * N * 16 * G;
             uint16_t* const p = static_cast<uint16_t*>(out) + first * N * N;
             if (scores_only)
-                hipLaunchKernelGGL((qk_heads_kernel<NKB, G, true>), dim3(grid), dim3(64 * nw), (size_t)lds, stream, q, k, p, N, d, c, flip, groups, total);
+                hipLaunchKernelGGL((qk_heads_kernel<NKB, G, true>), dim3(grid), dim3(64 * nw), (size_t)lds, stream, q, k, p, N, c, flip, groups, total);
             else
-                hipLaunchKernelGGL((qk_heads_kernel<NKB, G, false>), dim3(grid), dim3(64 * nw), (size_t)lds, stream, q, k, p, N, d, c, flip, groups, total);
+                hipLaunchKernelGGL((qk_heads_kernel<NKB, G, false>), dim3(grid), dim3(64 * nw), (size_t)lds, stream, q, k, p, N, c, flip, groups, total);
             return hipGetLastError();
         });
     }
@@ -287,24 +291,34 @@ hipError_t launch_heads_t(bool scores_only, const void* Q, const void* K, void* 
 template <int NKB>
 hipError_t launch_heads(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, int d, float scale, hipStream_t stream)
 {
-    if (d <= 16) return launch_heads_t<NKB, 1>(scores_only, Q, K, out, BH, N, d, scale, stream);
-    if (d <= 32) return launch_heads_t<NKB, 2>(scores_only, Q, K, out, BH, N, d, scale, stream);
-    if (d <= 48) return launch_heads_t<NKB, 3>(scores_only, Q, K, out, BH, N, d, scale, stream);
-    if (d <= 64) return launch_heads_t<NKB, 4>(scores_only, Q, K, out, BH, N, d, scale, stream);
-    if (d <= 96) return launch_heads_t<NKB, 6>(scores_only, Q, K, out, BH, N, d, scale, stream);
-    if (d <= 128) return launch_heads_t<NKB, 8>(scores_only, Q, K, out, BH, N, d, scale, stream);
-    if (d <= 192) return launch_heads_t<NKB, 12>(scores_only, Q, K, out, BH, N, d, scale, stream);
-    return launch_heads_t<NKB, 16>(scores_only, Q, K, out, BH, N, d, scale, stream);
+    switch (d / 16) {
+    case 1: return launch_heads_t<NKB, 1>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 2: return launch_heads_t<NKB, 2>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 3: return launch_heads_t<NKB, 3>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 4: return launch_heads_t<NKB, 4>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 5: return launch_heads_t<NKB, 5>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 6: return launch_heads_t<NKB, 6>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 7: return launch_heads_t<NKB, 7>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 8: return launch_heads_t<NKB, 8>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 9: return launch_heads_t<NKB, 9>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 10: return launch_heads_t<NKB, 10>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 11: return launch_heads_t<NKB, 11>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 12: return launch_heads_t<NKB, 12>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 13: return launch_heads_t<NKB, 13>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 14: return launch_heads_t<NKB, 14>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 15: return launch_heads_t<NKB, 15>(scores_only, Q, K, out, BH, N, scale, stream);
+    case 16: return launch_heads_t<NKB, 16>(scores_only, Q, K, out, BH, N, scale, stream);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
 
-// (K of a head, rows padded as above, at most 80 KiB: two workgroups on a compute unit)
+// (K of a head, rows counted as above, at most 80 KiB: two workgroups on a compute unit)
 bool qk_heads_supported(int64_t BH, int64_t N, int64_t d)
 {
     if (N < 1 || N > 384 || d < 16 || d > 256 || d % 16 != 0 || BH > (int64_t)0x0fffffff) return false;
-    const int64_t steps = d <= 64 ? d / 16 : d <= 96 ? 6 : d <= 128 ? 8 : d <= 192 ? 12 : 16;
-    return (N + 31) / 32 * steps <= 80;
+    return (N + 31) / 32 * counted_steps((int)(d / 16)) <= 80;
 }
 
 hipError_t launch_qk_heads(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d, float scale,
