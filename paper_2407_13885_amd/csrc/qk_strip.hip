@@ -29,14 +29,15 @@ constexpr int kStripDump = 48;                    // elements where a wave's key
 inline __host__ __device__ int strip_pitch(int N) { return N % 16 == 0 ? N + 8 : N; }
 inline __host__ __device__ int strip_area(int N) { return ((32 * strip_pitch(N) + 8) * 2 + 15) / 16 * 16; }
 
-// NT: 32-key blocks of a wave at most; G: 16-element steps of the contraction (d <= 16 G); NSLOT: blocks of K a wave holds in LDS
+// NT: 32-key blocks of a wave at most; G: 16-element steps of the contraction (d = 16 G: a row padded to fewer instantiations would
+// bring an infinity in K to zeros of Q, NaN for a key that weighs nothing); NSLOT: blocks of K a wave holds in LDS
 // SCORES: write scale * Q K^T instead of the weights; c is then the scale itself
 template <int NT, int G, int NSLOT, bool SCORES>
 __global__ __launch_bounds__(64 * kStripMaxWaves, 4)
-void qk_strip_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, uint16_t* __restrict__ out, int N, int d,
-                     float c, uint32_t sign_flip, uint32_t strips_per_head, uint32_t total_strips)
+void qk_strip_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, uint16_t* __restrict__ out, int N, float c,
+                     uint32_t sign_flip, uint32_t strips_per_head, uint32_t total_strips)
 {
-    constexpr int DB = 32 * G, CPR = 2 * G;       // bytes and 16-byte chunks of a row of K in LDS
+    constexpr int DB = 32 * G, CPR = 2 * G;       // bytes and 16-byte chunks of a row
     // chunk XOR row / RPL stays inside the row and puts the 16 rows that a fragment read serves at a time on different banks
     constexpr int P2 = G % 8 == 0 ? 16 : G % 4 == 0 ? 8 : G % 2 == 0 ? 4 : 2;
     constexpr int RPL = 16 / P2, SWZ_MASK = P2 - 1;
@@ -60,29 +61,24 @@ void qk_strip_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict_
     const int cnt = (wave + 1) * n_blocks / nw - b0;
     const int key0 = b0 * 32, key_end = min(N, (b0 + cnt) * 32);
 
-    const int row_bytes = 2 * d, row_chunks = d / 8;
-    const char* const Kh = reinterpret_cast<const char*>(K) + (int64_t)h * N * row_bytes;
+    const char* const Kh = reinterpret_cast<const char*>(K) + (int64_t)h * N * DB;
     const uint32_t ring = lds_offset_of(lds) + (uint32_t)(wave * NSLOT * SLOT);
-    // block t -> its slot (chunks XOR-swizzled by the row; rows past N are row N - 1 again, chunks past d the last one)
+    // block t -> its slot (chunks XOR-swizzled by the row; rows past N are row N - 1 again)
     auto bring = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             const int s = j * 64 + lane;
             const int row = s / CPR;
             const int chunk = (s % CPR) ^ ((row / RPL) & SWZ_MASK);
-            dma16_untracked(Kh + (int64_t)min(key0 + t * 32 + row, N - 1) * row_bytes + min(chunk, row_chunks - 1) * 16,
+            dma16_untracked(Kh + (int64_t)min(key0 + t * 32 + row, N - 1) * DB + chunk * 16,
                             __builtin_amdgcn_readfirstlane(ring + (uint32_t)((t % NSLOT) * SLOT + j * 1024)));
         }
     };
     u32x4 qf[G];
     {
-        const char* const p = reinterpret_cast<const char*>(Q) + ((int64_t)h * N + min(q0 + l32, N - 1)) * row_bytes + half * 16;
+        const char* const p = reinterpret_cast<const char*>(Q) + ((int64_t)h * N + min(q0 + l32, N - 1)) * DB + half * 16;
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const bool in = 16 * g < d;           // (uniform)
-            qf[g] = *reinterpret_cast<const u32x4*>(in ? p + g * 32 : p) ^ sign_flip;
-            if (!in) qf[g] = u32x4{0u, 0u, 0u, 0u};
-        }
+        for (int g = 0; g < G; ++g) qf[g] = *reinterpret_cast<const u32x4*>(p + g * 32) ^ sign_flip;
     }
 #pragma unroll
     for (int t = 0; t < NSLOT; ++t)
@@ -264,8 +260,7 @@ void qk_strip_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict_
 }
 
 template <int NT, int G>
-hipError_t launch_strip_t(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, int d, int nw, float scale,
-                          hipStream_t stream)
+hipError_t launch_strip_t(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, int nw, float scale, hipStream_t stream)
 {
     constexpr int NSLOT = G <= 4 ? 2 : 1;
     const int area = strip_area(N) + nw * 2 * kStripDump, rings = nw * NSLOT * 1024 * G;
@@ -276,13 +271,13 @@ hipError_t launch_strip_t(bool scores_only, const void* Q, const void* K, void* 
     return launch_by_heads(BH, strips, (uint32_t)(64 * nw), [&](int64_t first, int64_t heads) {
         const uint32_t total = (uint32_t)heads * strips;
         const uint32_t grid = (total + 7) / 8 * 8;
-        const uint16_t* const q = static_cast<const uint16_t*>(Q) + first * N * d;
-        const uint16_t* const k = static_cast<const uint16_t*>(K) + first * N * d;
+        const uint16_t* const q = static_cast<const uint16_t*>(Q) + first * N * 16 * G;
+        const uint16_t* const k = static_cast<const uint16_t*>(K) + first * N * 16 * G;
         uint16_t* const p = static_cast<uint16_t*>(out) + first * N * N;
         if (scores_only)
-            hipLaunchKernelGGL((qk_strip_kernel<NT, G, NSLOT, true>), dim3(grid), dim3(64 * nw), lds, stream, q, k, p, N, d, c, flip, strips, total);
+            hipLaunchKernelGGL((qk_strip_kernel<NT, G, NSLOT, true>), dim3(grid), dim3(64 * nw), lds, stream, q, k, p, N, c, flip, strips, total);
         else
-            hipLaunchKernelGGL((qk_strip_kernel<NT, G, NSLOT, false>), dim3(grid), dim3(64 * nw), lds, stream, q, k, p, N, d, c, flip, strips, total);
+            hipLaunchKernelGGL((qk_strip_kernel<NT, G, NSLOT, false>), dim3(grid), dim3(64 * nw), lds, stream, q, k, p, N, c, flip, strips, total);
         return hipGetLastError();
     });
 }
@@ -291,12 +286,17 @@ template <int NT>
 hipError_t launch_strip(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, int d, int nw, float scale,
                         hipStream_t stream)
 {
-    if (d <= 16) return launch_strip_t<NT, 1>(scores_only, Q, K, out, BH, N, d, nw, scale, stream);
-    if (d <= 32) return launch_strip_t<NT, 2>(scores_only, Q, K, out, BH, N, d, nw, scale, stream);
-    if (d <= 48) return launch_strip_t<NT, 3>(scores_only, Q, K, out, BH, N, d, nw, scale, stream);
-    if (d <= 64) return launch_strip_t<NT, 4>(scores_only, Q, K, out, BH, N, d, nw, scale, stream);
-    if (d <= 96) return launch_strip_t<NT, 6>(scores_only, Q, K, out, BH, N, d, nw, scale, stream);
-    return launch_strip_t<NT, 8>(scores_only, Q, K, out, BH, N, d, nw, scale, stream);
+    switch (d / 16) {
+    case 1: return launch_strip_t<NT, 1>(scores_only, Q, K, out, BH, N, nw, scale, stream);
+    case 2: return launch_strip_t<NT, 2>(scores_only, Q, K, out, BH, N, nw, scale, stream);
+    case 3: return launch_strip_t<NT, 3>(scores_only, Q, K, out, BH, N, nw, scale, stream);
+    case 4: return launch_strip_t<NT, 4>(scores_only, Q, K, out, BH, N, nw, scale, stream);
+    case 5: return launch_strip_t<NT, 5>(scores_only, Q, K, out, BH, N, nw, scale, stream);
+    case 6: return launch_strip_t<NT, 6>(scores_only, Q, K, out, BH, N, nw, scale, stream);
+    case 7: return launch_strip_t<NT, 7>(scores_only, Q, K, out, BH, N, nw, scale, stream);
+    case 8: return launch_strip_t<NT, 8>(scores_only, Q, K, out, BH, N, nw, scale, stream);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace

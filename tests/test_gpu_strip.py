@@ -62,3 +62,20 @@ def test_a_nan_poisons_its_own_row_only(monkeypatch):
     assert bad[1, 40].all()
     bad[1, 40] = False
     assert not bad.any()
+
+
+@pytest.mark.parametrize("N,d", [(577, 80), (333, 112), (700, 64)])
+def test_an_infinite_key_weighs_nothing(N, d, monkeypatch):
+    """-inf in the last column of a key, for every head size that was once padded: weight 0 where the query is positive there, a score of
+    -inf, everything else as without the key."""
+    x = wl.fused_inputs("t", "bf16", 1, 2, N, d, seed=6350 + N + d)
+    x.Q[0, 1, :, d - 1] = 0x3f80                  # 1.0
+    x.K[0, 1, 5, d - 1] = 0xff80                  # -inf
+    monkeypatch.setenv("ATTNW_FUSED_KERNEL", "strip")
+    got = gu.to_f64(gu.run_fused(x))[0]
+    S = gu.to_f64(gu.run_scores(x))[0]
+    assert (got[1, :, 5] == 0.0).all() and np.isneginf(S[1, :, 5]).all()
+    rest = np.arange(N) != 5
+    ref = oracle.attention_weights(x.Q[0, 1][rest], x.K[0, 1][rest], "bf16", x.scale)
+    gu.check_weights(got[1][rest][:, rest], ref, "bf16", f"N={N} d={d}")
+    assert np.isfinite(S[1][:, rest]).all() and np.isfinite(got[0]).all() and np.isfinite(S[0]).all()
