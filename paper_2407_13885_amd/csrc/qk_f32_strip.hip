@@ -274,8 +274,16 @@ void qk_f32_strip_kernel(const float* __restrict__ Q, const float* __restrict__ 
     // Running maximum and sum of exponentials over the lane's keys.  Exponentials refer to the rounded exponent e_run = fl(c max):
     // one rounding each, and factors between references are exactly 1 while the maximum stands.
     const float c_parts = c * kSplitDown;         // for scores of operands in parts
+    // In parts a score below -2^80 is -infinity, also where fp32 holds it, and would weigh nothing: it makes the sum NaN (an
+    // infinite maximum, or a NaN, does so by itself).
     float m_run, e_run, l_run;
-    auto fold = [&](f32x16& s, float c, int key0) __attribute__((always_inline)) {   // the scores become exponentials
+    auto fold = [&](f32x16& s, float c, int key0, auto partsc) __attribute__((always_inline)) {   // the scores become exponentials
+        float low = 0.0f;
+        if constexpr (decltype(partsc)::value != 0) {
+            low = fminf(s[0], s[1]);
+#pragma unroll
+            for (int r = 2; r < 16; r += 2) low = min3(low, s[r], s[r + 1]);
+        }
         float tm = max3(s[0], s[1], s[2]);
 #pragma unroll
         for (int r = 3; r < 15; r += 2) tm = max3(tm, s[r], s[r + 1]);
@@ -289,6 +297,7 @@ void qk_f32_strip_kernel(const float* __restrict__ Q, const float* __restrict__ 
                 if (key0 + 4 * half + 8 * (r / 4) + (r % 4) >= N) s[r] = 0.0f;
         }
         float sum = s[0];
+        if constexpr (decltype(partsc)::value != 0) sum = __builtin_fmaf(low, 0.0f, sum);
 #pragma unroll
         for (int r = 1; r < 16; ++r) sum += s[r];
         l_run = __builtin_fmaf(l_run, fast_exp2(e_run - en), sum);
@@ -367,13 +376,13 @@ void qk_f32_strip_kernel(const float* __restrict__ Q, const float* __restrict__ 
                 if (pending) put(kept[T], fast_exp2(e_kept[T] - e_row) * inv_row);
                 kept[T] = scores(young);
                 young = pending ? flush(P_before, q0_before, key0) : 0;
-                fold(kept[T], c_parts, key0);
+                fold(kept[T], c_parts, key0, IC<1>{});
                 e_kept[T] = e_run;
             });
             for (int j = NT; j < nb; ++j) {       // blocks whose exponentials do not stay
                 const int key0 = key_of(j);
                 f32x16 s = scores(0);
-                fold(s, c_parts, key0);
+                fold(s, c_parts, key0, IC<1>{});
             }
             merge_halves();
             if (half == 0) {
@@ -439,7 +448,7 @@ void qk_f32_strip_kernel(const float* __restrict__ Q, const float* __restrict__ 
             fold_begin(c);
             for (int key0 = 0; key0 < N; key0 += 32) {
                 f32x16 s = scores_f32(Qh, Kh, q0, key0);
-                fold(s, c, key0);
+                fold(s, c, key0, IC<0>{});
             }
             merge_halves();
             const float bias = e_run + fast_log2(l_run);

@@ -112,3 +112,28 @@ def run_softmax(S_dev: torch.Tensor, rows: int, cols: int, dtype: str, guard: in
     if canary is not None:
         assert guards_intact(canary), "softmax kernel wrote outside P"
     return P
+
+
+def large_scores(what: str, heads: int, N: int, d: int):
+    """fp32 operands whose scores fp32 holds and scales to moderate logits, and their scale: one column each, so that every product is
+    exact.  "straddling -2^80", "from -2^80 to 2^80": where operands times 2^24 each leave fp32's range; "all near -2^60": far below
+    where a maximum over such operands might start."""
+    j = np.arange(N)
+    step = (j * 5) % 8                            # (neighbouring keys in any order)
+    if what == "straddling -2^80":
+        q, k, scale = 2.0 ** 40, -2.0 ** 40 * (1 - 2.0 ** -6 + 2.0 ** -8 * step), 60 * 2.0 ** -80
+    elif what == "from -2^80 to 2^80":
+        q, k, scale = 2.0 ** 40, 2.0 ** 40 * (1 - 2.0 ** -6) * (step / 3.5 - 1.0).astype(np.float32), 4 * 2.0 ** -80
+    elif what == "all near -2^60":
+        q, k, scale = 2.0 ** 30, -2.0 ** 30 * (1 + 2.0 ** -6 * step), 86 * 2.0 ** -60
+    else:
+        raise ValueError(what)
+    Q = np.zeros((1, heads, N, d), np.float32)
+    K = np.zeros((1, heads, N, d), np.float32)
+    Q[..., d // 2] = q
+    K[..., d // 2] = k
+    # two roundings (c = scale log2(e), the fused multiply and add) of exponents up to 1.5 x 97
+    return Q, K, np.float32(scale), 2 * 1.5 * 97 * 2.0 ** -24
+
+
+LARGE_SCORES = ["straddling -2^80", "from -2^80 to 2^80", "all near -2^60"]

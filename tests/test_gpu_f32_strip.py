@@ -70,3 +70,14 @@ def test_not_finite(N, d):
         fin = np.isfinite(ref_s)
         assert (np.isfinite(S[0, h]) == fin).all() and (np.isnan(S[0, h]) == np.isnan(ref_s)).all(), f"scores, head {h}"
         assert np.abs(S[0, h][fin] - ref_s[fin]).max() <= 1e-5 * np.abs(ref_s[fin]).max(), f"scores, head {h}"
+
+
+@pytest.mark.parametrize("what", gu.LARGE_SCORES[:2])
+@pytest.mark.parametrize("heads,N,d", [(1, 128, 64), (3, 300, 36), (1, 2100, 100)])
+def test_large_scores(what, heads, N, d):
+    """Scores that fp32 holds and operands times 2^24 do not, with logits of ordinary size."""
+    Q, K, scale, rel = gu.large_scores(what, heads, N, d)
+    P = gu.to_f64(gu.run_fused(wl.FusedInputs("t", "f32", 1, heads, N, d, scale, Q, K), guard=4096))
+    ref = oracle.attention_weights(Q[0, 0], K[0, 0], "f32", scale)
+    for h in {0, heads - 1}:
+        gu.check_weights(P[0, h], ref, "f32", f"{what}: {heads} heads N={N} d={d} head {h}", abs_f32=2 * rel * ref.max())
