@@ -303,9 +303,11 @@ void qk_f32_strip_kernel(const float* __restrict__ Q, const float* __restrict__ 
         l_run = __builtin_fmaf(l_run, fast_exp2(e_run - en), sum);
         e_run = en;
     };
-    auto fold_begin = [&](float c) __attribute__((always_inline)) {
-        m_run = kNegBig;
-        e_run = kNegBig * c;
+    // The maximum over no keys.  In parts the lowest number there is: scores carry a factor of 2^48, and behind a higher one the
+    // exponentials of scores below it come out small, imprecise or zero.
+    auto fold_begin = [&](float m, float e) __attribute__((always_inline)) {
+        m_run = m;
+        e_run = e;
         l_run = 0.0f;
     };
     auto merge_halves = [&]() __attribute__((always_inline)) {   // the keys of the other half-wave
@@ -366,7 +368,7 @@ void qk_f32_strip_kernel(const float* __restrict__ Q, const float* __restrict__ 
             workgroup_barrier();
         } else {
             if (OWN_RAW && unit + 1 < last) request_q(unit + 1);
-            fold_begin(c_parts);
+            fold_begin(-0x1.fffffep127f, kNegBig);
             int young = 0;
             static_for<NT>([&](auto tc) __attribute__((always_inline)) {
                 constexpr int T = decltype(tc)::value;
@@ -445,7 +447,7 @@ void qk_f32_strip_kernel(const float* __restrict__ Q, const float* __restrict__ 
             const float* const Qh = Q + (int64_t)bh * N * d;
             const float* const Kh = K + (int64_t)bh * N * d;
             float* const Ph = P + (int64_t)bh * N * N;
-            fold_begin(c);
+            fold_begin(kNegBig, kNegBig * c);
             for (int key0 = 0; key0 < N; key0 += 32) {
                 f32x16 s = scores_f32(Qh, Kh, q0, key0);
                 fold(s, c, key0, IC<0>{});
