@@ -453,14 +453,14 @@ void qk_f32_strip_kernel(const float* __restrict__ Q, const float* __restrict__ 
                 fold(s, c, key0, IC<0>{});
             }
             merge_halves();
-            const float bias = e_run + fast_log2(l_run);
+            const float inv = 1.0f / l_run;
             for (int j = 0; j < nb; ++j) {
                 const int key0 = key_of(j);
                 const f32x16 s = scores_f32(Qh, Kh, q0, key0);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int key = key0 + 4 * half + 8 * (r / 4) + (r % 4);
-                    if (q0 + l32 < N && key < N) Ph[(int64_t)(q0 + l32) * N + key] = fast_exp2(__builtin_fmaf(s[r], c, -bias));
+                    if (q0 + l32 < N && key < N) Ph[(int64_t)(q0 + l32) * N + key] = fast_exp2(__builtin_fmaf(s[r], c, -e_run)) * inv;
                 }
             }
         }

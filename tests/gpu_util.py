@@ -117,13 +117,15 @@ def run_softmax(S_dev: torch.Tensor, rows: int, cols: int, dtype: str, guard: in
 def large_scores(what: str, heads: int, N: int, d: int):
     """fp32 operands whose scores fp32 holds and scales to moderate logits, and their scale: one column each, so that every product is
     exact.  "straddling -2^80", "from -2^80 to 2^80": where operands times 2^24 each leave fp32's range; "all near -2^60": far below
-    where a maximum over such operands might start."""
+    where a maximum over such operands might start.  "logits of -1000": exponents whose rounding (2^-14) must not reach the weights."""
     j = np.arange(N)
     step = (j * 5) % 8                            # (neighbouring keys in any order)
     if what == "straddling -2^80":
         q, k, scale = 2.0 ** 40, -2.0 ** 40 * (1 - 2.0 ** -6 + 2.0 ** -8 * step), 60 * 2.0 ** -80
     elif what == "from -2^80 to 2^80":
         q, k, scale = 2.0 ** 40, 2.0 ** 40 * (1 - 2.0 ** -6) * (step / 3.5 - 1.0).astype(np.float32), 4 * 2.0 ** -80
+    elif what == "straddling -2^80, logits of -1000":
+        q, k, scale = 2.0 ** 40, -2.0 ** 40 * (1 - 2.0 ** -10 + 2.0 ** -12 * step), 1000 * 2.0 ** -80
     elif what == "all near -2^60":
         q, k, scale = 2.0 ** 30, -2.0 ** 30 * (1 + 2.0 ** -6 * step), 86 * 2.0 ** -60
     else:
@@ -132,8 +134,8 @@ def large_scores(what: str, heads: int, N: int, d: int):
     K = np.zeros((1, heads, N, d), np.float32)
     Q[..., d // 2] = q
     K[..., d // 2] = k
-    # two roundings (c = scale log2(e), the fused multiply and add) of exponents up to 1.5 x 97
-    return Q, K, np.float32(scale), 2 * 1.5 * 97 * 2.0 ** -24
+    # logits differ by less than ten: three roundings (c = scale log2(e), the difference, the sum) of exponents up to 15
+    return Q, K, np.float32(scale), 3 * 15 * 2.0 ** -24
 
 
-LARGE_SCORES = ["straddling -2^80", "from -2^80 to 2^80", "all near -2^60"]
+LARGE_SCORES = ["straddling -2^80", "straddling -2^80, logits of -1000", "from -2^80 to 2^80", "all near -2^60"]
