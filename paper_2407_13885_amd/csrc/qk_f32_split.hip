@@ -121,8 +121,16 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
 
     const float c_parts = c * kSplitDown;         // for scores of operands in parts
     // running maximum and sum of exponentials over the lane's keys (accumulator r is key key0 + 4 half + 8 (r / 4) + r % 4)
+    // In parts scores beyond 2^79 either way (2^127 with the factor of the operands) make the sum NaN: from 2^80 on they are infinite
+    // where fp32 holds them, and differences of two of them overflow.
     float m_run = kNegBig, l_run = 0.0f;
-    auto fold = [&](const f32x16& s, float c, int key0) __attribute__((always_inline)) {
+    auto fold = [&](const f32x16& s, float c, int key0, auto partsc) __attribute__((always_inline)) {
+        float low = 0.0f;
+        if constexpr (decltype(partsc)::value != 0) {
+            low = fminf(s[0], s[1]);
+#pragma unroll
+            for (int r = 2; r < 16; r += 2) low = min3(low, s[r], s[r + 1]);
+        }
         float tm = max3(s[0], s[1], s[2]);
 #pragma unroll
         for (int r = 3; r < 15; r += 2) tm = max3(tm, s[r], s[r + 1]);
@@ -139,6 +147,7 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
 #pragma unroll
         for (int r = 1; r < 16; ++r) sum += e[r];
         l_run = l_run * fast_exp2((m_run - mn) * c) + sum;
+        if (decltype(partsc)::value != 0 && low < -0x1p127f) l_run = __builtin_nanf("");
         m_run = mn;
     };
     auto merge = [&](float m, float l, float c) __attribute__((always_inline)) {   // statistics of other keys of the same query
@@ -164,10 +173,11 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
 #pragma unroll
         for (int u = 0; u < SUBS; ++u) {
             const int key0 = tile_at(j) * BN + (u * WK + wk) * 32;
-            if (q0 < N && key0 < N) fold(scores(BUF, u), c_parts, key0);
+            if (q0 < N && key0 < N) fold(scores(BUF, u), c_parts, key0, IC<1>{});
         }
         __syncthreads();
     });
+    if (m_run > 0x1p127f) l_run = __builtin_nanf("");
     merge(__shfl_xor(m_run, 32, 64), __shfl_xor(l_run, 32, 64), c_parts);
     if (half == 0) {
         stat_lds[wave * 64 + l32] = m_run;
@@ -226,7 +236,7 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
     };
     m_run = kNegBig;
     l_run = 0.0f;
-    for (int key0 = 0; key0 < N; key0 += 32) fold(scores_f32(key0), c, key0);
+    for (int key0 = 0; key0 < N; key0 += 32) fold(scores_f32(key0), c, key0, IC<0>{});
     merge(__shfl_xor(m_run, 32, 64), __shfl_xor(l_run, 32, 64), c);
     const float bias_f32 = fast_log2(l_run);
     for (int key0 = wk * 32; key0 < N; key0 += WK * 32) {

@@ -71,3 +71,14 @@ def test_weights_f32_in_three_parts_not_finite():
         assert (np.isnan(P[0, h]) == np.isnan(ref)).all(), f"head {h}"
         ok = np.isfinite(ref)
         assert np.abs(P[0, h] - ref)[ok].max() <= gu.ABS_F32, f"head {h}"
+
+
+@pytest.mark.parametrize("what", gu.LARGE_SCORES[:3])
+@pytest.mark.parametrize("heads,N,d", [(128, 132, 64), (9, 3000, 100)])
+def test_weights_f32_in_three_parts_large_scores(what, heads, N, d):
+    """Scores that fp32 holds and operands times 2^24 do not, with logits of ordinary size."""
+    Q, K, scale, rel = gu.large_scores(what, heads, N, d)
+    P = gu.to_f64(gu.run_fused(wl.FusedInputs("t", "f32", 1, heads, N, d, scale, Q, K), guard=4096))
+    ref = oracle.attention_weights(Q[0, 0], K[0, 0], "f32", scale)
+    for h in {0, heads - 1}:
+        gu.check_weights(P[0, h], ref, "f32", f"{what}: {heads} heads N={N} d={d} head {h}", abs_f32=2 * rel * ref.max())
