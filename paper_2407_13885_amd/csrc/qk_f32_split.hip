@@ -123,7 +123,9 @@ void qk_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ 
     // running maximum and sum of exponentials over the lane's keys (accumulator r is key key0 + 4 half + 8 (r / 4) + r % 4)
     // In parts scores beyond 2^79 either way (2^127 with the factor of the operands) make the sum NaN: from 2^80 on they are infinite
     // where fp32 holds them, and differences of two of them overflow.
-    float m_run = kNegBig, l_run = 0.0f;
+    // (The maximum over no keys is the lowest number there is: scores in parts carry a factor of 2^48, and behind a higher one the
+    // exponentials of scores below it come out small, imprecise or zero.)
+    float m_run = -0x1.fffffep127f, l_run = 0.0f;
     auto fold = [&](const f32x16& s, float c, int key0, auto partsc) __attribute__((always_inline)) {
         float low = 0.0f;
         if constexpr (decltype(partsc)::value != 0) {
