@@ -6,7 +6,7 @@
 // max-subtracted softmax of the Softmax section, Eq. 1, is applied incrementally as in the other kernels.)
 //
 // What bounds it: the matrix instruction (12 x 32 cycles per 32 queries, 32 keys and 16 columns of d, where the fp32
-// instruction takes 16 x 64), under the board's power cap: busy 63 % of SIMD cycles at d = 128, vector ALU 34 %, both 8 % (14 registers
+// instruction takes 16 x 64), under the board's power cap: busy 63 % of SIMD cycles at d = 128, vector ALU 34 %, both 8 % (16 registers
 // spilled there: 4 of them are read back twice per tile, the others belong to the restart).  Eight waves of 32 queries share a tile of 32 keys: splitting a
 // K or V element costs six vector instructions, spread over 256 queries.  A thread loads 8 elements of a row, splits them
 // and writes a 16-byte chunk to each of the three planes of the tile; planes lie as rows in memory do, chunks
@@ -149,6 +149,10 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
         l_run += sum;
     };
 
+    // The smallest score so far, in parts: below -2^80 it is -infinity, also where fp32 holds it, and leaves no trace in the sums.
+    // (Eight instructions per 32 keys: 16 heads of N = 4096, d = 128 626 -> 636 us, 64 326 -> 327, 32 191 -> 198; a bound from the largest
+    // |Q| and |K|, which costs half of them, kept more registers and took longer, 646 / 336 / 189.)
+    float low = 0.0f;
     auto compute = [&](int t, int buf) __attribute__((always_inline)) {
         f32x16 s;
 #pragma unroll
@@ -162,6 +166,14 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
         }
         float p[16];
         weights(s, c * kSplitDown, t * BN, p);
+        {
+            float a = min3(s[0], s[1], s[2]), b = min3(s[3], s[4], s[5]);
+            a = min3(a, s[6], s[7]);
+            b = min3(b, s[8], s[9]);
+            a = min3(a, s[10], s[11]);
+            b = min3(b, s[12], s[13]);
+            low = min3(low, a, min3(b, s[14], s[15]));
+        }
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             float x[8];
@@ -199,11 +211,11 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
 
     // ---- infinities, NaN and overflows (rare): what the parts make of them is not what fp32 does.  The wave starts again on
     // the fp32 instruction, operands straight from memory ---------------------------------------------------------------------
-    float worst = l_run, down = kSplitDown;
+    float worst = __builtin_fmaf(low, 0.0f, l_run), down = kSplitDown;
 #pragma unroll
     for (int b = 0; b < DVB; ++b)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) worst = __builtin_fmaf(oacc[b][r], 0.0f, worst);   // NaN if any accumulator is not finite
+        for (int r = 0; r < 16; ++r) worst = __builtin_fmaf(oacc[b][r], 0.0f, worst);   // NaN if any of them is not finite
     if (__builtin_amdgcn_ballot_w64(!(fabsf(worst) < __builtin_inff())) != 0) {
         reset();
         down = 1.0f;

@@ -4,7 +4,7 @@
 // 2^24 x = hi + mid + lo with three bf16 numbers, each the rest rounded to nearest: 24 significand bits, the whole of x.  The
 // factor keeps the last part of the smallest fp32 number a normal bf16 number: without it |x| below 2^-110 lost up to 16 of its bits
 // (attention over V of 2^-118 / 2^-122: 9.5e-6 / 1.4e-4 off, 3e-7 in fp32).  Infinities, NaN and |x| from 2^104 on make NaN, sums of
-// products from 2^80 on infinity: the callers look for either in their results and start again in fp32.
+// products from 2^80 on infinity: the callers look for either in their scores and sums and start again in fp32.
 // Of the nine products of two such numbers the six above 2^-24 of the whole are kept.  Six v_mfma_f32_32x32x16_bf16 do the work of
 // eight v_mfma_f32_32x32x2_f32 in 6 x 32 instead of 8 x 64 cycles.
 // Against 64 bits (32 x 32 scores of normal vectors, relative error in units of 1e-7): fp32 instruction 1.02 / 1.45 / 2.06 /

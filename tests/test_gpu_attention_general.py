@@ -329,3 +329,18 @@ def test_attention_f32_one_wave_workgroups_of_a_few_blocks(heads, N, d):
     O = gu.to_f64(_run(x, V))
     for h in (0, heads // 2 + 1, heads - 1):
         _check(O[0, h], x, V, 0, h, (0, N), f"fp32 attention {heads} heads N={N} d={d} head {h}")
+
+
+@pytest.mark.parametrize("what", gu.LARGE_SCORES)
+@pytest.mark.parametrize("heads,N,d", [(2, 257, 64), (256, 257, 64), (256, 200, 128)])
+def test_attention_f32_large_scores(what, heads, N, d):
+    """Scores that fp32 holds and operands times 2^24 do not, with logits of ordinary size, on the fp32 instruction (two heads) and in
+    three bf16 parts."""
+    Q, K, scale, rel = gu.large_scores(what, heads, N, d)
+    x = wl.FusedInputs("t", "f32", 1, heads, N, d, scale, Q, K)
+    V = wl.value_inputs(x, seed=4901)
+    O = gu.to_f64(_run(x, V))
+    for h in {0, heads - 1}:
+        ref = oracle.attention_output(Q[0, h], K[0, h], V[0, h], "f32", scale, rows=(0, N))
+        # weights off by `rel` relative to each other, sums of N products
+        assert np.abs(O[0, h] - ref).max() <= (2 * rel + (N + 8) * 2.0 ** -24) * np.abs(V[0, h]).max(), f"{what}, {heads} heads, head {h}"
