@@ -736,6 +736,8 @@ hipError_t launch_ring(bool scores_only, const void* Q, const void* K, void* out
     return launch_ring_t<DB, 2>(scores_only, Q, K, out, BH, N, d, scale, stream);
 }
 
+constexpr int kWideStrips = 200;                  // from so many wide strips on there is work for every compute unit
+
 template <typename T>
 hipError_t launch_qk_t(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int N, int d,
                        float scale, hipStream_t stream, bool allow_split)
@@ -745,7 +747,7 @@ hipError_t launch_qk_t(bool scores_only, const void* Q, const void* K, void* out
     // wide strips (4 waves along the queries) when that still gives every compute unit work, also when it
     // does so only with the keys of a strip split over several workgroups (rows of 128 and 256 bytes)
     const int64_t wide_units = BH * ((N + 128 * QB - 1) / (128 * QB));
-    const bool big = wide_units >= 200;
+    const bool big = wide_units >= kWideStrips;
     // (not below 1024 keys: two launches of a few microseconds each cost more than the idle compute units)
     const bool split = allow_split && !big && N >= 1024 && row_bytes > 64 && row_bytes <= 256 &&
                        key_ranges(wide_units, (N + 127) / 128) > 1;
@@ -819,22 +821,38 @@ bool prefers_f32_split(int64_t BH, int64_t N, int64_t d)
     return N > 2048 || N < (d > 64 ? 192 : 512) || d <= 32;
 }
 
-// fp32 on 32-query strips whose scores stay in registers: weights of everything that the rule above leaves but very short rows of
-// short sequences (1969 heads of N = 65, d = 8 62 -> 73 us); measured against the general kernel: two heads of 2976, d = 84 416 -> 60, one of
-// 128, d = 64 8.9 -> 5.3, one of 416, d = 128 69 -> 11.5, nine of 2743, d = 128 417 -> 242, 25 of 730, d = 228 221 -> 86, 182 of 700, d = 256
-// 1094 -> 497, 1969 of 65, d = 64 128 -> 89.  Scores: four of 996, d = 256 152 -> 33, 93 of 1025, d = 64 241 -> 184; not taken where the
-// general kernel streams whole tiles as fast (93 of 1024: d = 32 81 -> 98, d = 256 451 -> 487) or splits the keys of a few long rows
-// over workgroups (one of 2048, d = 64 16.5 -> 20).
+// fp32 on 32-query strips whose scores stay in registers, after the rule above: weights of everything but short rows of many short
+// sequences, where the general kernel computes whole tiles of 128 queries in few rounds of workgroups.  Measured against that kernel, us:
+// two heads of 2976, d = 84 410 -> 61, one of 128, d = 64 8.9 -> 7.4, one of 416, d = 128 69 -> 11.5, nine of 2743, d = 128 420 -> 257, 25 of
+// 730, d = 228 219 -> 84, 1969 of 65, d = 64 128 -> 89; not 1969 of 65, d = 8 62 -> 73, 204 of 122, d = 32 12.8 -> 16.2, 740 of 117, d = 20 35 -> 41, 80
+// of 358, d = 16 20 -> 24.
+// Scores need no second sweep there either, and with short rows that kernel is bound by its stores: from some 500 random shapes of
+// each range, us.  d <= 16: 3797 of 108 60 -> 139, 434 of 120 11 -> 21, 637 of 60 10.8 -> 15.4, 85 of 381 14.7 -> 21 (tiles nearly full: not taken), but 204 of
+// 131 17.8 -> 16.4, 93 of 1025 59 -> 39 (taken).  d <= 32: 1024 strips of N = 101 to 127 9 -> 13 (not taken), of 131 24 -> 16, of 577 46 -> 26.  d <= 64:
+// 1470 of 104, d = 36 56 -> 74 (not taken), 194 of 100, d = 64 30 -> 15.5; one of 2810, d = 48 18.5 -> 32: the general kernel splits
+// the keys of a few long rows over workgroups (not taken).  Beyond d = 64: four of 996, d = 256 152 -> 33, 93 of 1025, d = 64 241 -> 184; not 93 of 1024, d = 256
+// 451 -> 487.
 bool prefers_f32_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 {
     if (N * d >= (int64_t)1 << 28) return false;
-    const int64_t cus = compute_units(), strips = BH * ((N + 31) / 32);
-    if (!scores_only) return d > 16 || N >= 128 || strips <= cus;
-    if (N % 4 != 0) return true;
-    if (d > 128) return N % 128 != 0 || strips <= 4 * cus;
-    if (d > 64) return true;
-    if (N >= 2048 && 2 * strips < cus) return false;
-    return d > 32 || N < 128 || strips <= 2 * cus;
+    const int64_t cus = compute_units(), strips = BH * ((N + 31) / 32), large = BH * ((N + 127) / 128);
+    const int64_t rounds = (strips + cus - 1) / cus, large_rounds = (large + cus - 1) / cus;
+    const bool wide = large >= kWideStrips;       // the general kernel takes 128 queries per workgroup
+    if (!scores_only) {
+        if (d <= 16 && N < 128) return strips <= cus;
+        if (d > 32 || !wide || 2 * rounds < 7 * large_rounds) return true;
+        return d > 16 ? N > 128 : N > 384 || large_rounds > 1;
+    }
+    if (d > 128) return N % 4 != 0 || N % 128 != 0 || strips <= 4 * cus;
+    if (d > 64 || N <= 32) return true;
+    // keys of few long rows split over workgroups
+    if (2 * strips <= cus && N >= (d <= 16 ? 2048 : d <= 32 ? 1152 : 1536) && (d > 16 || N % 4 == 0)) return false;
+    if (strips <= cus) return true;
+    if (d <= 32 && N % 4 == 0 && N >= 128 && strips > 2 * cus) return false;
+    if (d <= 16) return N > 128 && 10 * rounds < (N <= 160 ? 26 : N <= 384 ? 20 : 30) * large_rounds;
+    if (N > 128) return d > 32 || !wide || rounds < 4 * large_rounds;
+    if (d > 32) return N <= 96 || !wide || 2 * rounds < 7 * large_rounds;
+    return wide ? 10 * rounds < (large_rounds <= 2 ? 20 : 25) * large_rounds : strips <= 2 * cus;
 }
 
 // bf16 on 32-query strips, a workgroup each, 129 to 1280 tokens.  Measured, the kernel that would take it otherwise -> this one, fused /
