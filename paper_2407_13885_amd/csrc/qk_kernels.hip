@@ -831,7 +831,8 @@ bool prefers_f32_split(int64_t BH, int64_t N, int64_t d)
 // 131 17.8 -> 16.4, 93 of 1025 59 -> 39 (taken).  d <= 32: 1024 strips of N = 101 to 127 9 -> 13 (not taken), of 131 24 -> 16, of 577 46 -> 26.  d <= 64:
 // 1470 of 104, d = 36 56 -> 74 (not taken), 194 of 100, d = 64 30 -> 15.5; one of 2810, d = 48 18.5 -> 32: the general kernel splits
 // the keys of a few long rows over workgroups (not taken).  Beyond d = 64: four of 996, d = 256 152 -> 33, 93 of 1025, d = 64 241 -> 184; not 93 of 1024, d = 256
-// 451 -> 487.
+// 451 -> 487.  Four columns: the six products are less exact than four of the fp32 instruction (scores of normal vectors 4.10e-8 off
+// against 3.97e-8; eight columns 4.02e-8 against 5.4e-8).
 bool prefers_f32_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 {
     if (N * d >= (int64_t)1 << 28) return false;
@@ -843,6 +844,7 @@ bool prefers_f32_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
         if (d > 32 || !wide || 2 * rounds < 7 * large_rounds) return true;
         return d > 16 ? N > 128 : N > 384 || large_rounds > 1;
     }
+    if (d < 8) return false;
     if (d > 128) return N % 4 != 0 || N % 128 != 0 || strips <= 4 * cus;
     if (d > 64 || N <= 32) return true;
     // keys of few long rows split over workgroups

@@ -81,3 +81,15 @@ def test_large_scores(what, heads, N, d):
     ref = oracle.attention_weights(Q[0, 0], K[0, 0], "f32", scale)
     for h in {0, heads - 1}:
         gu.check_weights(P[0, h], ref, "f32", f"{what}: {heads} heads N={N} d={d} head {h}", abs_f32=2 * rel * ref.max())
+
+
+@pytest.mark.parametrize("heads,N", [(1, 100), (3, 257), (400, 100), (1, 2049)])
+def test_scores_of_four_columns(heads, N):
+    """Four products are too few for six of their parts to be as exact as the fp32 instruction: a score that is one product is that
+    product, rounded once (2^-24) and once more by the scale (a power of two: not at all)."""
+    x = wl.fused_inputs("t", "f32", 1, heads, N, 4, seed=7400 + N, scale=0.5)
+    x.Q[...] *= (np.arange(4) == (np.arange(N) % 4)[:, None]).astype(np.float32)
+    S = gu.to_f64(gu.run_scores(x, guard=4096))
+    for h in sorted({0, heads // 2, heads - 1}):
+        ref = 0.5 * (x.Q[0, h].astype(np.float64) @ x.K[0, h].astype(np.float64).T)
+        assert (np.abs(S[0, h] - ref) <= 2.0 ** -24 * np.abs(ref)).all(), f"{heads} heads N={N} head {h}"
