@@ -866,16 +866,32 @@ bool prefers_f32_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 //     228 / 165 -> 148 / 132; 130 of 1000, d = 64 151 / 112 -> 77 / 68; 128 of 1025 140 / 110 -> 86 / 82; 97 of 1152 85 / 58 -> 72 / 64; 495 of 512
 //     76 / 54 -> 68 / 58; 317 of 640 95 / 67 -> 69 / 62, d = 128 131 / 87 -> 142 / 121; 48 of 1024 26 -> 32, d = 128 97 / 60 -> 101 / 90; 647 of 448,
 //     d = 128 169 / 104 -> 125 / 124; 79 of 1279, d = 128 152 / 109 -> 151 / 129
+//   the last round of 256-query workgroups nearly full, so that whole tiles waste little (`filled`: 32-query strips per eight of those that the
+//     rounds hold), not taken, scores in us: 63 of 852, d = 128 29 -> 38, 127 of 880 54 -> 74, 57 of 1000 33 -> 46, d = 112 31 -> 38, 48 of 1250, d = 64 41 ->
+//     49, 102 of 1279 93 -> 111, 73 of 672 16.8 -> 20.1, 51 of 640 10.6 -> 13.3, 69 of 704, d = 32 14.6 -> 16.7; weights 51 of 1279, d = 128 80 -> 93; taken: 102
+//     of 1250, d = 96 120 -> 108, 127 of 1000, d = 80 68 -> 66, 190 of 1000, d = 112 (a third round) 153 -> 117
 bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 {
     const int64_t cus = compute_units(), strips = BH * ((N + 31) / 32);
     if (qk_heads_supported(BH, N, d))             // (against whole rows in a wave: short sequences)
         return strips <= cus || (N > 192 && 2 * strips <= (d > 64 ? 2 : 5) * cus);
+    const int64_t large = BH * ((N + 255) / 256), rounds = (large + cus - 1) / cus;
+    auto filled = [&](int percent) { return 100 * strips > percent * 8 * cus * rounds; };
     if (scores_only) {
         if (d > 96 && N > 1216) return false;     // (one workgroup to a compute unit)
-        if (strips <= cus || (N % 32) != 0) return true;
+        if (strips <= cus) return true;
+        if (N % 2 != 0) return d <= 32 || N < 704 || rounds > 3 || !filled(93);   // (against the ring)
+        const bool whole = N % 32 == 0;
+        if (large >= kWideStrips) {
+            if (d > 96 && rounds <= 2 && filled(75)) return false;
+            if (rounds == 1 && filled(whole ? 70 : 85)) return false;
+            if (whole && d > 32 && rounds == 2 && filled(90)) return false;
+        }
+        if (!whole) return true;
+        if (N % 128 == 0 && d > 32 && strips > 3 * cus) return false;
         return d <= 64 && (N % 256) != 0 && (d <= 32 || N < 704);
     }
+    if (d > 112 && N > 1216 && rounds <= 2 && filled(90)) return false;   // (one workgroup to a compute unit)
     if (N % 256 != 0) return !(d > 96 && N == 640 && strips > 2 * cus);   // (640: a fifth of 128-query strips is all that the tiles waste)
     if (d != 64 && d != 128) return N < 1280 || d > 64;
     // whole tiles of the two-sweep, resident and gang kernels
