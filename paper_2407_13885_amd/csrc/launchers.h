@@ -49,7 +49,7 @@ bool qk_resident_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_qk_resident(const void* Q, const void* K, void* out, int64_t BH, int64_t N, float scale,
                               hipStream_t stream);
 
-// Fused attention weights or scaled scores, bf16, 8 <= N <= 64, d = 16 or 32, many heads: a wave per
+// Fused attention weights or scaled scores, bf16, 8 <= N <= 64, d = 16, many heads: a wave per
 // (head, 32 queries) with the K of the head as matrix operands in its registers, no LDS but the way out, no barriers.
 bool qk_tiny_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_qk_tiny(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d,
@@ -75,7 +75,7 @@ hipError_t launch_qk_gang(const void* Q, const void* K, void* out, int64_t BH, i
                           hipStream_t stream);
 
 // Fused attention weights, fp32, d a multiple of 4 up to 128, N a multiple of 4: the contraction on the bf16 instruction,
-// operands in three parts.
+// operands in three parts, K split once per 128 queries.
 // (Scores of operands in parts carry a factor of 2^48 that leaves with the scale, which stays a normal number only from here on.)
 inline bool split_takes_scale(float scale) { return scale == 0.0f || scale >= 0x1p-78f || scale <= -0x1p-78f; }
 hipError_t launch_qk_f32_split(const void* Q, const void* K, void* P, int64_t BH, int64_t N, int64_t d, float scale, hipStream_t stream);

@@ -920,10 +920,11 @@ hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, v
     const bool tiny = force && strcmp(force, "tiny") == 0;
     const bool heads = force && strcmp(force, "heads") == 0;
     const bool strip = force && strcmp(force, "strip") == 0;
-    // Many windows of up to 64 tokens with heads of 16 or 32, off the 16-byte boundaries: waves that work alone on a stream of (head, 32
-    // queries) pairs (12288 heads of N = 49, d = 32: 26.7 us against 30.6 of the next kernel; 4096 of N = 64 12.5 against 11.3; scores 24.3
-    // against 23.6; d = 64 50.4 against 49.8).
-    if (qk_tiny_supported(BH, N, d) && (tiny || (!force && !scores_only && N % 8 != 0 && BH * ((N + 31) / 32) >= 8192)))
+    // Very many windows of up to 64 tokens with heads of 16, off the 16-byte boundaries: waves that work alone on a stream of (head, 32
+    // queries) pairs.  Against the kernel after the next, us: 12288 heads of N = 49 21.0 / 22.3, 16384 of 33 24.6 / 26.7, 30000 of 13 16.0 / 17.6;
+    // not 8192 pairs (4096 of 49 10.4 / 9.2), multiples of 8 (16384 of 56 27.6 / 25.4), scores (16384 of 49 24.9 / 21.9) or heads of 32 (12288 of 49
+    // 25.9 / 26.0, 4096 11.6 / 10.2, 12288 of 62 32.9 / 31.3).
+    if (qk_tiny_supported(BH, N, d) && (tiny || (!force && !scores_only && N % 8 != 0 && BH * ((N + 31) / 32) >= 16384)))
         return launch_qk_tiny(scores_only, Q, K, out, BH, N, d, scale, stream);
     if (qk_strip_supported(BH, N, d) && (strip || (!force && prefers_strip(scores_only, BH, N, d))))
         return launch_qk_strip(scores_only, Q, K, out, BH, N, d, scale, stream);
