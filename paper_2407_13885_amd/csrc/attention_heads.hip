@@ -7,8 +7,8 @@
 // then walks all keys for 32 queries of its own.  Without tiles to wait for the waves of a SIMD drift apart, and one's softmax is
 // the other's matrix instructions; V is turned by the transposing LDS read.
 //
-// Measured, 7267 heads of N = 129, d = 64: 122 us (238 MB a pass, 3.9 TB/s; 255 with tiles shared by 256-query workgroups), 7324 of 128 105
-// (163 with operands gathered by every wave for itself), 1953 of 400 166 (227).  What bounds it: short of N = 128 the traffic of Q, K, V
+// Measured, 7267 heads of N = 129, d = 64: 122 us (480 MB of Q, K, V and O, 3.9 TB/s; 255 with tiles shared by 256-query workgroups), 7324 of
+// 128 105 (163 with operands gathered by every wave for itself), 1953 of 400 168 (233).  What bounds it: short of N = 128 the traffic of Q, K, V
 // and O, beyond the vector ALU between the two matrix instructions of a wave (softmax of 32 x 32 scores: about 150 instructions against
 // 4 + 4 of the matrix at d = 64), and the time that a workgroup alone on its compute unit waits for K and V.
 #include "attention_common.h"
@@ -176,7 +176,7 @@ bool attention_heads_supported(int64_t BH, int64_t N, int64_t d)
 }
 
 // Against the kernel that would take it otherwise, us: d = 64 9375 heads of N = 100 146 -> 111, 7324 of 128 163 -> 105, 7267 of 129 255 -> 122, 4758 of
-// 197 188 -> 130, 3662 of 256 126 -> 128, 3647 of 257 255 -> 159, 1953 of 400 227 -> 166, 1192 of 512 136 -> 137; d = 32 18750 of 100 129 -> 110,
+// 197 188 -> 130, 4000 of 240 187 -> 138, 3662 of 256 126 -> 130, 3647 of 257 255 -> 159, 1953 of 400 227 -> 166, 1192 of 512 136 -> 137; d = 32 18750 of 100 129 -> 110,
 // 9517 of 197 172 -> 138, 7295 of 257 236 -> 163, 3906 of 400 227 -> 175, 2384 of 512 141 -> 149, 1877 of 577 182 -> 168; d = 128 14204 of 33 238 ->
 // 120, 7324 of 64 141 -> 108, 4687 of 100 137 -> 121, 3633 of 129 145 -> 151, 1823 of 257 201 -> 166; d = 96 9765 of 64 113 -> 108, 4844 of 129 115 ->
 // 118, 2034 of 320 178 -> 154, 1412 of 384 131 -> 179; d = 16 and 48 of 64 142 -> 103, 112 -> 101, of 197 216 -> 221, 136 -> 143.  Fewer heads: 200 of
@@ -186,7 +186,7 @@ bool prefers_attention_heads(int64_t BH, int64_t N, int64_t d)
 {
     const int64_t cus = compute_units(), blocks = BH * ((N + 31) / 32);
     if (2 * blocks < 11 * cus || (d == 32 && BH < 2 * cus)) return false;
-    if (d == 64) return N > 64 && N <= 480 && N != 256;
+    if (d == 64) return N > 64 && N <= 480 && N % 256 != 0;    // (256: the tiled kernel's workgroups are full)
     if (d == 32) return N > 64 && (N <= 448 || (N <= 608 && N % 32 != 0));
     if (d <= 48) return N > 32 && N <= 64;
     if (d <= 96) return N > 32 && (N <= 64 || (N > 256 && N <= 320));

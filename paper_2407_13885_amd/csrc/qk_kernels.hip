@@ -864,7 +864,7 @@ bool prefers_f32_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 //     -> 6.4, 24 of 512 8.4 -> 7.8; 24 of 1280 30 / 20 -> 33 / 28; 12 of 1024 scores 8.2 -> 9.5
 //   many: 192 of 577, d = 64 64 -> 41; 390 of 577, d = 32 108 / 81 -> 66 / 62, d = 64 123 / 102 -> 78 / 71, d = 96 219 / 154 -> 97 / 88, d = 128
 //     228 / 165 -> 148 / 132; 130 of 1000, d = 64 151 / 112 -> 77 / 68; 128 of 1025 140 / 110 -> 86 / 82; 97 of 1152 85 / 58 -> 72 / 64; 495 of 512
-//     76 / 54 -> 68 / 58; 317 of 640 95 / 67 -> 69 / 62, d = 128 131 / 87 -> 142 / 121; 48 of 1024 26 -> 32, d = 128 97 / 60 -> 101 / 90; 647 of 448,
+//     76 / 54 -> 68 / 58; 317 of 640 95 / 67 -> 69 / 62, d = 128 131 / 87 -> 102 / 121; 48 of 1024 26 -> 32, d = 128 97 / 60 -> 101 / 90; 647 of 448,
 //     d = 128 169 / 104 -> 125 / 124; 79 of 1279, d = 128 152 / 109 -> 151 / 129
 //   the last round of 256-query workgroups nearly full, so that whole tiles waste little (`filled`: 32-query strips per eight of those that the
 //     rounds hold), not taken, scores in us: 63 of 852, d = 128 29 -> 38, 127 of 880 54 -> 74, 57 of 1000 33 -> 46, d = 112 31 -> 38, 48 of 1250, d = 64 41 ->
@@ -892,7 +892,7 @@ bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
         return d <= 64 && (N % 256) != 0 && (d <= 32 || N < 704);
     }
     if (d > 112 && N > 1216 && rounds <= 2 && filled(90)) return false;   // (one workgroup to a compute unit)
-    if (N % 256 != 0) return !(d > 96 && N == 640 && strips > 2 * cus);   // (640: a fifth of 128-query strips is all that the tiles waste)
+    if (N % 256 != 0) return true;
     if (d != 64 && d != 128) return N < 1280 || d > 64;
     // whole tiles of the two-sweep, resident and gang kernels
     if (d == 64 && N == 512) return strips > cus;
