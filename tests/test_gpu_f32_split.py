@@ -32,11 +32,26 @@ def test_weights_f32_in_three_parts(N, d):
         gu.check_weights(P[0, h], ref, "f32", f"fused f32 in parts {heads} heads N={N} d={d} head {h}")
 
 
+# (the 260 and 512 keys of some head sizes above go to the strips of 32 queries; these do not)
+@pytest.mark.parametrize("heads,N,d", [(64, 400, 64), (64, 508, 36), (70, 188, 128), (9, 2996, 128), (10, 3000, 64), (8, 4096, 100)])
+def test_weights_f32_in_three_parts_long_sweeps(heads, N, d):
+    """Interior tiles and long sweeps of head sizes above 32: 256 to 511 keys up to d = 64, beyond 2048 keys rounds that are full."""
+    strips, small = heads * ((N + 127) // 128), heads * ((N + 31) // 32)
+    full = -(-small // 256) >= 4 * -(-strips // 256)
+    assert 2 * strips >= 256 and (N > 2048 or N < (192 if d > 64 else 512) if full else N < (192 if d > 64 else 256))
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=6400 + N + d)
+    P = gu.to_f64(gu.run_fused(x, guard=4096))
+    assert np.abs(P.sum(axis=-1) - 1.0).max() <= gu.ROWSUM_F32
+    for h in (0, heads - 1):
+        ref = oracle.attention_weights(x.Q[0, h], x.K[0, h], "f32", x.scale)
+        gu.check_weights(P[0, h], ref, "f32", f"fused f32 in parts {heads} heads N={N} d={d} head {h}")
+
+
 @pytest.mark.parametrize("heads", [2, 128])
 @pytest.mark.parametrize("what", ["Q and K columns", "scale 2^-70", "scale 2^-90"])
 def test_weights_f32_over_the_range_of_fp32(what, heads):
-    """Operands of every magnitude that fp32 holds, on the fp32 instruction (two heads) and in three bf16 parts (128): as exact as
-    ordinary ones."""
+    """Operands of every magnitude that fp32 holds, in three bf16 parts (strips of 32 queries for two heads, of 128 for 128) and, at a
+    scale of 2^-90, on the fp32 instruction: as exact as ordinary ones."""
     N, d = 132, 64
     scale = {"Q and K columns": 2.0 ** 20, "scale 2^-70": 2.0 ** -70, "scale 2^-90": 2.0 ** -90}[what]
     x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=6300 + len(what), scale=scale / math.sqrt(d))

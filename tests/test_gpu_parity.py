@@ -89,7 +89,7 @@ def test_fused_ragged_multi_tile(dtype, B, H, N, d):
 # sweep flush what is left, chunks shared with the neighbouring rows go element by element; the last strip has waves
 # without rows.  N a multiple of 8: rows on 16-byte boundaries (1376: on 64-byte boundaries, nothing is ever held
 # back); 1284: rows at elements 0 or 4 of a chunk (8-byte staging writes), 1286: even elements (4-byte), odd N: any
-# (2-byte).  d = 96 and 16 pad the rows of K on chip.
+# (2-byte).  d = 96 and 16 pad the rows of K on chip.  (Up to 1280 tokens other kernels take most of these calls unasked.)
 
 @pytest.mark.parametrize("B,H,N,d", [(1, 15, 1544, 64), (2, 17, 1288, 128), (1, 13, 2056, 128), (1, 17, 1416, 96),
                                      (1, 17, 1304, 16), (1, 12, 2200, 32), (1, 17, 1376, 64),
@@ -97,8 +97,10 @@ def test_fused_ragged_multi_tile(dtype, B, H, N, d):
                                      (1, 13, 2049, 64), (1, 20, 1279, 32), (1, 17, 1281, 96), (1, 7, 4097, 128),
                                      (1, 25, 785, 64)])
 @pytest.mark.parametrize("what", ["fused", "scores"])
-def test_rows_on_16_byte_boundaries_take_whole_line_stores(B, H, N, d, what):
+def test_ragged_lengths_take_whole_line_stores(B, H, N, d, what, monkeypatch):
     assert N % 256 != 0 and N >= (704 if N % 2 else 1280) and B * H * ((N + 255) // 256) >= 100
+    if N <= 1280:
+        monkeypatch.setenv("ATTNW_FUSED_KERNEL", "twopass")
     _ring_case(B, H, N, d, what)
 
 
@@ -122,22 +124,32 @@ def _ring_case(B, H, N, d, what, scale=None):
 
 
 # the last, partial strip as a launch of its own (32-query strips, keys over the 8 waves) where its workgroups would
-# start another round on the chip's 256 compute units: 8, 1, 41 and 90 queries in it (1, 1, 2, 3 strips of the second
-# launch), 128-query strips: 1 and 65
+# start another round on the chip's 256 compute units: 8, 1, 41, 90, 1 and 1 queries in it (1, 1, 2, 3, 1, 1 strips of the second
+# launch)
 @pytest.mark.parametrize("B,H,N,d,scale", [(1, 16, 4104, 128, None), (1, 16, 4097, 64, -0.2), (1, 32, 2089, 128, None),
-                                           (1, 51, 1370, 64, None), (1, 128, 513, 32, None), (1, 73, 961, 64, -0.1)])
+                                           (1, 51, 1370, 64, None), (1, 85, 769, 64, -0.1), (1, 63, 1025, 32, None)])
 @pytest.mark.parametrize("what", ["fused", "scores"])
-def test_last_strip_of_a_ragged_length_as_a_launch_of_its_own(B, H, N, d, scale, what):
-    BM = 256 if N >= (704 if N % 2 else 1280) and not (N % 2 and N < 1152 and d <= 64) else 128
-    full, slots = B * H * (N // BM), 256 * (1 if BM == 256 else 2)
-    assert 0 < N % BM <= 96 and -(-full // slots) < -(-(full + B * H) // slots)
+def test_last_strip_of_a_ragged_length_as_a_launch_of_its_own(B, H, N, d, scale, what, monkeypatch):
+    full = B * H * (N // 256)
+    assert N >= (704 if N % 2 else 1280) and 0 < N % 256 <= 96 and -(-full // 256) < -(-(full + B * H) // 256)
+    if N <= 1280:
+        monkeypatch.setenv("ATTNW_FUSED_KERNEL", "twopass")
     _ring_case(B, H, N, d, what, scale=scale)
 
 
-@pytest.mark.parametrize("B,H,N,d", [(4, 50, 577, 64), (2, 60, 333, 32), (1, 100, 1001, 64), (3, 70, 321, 48), (1, 40, 1151, 16)])
+@pytest.mark.parametrize("B,H,N,d", [(4, 50, 577, 64), (2, 60, 333, 32), (1, 100, 1001, 64), (3, 70, 321, 48), (1, 40, 1151, 16),
+                                     (1, 128, 513, 32), (1, 73, 961, 64)])
 @pytest.mark.parametrize("what", ["fused", "scores"])
-def test_odd_lengths_of_a_few_hundred_take_the_ring_with_128_query_strips(B, H, N, d, what):
-    assert N % 2 == 1 and 320 <= N < 1152 and d <= 64 and B * H * ((N + 127) // 128) >= 200
+def test_odd_lengths_of_a_few_hundred(B, H, N, d, what):
+    _ring_case(B, H, N, d, what)
+
+
+# scores (weights: d = 128 beyond 1216 tokens) of 256-query strips that fill their rounds of workgroups, and of some that do not:
+# both sides of the line between whole tiles and 32-query strips
+@pytest.mark.parametrize("B,H,N,d", [(1, 63, 852, 128), (1, 40, 852, 128), (1, 102, 1279, 64), (1, 80, 1279, 64), (1, 48, 1250, 64),
+                                     (1, 73, 672, 64), (1, 51, 640, 64), (1, 51, 1279, 128), (1, 63, 1000, 112), (1, 69, 704, 32)])
+@pytest.mark.parametrize("what", ["fused", "scores"])
+def test_strips_that_fill_their_rounds(B, H, N, d, what):
     _ring_case(B, H, N, d, what)
 
 
@@ -585,7 +597,8 @@ def test_softmax_random_shapes(src, dst, rows, cols, inplace):
 
 # ---- few strips: the keys of a strip are split over several workgroups, statistics through tables in P --------
 
-# (d = 128 on one head: taken from the persistent kernel; the others: shapes of the general kernel)
+# (d = 128 on one head: taken from the persistent kernel; bf16 of other head sizes: shapes of the general kernel; fp32: the strip kernel,
+# and for scales too small for operands in parts the general one)
 @pytest.mark.parametrize("dtype,B,H,N,d,scale", [("bf16", 1, 1, 2048, 128, 0.0884), ("bf16", 1, 1, 4096, 128, -0.0884),
                                                  ("bf16", 1, 2, 3000, 64, 0.125), ("bf16", 1, 1, 1500, 96, 0.1),
                                                  ("bf16", 1, 2, 2176, 128, 0.0884), ("f32", 1, 1, 2048, 64, 0.125),
@@ -612,6 +625,20 @@ def test_fused_and_scores_with_split_keys(dtype, B, H, N, d, scale):
         qa, ka = np.abs(wl.widen(x.Q[0, h], dtype))[rows], np.abs(wl.widen(x.K[0, h], dtype))
         bound = d * 2.0 ** -24 * abs(scale) * (qa @ ka.T) + (2.0 ** -8 if dtype == "bf16" else 2.0 ** -24) * np.abs(ref) + 1e-30
         assert (np.abs(S[0, h][rows] - ref) <= bound).all(), f"split-key scores {dtype} {N}x{d} head {h}"
+
+
+@pytest.mark.parametrize("H,N,d", [(1, 2048, 64), (2, 1026, 32), (1, 1025, 64), (1, 1024, 64)])
+def test_split_keys_fp32_weights(H, N, d):
+    """Scales below 2^-78: no kernel for operands in parts takes them, and the keys of few strips are split over workgroups, statistics
+    through tables in P (rows of P on and off the 8-byte boundaries)."""
+    scale = 2.0 ** -81 / math.sqrt(d)
+    x = wl.fused_inputs("t", "f32", 1, H, N, d, seed=8200 + N, scale=scale)
+    x.Q[...] *= np.float32(2.0 ** 41)
+    x.K[...] *= np.float32(2.0 ** 40)
+    P = gu.to_f64(gu.run_fused(x, guard=8192))
+    for h in range(H):
+        ref = oracle.attention_weights(x.Q[0, h], x.K[0, h], "f32", x.scale)
+        gu.check_weights(P[0, h], ref, "f32", f"split keys f32, scale 2^-81, N={N} d={d} head {h}")
 
 
 def test_split_keys_match_the_unsplit_kernel_bit_for_bit_in_the_scores(monkeypatch):

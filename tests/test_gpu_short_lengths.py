@@ -1,6 +1,6 @@
-"""GPU parity of attnw_fused on short sequences of any length (bf16, d = 64, N <= 608: the kernel that stages a strip
-of 32 queries as the contiguous block of P that it is) against the fp64 oracle: every element of sampled heads at the
-bf16 bar, every row sum, the guard bands around P."""
+"""GPU parity of attnw_fused and attnw_gemm_scores on sequences of up to some hundred tokens of any length (bf16, d = 32 and 64, the
+kernels that take them unasked) against the fp64 oracle: every element of sampled heads at the bf16 bar, every row sum, the guard bands
+around P."""
 import os
 
 import numpy as np
@@ -31,8 +31,8 @@ def _check(B, H, N, scale=None, row_factor=(0.5, 2.0), seed=0, d=64):
     assert np.abs(got.sum(-1) - 1.0).max() <= gu.ROWSUM_BF16
 
 
-# odd lengths (2-byte staging writes), even (4-byte), multiples of 4 (8-byte); one to four pieces of keys per wave;
-# lengths with waves that own no key (197: the eighth), with a last strip of one query (33, 65, 257, 577), of 31 (607)
+# odd lengths (pairs made up across the half-waves), even (4-byte staging writes), multiples of 4 (8-byte); a last strip of one query
+# (33, 65, 257, 577), of 31 (607)
 @pytest.mark.parametrize("N", [1, 2, 3, 31, 33, 65, 100, 197, 198, 200, 255, 257, 258, 260, 333, 511, 513, 577, 578, 580,
                                601, 607])
 def test_short_sequences_any_length(N):
@@ -41,7 +41,7 @@ def test_short_sequences_any_length(N):
 
 @pytest.mark.parametrize("N", [129, 144, 197, 255, 257, 333, 510, 577, 607])
 def test_short_sequences_of_32_element_heads(N):
-    """d = 32: rows of 64 bytes, four K rows per 256-byte line of LDS."""
+    """d = 32: rows of 64 bytes, four K rows per 256-byte line of LDS; few and many heads."""
     _check(1, 3, N, d=32, seed=3)
     if N in (144, 197):
         _check(2, 150, N, d=32, seed=4)
@@ -49,8 +49,7 @@ def test_short_sequences_of_32_element_heads(N):
 
 @pytest.mark.parametrize("B,H,N", [(4, 70, 197), (2, 150, 257), (1, 300, 65), (3, 40, 577), (1, 9, 601)])
 def test_short_sequences_many_heads(B, H, N):
-    """More (head, strip) pairs than workgroups: strip lists that cross head boundaries (the K of the next head
-    replaces the one in LDS in the middle of a list); few heads: several workgroups share a head."""
+    """Many more (head, strip) pairs than compute units; few heads: several workgroups share a head."""
     _check(B, H, N)
 
 
@@ -62,8 +61,8 @@ def test_short_sequences_scale_values(N, scale):
 
 @pytest.mark.parametrize("N", [33, 197, 333, 577])
 def test_the_general_kernel_still_serves_these_lengths(N, monkeypatch):
-    """ATTNW_FUSED_KERNEL=twopass keeps the same problems on the two-pass kernel (its ragged paths at d = 64 would
-    otherwise only be reached by the score GEMM)."""
+    """ATTNW_FUSED_KERNEL=twopass keeps the same problems on the two-pass kernel (its ragged paths at d = 64 are
+    otherwise reached by long sequences only)."""
     monkeypatch.setenv("ATTNW_FUSED_KERNEL", "twopass")
     _check(1, 3, N, seed=11)
 
@@ -84,7 +83,7 @@ def _check_scores(x, S, what):
                                          (1, 2, 200, 1.0), (1, 150, 257, None), (1, 3, 333, 0.0), (2, 20, 577, None),
                                          (1, 3, 578, None), (1, 3, 607, -1.0)])
 def test_scaled_scores_of_short_sequences(B, H, N, scale, monkeypatch, d=64):
-    """attnw_gemm_scores on the same lengths: the same kernel without the statistics.  Against the oracle, the
+    """attnw_gemm_scores on the same lengths: the same kernels without the statistics.  Against the oracle, the
     guard bands around S, and bit for bit against the general kernel (same order of accumulation, one rounding)."""
     x = wl.fused_inputs("t", "bf16", B, H, N, d, seed=4300 + N, scale=scale, row_factor=(0.5, 2.0))
     S = gu.run_scores(x, guard=8192)
