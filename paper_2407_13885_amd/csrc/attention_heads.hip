@@ -181,13 +181,18 @@ bool attention_heads_supported(int64_t BH, int64_t N, int64_t d)
 // 120, 7324 of 64 141 -> 108, 4687 of 100 137 -> 121, 3633 of 129 145 -> 151, 1823 of 257 201 -> 166; d = 96 9765 of 64 113 -> 108, 4844 of 129 115 ->
 // 118, 2034 of 320 178 -> 154, 1412 of 384 131 -> 179; d = 16 and 48 of 64 142 -> 103, 112 -> 101, of 197 216 -> 221, 136 -> 143.  Fewer heads: 200 of
 // 129, d = 64 7.6 both, of 197 11.5 -> 9.8, of 320, d = 32 9.8 -> 11.0, 300
-// of 192, d = 32 6.7 -> 8.3, 200 of 64, d = 128 6.4 -> 7.0.
+// of 192, d = 32 6.7 -> 8.3, 200 of 64, d = 128 6.4 -> 7.0.  d = 64 beyond 256 tokens is one workgroup to a compute unit: not where the 256-query
+// strips make one round (102 of 480 16.0 -> 19.5, 114 of 450 16.2 -> 19.8, 110 of 415 16.4 -> 18.5; 153 of 400 taken), nor the few heads of a second
+// round (263 of 288 18.8 -> 21.3, 320 of 288 20.9 -> 23.2, 257 of 336 24.6 -> 28.4; taken 345 of 288 and 310 of 310, 0.69 times).  d = 32 of 256: 755 15.3 -> 18.1,
+// 1648 34 -> 39.
 bool prefers_attention_heads(int64_t BH, int64_t N, int64_t d)
 {
     const int64_t cus = compute_units(), blocks = BH * ((N + 31) / 32);
     if (2 * blocks < 11 * cus || (d == 32 && BH < 2 * cus)) return false;
+    if (d == 64 && N > 256 && 2 * BH <= cus) return false;
+    if (d == 64 && N > 256 && N <= 352 && BH > cus && 20 * BH < (N <= 288 ? 27 : 23) * cus) return false;
     if (d == 64) return N > 64 && N <= 480 && N % 256 != 0;    // (256: the tiled kernel's workgroups are full)
-    if (d == 32) return N > 64 && (N <= 448 || (N <= 608 && N % 32 != 0));
+    if (d == 32) return N > 64 && N != 256 && (N <= 448 || (N <= 608 && N % 32 != 0));
     if (d <= 48) return N > 32 && N <= 64;
     if (d <= 96) return N > 32 && (N <= 64 || (N > 256 && N <= 320));
     return N > 32 && (N <= 112 || N > 256);

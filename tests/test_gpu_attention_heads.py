@@ -35,3 +35,14 @@ def test_negative_scale(monkeypatch):
     O = gu.to_f64(_run(x, V))
     for h in range(2):
         _check(O[0, h], x, V, 0, h, (0, 333), f"negative scale, head {h}")
+
+
+# few heads of more than 256 tokens, and 256 tokens of d = 32: left to the kernels of 256-query strips; and the neighbours that are not
+@pytest.mark.parametrize("heads,N,d", [(102, 480, 64), (263, 288, 64), (257, 336, 64), (755, 256, 32), (135, 450, 64), (346, 288, 64),
+                                       (755, 255, 32)])
+def test_as_dispatched(heads, N, d):
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=3960 + N + d, row_factor=(0.5, 2.0))
+    V = wl.value_inputs(x, seed=3961 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in {0, heads - 1}:
+        _check(O[0, h], x, V, 0, h, (0, N), f"{heads} heads of {N} x {d}, head {h}")
