@@ -757,9 +757,10 @@ hipError_t launch_qk_t(bool scores_only, const void* Q, const void* K, void* out
         // fused / scores in us.  B1 H16 d128: N = 2056 223 / 110 -> 88 / 52, 4072 286 / 215 -> 240 / 168, 4097 462 / 322 ->
         // 325 / 201, 4100 398 / 265 -> 294 / 175, 4104 (a 17th strip of 8 rows) 369 / 242 -> 340 / 226, 8168 1069 / 828 ->
         // 929 / 711; 4000 (rows on 64-byte boundaries) 225 / 151 both.  B8 H16 d64: N = 1543 368 / 283 -> 300 / 213,
-        // 1544 283 / 230 -> 259 / 169, 1284 209 / 157 -> 181 / 119; 1025 193 / 139 -> 182 / 126, B16 H16 N = 785 208 / 152 ->
-        // 179 / 126; not taken: 1032 121 / 78 -> 163 / 104, 1030 144 / 93 -> 164 / 120, B16 H12 N = 577 105 / 77 -> 111 / 84,
-        // B64 H16 N = 197 74 / 53 -> 95 / 77.  Odd lengths gain earlier: their alternative is 2-byte stores.
+        // 1544 283 / 230 -> 259 / 169, 1284 209 / 157 -> 181 / 119.  Odd lengths gain earlier, as their alternative is 2-byte stores:
+        // 1025 193 / 139 -> 182 / 126, B16 H16 N = 785 208 / 152 -> 179 / 126, but not B16 H12 N = 577 105 / 77 -> 111 / 84.  Up to 1280
+        // tokens, though, most calls are on the 32-query strips (prefers_strip); here arrive the odd lengths that it leaves: scores
+        // from 704 tokens on whose last round of 256-query strips is nearly full, and d above 96 from 1217 on.
         if (N >= ((N & 1) ? 704 : 1280) && (N % 256) != 0 && row_bytes <= 256 && BH * ((N + 255) / 256) >= 100) {
             if (row_bytes <= 64) return launch_ring<64>(scores_only, Q, K, out, BH, N, d, scale, stream);
             if (row_bytes <= 128) return launch_ring<128>(scores_only, Q, K, out, BH, N, d, scale, stream);
@@ -870,6 +871,10 @@ bool prefers_f32_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 //     rounds hold), not taken, scores in us: 63 of 852, d = 128 29 -> 38, 127 of 880 54 -> 74, 57 of 1000 33 -> 46, d = 112 31 -> 38, 48 of 1250, d = 64 41 ->
 //     49, 102 of 1279 93 -> 111, 73 of 672 16.8 -> 20.1, 51 of 640 10.6 -> 13.3, 69 of 704, d = 32 14.6 -> 16.7; weights 51 of 1279, d = 128 80 -> 93; taken: 102
 //     of 1250, d = 96 120 -> 108, 127 of 1000, d = 80 68 -> 66, 190 of 1000, d = 112 (a third round) 153 -> 117
+//     the same of multiples of 4: 124 of 860, d = 64 47 -> 58, 116 of 984 54 -> 66, 42 of 1156 30 -> 35, 76 of 620, d = 128 24 -> 29, 42 of 1036 34 -> 43
+//   scores of whole 32-query strips, not taken: d = 32 86 of 1248 53 -> 67, 113 of 960 37 -> 44, 38 of 1088 19 -> 23, 40 of 640 8.3 -> 11.3, 24 of 1152 14.9 ->
+//     17.6; d = 64 148 of 672 34 -> 46, 226 of 672 50 -> 70; taken: d = 32 26 of 992 16.8 -> 14.0, 58 of 1120 38 -> 31, 129 of 960 (a third round) 50 -> 47, 25 of
+//     736 13.3 -> 8.5; d = 64 47 of 672 16.6 -> 14.8, 206 of 608 41 -> 37
 bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 {
     const int64_t cus = compute_units(), strips = BH * ((N + 31) / 32);
@@ -886,10 +891,12 @@ bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
             if (d > 96 && rounds <= 2 && filled(75)) return false;
             if (rounds == 1 && filled(whole ? 70 : 85)) return false;
             if (whole && d > 32 && rounds == 2 && filled(90)) return false;
+            if (N % 4 == 0 && (d > 96 ? rounds == 1 && filled(68) : rounds <= 2 && N > 704 && filled(72))) return false;
         }
         if (!whole) return true;
-        if (N % 128 == 0 && d > 32 && strips > 3 * cus) return false;
-        return d <= 64 && (N % 256) != 0 && (d <= 32 || N < 704);
+        if (N % 128 == 0 && d >= 32 && strips > (d > 32 ? 3 : 2) * cus) return false;
+        if (d <= 32 && N > 800 && rounds <= 2 && filled(rounds == 1 ? 50 : 62)) return false;
+        return d <= 64 && (N % 256) != 0 && (d <= 32 || N < 640 || (N < 704 && !filled(50)));
     }
     if (d > 112 && N > 1216 && rounds <= 2 && filled(90)) return false;   // (one workgroup to a compute unit)
     if (N % 256 != 0) return true;

@@ -147,7 +147,8 @@ def test_odd_lengths_of_a_few_hundred(B, H, N, d, what):
 # scores (weights: d = 128 beyond 1216 tokens) of 256-query strips that fill their rounds of workgroups, and of some that do not:
 # both sides of the line between whole tiles and 32-query strips
 @pytest.mark.parametrize("B,H,N,d", [(1, 63, 852, 128), (1, 40, 852, 128), (1, 102, 1279, 64), (1, 80, 1279, 64), (1, 48, 1250, 64),
-                                     (1, 73, 672, 64), (1, 51, 640, 64), (1, 51, 1279, 128), (1, 63, 1000, 112), (1, 69, 704, 32)])
+                                     (1, 73, 672, 64), (1, 51, 640, 64), (1, 51, 1279, 128), (1, 63, 1000, 112), (1, 69, 704, 32),
+                                     (1, 86, 1248, 32), (1, 40, 640, 32), (1, 148, 672, 64), (1, 124, 860, 64), (1, 76, 620, 128)])
 @pytest.mark.parametrize("what", ["fused", "scores"])
 def test_strips_that_fill_their_rounds(B, H, N, d, what):
     _ring_case(B, H, N, d, what)
