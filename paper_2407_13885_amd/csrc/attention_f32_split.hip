@@ -6,7 +6,7 @@
 // max-subtracted softmax of the Softmax section, Eq. 1, is applied incrementally as in the other kernels.)
 //
 // What bounds it: the matrix instruction (12 x 32 cycles per 32 queries, 32 keys and 16 columns of d, where the fp32
-// instruction takes 16 x 64), under the board's power cap: busy 63 % of SIMD cycles at d = 128, vector ALU 34 %, both 8 % (16 registers
+// instruction takes 16 x 64), under the board's power cap: busy 63 % of SIMD cycles at d = 128, vector ALU 34 %, both 8 % (14 registers
 // spilled there: 4 of them are read back twice per tile, the others belong to the restart).  Eight waves of 32 queries share a tile of 32 keys: splitting a
 // K or V element costs six vector instructions, spread over 256 queries.  A thread loads 8 elements of a row, splits them
 // and writes a 16-byte chunk to each of the three planes of the tile; planes lie as rows in memory do, chunks
@@ -40,6 +40,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
     static_assert(CHUNKS % 64 == 0, "a wave's slots are of one tensor");
 
     __shared__ __align__(1024) char lds[2 * BUF_BYTES];
+    __shared__ int k_large[NW];                   // a wave has brought a |K| beyond kLarge, beyond kHuge (1, 2)
 
     const uint32_t logical = xcd_contiguous_block_id(blockIdx.x, gridDim.x);
     if (logical >= total) return;
@@ -55,17 +56,30 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
     float* Oh = O + (int64_t)bh * N * d;
     const int q0 = strip * 32 * NW + wave * 32;
 
+    float q_max = 0.0f;
     Split8 qf[G];                                 // (q_sign: a negative scale negates Q)
     {
         const float* qrow = Qh + (int64_t)min(q0 + l32, N - 1) * d;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int col = g * 16 + half * 8;
-            qf[g] = split_row8(load_row8(qrow, col, d), col, d, q_sign * kSplitUp);
+            const Row8 row = load_row8(qrow, col, d);
+            q_max = fmaxf(q_max, largest(row));
+            qf[g] = split_row8(row, col, d, q_sign * kSplitUp);
         }
     }
+    // From 2^80 on, either way, a score in parts is infinite also where fp32 holds it, and one of -infinity leaves no trace in the sums.
+    // No score of 128 products gets there while |Q| and |K| stay within 2^20 and 2^52, either of them the larger one; waves whose
+    // operands do not start again on the fp32 instruction.  (Six instructions per 32 keys, before
+    // the split, and nothing kept but scalar masks: without / with, us: 16 heads of N = 4096, d = 128 652 / 656, 64 330 / 333, 32 192.5 both, 300 of
+    // 197, d = 64 39.5 / 40.6.  The smallest score beside the sums, a vector register and eight instructions: 672 / 333 / 199 / 39.8; a limit for
+    // |K| from the largest |Q| of the workgroup, one more barrier: 653 / 336 / 192 / 41.9.)
+    constexpr float kLarge = 0x1p20f, kHuge = 0x1p52f;
+    const uint64_t q_large = __builtin_amdgcn_ballot_w64(q_max > kLarge), q_huge = __builtin_amdgcn_ballot_w64(q_max > kHuge);
+    uint64_t large = 0, huge = 0;                 // of K
 
     // ---- tiles: slot s of a tile is chunk s of K or chunk s - CHUNKS of V --------------------------------------------------
+    static_assert(CHUNKS <= NW * 64, "all of K in the first slots");
     Row8 reg[SLOTS];
     auto load = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
@@ -87,6 +101,11 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
                 const bool v = w * 64 >= CHUNKS;
                 const int s = (v ? w * 64 - CHUNKS : w * 64) + lane;
                 const int key = s / CPR, ch = s - key * CPR;
+                if (j == 0) {
+                    const float k_max = largest(reg[j]);
+                    large |= __builtin_amdgcn_ballot_w64(k_max > kLarge);
+                    huge |= __builtin_amdgcn_ballot_w64(k_max > kHuge);
+                }
                 const Split8 x = split_row8(reg[j], ch * 8, d);
                 char* to = lds + buf * BUF_BYTES + (v ? 3 * PLANE : 0) + key * DB + (ch ^ (v ? L::v_block(key) * 4 : L::k_chunk(key))) * 16;
                 *reinterpret_cast<u32x4*>(to) = x.hi;
@@ -149,10 +168,6 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
         l_run += sum;
     };
 
-    // The smallest score so far, in parts: below -2^80 it is -infinity, also where fp32 holds it, and leaves no trace in the sums.
-    // (Eight instructions per 32 keys: 16 heads of N = 4096, d = 128 626 -> 636 us, 64 326 -> 327, 32 191 -> 198; a bound from the largest
-    // |Q| and |K|, which costs half of them, kept more registers and took longer, 646 / 336 / 189.)
-    float low = 0.0f;
     auto compute = [&](int t, int buf) __attribute__((always_inline)) {
         f32x16 s;
 #pragma unroll
@@ -166,14 +181,6 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
         }
         float p[16];
         weights(s, c * kSplitDown, t * BN, p);
-        {
-            float a = min3(s[0], s[1], s[2]), b = min3(s[3], s[4], s[5]);
-            a = min3(a, s[6], s[7]);
-            b = min3(b, s[8], s[9]);
-            a = min3(a, s[10], s[11]);
-            b = min3(b, s[12], s[13]);
-            low = min3(low, a, min3(b, s[14], s[15]));
-        }
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             float x[8];
@@ -203,6 +210,8 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
         if (t + 1 < n_tiles) {
             store(BUF ^ 1);
             if (t + 2 < n_tiles) load(t + 2);
+        } else if (lane == 0) {
+            k_large[wave] = wave * 64 < CHUNKS ? (large != 0) + (huge != 0) : 0;   // (else its first slots are of V)
         }
         if (q0 < N) compute(t, BUF);              // (a wave without queries only moves tiles)
         __syncthreads();
@@ -211,7 +220,10 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
 
     // ---- infinities, NaN and overflows (rare): what the parts make of them is not what fp32 does.  The wave starts again on
     // the fp32 instruction, operands straight from memory ---------------------------------------------------------------------
-    float worst = __builtin_fmaf(low, 0.0f, l_run), down = kSplitDown;
+    int k_most = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) k_most = max(k_most, k_large[w]);
+    float worst = (k_most == 0 ? q_huge : q_large) != 0 || k_most == 2 ? __builtin_inff() : l_run, down = kSplitDown;
 #pragma unroll
     for (int b = 0; b < DVB; ++b)
 #pragma unroll

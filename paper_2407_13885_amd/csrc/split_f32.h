@@ -46,6 +46,12 @@ __device__ __forceinline__ Row8 load_row8(const float* row, int col, int d)
     return {*reinterpret_cast<const f32x4*>(row + (col < d ? col : 0)), *reinterpret_cast<const f32x4*>(row + (col + 4 < d ? col + 4 : 0))};
 }
 
+__device__ __forceinline__ float largest(const Row8& r)   // |element|, NaN aside
+{
+    const float x = fmaxf(max3(fabsf(r.a[0]), fabsf(r.a[1]), fabsf(r.a[2])), fabsf(r.a[3]));
+    return max3(max3(x, fabsf(r.b[0]), fabsf(r.b[1])), fabsf(r.b[2]), fabsf(r.b[3]));
+}
+
 // Their parts, zeros past the row's end (NaN where the copies are not finite: as the elements that they are copies of)
 __device__ __forceinline__ Split8 split_row8(const Row8& r, int col, int d, float up = kSplitUp)
 {

@@ -344,3 +344,23 @@ def test_attention_f32_large_scores(what, heads, N, d):
         ref = oracle.attention_output(Q[0, h], K[0, h], V[0, h], "f32", scale, rows=(0, N))
         # weights off by `rel` relative to each other, sums of N products
         assert np.abs(O[0, h] - ref).max() <= (2 * rel + (N + 8) * 2.0 ** -24) * np.abs(V[0, h]).max(), f"{what}, {heads} heads, head {h}"
+
+
+@pytest.mark.parametrize("q,k", [(20, 52), (52, 20), (21, 52), (20, 53), (53, 20)])
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+def test_attention_f32_operands_at_the_limits_of_parts(d, q, k):
+    """|Q| and |K| at 2^20 and 2^52, up to which no score in three bf16 parts overflows, and beyond, where the fp32 instruction takes over:
+    only one key is so large, in the last tile, and its score of up to -2^80 must leave its weight."""
+    N, heads = 200, 256
+    Q = np.full((1, heads, N, d), 2.0 ** q, np.float32)
+    K = np.full((1, heads, N, d), -2.0 ** (k - 1), np.float32)
+    K[0, :, 197] *= 2.0 * (1.0 - 2.0 ** -8)
+    scale = np.float32(4.0 / d * 2.0 ** -(q + k))  # logits of -2 and about -4, every product and sum exact
+    x = wl.FusedInputs("t", "f32", 1, heads, N, d, scale, Q, K)
+    V = wl.value_inputs(x, seed=4907)
+    V[0, :, 197] = 1000.0                         # (a weight of e^-2 / 200 in a sum of some 1)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads - 1):
+        ref = oracle.attention_output(Q[0, h], K[0, h], V[0, h], "f32", scale, rows=(0, N))
+        # weights as in the test above (exponents below 15), sums of N products
+        assert np.abs(O[0, h] - ref).max() <= (2 * 3 * 15 * 2.0 ** -24 + (N + 8) * 2.0 ** -24) * np.abs(V[0, h]).max(), f"d={d} head {h}"
