@@ -16,14 +16,21 @@
  *     are [B][H][N][N] (key index fastest) or [rows][cols] (cols fastest).
  *   - `dtype` selects ONE element type for inputs and output: ATTNW_F32
  *     (IEEE binary32) or ATTNW_BF16 (upper 16 bits of a binary32).  All
- *     arithmetic between load and store is fp32 or no less exact: bf16 inputs
- *     are multiplied on the matrix cores with fp32 accumulation; fp32 inputs
- *     with d <= 128 and enough heads (attnw_fused, attnw_attention) go to the
- *     bf16 matrix instruction as three bf16 parts each, which hold all 24 bits
- *     of every fp32 number, six of the nine products kept (those above 2^-24
- *     of the whole), fp32 accumulation: errors measured at or below those of
- *     the fp32 instruction over the whole range of fp32 magnitudes.  bf16
- *     results are rounded once, to nearest even, at the store.
+ *     arithmetic between load and store is fp32, but for contractions in parts:
+ *     bf16 inputs are multiplied on the matrix cores with fp32 accumulation; most fp32
+ *     calls (attnw_fused at any number of heads and head size unless rows are
+ *     short and heads small; attnw_gemm_scores with d of 8 or more on rows off
+ *     the tiles or with d above 64; attnw_attention with d <= 128 and enough
+ *     heads) go to the bf16 matrix instruction too, operands as three bf16 parts
+ *     each, which hold all 24 bits of every fp32 number, six of the nine
+ *     products kept (those above 2^-24 of the whole), fp32 accumulation.
+ *     Against 64 bits, scores of normal vectors are 0.55 to 0.75 times as far
+ *     off as on the fp32 instruction (d = 8 to 256), over the whole range of
+ *     fp32 magnitudes; where few products make a sum it is the other way
+ *     round: one operand in eight other than zero 1.2 to 1.3 times, a single
+ *     product off by up to 1.6e-7, root mean square 3.7e-8, where one rounding
+ *     has 6.0e-8 and 2.5e-8.  bf16 results are rounded once, to nearest even,
+ *     at the store.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued on it and the call returns without waiting.  A call is
  *     one kernel launch (two for a softmax of few rows too long for the
@@ -51,10 +58,11 @@
  *     attnw_fused / attnw_gemm_scores for bf16 shapes that several of them
  *     serve (read at every call; tests and measurements compare them):
  *       unset    N up to 384 (K of a head up to 80 KiB): a wave per head and 32
- *                queries, scores in its registers, K in LDS (windows of up to 64
- *                tokens with d = 16 or 32 in great number: the same, a wave
- *                alone); N up to 1280, d up to 128, lengths off the tiles or few
- *                heads: a workgroup per 32 queries, scores in its registers;
+ *                queries, scores in its registers, K in LDS (windows of 8 to
+ *                64 tokens, no multiple of 8, with d = 16 in great number, weights:
+ *                the same, a wave alone); N up to 1280, d up to 128, lengths off the tiles or few
+ *                heads: a workgroup per 32 queries, scores in its registers (not
+ *                where strips of 256 queries nearly fill their last round);
  *                d = 64 and N = 512 or 1024: scores of a strip held in registers,
  *                one sweep; one
  *                to a few heads of 1024 to 8192 keys: scores held across a
