@@ -9,11 +9,11 @@
 // waves take the 32-key sub-tiles in turn (wave w has sub-tiles w, w + WK, ..), each with a reference exponent, a sum and
 // output accumulators of its own, and the partial results are merged through LDS at the end.
 //
-// What bounds it: every compute unit reads the whole K and V of its head from the caches, 64 bytes per cycle at best (15 us for
-// 2 MiB; 35 bytes per cycle counted, matrix pipe 26 %, waves waiting 33 % of their life), with little arithmetic per byte
-// (and where the blocks leave compute units idle, several of them share a block's columns: CS below).  No byte is used by two waves, so a wave stages its own sub-tiles in an LDS area
-// of its own and no barrier ties the waves together: while one requests and stores, the others compute.  K and V lie in
-// LDS as they lie in memory; V is turned by the transposing LDS read.
+// What bounds it: every compute unit reads the whole K of its head and its columns of V from the caches, 64 bytes per cycle at best
+// (one head of N = 4096, d = 128: 11 us for K and half of V), with little arithmetic per byte; the waves wait 33 % of their life.
+// Where the blocks leave compute units idle, several of them share a block's columns (CS below).  No byte is used by two waves, so a
+// wave stages its own sub-tiles in an LDS area of its own and no barrier ties the waves together: while one requests and stores, the
+// others compute.  K and V lie in LDS as they lie in memory; V is turned by the transposing LDS read.
 #include "attention_common.h"
 #include "launchers.h"
 
@@ -43,8 +43,9 @@ struct RangesCfg {
 // N = 4096, d = 128 27.4 us, K through registers too 29.5; four waves instead of eight 38).
 // q_base: the launch covers the queries from that one on.
 // Where 32-query workgroups leave half of the compute units idle, CS of them share a block: each makes all scores, but reads and
-// multiplies its share of the columns of V only -- the larger part of what a compute unit's port has to carry.  No exchange, the
-// sums are those of one workgroup.
+// multiplies its share of the columns of V only, so that half or a quarter of V passes a compute unit's port.  No exchange between
+// them.  (Sums: those of one workgroup of as many waves; d = 192 and 256 take eight and six waves here instead of four, which
+// divides the keys differently.)
 template <int DVB, bool HALF, int WK, int CS>
 __global__ __launch_bounds__(64 * WK)
 void attention_ranges_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,

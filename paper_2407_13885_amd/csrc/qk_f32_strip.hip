@@ -14,12 +14,14 @@
 //
 // Why 32 queries: a compute unit's registers hold 32 x 2048 scores beside the operands, and one sweep needs half the matrix
 // instructions and exponentials of two; a few short heads then also spread over four times the compute units.  Measured, two
-// heads of N = 2976, d = 84: 416 us on the fp32 instruction with the keys split over workgroups, 60 here; 16 heads of N = 2048, d = 64 115 us in
-// two sweeps over 128-query strips, 100 here (d = 128 199 -> 150); one head of N = 128, d = 64 8.9 -> 5.3.
-// What bounds it (16 heads of N = 2048, d = 64): the vector ALU (per wave and block of 32 keys 200 instructions of splitting,
-// 75 of softmax) with the matrix pipe beside it, and the time that a wave needs to issue its K transfers (75 cycles each, a tenth of its
-// life).  Taken out one at a time: splitting 20 us, stores 11, transfers 6, matrix instructions 4.  Interleaving the split of one group with
-// the matrix instructions of the other by hand changed nothing (the two waves of a SIMD do that for each other) and spilled.
+// heads of N = 2976, d = 84: 416 us on the fp32 instruction with the keys split over workgroups, 60 here; 16 heads of N = 2048, d = 64 116 us in
+// two sweeps over 128-query strips, 105 here (on the same inputs again 101; d = 128 199 -> 162); one head of N = 128, d = 64 8.9 -> 7.7 (5.4).
+// What bounds it (16 heads of N = 2048, d = 64): the vector ALU, 53 % of SIMD cycles (per wave and block of 32 keys 382 instructions, some
+// 200 of them splitting), with the matrix pipe beside it (25 %, both at once 9 %), and the time that a wave needs to issue its K
+// transfers (75 cycles each, a tenth of its life); the waves wait 34 % of theirs.  With NT = 8 the 256 registers are full: two vector and 25
+// scalar ones are spilled.  Taken out one at a time: splitting 20 us, stores 11, transfers 6, matrix instructions 4.  Interleaving the
+// split of one group with the matrix instructions of the other by hand changed nothing (the two waves of a SIMD do that for each other)
+// and spilled.
 #include "attention_common.h"
 #include "launchers.h"
 #include "split_f32.h"

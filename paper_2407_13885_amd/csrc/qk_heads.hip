@@ -11,10 +11,10 @@
 // 16-byte chunks, consecutive lanes consecutive chunks; the first and last chunk, shared with the neighbouring blocks, element
 // by element.  A workgroup is a few blocks of one head and ends with its stores, so nothing ever waits for a store.
 //
-// Measured, 1024 heads of N = 197, d = 64: 28.7 us (131 MB of Q, K and P: 4.6 TB/s).  The wave-per-head kernel whose waves each took K
+// Measured, 1024 heads of N = 197, d = 64: 26.7 us (131 MB of Q, K and P: 4.9 TB/s).  The wave-per-head kernel whose waves each took K
 // from memory as operands, every lane in a memory line of its own, 44.6 (half of that the vector-memory pipe); the kernel that spread the
 // keys of a strip over eight waves, an exchange and a barrier per strip, 49.  Because the K area serves as staging too, three
-// workgroups of four waves share a compute unit at that length, each at another phase.  What bounds it: the vector ALU, about 1200
+// workgroups of four waves share a compute unit at that length, each at another phase.  What bounds it: the vector ALU, about 1000
 // instructions per wave and 32 x 197 weights (exponentials, scaling and rounding, the pairs of an odd length), 16 of the 28 us,
 // in the shadow of the stores.
 #include "launchers.h"
