@@ -19,8 +19,8 @@
  *     arithmetic between load and store is fp32, but for contractions in parts:
  *     bf16 inputs are multiplied on the matrix cores with fp32 accumulation; most fp32
  *     calls (attnw_fused at any number of heads and head size unless rows are
- *     short and heads small; attnw_gemm_scores with d of 8 or more on rows off
- *     the tiles or with d above 64; attnw_attention with d <= 128 and enough
+ *     short and heads small; attnw_gemm_scores with d above 32, but for few
+ *     long or short odd rows, and many with d of 8 to 32; attnw_attention with d <= 128 and enough
  *     heads) go to the bf16 matrix instruction too, operands as three bf16 parts
  *     each, which hold all 24 bits of every fp32 number, six of the nine
  *     products kept (those above 2^-24 of the whole), fp32 accumulation.

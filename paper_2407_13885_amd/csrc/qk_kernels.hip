@@ -831,7 +831,9 @@ bool prefers_f32_split(int64_t BH, int64_t N, int64_t d)
 // each range, us.  d <= 16: 3797 of 108 60 -> 139, 434 of 120 11 -> 21, 637 of 60 10.8 -> 15.4, 85 of 381 14.7 -> 21 (tiles nearly full: not taken), but 204 of
 // 131 17.8 -> 16.4, 93 of 1025 59 -> 39 (taken).  d <= 32: 1024 strips of N = 101 to 127 9 -> 13 (not taken), of 131 24 -> 16, of 577 46 -> 26.  d <= 64:
 // 1470 of 104, d = 36 56 -> 74 (not taken), 194 of 100, d = 64 30 -> 15.5; one of 2810, d = 48 18.5 -> 32: the general kernel splits
-// the keys of a few long rows over workgroups (not taken).  Beyond d = 64: four of 996, d = 256 152 -> 33, 93 of 1025, d = 64 241 -> 184; not 93 of 1024, d = 256
+// the keys of a few long rows over workgroups (not taken).  Multiples of 4 whose 128-query strips fill their rounds lose a tenth, 16 of 2048, d = 64
+// 88.9 -> 98.0, 64 of 1024 92 -> 105, 128 of 512 52 -> 56 (others gain: 20 of 1024 67 -> 34, 300 of 256 45 -> 41), and are taken all the same for
+// errors of 8.3e-8 against 1.45e-7.  Beyond d = 64: four of 996, d = 256 152 -> 33, 93 of 1025, d = 64 241 -> 184; not 93 of 1024, d = 256
 // 451 -> 487.  Four columns: the six products are less exact than four of the fp32 instruction (scores of normal vectors 4.10e-8 off
 // against 3.97e-8; eight columns 4.02e-8 against 5.4e-8).
 bool prefers_f32_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
