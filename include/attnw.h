@@ -63,6 +63,9 @@
  *                the same, a wave alone); N up to 1280, d up to 128, lengths off the tiles or few
  *                heads: a workgroup per 32 queries, scores in its registers (not
  *                where strips of 256 queries nearly fill their last round);
+ *                above that, or d above 128: persistent workgroups with strips of
+ *                32 queries, but for whole tiles of the kernels that follow
+ *                and calls whose larger strips fill the chip;
  *                d = 64 and N = 512 or 1024: scores of a strip held in registers,
  *                one sweep; one
  *                to a few heads of 1024 to 8192 keys: scores held across a
@@ -74,6 +77,8 @@
  *       tiny     the kernel of a wave alone wherever it takes the shape
  *       heads    the kernel of a wave per head and 32 queries wherever it takes it
  *       strip    the kernel of a workgroup per 32 queries wherever it takes it
+ *       stream   the persistent kernel of 32-query strips wherever it takes the
+ *                shape (more than 512 tokens)
  *     Weights of all of them agree to rounding of the row sum, scores bit for bit.
  *     The workgroups of the gang kernel wait for each other's row statistics
  *     inside one launch, so all of a gang must be running at once: the grid is

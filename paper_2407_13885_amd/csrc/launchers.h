@@ -67,6 +67,12 @@ bool qk_strip_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_qk_strip(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d, float scale,
                            hipStream_t stream);
 
+// Fused attention weights or scaled scores, bf16, any N up to 2^22, d a multiple of 16 up to 256: persistent workgroups, strips of 32
+// queries whose keys are shared between the waves, scores of up to some 2500 keys in their registers, the rest computed twice.
+bool qk_stream_supported(int64_t BH, int64_t N, int64_t d);
+hipError_t launch_qk_stream(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d, float scale,
+                            hipStream_t stream);
+
 // Fused attention weights, bf16, d = 64 or 128, N a multiple of 512 from 1024 to 16384: the scores of a strip stay
 // in the registers of the N / 512 workgroups that share its rows (one sweep over the keys; the workgroups exchange
 // their row statistics through tables parked in P).  Two launches: table slots zeroed, then the kernel.

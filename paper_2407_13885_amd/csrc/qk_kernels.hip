@@ -909,6 +909,44 @@ bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
     return strips <= (N == 1024 ? 3 : 2) * cus;
 }
 
+// bf16 on persistent workgroups with 32-query strips, more than 512 tokens.  From 60000 random shapes of 513 to 8192 tokens, time there /
+// time on the kernel that would take the call otherwise, by strips per compute unit (x below):
+//   weights, d <= 128, 1281 tokens and more: x up to 1 0.15 to 0.75, to 2 0.26 to 0.8, to 4 0.4 to 0.8, to 5 0.6 to 0.95.  Beyond that rows on
+//     16-byte boundaries 0.7 to 1.0 but for last rounds of the others' 256-query workgroups that are nearly full (x of 6 to 8.2 and of 14 to 17: 1.0 to
+//     1.26), other rows only from 8.3 to 10.2 (0.73 to 0.99; 6 to 8 and above 12 1.0 to 1.25).  Whole tiles of 256: d = 64 0.84 to 1.4, d = 128 0.74 to
+//     0.87 up to 2048 tokens, then 0.8 to 1.3; other d as the rest.  Up to 1280 tokens the one-workgroup-per-strip kernel is faster (1.0 to 3).
+//   weights, d > 128: x up to 1 0.3 to 0.6, to 2 0.5 to 0.8, beyond 0.55 to 0.95 but where the 128-query workgroups of the general kernel nearly
+//     fill a round (3 to 4 1.0 to 1.35, 6 to 8 to 1.3), and d above 192 that are not whole pieces of 64 columns, more than 2048 tokens (1.1 to 1.36)
+//   scores, against a general kernel that splits the keys of few strips over workgroups.  Odd lengths of 1281 and more 0.13 to 0.9 (beyond 2048
+//     tokens with d > 32 and few strips 1.1 to 1.3); d <= 32 0.23 to 0.8, whole blocks of 32 keys up to x of 12 0.59 to 0.98; larger d whole blocks 0.64 to 0.9
+//     from 3.1 to 5.5 and 9 to 12, other even lengths 0.65 to 0.98 from 3.2 to 4; else 0.95 to 1.5.  Whole blocks of 513 to 1280 tokens, d > 64, 1.6 to
+//     4.5: 0.43 to 0.95.  d > 128: 0.26 to 0.95 up to 2 (d > 192: 1.4, up to 896 tokens 1), odd lengths up to 2.2 and 4 to 6.
+bool prefers_stream(bool scores_only, int64_t BH, int64_t N, int64_t d)
+{
+    if (N <= 512) return false;
+    const double x = (double)(BH * ((N + 31) / 32)) / (double)compute_units();
+    auto within = [&](double lo, double hi) { return x > lo && x <= hi; };
+    const bool odd = N % 2 != 0, blocks = N % 32 == 0, tiles = N % 256 == 0;
+    if (d > 128) {
+        if (scores_only) return within(0, d <= 192 ? 2 : N <= 896 ? 1 : 1.4) || (odd && (within(0, 2.2) || within(4, 6)));
+        if (d > 192 && N > 2048) return within(0, 2.1) || (d == 256 && within(4, 6));
+        if (d > 192) return !within(2.8, 4) && !within(6, 8);
+        return N <= 2048 || (!within(3, 4) && !within(6, 8));
+    }
+    if (N <= 1280) return scores_only && d > 64 && blocks && !tiles && within(1.6, 4.5);
+    if (!scores_only) {
+        if (tiles && d == 64) return false;
+        if (tiles && d == 128) return N <= 2048 && within(0.25, 6);
+        if (N % 8 == 0) return d <= 32 || (!within(6, 8.2) && !within(14, 17));
+        return within(0, d <= 32 ? 6 : 5) || within(8.3, 10.2);
+    }
+    if (odd && d <= 32) return within(0, 6);
+    if (odd) return N <= 2048 ? within(0, 1) || within(1.35, 5) : within(0.9, 1) || within(1.35, 1.95) || within(2, 4.4);
+    if (d <= 32) return tiles ? within(0, 4) : blocks ? within(0, 12) : N % 8 == 0 ? within(0, 2) || within(3.1, 4) : within(0, 4);
+    if (tiles) return false;
+    return blocks ? within(3.1, 5.5) || within(9, 12) : N <= 4096 && within(3.2, 4);
+}
+
 }  // namespace
 
 hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, void* out,
@@ -929,12 +967,15 @@ hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, v
     const bool tiny = force && strcmp(force, "tiny") == 0;
     const bool heads = force && strcmp(force, "heads") == 0;
     const bool strip = force && strcmp(force, "strip") == 0;
+    const bool streamed = force && strcmp(force, "stream") == 0;
     // Very many windows of up to 64 tokens with heads of 16, off the 16-byte boundaries: waves that work alone on a stream of (head, 32
     // queries) pairs.  Against the kernel after the next, us: 12288 heads of N = 49 21.0 / 22.3, 16384 of 33 24.6 / 26.7, 30000 of 13 16.0 / 17.6;
     // not 8192 pairs (4096 of 49 10.4 / 9.2), multiples of 8 (16384 of 56 27.6 / 25.4), scores (16384 of 49 24.9 / 21.9) or heads of 32 (12288 of 49
     // 25.9 / 26.0, 4096 11.6 / 10.2, 12288 of 62 32.9 / 31.3).
     if (qk_tiny_supported(BH, N, d) && (tiny || (!force && !scores_only && N % 8 != 0 && BH * ((N + 31) / 32) >= 16384)))
         return launch_qk_tiny(scores_only, Q, K, out, BH, N, d, scale, stream);
+    if (qk_stream_supported(BH, N, d) && (streamed || (!force && prefers_stream(scores_only, BH, N, d))))
+        return launch_qk_stream(scores_only, Q, K, out, BH, N, d, scale, stream);
     if (qk_strip_supported(BH, N, d) && (strip || (!force && prefers_strip(scores_only, BH, N, d))))
         return launch_qk_strip(scores_only, Q, K, out, BH, N, d, scale, stream);
     // Up to 384 tokens: whole rows of scores in the registers of a wave, K of the head in LDS.  Measured against the kernels below and
