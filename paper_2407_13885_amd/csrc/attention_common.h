@@ -26,6 +26,31 @@ __device__ __forceinline__ float half_wave_sum(float x)
 #endif
 }
 
+// The exponent that a query's weights are taken against follows its running maximum only when the 16 weights that a lane makes of
+// a sub-tile sum to more than this: a look at the sum that is needed anyway instead of at the maximum of the scores in front of the
+// exponentials (7 v_max3, an exchange between the half-waves and a branch per 32 keys, all of it in the way).  No weight is larger: fp32
+// sums and bf16 operands have the same relative precision at every magnitude.  The exponent then moves to the largest weight, which comes to
+// be 1 (and has no rounding as a bf16 operand: in sharp rows most of the error); weights that overflow are made again from the scores.
+constexpr float kFarSum = 256.0f, kOverflow = 3.0e38f;
+
+// the largest of a lane's 16 scores of a sub-tile
+__device__ __forceinline__ float max16(const f32x16& s)
+{
+    float m = max3(s[0], s[1], s[2]);
+#pragma unroll
+    for (int r = 3; r < 15; r += 2) m = max3(m, s[r], s[r + 1]);
+    return fmaxf(m, s[15]);
+}
+
+// By so much the exponent moves: log2 of the largest of a query's weights, 16 in each of two lanes, where that is above 0.
+__device__ __forceinline__ float far_exponent(const float (&p)[16])
+{
+    float m = max3(p[0], p[1], p[2]);
+#pragma unroll
+    for (int r = 3; r < 15; r += 2) m = max3(m, p[r], p[r + 1]);
+    return fmaxf(fast_log2(half_wave_max(fmaxf(m, p[15]))), 0.0f);
+}
+
 // Rows of DVB x 64 bytes on chip (DVB x 32 bf16 columns), 16-byte chunks swizzled within the row (involutions that stay
 // inside it).  A K fragment read takes one chunk of 32 consecutive rows: 16 rows hit 16 different chunk positions modulo
 // 256 bytes.  The transposing read of V takes 64 bytes of four consecutive rows: those lie in different quarters of 256.

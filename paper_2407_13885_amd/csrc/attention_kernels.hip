@@ -17,7 +17,8 @@
 //           keys, and a matrix-core operand wants its 8 contraction elements contiguous per lane.
 // Per 32-key sub-tile and query block (all on v_mfma_f32_32x32x16_bf16, fp32 accumulate):
 //   S^T = K_sub * Q^T          lane (query l32, half h) holds keys 8i + 4h + j of its query;
-//   sub-tile max (shared by lanes l, l+32: both feed the same second contraction), p = 2^(c s - ref),
+//   sub-tile max (shared by lanes l, l+32: both feed the same second contraction; long rows: only where the weights'
+//   sums call for it), p = 2^(c s - ref),
 //   l += sum p (fp32), p rounded to bf16;
 //   O^T += Vt_sub * P^T        lane (query l32, half h) holds O[query][8i + 4h + j] per 32-wide block.
 // The k-index of the second contraction is a permutation of the keys chosen so that a lane's own
@@ -51,7 +52,8 @@ struct AttnCfg {
 
 // TAIL: N is not a whole number of tiles / strips.  Rows past the end are read as row N-1 (every load
 // stays inside the arrays), their weights are forced to 0 and their queries are not stored.
-template <int DB, int QB, bool TAIL>
+// SUMS: the exponent of the weights follows their sums (kFarSum) and not the maximum of the scores.
+template <int DB, int QB, bool TAIL, bool SUMS>
 __global__ __launch_bounds__(512)
 void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                       uint16_t* __restrict__ O, int N, float c, uint32_t sign_flip, uint32_t strips, uint32_t total)
@@ -211,41 +213,56 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                     vf[b][m] = *reinterpret_cast<const u32x4*>(vb + b * 32 * VT_PITCH + (u * 32 + 16 * m) * 2);
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
-                // maximum of this sub-tile, shared by the two lanes of a query
-                float tm = max3(s[qb][0], s[qb][1], s[qb][2]);
+                float p[16], sum;
+                auto weigh = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int r = 3; r < 15; r += 2) tm = max3(tm, s[qb][r], s[qb][r + 1]);
-                const float mbn = half_wave_max(fmaxf(tm, s[qb][15])) * c;
-                // The exponent the weights are taken against (mb_run) follows the running maximum lazily:
-                // it moves only when some query of the wave exceeds it by more than kLazy binades.  Until
-                // then weights up to 2^kLazy appear, which costs nothing (fp32 sums, and bf16 has the same
-                // relative precision at every magnitude), and the 16 * DVB multiplies of the output
-                // accumulator - needed at every new maximum otherwise, i.e. in most of the early sub-tiles
-                // of a row - become rare.  Lanes whose exponent stands get the factor 2^0 = 1 exactly.
-                if (__builtin_amdgcn_ballot_w64(mbn > mb_run[qb] + kLazy) != 0) {
-                    const float mb_new = fmaxf(mb_run[qb], mbn);
-                    const float alpha = fast_exp2(mb_run[qb] - mb_new);
+                    for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[qb][r], c, -mb_run[qb]));
+                    if constexpr (MASK) {
+                        // keys past the end were read as key N-1 (their scores change no maximum): no weight
+                        const int kbase = t * BN + u * 32 + 4 * half;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (kbase + 8 * (r / 4) + (r % 4) >= N) p[r] = 0.0f;
+                    }
+                    float part[4] = {p[0], p[1], p[2], p[3]};
+#pragma unroll
+                    for (int r = 4; r < 16; ++r) part[r & 3] += p[r];
+                    sum = (part[0] + part[1]) + (part[2] + part[3]);
+                };
+                // The exponent the weights are taken against (mb_run) follows the running maximum lazily.  The 16 * DVB multiplies
+                // of the output accumulator - needed at every new maximum otherwise, i.e. in most of the early sub-tiles of a
+                // row - become rare.  Lanes whose exponent stands get the factor 2^0 = 1 exactly.
+                auto move = [&](float to) __attribute__((always_inline)) {
+                    const float alpha = fast_exp2(mb_run[qb] - to);
                     l_run[qb] *= alpha;
 #pragma unroll
                     for (int b = 0; b < DVB; ++b)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) oacc[qb][b][r] *= alpha;
-                    mb_run[qb] = mb_new;
+                    mb_run[qb] = to;
+                };
+                // (shared by the two lanes of a query)
+                auto maximum = [&]() __attribute__((always_inline)) { return fmaxf(mb_run[qb], half_wave_max(max16(s[qb])) * c); };
+                if constexpr (!SUMS) {
+                    const float to = maximum();
+                    if (__builtin_amdgcn_ballot_w64(to > mb_run[qb] + kLazy) != 0) move(to);
+                    weigh();
+                } else {
+                    if (u == 0 && t == 0) mb_run[qb] = maximum();
+                    weigh();
+                    if (__builtin_amdgcn_ballot_w64(sum > kFarSum) != 0) {
+                        if (__builtin_amdgcn_ballot_w64(sum > kOverflow) != 0) {
+                            move(maximum());
+                            weigh();
+                        } else {
+                            const float by = far_exponent(p), a = fast_exp2(-by);
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) p[r] *= a;
+                            sum *= a;
+                            move(mb_run[qb] + by);
+                        }
+                    }
                 }
-                const float mb = mb_run[qb];
-                float p[16];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[qb][r], c, -mb));
-                if constexpr (MASK) {
-                    // keys past the end were read as key N-1 (their scores change no maximum): no weight
-                    const int kbase = t * BN + u * 32 + 4 * half;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (kbase + 8 * (r / 4) + (r % 4) >= N) p[r] = 0.0f;
-                }
-                float sum = p[0];
-#pragma unroll
-                for (int r = 1; r < 16; ++r) sum += p[r];
                 l_run[qb] += sum;
                 // a lane's weights of group m are accumulators 8m .. 8m+7: exactly its operand of the second contraction
 #pragma unroll
@@ -319,14 +336,23 @@ hipError_t launch_attention_t(const void* Q, const void* K, const void* V, void*
     const uint32_t strips = (uint32_t)(((q_end < 0 ? N : q_end) + C::BM - 1) / C::BM);
     const float c = fabsf(scale) * kLog2e;
     const uint32_t flip = scale < 0.0f ? Mma<uint16_t>::kSignMask : 0u;
-    return launch_by_heads(BH, strips, 512, [&](int64_t first, int64_t heads) {
-        const int64_t at = first * N * C::D;
-        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
-        hipLaunchKernelGGL((attention_kernel<DB, QB, TAIL>), dim3(grid), dim3(512), 0, stream, static_cast<const uint16_t*>(Q) + at,
-                           static_cast<const uint16_t*>(K) + at, static_cast<const uint16_t*>(V) + at, static_cast<uint16_t*>(O) + at, N,
-                           c, flip, strips, total);
-        return hipGetLastError();
-    });
+    auto go = [&](auto kernel) {
+        return launch_by_heads(BH, strips, 512, [&](int64_t first, int64_t heads) {
+            const int64_t at = first * N * C::D;
+            const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), 0, stream, static_cast<const uint16_t*>(Q) + at,
+                               static_cast<const uint16_t*>(K) + at, static_cast<const uint16_t*>(V) + at, static_cast<uint16_t*>(O) + at, N,
+                               c, flip, strips, total);
+            return hipGetLastError();
+        });
+    };
+    // A look at the sums costs more where the exponent moves, in the first tiles of a row, and saves in all others.  us, maxima -> sums: 16 heads
+    // of N = 4096, d = 32 64.0 -> 59.1, 48 of 4096, d = 64 270 -> 250, 72 of 1120, d = 32 32.3 -> 29.6; rows of every sharpness 276 -> 271 (48 of 4096),
+    // 607 -> 585 (8 of 16384); but 200 of 512, d = 64 27.4 -> 28.4, 128 of 2048 in two query blocks a wave 162 -> 171.  (Two blocks and ragged
+    // ends: registers for the scores and their weights spill.)
+    if constexpr (QB == 1 || !TAIL)
+        if (N >= (QB == 1 ? 1024 : 2560)) return go(attention_kernel<DB, QB, TAIL, true>);
+    return go(attention_kernel<DB, QB, TAIL, false>);
 }
 
 // A ragged length whose last strip (256 queries, 512 with two query blocks per wave) holds at most 64 queries, and whose partial strips start another round
