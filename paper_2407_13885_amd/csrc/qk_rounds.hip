@@ -25,6 +25,10 @@
 //   - the MFMAs of the next sub-tile into the other accumulator set (`nxt`), one per chunk of VALU
 //     work, so that the matrix pipe and the vector ALU are fed from the same instruction stream,
 //   - the LDS reads of the K fragments of the sub-tile after next (a full step of latency slack).
+// The statistics are taken per lane against the maximum of the round's first sub-tile, not the running one: 9 vector instructions
+// and an exponential less of 140 a step (16 heads of N = 4096, d = 128 179.5 -> 175.3 us, 8 of 16384, d = 64 1024 -> 990).  fp32 sums hold 100 binades above it; a strip that has
+// more has its statistics gathered again with the running maximum.
+//
 // As in the two-pass kernel, the MFMA computes the transposed tile (K sub-tile) * (Q block)^T: a
 // lane's 16 accumulators are 16 keys of one query.
 //
@@ -74,7 +78,7 @@ struct RoundsCfg {
     static constexpr int LDS_K = NBUF * K_TILE_BYTES;
     static constexpr int LDS_ST = NW * ST_BYTES;
     static constexpr int LDS_STAT = NW * 32 * 2 * 4;
-    static constexpr int LDS_TOTAL = LDS_K + LDS_ST + LDS_STAT;
+    static constexpr int LDS_TOTAL = LDS_K + LDS_ST + LDS_STAT + 16;
 };
 
 template <int DB, int WQ, int WK, bool SCORES, bool PAIR = false>
@@ -96,6 +100,7 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
     char* const k_lds = lds;
     char* const st_lds = lds + C::LDS_K;
     float* const stat_lds = reinterpret_cast<float*>(lds + C::LDS_K + C::LDS_ST);
+    volatile int* const outgrown = reinterpret_cast<volatile int*>(lds + C::LDS_K + C::LDS_ST + C::LDS_STAT);
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -141,6 +146,7 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
     for (int f = 0; f < NFL; ++f) out_lane_off[f] = (uint32_t)(((rd_row0 + f * RPI + lane / CPS) * N + (lane % CPS) * 8) * 2);
 
     const int n_tiles = N / BN;
+    if (tid == 0) *outgrown = 0;                  // (a segment begins with a barrier)
 
     while (s_cur < s_end) {
         // ======== one segment: strips [s0, s1) of head bh ================================================
@@ -196,13 +202,14 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
         __syncthreads();
 
         // One step: see the head of the file.  t = position of the tile in the round's sweep.
-        auto step = [&](auto bufc, auto uc, auto hasac, auto hasbc, auto flushc, f32x16 (&cur)[2], f32x16 (&nxt)[2],
+        auto step = [&](auto bufc, auto uc, auto hasac, auto hasbc, auto flushc, auto maxc, f32x16 (&cur)[2], f32x16 (&nxt)[2],
                         int t, char* out_prev) __attribute__((always_inline)) {
             constexpr int BUF = decltype(bufc)::value;
             constexpr int U = decltype(uc)::value;
             constexpr bool HAS_A = decltype(hasac)::value != 0;
             constexpr bool HAS_B = decltype(hasbc)::value != 0;
             constexpr bool FLUSH_PREV = decltype(flushc)::value != 0;   // the previous tile's rows are still staged
+            constexpr bool MAX = decltype(maxc)::value != 0;            // the running maximum follows the scores
             constexpr int BUF_NEXT_TILE = (BUF + 1) % NBUF;
 
             if constexpr (U == 0) {
@@ -220,7 +227,7 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
 
             float pv[16];
             uint32_t pk[8];
-            float mbl = 0.0f;
+            float mbl = 0.0f, l_part[2] = {0.0f, 0.0f};
             static_for<NCH>([&](auto cic) __attribute__((always_inline)) {
                 constexpr int ci = decltype(cic)::value;
                 // ---- staged rows of the previous tile: read them all before this step's first staging write
@@ -254,9 +261,14 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                         *reinterpret_cast<u32x2*>(st_wr + (PAIR ? BUF * (BN * 2) : 0) + (U * 32 + 8 * r4) * 2) = w;
                     }
                 }
-                // ---- slot B: running maximum and sum of exponentials (Eq. 1); chunk 0 folds the maximum
+                // ---- slot B: sum of exponentials (Eq. 1) against the maximum of the round's first sub-tile, or (MAX) against the
+                //      running maximum, which chunk 0 folds
                 if constexpr (HAS_B) {
-                    if constexpr (ci == 0) {
+                    if constexpr (!MAX) {
+                        constexpr int e0 = ci * 16 / NCH, e1 = (ci + 1) * 16 / NCH;
+#pragma unroll
+                        for (int r = e0; r < e1; ++r) l_part[r & 1] += fast_exp2(__builtin_fmaf(cur[1][r], c, -mb_run));
+                    } else if constexpr (ci == 0) {
                         float tm = max3(cur[1][0], cur[1][1], cur[1][2]);
 #pragma unroll
                         for (int r = 3; r < 15; r += 2) tm = max3(tm, cur[1][r], cur[1][r + 1]);
@@ -300,21 +312,24 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                 // the chunk order is the schedule: keep the compiler from merging chunks
                 __builtin_amdgcn_sched_barrier(0);
             });
+            if constexpr (HAS_B && !MAX) l_run += l_part[0] + l_part[1];
         };
 
-        auto tile_body = [&](int t, auto bufc, auto hasac, auto hasbc, auto flushc, char* out_rows) __attribute__((always_inline)) {
+        auto tile_body = [&](int t, auto bufc, auto hasac, auto hasbc, auto flushc, auto max0c, auto max1c, char* out_rows) __attribute__((always_inline)) {
             char* out_prev = nullptr;
             if constexpr (decltype(hasac)::value != 0 && decltype(flushc)::value != 0) {
                 if constexpr (PAIR) out_prev = out_rows + (int64_t)(tile_at(t - 2 - decltype(bufc)::value) * BN) * 2;   // first tile of the pair before
                 else out_prev = out_rows + (int64_t)(tile_at(t - 1) * BN + wk * SUBS * 32) * 2;
             }
-            step(bufc, IC<0>{}, hasac, hasbc, flushc, accX, accY, t, out_prev);
-            step(bufc, IC<1>{}, hasac, hasbc, flushc, accY, accX, t, out_prev);
+            step(bufc, IC<0>{}, hasac, hasbc, flushc, max0c, accX, accY, t, out_prev);
+            step(bufc, IC<1>{}, hasac, hasbc, flushc, max1c, accY, accX, t, out_prev);
         };
 
         // One round: a full sweep over the keys; its first tile sits in buffer 0 (n_tiles is a multiple of NBUF).
-        auto round = [&](auto hasac, auto hasbc, char* out_rows) __attribute__((always_inline)) {
+        // allmaxc: the running maximum follows the scores in every step, not the first alone.
+        auto round = [&](auto hasac, auto hasbc, auto allmaxc, char* out_rows) __attribute__((always_inline)) {
             constexpr bool HAS_A = decltype(hasac)::value != 0;
+            constexpr int ALL = decltype(allmaxc)::value;
             constexpr bool HAS_B = decltype(hasbc)::value != 0;
             // scores of the first sub-tile with this round's Q fragments, then the fragments of the second
 #pragma unroll
@@ -333,12 +348,11 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
             // first group of NBUF tiles: nothing is staged before tile 0
             static_for<NBUF>([&](auto bc) __attribute__((always_inline)) {
                 constexpr int b = decltype(bc)::value;
-                if constexpr (b == 0 || PAIR) tile_body(b, bc, hasac, hasbc, IC<0>{}, out_rows);
-                else tile_body(b, bc, hasac, hasbc, IC<1>{}, out_rows);
+                tile_body(b, bc, hasac, hasbc, IC<b == 0 || PAIR ? 0 : 1>{}, IC<b == 0 ? 1 : ALL>{}, IC<ALL>{}, out_rows);
             });
             for (int t = NBUF; t < n_tiles; t += NBUF)
                 static_for<NBUF>([&](auto bc) __attribute__((always_inline)) {
-                    tile_body(t + decltype(bc)::value, bc, hasac, hasbc, IC<1>{}, out_rows);
+                    tile_body(t + decltype(bc)::value, bc, hasac, hasbc, IC<1>{}, allmaxc, allmaxc, out_rows);
                 });
             // rows of the last tile
             if constexpr (HAS_A && PAIR) {
@@ -367,17 +381,22 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
         // query's keys of this wave; the WK waves that share the queries each saw a slice of every
         // tile), fold maximum and normaliser into one constant and hand the strip over to slot A.
         // All exponents are the rounded mb = fl(c * max) the sums were built against.
+        // False (for the whole workgroup) if a sum outgrew its exponent: the maximum of the first sub-tile was exceeded by 100 binades.
         auto handover = [&]() __attribute__((always_inline)) {
             const float mo = __shfl_xor(mb_run, 32, 64);
             const float lo = __shfl_xor(l_run, 32, 64);
             float mb = fmaxf(mb_run, mo);
             float l = l_run * fast_exp2(mb_run - mb) + lo * fast_exp2(mo - mb);
+            bool kept = true;
+            static_assert(WK > 1, "the workgroup's flag travels with the exchange");
             if constexpr (WK > 1) {
                 if (half == 0) {
                     stat_lds[(wave * 32 + l32) * 2] = mb;
                     stat_lds[(wave * 32 + l32) * 2 + 1] = l;
                 }
+                if (__builtin_amdgcn_ballot_w64(!(l < 0x1p100f)) != 0 && lane == 0) *outgrown = 1;
                 __syncthreads();
+                kept = __builtin_amdgcn_readfirstlane(*outgrown) == 0;
 #pragma unroll
                 for (int o = 1; o < WK; ++o) {
                     const int other = wq * WK + (wk + o) % WK;
@@ -388,13 +407,22 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                     mb = mx;
                 }
                 __syncthreads();      // the exchange buffer is written again after the next round
+                if (tid == 0) *outgrown = 0;
             }
             bias = mb + fast_log2(l);
-#pragma unroll
-            for (int g = 0; g < G; ++g) qf[0][g] = qf[1][g];
             m_run = kNegBig;
             mb_run = kNegBig;
             l_run = 0.0f;
+            return kept;
+        };
+        // The strip of slot B moves to slot A, its statistics gathered once more where they were lost (sums of NaN among them: once).
+        auto hand_over = [&]() __attribute__((always_inline)) {
+            if (__builtin_expect(!handover(), 0)) {
+                round(IC<0>{}, IC<1>{}, IC<1>{}, nullptr);
+                handover();
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) qf[0][g] = qf[1][g];
         };
         auto rows_of = [&](uint32_t strip) __attribute__((always_inline)) {
             return out_h + (int64_t)(strip * BS + wq * 32) * (int64_t)N * 2;
@@ -404,17 +432,17 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
             // scaled scores: no statistics, every round writes its own strip
             for (uint32_t s = s0; s < s1; ++s) {
                 if (s > s0) load_q(qf[0], s);
-                round(IC<1>{}, IC<0>{}, rows_of(s));
+                round(IC<1>{}, IC<0>{}, IC<0>{}, rows_of(s));
             }
         } else {
-            round(IC<0>{}, IC<1>{}, nullptr);                  // first strip: statistics only
+            round(IC<0>{}, IC<1>{}, IC<0>{}, nullptr);         // first strip: statistics only
             for (uint32_t s = s0 + 1; s < s1; ++s) {
-                handover();
+                hand_over();
                 load_q(qf[1], s);
-                round(IC<1>{}, IC<1>{}, rows_of(s - 1));
+                round(IC<1>{}, IC<1>{}, IC<0>{}, rows_of(s - 1));
             }
-            handover();
-            round(IC<1>{}, IC<0>{}, rows_of(s1 - 1));          // last strip: weights only
+            hand_over();
+            round(IC<1>{}, IC<0>{}, IC<0>{}, rows_of(s1 - 1)); // last strip: weights only
         }
     }
     wait_vmem();   // no K transfer may be in flight when the workgroup's LDS is released
