@@ -6,13 +6,24 @@ in ``include/attnw.h``.  The functions here have the same names as the C entry
 points, accept either raw device addresses (ints) or objects with a
 ``data_ptr()`` method (PyTorch tensors), and raise :class:`AttnwError` on a
 non-zero status.  There is no CPU fallback: a missing library is an error.
+
+A small call costs the host more than the device, so the public names are
+callables of ``_entry.so`` (``csrc/entry.cpp``) that hand arguments of the usual
+kinds straight to the C function and everything else to the functions here.
 """
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import subprocess
+import sysconfig
 from typing import Optional
+
+try:
+    from . import _entry
+except ImportError:         # not built yet: ctypes alone
+    _entry = None
 
 ATTNW_F32 = 0
 ATTNW_BF16 = 1
@@ -21,6 +32,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_PKG)
 _CSRC = os.path.join(_PKG, "csrc")
 _LIB = os.path.join(_PKG, "libattnw.so")
+_ENTRY = os.path.join(_PKG, "_entry.so")
 
 EXPORTS = ("attnw_fused", "attnw_softmax", "attnw_softmax_cast", "attnw_gemm_scores", "attnw_scale", "attnw_attention",
            "attnw_status_string", "attnw_version")
@@ -32,6 +44,7 @@ HIPCC_FLAGS = [
 ]
 
 _lib = None
+_entries = {}
 
 
 class AttnwError(RuntimeError):
@@ -50,8 +63,9 @@ def sources() -> list:
 
 def build(verbose: bool = False) -> str:
     """Compile every HIP source for gfx950 into ``libattnw.so`` (always recompiles): one hipcc process per
-    source, side by side, objects in a temporary directory, then one link step."""
+    source, side by side, objects in a temporary directory, then one link step; and ``_entry.so``."""
     import concurrent.futures
+    import shutil
     import tempfile
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     compile_flags = [f for f in HIPCC_FLAGS if f != "-shared"]
@@ -65,6 +79,10 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + proc.stdout + proc.stderr)
 
     with tempfile.TemporaryDirectory(prefix="attnw_build_") as tmp:
+        entry = os.path.join(tmp, "_entry.so")
+        run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-Wno-missing-field-initializers", "-shared", "-fPIC", "-I",
+             sysconfig.get_paths()["include"], os.path.join(_CSRC, "entry.cpp"), "-o", entry])
+        shutil.move(entry, _ENTRY)                # (a new file: a process that has loaded the old one keeps it)
         jobs = [(src, os.path.join(tmp, os.path.basename(src) + ".o")) for src in sources()]
         workers = max(1, min(len(jobs), os.cpu_count() or 1, 8))
         with concurrent.futures.ThreadPoolExecutor(max_workers=workers) as pool:
@@ -101,6 +119,8 @@ def load_library():
         lib.attnw_version.argtypes = []
         lib.attnw_version.restype = ci
         _lib = lib
+        for name, entry in _entries.items():
+            entry.bind(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value)
     return _lib
 
 
@@ -133,34 +153,51 @@ def attnw_version() -> int:
     return int(load_library().attnw_version())
 
 
+def _entry_point(pointers: int, sizes: int, scales: int, dtypes: int):
+    """The function as a callable of ``_entry.so``, for arguments: pointers, sizes, a scale, element types, a stream."""
+    def wrap(function):
+        if _entry is None:
+            return function
+        entry = _entry.Entry(function, _check, pointers, sizes, scales, dtypes)
+        _entries[function.__name__] = entry
+        return functools.update_wrapper(entry, function)
+    return wrap
+
+
+@_entry_point(3, 4, 1, 1)
 def attnw_fused(Q, K, P, B: int, H: int, N: int, d: int, scale: float, dtype: int, stream=None) -> None:
     """P = softmax(scale * Q K^T) over keys; see ``attnw_fused`` in include/attnw.h."""
     _check(load_library().attnw_fused(_ptr(Q), _ptr(K), _ptr(P), B, H, N, d, float(scale), int(dtype),
                                       _stream(stream)))
 
 
+@_entry_point(2, 2, 0, 1)
 def attnw_softmax(S, P, rows: int, cols: int, dtype: int, stream=None) -> None:
     """Row softmax of S into P; see ``attnw_softmax`` in include/attnw.h."""
     _check(load_library().attnw_softmax(_ptr(S), _ptr(P), rows, cols, int(dtype), _stream(stream)))
 
 
+@_entry_point(2, 2, 0, 2)
 def attnw_softmax_cast(S, P, rows: int, cols: int, in_dtype: int, out_dtype: int, stream=None) -> None:
     """Row softmax with separate input and output types; see ``attnw_softmax_cast`` in include/attnw.h."""
     _check(load_library().attnw_softmax_cast(_ptr(S), _ptr(P), rows, cols, int(in_dtype), int(out_dtype),
                                              _stream(stream)))
 
 
+@_entry_point(2, 1, 1, 1)
 def attnw_scale(X, Y, count: int, scale: float, dtype: int, stream=None) -> None:
     """Y = scale * X elementwise; see ``attnw_scale`` in include/attnw.h."""
     _check(load_library().attnw_scale(_ptr(X), _ptr(Y), count, float(scale), int(dtype), _stream(stream)))
 
 
+@_entry_point(3, 4, 1, 1)
 def attnw_gemm_scores(Q, K, S, B: int, H: int, N: int, d: int, scale: float, dtype: int, stream=None) -> None:
     """S = scale * Q K^T written to device memory; see ``attnw_gemm_scores`` in include/attnw.h."""
     _check(load_library().attnw_gemm_scores(_ptr(Q), _ptr(K), _ptr(S), B, H, N, d, float(scale), int(dtype),
                                             _stream(stream)))
 
 
+@_entry_point(4, 4, 1, 1)
 def attnw_attention(Q, K, V, O, B: int, H: int, N: int, d: int, scale: float, dtype: int, stream=None) -> None:
     """O = softmax(scale * Q K^T) V, weights kept on chip; see ``attnw_attention`` in include/attnw.h."""
     _check(load_library().attnw_attention(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), B, H, N, d, float(scale), int(dtype),
