@@ -914,12 +914,13 @@ bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 //   weights, d <= 128, 1281 tokens and more: x up to 1 0.15 to 0.75, to 2 0.26 to 0.8, to 4 0.4 to 0.8, to 5 0.6 to 0.95.  Beyond that rows on
 //     16-byte boundaries 0.7 to 1.0 but for last rounds of the others' 256-query workgroups that are nearly full (x of 6 to 8.2 and of 14 to 17: 1.0 to
 //     1.26), other rows only from 8.3 to 10.2 (0.73 to 0.99; 6 to 8 and above 12 1.0 to 1.25).  Whole tiles of 256: d = 64 0.84 to 1.4, d = 128 0.74 to
-//     0.87 up to 2048 tokens, then 0.8 to 1.3; other d as the rest.  Up to 1280 tokens the one-workgroup-per-strip kernel is faster (1.0 to 3).
+//     0.87 up to 2048 tokens, then 0.8 to 1.3; other d 0.4 to 0.95 up to 5, then to 1.11.  Up to 1280 tokens the one-workgroup-per-strip kernel is faster (1.0 to 3).
 //   weights, d > 128: x up to 1 0.3 to 0.6, to 2 0.5 to 0.8, beyond 0.55 to 0.95 but where the 128-query workgroups of the general kernel nearly
-//     fill a round (3 to 4 1.0 to 1.35, 6 to 8 to 1.3), and d above 192 that are not whole pieces of 64 columns, more than 2048 tokens (1.1 to 1.36)
+//     fill a round (1.0 to 1.35), d above 192 that are not whole pieces of 64 columns, more than 2048 tokens (1.1 to 1.36), and many strips (d <= 192 up to
+//     16 to 25 0.66 to 0.97, then to 1.2; d > 192 up to 12 and 1280 tokens 0.83 to 1.0, then to 1.8)
 //   scores, against a general kernel that splits the keys of few strips over workgroups.  Odd lengths of 1281 and more 0.13 to 0.9 (beyond 2048
-//     tokens with d > 32 and few strips 1.1 to 1.3); d <= 32 0.23 to 0.8, whole blocks of 32 keys up to x of 12 0.59 to 0.98; larger d whole blocks 0.64 to 0.9
-//     from 3.1 to 5.5 and 9 to 12, other even lengths 0.65 to 0.98 from 3.2 to 4; else 0.95 to 1.5.  Whole blocks of 513 to 1280 tokens, d > 64, 1.6 to
+//     tokens with d > 32 and few strips 1.1 to 1.3); d <= 32 0.23 to 0.8, whole blocks of 32 keys up to x of 6 0.59 to 0.95; larger d whole blocks 0.64 to 0.9
+//     from 3.1 to 4.6 and 9 to 12, other even lengths 0.65 to 0.98 from 3.2 to 4; else 0.95 to 1.5.  Whole blocks of 513 to 1280 tokens, d > 64, 1.6 to
 //     4.5: 0.43 to 0.95.  d > 128: 0.26 to 0.95 up to 2 (d > 192: 1.4, up to 896 tokens 1), odd lengths up to 2.2 and 4 to 6.
 bool prefers_stream(bool scores_only, int64_t BH, int64_t N, int64_t d)
 {
@@ -929,22 +930,25 @@ bool prefers_stream(bool scores_only, int64_t BH, int64_t N, int64_t d)
     const bool odd = N % 2 != 0, blocks = N % 32 == 0, tiles = N % 256 == 0;
     if (d > 128) {
         if (scores_only) return within(0, d <= 192 ? 2 : N <= 896 ? 1 : 1.4) || (odd && (within(0, 2.2) || within(4, 6)));
-        if (d > 192 && N > 2048) return within(0, 2.1) || (d == 256 && within(4, 6));
-        if (d > 192) return !within(2.8, 4) && !within(6, 8);
-        return N <= 2048 || (!within(3, 4) && !within(6, 8));
+        const int64_t rounds = (BH * ((N + 127) / 128) + compute_units() - 1) / compute_units();
+        if (d > 192 && N > 2048) return rounds == 1 ? x <= 2.1 : rounds == 2 && d == 256 && within(4, 6);
+        if (d > 192) return rounds == 1 ? x <= 2.8 : rounds == 2 ? x <= 6 : rounds == 3 && N <= 1280 && x <= 10;
+        if (N > 2048 && rounds <= 2) return x <= 3 * rounds;
+        return x <= (N <= 640 ? 16 : N <= 896 ? 20 : 25);
     }
     if (N <= 1280) return scores_only && d > 64 && blocks && !tiles && within(1.6, 4.5);
     if (!scores_only) {
         if (tiles && d == 64) return false;
         if (tiles && d == 128) return N <= 2048 && within(0.25, 6);
-        if (N % 8 == 0) return d <= 32 || (!within(6, 8.2) && !within(14, 17));
+        if (tiles) return x <= 5;                 // (d other than 64 and 128)
+        if (N % 8 == 0) return !within(6, d <= 32 ? 7.5 : 8.2) && (d <= 32 || !within(14, 17));
         return within(0, d <= 32 ? 6 : 5) || within(8.3, 10.2);
     }
     if (odd && d <= 32) return within(0, 6);
     if (odd) return N <= 2048 ? within(0, 1) || within(1.35, 5) : within(0.9, 1) || within(1.35, 1.95) || within(2, 4.4);
-    if (d <= 32) return tiles ? within(0, 4) : blocks ? within(0, 12) : N % 8 == 0 ? within(0, 2) || within(3.1, 4) : within(0, 4);
+    if (d <= 32) return tiles ? within(0, 4) : blocks ? within(0, 6) : N % 8 == 0 ? within(0, 2) || within(3.1, 4) : within(0, 4);
     if (tiles) return false;
-    return blocks ? within(3.1, 5.5) || within(9, 12) : N <= 4096 && within(3.2, 4);
+    return blocks ? within(3.1, 4.6) || within(9, 12) : N <= 4096 && within(3.2, 4);
 }
 
 }  // namespace
