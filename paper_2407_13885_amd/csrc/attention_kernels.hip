@@ -348,10 +348,10 @@ hipError_t launch_attention_t(const void* Q, const void* K, const void* V, void*
     };
     // A look at the sums costs more where the exponent moves, in the first tiles of a row, and saves in all others.  us, maxima -> sums: 16 heads
     // of N = 4096, d = 32 64.0 -> 59.1, 48 of 4096, d = 64 270 -> 250, 72 of 1120, d = 32 32.3 -> 29.6; rows of every sharpness 276 -> 271 (48 of 4096),
-    // 607 -> 585 (8 of 16384); but 200 of 512, d = 64 27.4 -> 28.4, 128 of 2048 in two query blocks a wave 162 -> 171.  (Two blocks and ragged
-    // ends: registers for the scores and their weights spill.)
-    if constexpr (QB == 1 || !TAIL)
-        if (N >= (QB == 1 ? 1024 : 2560)) return go(attention_kernel<DB, QB, TAIL, true>);
+    // 607 -> 585 (8 of 16384); but 200 of 512, d = 64 27.4 -> 28.4, 128 of 2048 in two query blocks a wave 162 -> 171.  216 of 2191, d = 32 288 -> 281.  (d = 64, two
+    // blocks and ragged ends: registers for the scores and their weights spill.)
+    if constexpr (QB == 1 || !TAIL || DB == 64)
+        if (N >= (QB == 1 ? 1024 : DB == 64 ? 2048 : 2560)) return go(attention_kernel<DB, QB, TAIL, true>);
     return go(attention_kernel<DB, QB, TAIL, false>);
 }
 
