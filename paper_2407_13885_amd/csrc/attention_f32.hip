@@ -30,7 +30,8 @@ namespace {
 
 __device__ const u32x4 kZeros = {0u, 0u, 0u, 0u};
 
-template <int DVB, int WQ, int WK>
+// CS: workgroups that share the columns of V and O of a query block
+template <int DVB, int WQ, int WK, int CS>
 struct F32Cfg {
     static constexpr int NW = WQ * WK;            // waves per workgroup
     static constexpr int BM = 32 * WQ;            // queries per workgroup
@@ -39,22 +40,27 @@ struct F32Cfg {
     static constexpr int CPR = DB / 16;
     static constexpr int TILE = BN * DB;
     static constexpr int LOADS = TILE / 1024 / NW;   // wave-wide transfers per wave and tile
-    static constexpr int SLOTS = 2 + DVB * 16;    // merge: reference exponent, sum, output accumulators
+    static constexpr int OB = DVB / CS;           // 32-column blocks of V and O
+    static constexpr int V_TILE = TILE / CS;
+    static constexpr int SLOTS = 2 + OB * 16;     // merge: reference exponent, sum, output accumulators
     static constexpr int MERGE = WK > 1 ? NW * SLOTS * 256 : 0;
-    static constexpr int LDS = 2 * TILE > MERGE ? 2 * TILE : MERGE;
-    static_assert(2 * TILE <= kDirectLds, "reach of direct transfers");
+    static constexpr int LDS = TILE + V_TILE > MERGE ? TILE + V_TILE : MERGE;
+    static_assert(DVB % CS == 0 && TILE % (1024 * NW) == 0 && V_TILE % (1024 * NW) == 0, "whole column blocks, whole transfers");
+    static_assert(TILE + V_TILE <= kDirectLds, "reach of direct transfers");
 };
 
 // DVB: 32-column blocks of an output row, ceil(d / 32); rows are padded to 32 DVB elements on chip (rb: bytes of a row
 // in memory).  Padding chunks are transferred from an array of zeros (any of the caller's numbers could be infinite, and NaN
 // against the zeros of the padded Q fragments).  Rows past N are read as row N - 1.
-template <int DVB, int WQ, int WK>
+// CS > 1 (few heads): CS workgroups share a block, each makes all scores but reads and multiplies its share of the columns of V only.  (d >
+// 128: the tiles of V are smaller, so that three or four key ranges fit instead of two.)
+template <int DVB, int WQ, int WK, int CS>
 __global__ __launch_bounds__(64 * WQ * WK, DVB <= 4 ? 2 : 1)
 void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
                           float* __restrict__ O, int N, int rb, float c, uint32_t sign_flip, uint32_t strips, uint32_t total)
 {
-    using C = F32Cfg<DVB, WQ, WK>;
-    constexpr int NW = C::NW, DB = C::DB, CPR = C::CPR, BN = C::BN, LOADS = C::LOADS;
+    using C = F32Cfg<DVB, WQ, WK, CS>;
+    constexpr int NW = C::NW, DB = C::DB, CPR = C::CPR, BN = C::BN, LOADS = C::LOADS, OB = C::OB, DBV = OB * 128;
     constexpr int G = DVB * 4;                    // 32-byte contraction groups of a padded row
 
     __shared__ __align__(1024) char lds[C::LDS];
@@ -63,8 +69,10 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
 
     const uint32_t logical = xcd_contiguous_block_id(blockIdx.x, gridDim.x);
     if (logical >= total) return;
-    const uint32_t bh = logical / strips;
-    const uint32_t strip = logical - bh * strips;
+    const uint32_t block = logical / CS;
+    const int col0 = (int)(logical % CS) * OB * 32;   // this workgroup's first column of V and O
+    const uint32_t bh = block / strips;
+    const uint32_t strip = block - bh * strips;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int l32 = lane & 31;
@@ -92,30 +100,38 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
 
     // ---- tile transfers: chunk s = (wave + NW j) 64 + lane of the tile; the swizzle permutes chunks within a row ----
     const uint32_t k_base = lds_offset_of(k_lds), v_base = lds_offset_of(v_lds);
-    auto issue = [&](const char* head, uint32_t dst, int key0, auto swzc) __attribute__((always_inline)) {
+    auto k_issue = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < LOADS; ++j) {
             const int s = (wave + NW * j) * 64 + lane;
             const int key = s / CPR;
-            int ch = s - key * CPR;
-            if constexpr (decltype(swzc)::value != 0) ch ^= key & 7;
-            const char* src = head + (int64_t)min(key0 + key, N - 1) * rb + ch * 16;
+            const int ch = (s - key * CPR) ^ (key & 7);
+            const char* src = Kh + (int64_t)min(t * BN + key, N - 1) * rb + ch * 16;
             if (ch >= row_chunks) src = reinterpret_cast<const char*>(&kZeros);
-            dma16_untracked(src, dst + (wave + NW * j) * 1024);
+            dma16_untracked(src, k_base + (wave + NW * j) * 1024);
         }
     };
-    auto k_issue = [&](int t) __attribute__((always_inline)) { issue(Kh, k_base, t * BN, IC<1>{}); };
-    auto v_issue = [&](int t) __attribute__((always_inline)) { issue(Vh, v_base, t * BN, IC<0>{}); };
+    auto v_issue = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < LOADS / CS; ++j) {
+            const int s = (wave + NW * j) * 64 + lane;
+            const int key = s / (CPR / CS);
+            const int ch = s - key * (CPR / CS) + col0 / 4;
+            const char* src = Vh + (int64_t)min(t * BN + key, N - 1) * rb + ch * 16;
+            if (ch >= row_chunks) src = reinterpret_cast<const char*>(&kZeros);
+            dma16_untracked(src, v_base + (wave + NW * j) * 1024);
+        }
+    };
 
     const char* const krow = k_lds + (wk * 32 + l32) * DB;
     int kswz[4];                                  // chunk (2g + half) ^ (key & 7): its low three bits repeat every four groups
 #pragma unroll
     for (int g = 0; g < 4; ++g) kswz[g] = ((2 * g + half) ^ (l32 & 7)) * 16;
-    const char* const vrow = v_lds + (wk * 32 + 4 * half) * DB + l32 * 4;
+    const char* const vrow = v_lds + (wk * 32 + 4 * half) * DBV + l32 * 4;
 
-    f32x16 oacc[DVB];
+    f32x16 oacc[OB];
 #pragma unroll
-    for (int b = 0; b < DVB; ++b)
+    for (int b = 0; b < OB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[b][r] = 0.0f;
     float mb_run = kNegBig, l_run = 0.0f;
@@ -147,7 +163,7 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
                 const float alpha = fast_exp2(mb_run - mb_new);   // exactly 1 for lanes whose exponent stands
                 l_run *= alpha;
 #pragma unroll
-                for (int b = 0; b < DVB; ++b)
+                for (int b = 0; b < OB; ++b)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) oacc[b][r] *= alpha;
                 mb_run = mb_new;
@@ -171,16 +187,16 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
 #pragma unroll
             for (int r = 0; r < 16; ++r)
 #pragma unroll
-                for (int b = 0; b < DVB; ++b)
+                for (int b = 0; b < OB; ++b)
                     oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                        *reinterpret_cast<const float*>(vrow + (8 * (r / 4) + r % 4) * DB + b * 128), p[r], oacc[b], 0, 0, 0);
+                        *reinterpret_cast<const float*>(vrow + (8 * (r / 4) + r % 4) * DBV + b * 128), p[r], oacc[b], 0, 0, 0);
         }
     }
     wait_vmem();                                  // no transfer may be in flight when the LDS is reused or released
 
     // ---- normalise and store: a lane owns runs of 4 consecutive output columns of its query ----------------------
-    const int d = rb / 4;
-    char* const orow = Oh + (int64_t)(q0 + l32) * rb + half * 16;
+    const int d = rb / 4 - col0;              // columns from this workgroup's first on
+    char* const orow = Oh + (int64_t)(q0 + l32) * rb + col0 * 4 + half * 16;
     if constexpr (WK > 1) {
         constexpr int SLOTS = C::SLOTS;
         float* const part = reinterpret_cast<float*>(lds);
@@ -189,7 +205,7 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
         mine[0] = mb_run;
         mine[64] = l_run;
 #pragma unroll
-        for (int b = 0; b < DVB; ++b)
+        for (int b = 0; b < OB; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) mine[(2 + b * 16 + r) * 64] = oacc[b][r];
         __syncthreads();
@@ -204,7 +220,7 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
         }
         const float inv = 1.0f / half_wave_sum(L);
         if (q0 + l32 >= N) return;
-        for (int b = wk; b < DVB; b += WK)
+        for (int b = wk; b < OB; b += WK)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -220,7 +236,7 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
         const float inv = 1.0f / half_wave_sum(l_run);
         if (q0 + l32 >= N) return;
 #pragma unroll
-        for (int b = 0; b < DVB; ++b)
+        for (int b = 0; b < OB; ++b)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const f32x4 o = {oacc[b][4 * i], oacc[b][4 * i + 1], oacc[b][4 * i + 2], oacc[b][4 * i + 3]};
@@ -229,16 +245,16 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
     }
 }
 
-template <int DVB, int WQ, int WK>
+template <int DVB, int WQ, int WK, int CS = 1>
 hipError_t launch_f32_t(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, int d, float scale,
                         hipStream_t stream)
 {
-    using C = F32Cfg<DVB, WQ, WK>;
+    using C = F32Cfg<DVB, WQ, WK, CS>;
     const uint32_t strips = (uint32_t)((N + C::BM - 1) / C::BM);
-    return launch_by_heads(BH, strips, 64 * C::NW, [&](int64_t first, int64_t heads) {
+    return launch_by_heads(BH, strips * CS, 64 * C::NW, [&](int64_t first, int64_t heads) {
         const int64_t at = first * N * d;
-        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
-        hipLaunchKernelGGL((attention_f32_kernel<DVB, WQ, WK>), dim3(grid), dim3(64 * C::NW), 0, stream, static_cast<const float*>(Q) + at,
+        const uint32_t total = (uint32_t)heads * strips * CS, grid = (total + 7) / 8 * 8;
+        hipLaunchKernelGGL((attention_f32_kernel<DVB, WQ, WK, CS>), dim3(grid), dim3(64 * C::NW), 0, stream, static_cast<const float*>(Q) + at,
                            static_cast<const float*>(K) + at, static_cast<const float*>(V) + at, static_cast<float*>(O) + at, N, d * 4,
                            fabsf(scale) * kLog2e, scale < 0.0f ? Mma<float>::kSignMask : 0u, strips, total);
         return hipGetLastError();
@@ -287,6 +303,17 @@ hipError_t launch_f32_ranges(const void* Q, const void* K, const void* V, void* 
             return launch_f32_t<DVB, 1, 1>(Q, K, V, O, BH, N, d, scale, stream);
     }
     if (N <= 64) return launch_f32_t<DVB, 2, 1>(Q, K, V, O, BH, N, d, scale, stream);
+    // d > 128, few heads: workgroups of one query block that share its columns.  What a launch takes goes as rounds x sub-tiles of a wave x
+    // (blocks of columns contracted and multiplied); taken where that is a fifth less.  us, key ranges alone -> columns shared: one head of 1916,
+    // d = 208 240 -> 168, two of 674, d = 256 104 -> 58, one of 200, d = 132 28 -> 13, three of 96, d = 144 21 -> 9, one of 4096, d = 192 422 -> 344; by less than
+    // that: d = 256 561 -> 571, d = 160 347 -> 387.
+    if constexpr (DVB > 4) {
+        constexpr int CS = DVB == 8 ? 4 : DVB == 6 ? 3 : DVB, WK = DVB == 8 ? 3 : 4;
+        const int64_t cus = compute_units(), blocks = BH * ((N + 31) / 32), pairs = BH * ((N + 63) / 64), quads = BH * ((N + 127) / 128);
+        const int64_t shared = (CS * blocks + cus - 1) / cus * ((N + 32 * WK - 1) / (32 * WK) + 1) * (DVB + DVB / CS);
+        const int64_t two = (pairs + cus - 1) / cus * ((N + 63) / 64 + 1) * 2 * DVB, one = (quads + cus - 1) / cus * ((N + 31) / 32) * 2 * DVB;
+        if (5 * shared < 4 * two && 5 * shared < 4 * one) return launch_f32_t<DVB, 1, WK, CS>(Q, K, V, O, BH, N, d, scale, stream);
+    }
     // (d > 128: the K and V tiles of four ranges do not fit the LDS)
     constexpr int most = DVB <= 4 ? 4 : 2;
     const int wk = key_ranges_f32(BH, N, most);
@@ -299,7 +326,18 @@ hipError_t launch_f32_ranges(const void* Q, const void* K, const void* V, void* 
             return launch_attention_f32_split(Q, K, V, O, BH, N, d, scale, stream);
     }
     if constexpr (most == 4)
-        if (wk == 4) return launch_f32_t<DVB, 1, 4>(Q, K, V, O, BH, N, d, scale, stream);
+        if (wk == 4) {
+            // One-block workgroups for less than half, a third or a quarter of the compute units: the others share the columns.  us, one head of
+            // 4096, d = 128 163 -> 140, d = 64 82 -> 71, of 2048, d = 128 80 -> 59, of 2000, d = 96 63 -> 47, two of 674, d = 128 33 -> 24, one of 300 19.5 -> 14.
+            const int64_t cus = compute_units(), blocks = BH * ((N + 31) / 32);
+            if constexpr (DVB == 4)
+                if (4 * blocks <= cus) return launch_f32_t<DVB, 1, 4, 4>(Q, K, V, O, BH, N, d, scale, stream);
+            if constexpr (DVB == 3)
+                if (3 * blocks <= cus) return launch_f32_t<DVB, 1, 4, 3>(Q, K, V, O, BH, N, d, scale, stream);
+            if constexpr (DVB % 2 == 0)
+                if (2 * blocks <= cus) return launch_f32_t<DVB, 1, 4, 2>(Q, K, V, O, BH, N, d, scale, stream);
+            return launch_f32_t<DVB, 1, 4>(Q, K, V, O, BH, N, d, scale, stream);
+        }
     if (wk == 2) return launch_f32_t<DVB, 2, 2>(Q, K, V, O, BH, N, d, scale, stream);
     return launch_f32_t<DVB, 4, 1>(Q, K, V, O, BH, N, d, scale, stream);
 }
