@@ -213,25 +213,11 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                     vf[b][m] = *reinterpret_cast<const u32x4*>(vb + b * 32 * VT_PITCH + (u * 32 + 16 * m) * 2);
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
-                float p[16], sum;
-                auto weigh = [&]() __attribute__((always_inline)) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[qb][r], c, -mb_run[qb]));
-                    if constexpr (MASK) {
-                        // keys past the end were read as key N-1 (their scores change no maximum): no weight
-                        const int kbase = t * BN + u * 32 + 4 * half;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            if (kbase + 8 * (r / 4) + (r % 4) >= N) p[r] = 0.0f;
-                    }
-                    float part[4] = {p[0], p[1], p[2], p[3]};
-#pragma unroll
-                    for (int r = 4; r < 16; ++r) part[r & 3] += p[r];
-                    sum = (part[0] + part[1]) + (part[2] + part[3]);
-                };
-                // The exponent the weights are taken against (mb_run) follows the running maximum lazily.  The 16 * DVB multiplies
-                // of the output accumulator - needed at every new maximum otherwise, i.e. in most of the early sub-tiles of a
-                // row - become rare.  Lanes whose exponent stands get the factor 2^0 = 1 exactly.
+                // The exponent the weights are taken against (mb_run) follows the running maximum lazily: it moves only when some query
+                // of the wave exceeds it by more than kLazy binades (SUMS: when the weights' sums say so).  Until then weights up to
+                // 2^kLazy appear, which costs nothing (fp32 sums, and bf16 has the same relative precision at every magnitude),
+                // and the 16 * DVB multiplies of the output accumulator - needed at every new maximum otherwise, i.e. in most of
+                // the early sub-tiles of a row - become rare.  Lanes whose exponent stands get the factor 2^0 = 1 exactly.
                 auto move = [&](float to) __attribute__((always_inline)) {
                     const float alpha = fast_exp2(mb_run[qb] - to);
                     l_run[qb] *= alpha;
@@ -241,19 +227,44 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                         for (int r = 0; r < 16; ++r) oacc[qb][b][r] *= alpha;
                     mb_run[qb] = to;
                 };
-                // (shared by the two lanes of a query)
-                auto maximum = [&]() __attribute__((always_inline)) { return fmaxf(mb_run[qb], half_wave_max(max16(s[qb])) * c); };
+                // maximum of this sub-tile, shared by the two lanes of a query
+                auto maximum = [&]() __attribute__((always_inline)) { return half_wave_max(max16(s[qb])) * c; };
+                float p[16];
+                auto weigh = [&]() __attribute__((always_inline)) {
+                    const float mb = mb_run[qb];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[qb][r], c, -mb));
+                    if constexpr (MASK) {
+                        // keys past the end were read as key N-1 (their scores change no maximum): no weight
+                        const int kbase = t * BN + u * 32 + 4 * half;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (kbase + 8 * (r / 4) + (r % 4) >= N) p[r] = 0.0f;
+                    }
+                };
                 if constexpr (!SUMS) {
-                    const float to = maximum();
-                    if (__builtin_amdgcn_ballot_w64(to > mb_run[qb] + kLazy) != 0) move(to);
+                    const float mbn = maximum();
+                    if (__builtin_amdgcn_ballot_w64(mbn > mb_run[qb] + kLazy) != 0) move(fmaxf(mb_run[qb], mbn));
                     weigh();
+                    float sum = p[0];
+#pragma unroll
+                    for (int r = 1; r < 16; ++r) sum += p[r];
+                    l_run[qb] += sum;
                 } else {
-                    if (u == 0 && t == 0) mb_run[qb] = maximum();
+                    auto total = [&]() __attribute__((always_inline)) {
+                        float part[4] = {p[0], p[1], p[2], p[3]};
+#pragma unroll
+                        for (int r = 4; r < 16; ++r) part[r & 3] += p[r];
+                        return (part[0] + part[1]) + (part[2] + part[3]);
+                    };
+                    if (u == 0 && t == 0) mb_run[qb] = fmaxf(mb_run[qb], maximum());
                     weigh();
+                    float sum = total();
                     if (__builtin_amdgcn_ballot_w64(sum > kFarSum) != 0) {
                         if (__builtin_amdgcn_ballot_w64(sum > kOverflow) != 0) {
-                            move(maximum());
+                            move(fmaxf(mb_run[qb], maximum()));
                             weigh();
+                            sum = total();
                         } else {
                             const float by = far_exponent(p), a = fast_exp2(-by);
 #pragma unroll
@@ -262,8 +273,8 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                             move(mb_run[qb] + by);
                         }
                     }
+                    l_run[qb] += sum;
                 }
-                l_run[qb] += sum;
                 // a lane's weights of group m are accumulators 8m .. 8m+7: exactly its operand of the second contraction
 #pragma unroll
                 for (int m = 0; m < 2; ++m) {
