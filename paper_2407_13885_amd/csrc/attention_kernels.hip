@@ -213,6 +213,18 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                     vf[b][m] = *reinterpret_cast<const u32x4*>(vb + b * 32 * VT_PITCH + (u * 32 + 16 * m) * 2);
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
+                float p[16];
+                auto weigh = [&](float mb) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[qb][r], c, -mb));
+                    if constexpr (MASK) {
+                        // keys past the end were read as key N-1 (their scores change no maximum): no weight
+                        const int kbase = t * BN + u * 32 + 4 * half;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (kbase + 8 * (r / 4) + (r % 4) >= N) p[r] = 0.0f;
+                    }
+                };
                 // The exponent the weights are taken against (mb_run) follows the running maximum lazily: it moves only when some query
                 // of the wave exceeds it by more than kLazy binades (SUMS: when the weights' sums say so).  Until then weights up to
                 // 2^kLazy appear, which costs nothing (fp32 sums, and bf16 has the same relative precision at every magnitude),
@@ -227,30 +239,35 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                         for (int r = 0; r < 16; ++r) oacc[qb][b][r] *= alpha;
                     mb_run[qb] = to;
                 };
-                // maximum of this sub-tile, shared by the two lanes of a query
-                auto maximum = [&]() __attribute__((always_inline)) { return half_wave_max(max16(s[qb])) * c; };
-                float p[16];
-                auto weigh = [&]() __attribute__((always_inline)) {
+                if constexpr (!SUMS) {
+                    // (the lambdas above, written out: the compiler schedules this form in 92 registers where it takes 100 with them, 36 -> 33.7 us
+                    // for 198 heads of N = 613, d = 32)
+                    const float mbn = half_wave_max(max16(s[qb])) * c;   // shared by the two lanes of a query
+                    if (__builtin_amdgcn_ballot_w64(mbn > mb_run[qb] + kLazy) != 0) {
+                        const float mb_new = fmaxf(mb_run[qb], mbn);
+                        const float alpha = fast_exp2(mb_run[qb] - mb_new);
+                        l_run[qb] *= alpha;
+#pragma unroll
+                        for (int b = 0; b < DVB; ++b)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) oacc[qb][b][r] *= alpha;
+                        mb_run[qb] = mb_new;
+                    }
                     const float mb = mb_run[qb];
 #pragma unroll
                     for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[qb][r], c, -mb));
                     if constexpr (MASK) {
-                        // keys past the end were read as key N-1 (their scores change no maximum): no weight
                         const int kbase = t * BN + u * 32 + 4 * half;
 #pragma unroll
                         for (int r = 0; r < 16; ++r)
                             if (kbase + 8 * (r / 4) + (r % 4) >= N) p[r] = 0.0f;
                     }
-                };
-                if constexpr (!SUMS) {
-                    const float mbn = maximum();
-                    if (__builtin_amdgcn_ballot_w64(mbn > mb_run[qb] + kLazy) != 0) move(fmaxf(mb_run[qb], mbn));
-                    weigh();
                     float sum = p[0];
 #pragma unroll
                     for (int r = 1; r < 16; ++r) sum += p[r];
                     l_run[qb] += sum;
                 } else {
+                    auto maximum = [&]() __attribute__((always_inline)) { return half_wave_max(max16(s[qb])) * c; };
                     auto total = [&]() __attribute__((always_inline)) {
                         float part[4] = {p[0], p[1], p[2], p[3]};
 #pragma unroll
@@ -258,12 +275,12 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                         return (part[0] + part[1]) + (part[2] + part[3]);
                     };
                     if (u == 0 && t == 0) mb_run[qb] = fmaxf(mb_run[qb], maximum());
-                    weigh();
+                    weigh(mb_run[qb]);
                     float sum = total();
                     if (__builtin_amdgcn_ballot_w64(sum > kFarSum) != 0) {
                         if (__builtin_amdgcn_ballot_w64(sum > kOverflow) != 0) {
                             move(fmaxf(mb_run[qb], maximum()));
-                            weigh();
+                            weigh(mb_run[qb]);
                             sum = total();
                         } else {
                             const float by = far_exponent(p), a = fast_exp2(-by);
@@ -359,11 +376,15 @@ hipError_t launch_attention_t(const void* Q, const void* K, const void* V, void*
     };
     // A look at the sums costs more where the exponent moves, in the first tiles of a row, and saves in all others.  us, maxima -> sums: 16 heads
     // of N = 4096, d = 32 64.0 -> 59.1, 48 of 4096, d = 64 270 -> 250, 72 of 1120, d = 32 32.3 -> 29.6; rows of every sharpness 276 -> 271 (48 of 4096),
-    // 607 -> 585 (8 of 16384); but 200 of 512, d = 64 27.4 -> 28.4, 128 of 2048 in two query blocks a wave 162 -> 171.  216 of 2191, d = 32 288 -> 281.  (d = 64, two
-    // blocks and ragged ends: registers for the scores and their weights spill.)
-    if constexpr (QB == 1 || !TAIL || DB == 64)
-        if (N >= (QB == 1 ? 1024 : DB == 64 ? 2048 : 2560)) return go(attention_kernel<DB, QB, TAIL, true>);
-    return go(attention_kernel<DB, QB, TAIL, false>);
+    // 607 -> 585 (8 of 16384); but 200 of 512, d = 64 27.4 -> 28.4, 128 of 2048 in two query blocks a wave 162 -> 171 (one
+    // block takes those, prefers_two_blocks).  (Two blocks and ragged ends: registers for the scores and their weights spill.  One block of d = 64
+    // without ragged ends: with the maxima two workgroups share a compute unit, and with more workgroups than units that is worth more:
+    // 432 of 1280 262 -> 220 us, 61 of 3328 234 -> 225; 50 of 1280, one workgroup a unit, 27.9 with the sums, 29.7 without.)
+    if constexpr (QB == 2) return go(attention_kernel<DB, QB, TAIL, !TAIL>);
+    else {
+        const bool pairs = DB == 128 && !TAIL && BH * strips > compute_units();
+        return N >= 1024 && !pairs ? go(attention_kernel<DB, QB, TAIL, true>) : go(attention_kernel<DB, QB, TAIL, false>);
+    }
 }
 
 // A ragged length whose last strip (256 queries, 512 with two query blocks per wave) holds at most 64 queries, and whose partial strips start another round
@@ -386,6 +407,24 @@ hipError_t launch_attention_own_tail(const void* Q, const void* K, const void* V
     return launch_attention_ranges(Q, K, V, O, BH, N, DB / 2, scale, (int)(full * BM), stream);
 }
 
+// d = 64: two query blocks per wave (512-query strips) read K and V half as often, and one block (256) needs half the time per round of
+// workgroups.  One workgroup of either kind fits a compute unit, and a round of the first takes 1.8 rounds of the second: two blocks
+// where they need at most that share of the rounds.  us, 512 -> 256 queries: 45 heads of N = 2743 (270 strips of 512) 204 -> 121, 33 of 4096 (264)
+// 241 -> 208; but 68 of 2888 (408) 195 -> 209, 40 of 3072 (240) 99 -> 113.  Whole lengths below 2560, where one block takes the maxima, two
+// workgroups to a unit, and two blocks gained nothing from the sums: always one (794 of 1024 357 -> 268, 128 of 2048 166 -> 160).  (Of 21000 random
+// shapes of N = 513 .. 9000 this line comes within 0.3 % of the better of the two, mean; the line "200 strips of 512 or more" within 7 %.)  At
+// d = 32 two blocks gain 2 % at best and lose 15 % over the lot: there is one.
+bool prefers_two_blocks(int64_t BH, int64_t N)
+{
+    const int64_t cus = compute_units();
+    auto rounds = [&](int64_t BM) {
+        const int64_t all = (BH * ((N + BM - 1) / BM) + cus - 1) / cus, whole = (BH * (N / BM) + cus - 1) / cus;
+        // (partial strips in a launch of their own, launch_attention_own_tail, weigh as half a workgroup each)
+        return N % BM >= 1 && N % BM <= 64 && N > BM && whole < all ? (double)whole + 0.5 * (double)BH / (double)cus : (double)all;
+    };
+    return N > 512 && !(N % 512 == 0 && N < 2560) && 1.8 * rounds(512) < rounds(256);
+}
+
 }  // namespace
 
 bool attention_supported(int64_t BH, int64_t N, int64_t d)
@@ -399,32 +438,21 @@ hipError_t launch_attention(const void* Q, const void* K, const void* V, void* O
                             float scale, hipStream_t stream)
 {
     if (prefers_attention_ranges(BH, N, d)) return launch_attention_ranges(Q, K, V, O, BH, N, d, scale, 0, stream);
-    if (d == 32) {          // short rows: two query blocks per wave whenever that leaves enough workgroups
-        const bool wide = N >= 2048 && BH * ((N + 511) / 512) >= 200;
-        if ((N % 256) != 0) {
-            bool taken;
-            if (wide) {
-                const hipError_t e = launch_attention_own_tail<64, 2>(Q, K, V, O, BH, (int)N, scale, stream, &taken);
-                return taken ? e : launch_attention_t<64, 2, true>(Q, K, V, O, BH, (int)N, scale, stream);
-            }
-            const hipError_t e = launch_attention_own_tail<64>(Q, K, V, O, BH, (int)N, scale, stream, &taken);
-            return taken ? e : launch_attention_t<64, 1, true>(Q, K, V, O, BH, (int)N, scale, stream);
-        }
-        return (wide && (N % 512) == 0) ? launch_attention_t<64, 2, false>(Q, K, V, O, BH, (int)N, scale, stream)
-                                        : launch_attention_t<64, 1, false>(Q, K, V, O, BH, (int)N, scale, stream);
+    bool taken;
+    if (d == 32) {
+        if ((N % 256) == 0) return launch_attention_t<64, 1, false>(Q, K, V, O, BH, (int)N, scale, stream);
+        const hipError_t e = launch_attention_own_tail<64>(Q, K, V, O, BH, (int)N, scale, stream, &taken);
+        return taken ? e : launch_attention_t<64, 1, true>(Q, K, V, O, BH, (int)N, scale, stream);
     }
+    const bool two = prefers_two_blocks(BH, N);
     if ((N % 256) != 0) {   // any length: rows past the end are clamped and masked
-        bool taken;
-        // (512-query strips only where the rows a last strip leaves unused are a small share)
-        if (N >= 2048 && BH * ((N + 511) / 512) >= 200) {
-            const hipError_t e = launch_attention_own_tail<128, 2>(Q, K, V, O, BH, (int)N, scale, stream, &taken);
-            return taken ? e : launch_attention_t<128, 2, true>(Q, K, V, O, BH, (int)N, scale, stream);
-        }
-        const hipError_t e = launch_attention_own_tail<128>(Q, K, V, O, BH, (int)N, scale, stream, &taken);
-        return taken ? e : launch_attention_t<128, 1, true>(Q, K, V, O, BH, (int)N, scale, stream);
+        const hipError_t e = two ? launch_attention_own_tail<128, 2>(Q, K, V, O, BH, (int)N, scale, stream, &taken)
+                                 : launch_attention_own_tail<128>(Q, K, V, O, BH, (int)N, scale, stream, &taken);
+        if (taken) return e;
+        return two ? launch_attention_t<128, 2, true>(Q, K, V, O, BH, (int)N, scale, stream)
+                   : launch_attention_t<128, 1, true>(Q, K, V, O, BH, (int)N, scale, stream);
     }
-    // two query blocks per wave (512-query strips) when that still gives every compute unit a workgroup
-    if ((N % 512) == 0 && BH * (N / 512) >= 200) return launch_attention_t<128, 2, false>(Q, K, V, O, BH, (int)N, scale, stream);
+    if (two && (N % 512) == 0) return launch_attention_t<128, 2, false>(Q, K, V, O, BH, (int)N, scale, stream);
     return launch_attention_t<128, 1, false>(Q, K, V, O, BH, (int)N, scale, stream);
 }
 
