@@ -36,7 +36,7 @@ struct WideCfg {
 // copies of the row's first chunks, left out of the first contraction and not stored by the second.  rb: bytes of a row
 // in memory.  Rows past N are read as row N - 1, weigh nothing and are not stored.
 template <int DVB, bool HALF, int WQ, int SUBS>
-__global__ __launch_bounds__(64 * WQ)
+__global__ __launch_bounds__(64 * WQ, WQ == 4 ? 2 : 1)
 void attention_wide_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                            uint16_t* __restrict__ O, int N, float c, uint32_t sign_flip, uint32_t strips, uint32_t total)
 {
@@ -226,13 +226,25 @@ hipError_t launch_wide(const void* Q, const void* K, const void* V, void* O, int
     // short rows: a tile of four sub-tiles per barrier (16 heads of N = 4096: d = 16 65.5 -> 57 us, 48 79.9 -> 75.0; d = 128 with two:
     // 130.5 -> 132.7)
     constexpr int SUBS = DVB <= 2 ? 4 : 1;
+    const int64_t cus = compute_units(), full = N / 256, tail_rows = N - full * 256, eights = (BH * ((N + 255) / 256) + cus - 1) / cus;
     // A last strip of at most 64 queries that would start another round of workgroups spends what ONE of its waves spends on
-    // a full strip: it follows as a launch of the kernel for few heads (16 heads of N = 4097, d = 128: 209 -> 170 us).
-    const int64_t full = N / 256, tail_rows = N - full * 256, slots = compute_units();
-    if (full >= 1 && tail_rows >= 1 && tail_rows <= 64 && (BH * full + slots - 1) / slots < (BH * (full + 1) + slots - 1) / slots) {
+    // a full strip: it follows as a launch of the kernel for few heads (16 heads of N = 4097, d = 128: 209 -> 170 us).  (From d = 80 only where
+    // the full strips are nine tenths of one round or more: 19 heads of N = 3360, d = 256 350 -> 237 us; workgroups of four waves take the
+    // others as they are, 2 to 30 % faster over 2000 random shapes, at d = 144 and 160 those too, 14 %.)
+    const bool one_round = DVB != 5 && BH * full <= cus && 10 * BH * full > 9 * cus;
+    if (full >= 1 && tail_rows >= 1 && tail_rows <= 64 && (BH * full + cus - 1) / cus < eights && (DVB <= 2 || one_round)) {
         const hipError_t e = launch_wide_t<DVB, HALF, 8, SUBS>(Q, K, V, O, BH, N, scale, stream, (int)full * 256);
         return e != hipSuccess ? e : launch_attention_ranges(Q, K, V, O, BH, N, DVB * 32 - (HALF ? 16 : 0), scale, (int)full * 256, stream);
     }
+    // d of 80 and more: workgroups of four waves (128 queries), two to a compute unit.  They move K and V twice as often, and where one
+    // waits at a tile's barrier the other computes; the rounds of workgroups end in smaller steps.  Workgroups of eight stay where they need at most
+    // two rounds and those of four fill the last of theirs more than half, and where the second 128 queries are few (N of at most 192: 2018 heads
+    // of N = 133, d = 96 50 us with four, 43 with eight).  us, eight -> four waves: 64 heads of N = 4096, d = 128 622 -> 566, 400 of
+    // 512, d = 80 57.4 -> 51.4, 40 of 600, d = 128 23.9 -> 19.1.  (Of 13900 random shapes of N = 256 .. 6000 this line comes
+    // within 0.4 % of the better of the two, mean; always eight within 11 %.  d = 16 and 48: 2 % at most, many shapes slower.)
+    if constexpr (DVB >= 3)
+        if (N > 192 && (eights > 2 || BH * ((N + 127) / 128) <= (2 * eights - 1) * cus))
+            return launch_wide_t<DVB, HALF, 4, SUBS>(Q, K, V, O, BH, N, scale, stream, N);
     return launch_wide_t<DVB, HALF, 8, SUBS>(Q, K, V, O, BH, N, scale, stream, N);
 }
 
