@@ -30,8 +30,9 @@ __device__ __forceinline__ float half_wave_sum(float x)
 // a sub-tile sum to more than this: a look at the sum that is needed anyway instead of at the maximum of the scores in front of the
 // exponentials (7 v_max3, an exchange between the half-waves and a branch per 32 keys, all of it in the way).  No weight is larger: fp32
 // sums and bf16 operands have the same relative precision at every magnitude.  The exponent then moves to the largest weight, which comes to
-// be 1 (and has no rounding as a bf16 operand: in sharp rows most of the error); weights that overflow are made again from the scores.
-constexpr float kFarSum = 256.0f, kOverflow = 3.0e38f;
+// be 1 (and has no rounding as a bf16 operand: in sharp rows most of the error).  Sums above 2^100 have their weights made again from the scores:
+// the factor between the exponents stays a normal number (v_exp_f32 gives 0 below 2^-126, for the largest weight too).
+constexpr float kFarSum = 256.0f, kOverflow = 0x1p100f;
 
 // the largest of a lane's 16 scores of a sub-tile
 __device__ __forceinline__ float max16(const f32x16& s)
