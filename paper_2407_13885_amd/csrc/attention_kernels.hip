@@ -283,11 +283,12 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                             weigh(mb_run[qb]);
                             sum = total();
                         } else {
-                            const float by = far_exponent(p), a = fast_exp2(-by);
+                            // (one factor, between the exponents as rounded, for these weights and all before them)
+                            const float to = mb_run[qb] + far_exponent(p), a = fast_exp2(mb_run[qb] - to);
 #pragma unroll
                             for (int r = 0; r < 16; ++r) p[r] *= a;
                             sum *= a;
-                            move(mb_run[qb] + by);
+                            move(to);
                         }
                     }
                     l_run[qb] += sum;

@@ -59,3 +59,19 @@ def test_scores_jump_by_the_range_of_fp32(heads, N, d, again):
     O = gu.to_f64(_run(x, V))
     for h in range(18):
         _check_rows(O[0, h], x, V, 0, h, [(0, 32), (N - 32, N)], f"{heads} heads of {N} x {d}, jump {h} of 17")
+
+
+@pytest.mark.parametrize("heads,N,d", SHAPES)
+def test_exponents_of_a_million(heads, N, d):
+    """Exponents of 1.5 million (an ulp is an eighth): the keys of two blocks weigh the same, whichever of them moved the exponent."""
+    x = _pairs(heads, N, d, 3900 + N + d)
+    x.Q[..., :d - 2] = 0
+    x.K[..., d - 2] = wl.store(np.float32(2.0 ** 23), "bf16")
+    V = np.zeros_like(x.K)
+    first, second = slice(N // 2, N // 2 + 32), slice(N // 2 + 160, N // 2 + 192)
+    V[:, :, first], V[:, :, second] = 0x3f80, 0xbf80
+    for h in range(heads):
+        x.K[0, h, first, d - 1] = x.K[0, h, second, d - 1] = wl.store(np.float32(80 + h), "bf16")
+    O = gu.to_f64(_run(x, V))
+    for h in range(heads):
+        _check_rows(O[0, h], x, V, 0, h, [(0, 2), (N - 2, N)], f"{heads} heads of {N} x {d}, head {h}")
