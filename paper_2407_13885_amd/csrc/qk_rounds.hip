@@ -394,7 +394,8 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                     stat_lds[(wave * 32 + l32) * 2] = mb;
                     stat_lds[(wave * 32 + l32) * 2 + 1] = l;
                 }
-                if (__builtin_amdgcn_ballot_w64(!(l < 0x1p100f)) != 0 && lane == 0) *outgrown = 1;
+                // (each lane's own sum: against the other half's exponent it may already have become 0)
+                if (__builtin_amdgcn_ballot_w64(!(l_run < 0x1p100f)) != 0 && lane == 0) *outgrown = 1;
                 __syncthreads();
                 kept = __builtin_amdgcn_readfirstlane(*outgrown) == 0;
 #pragma unroll

@@ -60,3 +60,23 @@ def test_a_nan_poisons_its_own_row_only(monkeypatch):
     assert bad[1, 40].all()
     bad[1, 40] = False
     assert not bad.any()
+
+
+# the second half-wave's first keys lie `units` eighths of a logit above everything that the first half-wave sees before one key of its own
+@pytest.mark.parametrize("BH,N,d", [(3, 512, 64), (80, 1792, 64), (3, 512, 128), (2, 768, 128)])
+@pytest.mark.parametrize("units", [700, 704, 708])
+def test_half_waves_far_apart(BH, N, d, units, monkeypatch):
+    """Sums of 2^126 to 2^128 in one half-wave, its exponent 126 binades and more below the other's."""
+    x = wl.fused_inputs("t", "bf16", 1, BH, N, d, seed=6960 + N + d, scale=0.125)
+    x.Q[...] = wl.store(wl.widen(x.Q, "bf16") * 0.25, "bf16")
+    x.K[...] = wl.store(wl.widen(x.K, "bf16") * 0.25, "bf16")
+    x.Q[..., d - 1] = 0x3f80
+    j = np.arange(N)
+    # (keys j % 8 < 4 are the first half-wave's, j % 64 < 32 in a first sub-tile)
+    high = (j % 64 == 4) | ((j >= N - 128) & (j % 64 == 33))
+    x.K[..., d - 1] = wl.store(np.where(high, np.float32(units), np.float32(0.0)), "bf16")
+    monkeypatch.setenv("ATTNW_FUSED_KERNEL", "rounds")
+    got = gu.run_fused(x, guard=8192)[0]
+    for head in sorted({0, BH - 1}):
+        ref = oracle.attention_weights(x.Q[0, head], x.K[0, head], "bf16", x.scale)
+        gu.check_weights(gu.to_f64(got[head]), ref, "bf16", f"{BH} heads of {N} x {d}, {units}, head {head}")
