@@ -354,11 +354,13 @@ void qk_stream_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
             float m = arg[0];
 #pragma unroll
             for (int r = 1; r < 16; ++r) m = fmaxf(m, arg[r]);
-            m = fmaxf(m, 0.0f);                   // by so much the reference moves
+            // by so much the reference moves, as rounded: blocks after this one are taken against ref itself
+            const float to = ref + fmaxf(m, 0.0f);
+            m = to - ref;
+            ref = to;
             const float a = fast_exp2(-m);
             l *= a;
             rescale(a);
-            ref += m;
 #pragma unroll
             for (int r = 0; r < 16; ++r) arg[r] -= m;
             static_for<16>([&](auto rc) __attribute__((always_inline)) { weigh(e, rc); });

@@ -93,3 +93,23 @@ def test_infinite_keys_weigh_nothing(N, d, monkeypatch):
     ref = oracle.attention_weights(x.Q[0, 1][rest], x.K[0, 1][rest], "bf16", x.scale)
     gu.check_weights(got[1][rest][:, rest], ref, "bf16", f"N={N} d={d}")
     assert np.isfinite(S[1][:, ~gone]).all() and np.isfinite(got[0]).all() and np.isfinite(S[0]).all()
+
+
+# windows held in registers, all of them; N = 1536: workgroups start at different ones
+@pytest.mark.parametrize("N,d", [(1100, 128), (1536, 128), (1280, 96)])
+def test_exponents_of_a_million(N, d, monkeypatch):
+    """Exponents of 1.5 million (an ulp is an eighth): keys of the same score weigh the same, whether their block moved the reference or not."""
+    x = wl.fused_inputs("t", "bf16", 1, 4, N, d, seed=6800 + N + d, scale=0.125)
+    x.Q[...] = 0
+    x.Q[..., d - 2:] = 0x3f80
+    x.K[..., d - 2] = wl.store(np.float32(2.0 ** 23), "bf16")
+    x.K[..., d - 1] = 0
+    block = np.arange(N) // 32
+    for h in range(4):
+        # (one wave of eight has these blocks)
+        x.K[0, h, (block == 11) | (block == 19), d - 1] = wl.store(np.float32(81 + 11 * h), "bf16")
+    monkeypatch.setenv("ATTNW_FUSED_KERNEL", "stream")
+    got = gu.to_f64(gu.run_fused(x))[0]
+    for h in range(4):
+        ref = oracle.attention_weights(x.Q[0, h], x.K[0, h], "bf16", x.scale)
+        gu.check_weights(got[h], ref, "bf16", f"N={N} d={d} head {h}")
