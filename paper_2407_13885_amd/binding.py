@@ -7,14 +7,16 @@ points, accept either raw device addresses (ints) or objects with a
 ``data_ptr()`` method (PyTorch tensors), and raise :class:`AttnwError` on a
 non-zero status.  There is no CPU fallback: a missing library is an error.
 
-A small call costs the host more than the device, so the public names are
-callables of ``_entry.so`` (``csrc/entry.cpp``) that hand arguments of the usual
-kinds straight to the C function and everything else to the functions here.
+A small call costs the host more than the device, so the public functions pass
+their arguments on to callables of ``_entry.so`` (``csrc/entry.cpp``), which hand
+the usual kinds straight to the C function and everything else to the functions
+written here.
 """
 from __future__ import annotations
 
 import ctypes
 import functools
+import inspect
 import os
 import subprocess
 import sysconfig
@@ -44,7 +46,8 @@ HIPCC_FLAGS = [
 ]
 
 _lib = None
-_entries = {}
+_entries = {}               # the public functions by name
+_direct = {}                # what they call
 
 
 class AttnwError(RuntimeError):
@@ -119,7 +122,7 @@ def load_library():
         lib.attnw_version.argtypes = []
         lib.attnw_version.restype = ci
         _lib = lib
-        for name, entry in _entries.items():
+        for name, entry in _direct.items():
             entry.bind(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value)
     return _lib
 
@@ -154,13 +157,18 @@ def attnw_version() -> int:
 
 
 def _entry_point(pointers: int, sizes: int, scales: int, dtypes: int):
-    """The function as a callable of ``_entry.so``, for arguments: pointers, sizes, a scale, element types, a stream."""
+    """The function by way of a callable of ``_entry.so``, for arguments: pointers, sizes, a scale, element types, a stream.  What
+    is returned is a function still, of the same signature (copied, pickled, referred to weakly, inspected, bound like one)."""
     def wrap(function):
         if _entry is None:
             return function
-        entry = _entry.Entry(function, _check, pointers, sizes, scales, dtypes)
-        _entries[function.__name__] = entry
-        return functools.update_wrapper(entry, function)
+        name, arguments = function.__name__, ", ".join(inspect.signature(function).parameters)
+        _direct[name] = _entry.Entry(function, _check, pointers, sizes, scales, dtypes)
+        scope = {"direct": _direct[name]}
+        exec(f"def {name}({arguments}):\n    return direct({arguments})", scope)
+        _entries[name] = functools.update_wrapper(scope[name], function)
+        _entries[name].__defaults__ = function.__defaults__
+        return _entries[name]
     return wrap
 
 

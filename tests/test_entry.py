@@ -1,8 +1,11 @@
 """The callables of _entry.so against the functions that they stand for: the same results, errors and statuses for arguments of every kind
 (statuses from calls that the host refuses or that have no rows: nothing is launched)."""
+import copy
 import inspect
 import os
+import pickle
 import threading
+import weakref
 
 import numpy as np
 import pytest
@@ -80,6 +83,18 @@ def test_same_as_the_function(name, good):
     assert _outcome(entry, [], dict(zip(names, bad))) == _outcome(plain, bad, {})
     for wrong in (good[:-1], tuple(good) + (None, None)):
         assert _outcome(entry, wrong, {}) == _outcome(plain, wrong, {})
+
+
+@pytest.mark.parametrize("name,good", CALLS)
+def test_functions_like_any_other(name, good):
+    f = getattr(binding, name)
+    assert inspect.isfunction(f) and copy.deepcopy(f) is f and pickle.loads(pickle.dumps(f)) is f and weakref.ref(f)() is f
+    assert f.__defaults__ == (None,) and f.__code__.co_varnames[:len(good)] == tuple(inspect.signature(f).parameters)[:len(good)]
+    assert f.__module__ == binding.__name__ and name in repr(f)
+
+    class Holder:
+        call = f
+    assert Holder().call.__func__ is f
 
 
 def test_no_rows():
