@@ -93,6 +93,8 @@ def build(verbose: bool = False) -> str:
         run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *[o for _, o in jobs], "-o", _LIB])
     global _lib
     _lib = None
+    for entry in _direct.values():                # (their C functions are the old library's)
+        entry.bind(0)
     return _LIB
 
 

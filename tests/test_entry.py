@@ -4,6 +4,8 @@ import copy
 import inspect
 import os
 import pickle
+import shutil
+import subprocess
 import threading
 import weakref
 
@@ -125,3 +127,33 @@ def test_threads():
     for t in threads:
         t.join()
     assert len(seen) == 4
+
+
+def test_calls_after_a_build_reach_the_library_built(monkeypatch, tmp_path):
+    """build() without its compilers, the library that it would have made in place of the one loaded: every entry point returns 77."""
+    source = tmp_path / "lib.c"
+    source.write_text("".join(f"int {name}() {{ return 77; }}\n" for name in binding.EXPORTS if name != "attnw_status_string")
+                      + 'const char* attnw_status_string(int s) { return "the new one"; }\n')
+    other = tmp_path / "libother.so"
+    subprocess.run(["gcc", "-w", "-shared", "-fPIC", str(source), "-o", str(other)], check=True)
+    bad = {name: (A + 2,) + tuple(good[1:]) for name, good in CALLS}
+    for name, args in bad.items():                # (refused by the library loaded now)
+        with pytest.raises(binding.AttnwError, match="aligned"):
+            getattr(binding, name)(*args)
+    try:
+        with monkeypatch.context() as m:
+            m.setattr(subprocess, "run", lambda cmd, **_: subprocess.CompletedProcess(cmd, 0, "", ""))
+            m.setattr(shutil, "move", lambda *_: None)
+            m.setattr(binding, "_LIB", str(other))
+            binding.build()
+            for name, args in bad.items():
+                with pytest.raises(binding.AttnwError, match="the new one") as e:
+                    getattr(binding, name)(*args)
+                assert e.value.status == 77
+            assert binding.attnw_version() == 77
+    finally:
+        binding._lib = None
+        binding.load_library()
+    for name, args in bad.items():
+        with pytest.raises(binding.AttnwError, match="aligned"):
+            getattr(binding, name)(*args)
