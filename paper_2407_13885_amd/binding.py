@@ -16,16 +16,13 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib
 import inspect
 import os
 import subprocess
 import sysconfig
+import warnings
 from typing import Optional
-
-try:
-    from . import _entry
-except ImportError:         # not built yet: ctypes alone
-    _entry = None
 
 ATTNW_F32 = 0
 ATTNW_BF16 = 1
@@ -46,8 +43,10 @@ HIPCC_FLAGS = [
 ]
 
 _lib = None
+_entry = None
 _entries = {}               # the public functions by name
-_direct = {}                # what they call
+_points = []                # (function that one stands for, kinds of its arguments, what it looks `direct` up in)
+_direct = {}                # the callables of _entry.so among what they call
 
 
 class AttnwError(RuntimeError):
@@ -95,6 +94,7 @@ def build(verbose: bool = False) -> str:
     _lib = None
     for entry in _direct.values():                # (their C functions are the old library's)
         entry.bind(0)
+    _attach()
     return _LIB
 
 
@@ -162,16 +162,29 @@ def _entry_point(pointers: int, sizes: int, scales: int, dtypes: int):
     """The function by way of a callable of ``_entry.so``, for arguments: pointers, sizes, a scale, element types, a stream.  What
     is returned is a function still, of the same signature (copied, pickled, referred to weakly, inspected, bound like one)."""
     def wrap(function):
-        if _entry is None:
-            return function
         name, arguments = function.__name__, ", ".join(inspect.signature(function).parameters)
-        _direct[name] = _entry.Entry(function, _check, pointers, sizes, scales, dtypes)
-        scope = {"direct": _direct[name]}
+        scope = {"direct": function}
         exec(f"def {name}({arguments}):\n    return direct({arguments})", scope)
+        _points.append((function, (pointers, sizes, scales, dtypes), scope))
         _entries[name] = functools.update_wrapper(scope[name], function)
         _entries[name].__defaults__ = function.__defaults__
         return _entries[name]
     return wrap
+
+
+def _attach() -> None:
+    """The public functions onto ``_entry.so``, once it is there; ctypes alone until then, and aloud if it is there and does not load."""
+    global _entry
+    if _entry is not None or not os.path.exists(_ENTRY):
+        return
+    try:
+        importlib.invalidate_caches()
+        _entry = importlib.import_module("._entry", __package__)
+    except ImportError as e:
+        warnings.warn(f"{_ENTRY} does not load, calls take the longer way through ctypes: {e}", RuntimeWarning, stacklevel=2)
+        return
+    for function, kinds, scope in _points:
+        scope["direct"] = _direct[function.__name__] = _entry.Entry(function, _check, *kinds)
 
 
 @_entry_point(3, 4, 1, 1)
@@ -212,3 +225,6 @@ def attnw_attention(Q, K, V, O, B: int, H: int, N: int, d: int, scale: float, dt
     """O = softmax(scale * Q K^T) V, weights kept on chip; see ``attnw_attention`` in include/attnw.h."""
     _check(load_library().attnw_attention(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), B, H, N, d, float(scale), int(dtype),
                                           _stream(stream)))
+
+
+_attach()

@@ -6,6 +6,7 @@ import os
 import pickle
 import shutil
 import subprocess
+import sys
 import threading
 import weakref
 
@@ -20,10 +21,9 @@ A, B, C, D = 0x10000000, 0x20000000, 0x40000000, 0x60000000
 
 @pytest.fixture(scope="module", autouse=True)
 def _lib():
-    if not os.path.exists(binding.library_path()):
+    if not os.path.exists(binding.library_path()) or not os.path.exists(binding._ENTRY):
         binding.build()
-    if binding._entry is None:
-        pytest.skip("_entry.so was built by this process after the package was imported")
+    assert binding._entry is not None
     binding.load_library()
 
 
@@ -157,3 +157,38 @@ def test_calls_after_a_build_reach_the_library_built(monkeypatch, tmp_path):
     for name, args in bad.items():
         with pytest.raises(binding.AttnwError, match="aligned"):
             getattr(binding, name)(*args)
+
+
+def _child(tmp_path, entry, then):
+    """Runs `then` in a process of its own, on a copy of the package's Python files with the given bytes for _entry.so (None: no such file)."""
+    package = tmp_path / "paper_2407_13885_amd"
+    package.mkdir()
+    for f in os.listdir(binding._PKG):
+        if f.endswith(".py"):
+            shutil.copy(os.path.join(binding._PKG, f), package / f)
+    if entry is not None:
+        (package / "_entry.so").write_bytes(entry)
+    return subprocess.run([sys.executable, "-W", "always", "-c", then], cwd=tmp_path, capture_output=True, text=True,
+                          env={**os.environ, "PYTHONPATH": str(tmp_path)})
+
+
+def test_an_extension_that_does_not_load_is_heard_of(tmp_path):
+    done = _child(tmp_path, b"not a library", "from paper_2407_13885_amd import binding as b; assert b._entry is None; b.attnw_fused")
+    assert done.returncode == 0 and "RuntimeWarning" in done.stderr and "_entry.so does not load" in done.stderr, done.stderr
+
+
+def test_an_extension_built_after_the_import_is_taken(tmp_path):
+    done = _child(tmp_path, None, f"""if True:
+        import shutil, subprocess
+        from paper_2407_13885_amd import binding as b
+        f = b.attnw_softmax
+        assert b._entry is None and not b._direct
+        def run(cmd, **_):
+            if "entry.cpp" in " ".join(cmd): shutil.copy({binding._ENTRY!r}, cmd[-1])
+            return subprocess.CompletedProcess(cmd, 0, "", "")
+        b.subprocess = type("S", (), {{"run": staticmethod(run)}})
+        b.sources = lambda: []
+        b.build()
+        assert b._entry is not None and len(b._direct) == 6 and f is b.attnw_softmax and f.__globals__["direct"] is b._direct["attnw_softmax"]
+        """)
+    assert done.returncode == 0 and "Warning" not in done.stderr, done.stderr
