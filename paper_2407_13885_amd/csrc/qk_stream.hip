@@ -35,8 +35,8 @@ template <int G> struct StreamCfg {
     static constexpr int NS = NW == 16 ? 2 : NP == 3 || NP == 1 ? 3 : 2;                  // pieces that a wave holds in LDS
     static constexpr int SLOT = PW * 1024;
     static constexpr int RING = NS * SLOT;
-    // windows whose exponentials stay in registers (one more spills)
-    static constexpr int held(bool whole) { return NW == 16 ? 0 : (G <= 7 ? 7 : G <= 10 ? 6 : G <= 14 ? 5 : 4) - (whole ? 0 : 1); }
+    // windows whose exponentials stay in registers (one more spills; some 60 scalars spill with any)
+    static constexpr int held(bool whole) { return NW == 16 ? 0 : (G <= 6 ? 7 : G <= 10 ? 6 : G <= 14 ? 5 : 4) - (whole ? 0 : 1); }
     static constexpr int QBUF = NW * RING, STAGE = QBUF + NP * SLOT, STAT = STAGE + 2 * STAGED, LDS = STAT + NW * 32 * 8;
     static_assert(LDS <= 160 * 1024 && STAGE <= kDirectLds, "LDS of a workgroup, reach of direct transfers");
     static constexpr int piece_col(int p) { return p * PW < G - PW ? p * PW : G - PW; }
