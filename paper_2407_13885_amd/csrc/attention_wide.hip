@@ -237,14 +237,18 @@ hipError_t launch_wide(const void* Q, const void* K, const void* V, void* O, int
         return e != hipSuccess ? e : launch_attention_ranges(Q, K, V, O, BH, N, DVB * 32 - (HALF ? 16 : 0), scale, (int)full * 256, stream);
     }
     // d of 80 and more: workgroups of four waves (128 queries), two to a compute unit.  They move K and V twice as often, and where one
-    // waits at a tile's barrier the other computes; the rounds of workgroups end in smaller steps.  Workgroups of eight stay where they need at most
-    // two rounds and those of four fill the last of theirs more than half, and where the second 128 queries are few (N of at most 192: 2018 heads
-    // of N = 133, d = 96 50 us with four, 43 with eight).  us, eight -> four waves: 64 heads of N = 4096, d = 128 622 -> 566, 400 of
-    // 512, d = 80 57.4 -> 51.4, 40 of 600, d = 128 23.9 -> 19.1.  (Of 13900 random shapes of N = 256 .. 6000 this line comes
-    // within 0.4 % of the better of the two, mean; always eight within 11 %.  d = 16 and 48: 2 % at most, many shapes slower.)
-    if constexpr (DVB >= 3)
-        if (N > 192 && (eights > 2 || BH * ((N + 127) / 128) <= (2 * eights - 1) * cus))
-            return launch_wide_t<DVB, HALF, 4, SUBS>(Q, K, V, O, BH, N, scale, stream, N);
+    // waits at a tile's barrier the other computes; the rounds of workgroups end in smaller steps.  Workgroups of eight stay where the second 128 queries
+    // are few (N of at most 192: 2018 heads of N = 133, d = 96 50 us with four, 43 with eight), and where those of four fill the last round of theirs more than
+    // half.  That full they are faster at d of 112 to 160 and up to 1024 tokens only, from the third round on (four / eight waves 0.73 to 0.95); beyond,
+    // d = 80, 96 and from 208 1.03 to 1.1 at any number of rounds, 176 and 192 0.98 to 1.06.  Not full 0.88 to 1.0, but d = 96 from the fourth round on (to 1.06)
+    // and d of 240 and 256 beyond 4096 tokens (1.02).  us, eight -> four waves: 64 heads of N = 4096, d = 128 622 -> 566, 400 of 512, d = 80 57.4 -> 51.4, 40 of
+    // 600, d = 128 23.9 -> 19.1.  (25000 random shapes of N = 200 to 40000.  d = 16 and 48: 2 % at most, many shapes slower.)
+    if constexpr (DVB >= 3) {
+        const bool half = BH * ((N + 127) / 128) <= (2 * eights - 1) * cus;
+        const bool four = N <= 1024 || DVB == 4 || DVB == 5 ? half || eights > 2
+                                                            : half && !(DVB == 3 && !HALF && eights > 3) && !(DVB == 8 && N > 4096 && eights > 2);
+        if (N > 192 && four) return launch_wide_t<DVB, HALF, 4, SUBS>(Q, K, V, O, BH, N, scale, stream, N);
+    }
     return launch_wide_t<DVB, HALF, 8, SUBS>(Q, K, V, O, BH, N, scale, stream, N);
 }
 
