@@ -916,7 +916,7 @@ bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 //     1.26), other rows only from 8.3 to 10.2 (0.73 to 0.99; 6 to 8 and above 12 1.0 to 1.25).  Whole tiles of 256: d = 64 0.84 to 1.4, d = 128 0.74 to
 //     0.87 up to 2048 tokens, then 0.8 to 1.3; other d 0.4 to 0.95 up to 5, then to 1.11.  Up to 1280 tokens the one-workgroup-per-strip kernel is faster (1.0 to 3).
 //   weights, d > 128: x up to 1 0.3 to 0.6, to 2 0.5 to 0.8, beyond 0.55 to 0.95 but where the 128-query workgroups of the general kernel nearly
-//     fill a round (1.0 to 1.35), d above 192 that are not whole pieces of 64 columns, more than 2048 tokens (1.1 to 1.36), and many strips (d <= 192 up to
+//     fill a round (1.0 to 1.42), d above 192 that are not whole pieces of 64 columns, more than 2048 tokens (1.1 to 1.36), and many strips (d <= 192 up to
 //     16 to 25 0.66 to 0.97, then to 1.2; d > 192 up to 12 and 1280 tokens 0.83 to 1.0, then to 1.8)
 //   scores, against a general kernel that splits the keys of few strips over workgroups.  Odd lengths of 1281 and more 0.13 to 0.9 (beyond 2048
 //     tokens with d > 32 and few strips 1.1 to 1.3); d <= 32 0.23 to 0.8, whole blocks of 32 keys up to x of 6 0.59 to 0.95; larger d whole blocks 0.64 to 0.9
@@ -927,16 +927,17 @@ bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 //   K of one head: weights up to 8 MiB 0.73 to 1.0, beyond 1.0 to 1.5 (d of 144 to 192 up to 12 MiB 0.76 to 0.9, beyond 1.2 to 1.4); scores, d up to
 //     128, up to 6 MiB 0.72 to 0.95, beyond 1.0 to 1.3; d above 128 up to 12 MiB 0.63 to 0.9.
 //   Weights, K of the heads that 32 workgroups are in at a time, which goes as x d: rows on 16-byte boundaries, d up to 64, x d up to 1280 0.64 to 1.0, then 1.05 to
-//     2.1 (128 heads of 1536 + 8, d = 64 2.0; d = 32 up to 2048 tokens never above 1.0); d of 80 to 128 up to 2048 tokens 0.75 to 1.0 up to x of 24, up to 3072 0.85 to
+//     2.1 (128 heads of 1544, d = 64 2.0; d = 32 up to 2048 tokens never above 1.0); d of 80 to 128 up to 2048 tokens 0.75 to 1.0 up to x of 24, up to 3072 0.85 to
 //     1.0 up to 18, others 0.7 to 0.95 up to 10, then 1.05 to 1.9.  d of 144 to 192 beyond 1280 tokens 0.5 to 0.95, then 1.0 to 1.3: the lines below lie
-//     earlier where pieces of K overlap (160, 176).  Whole blocks, scores, d above 64, beyond 4096 tokens and x of 9: 1.0 to 1.3.
+//     earlier where pieces of K overlap (112, 160, 176): d = 112 beyond 8192 tokens 1.05 to 1.3 from x of 4, whole tiles 2.  Whole blocks, scores, d above 64, beyond 4096 tokens and x of 9: 1.0 to 1.3.
 bool stream_keeps_k(bool scores_only, int64_t N, int64_t d, double x)
 {
-    if (N * d > ((d > 128 && (scores_only || d <= 192) ? 6 : scores_only ? 3 : 4) << 20)) return false;
+    if (N * d > (d > 128 && (scores_only ? d <= 192 : d != 176 && d <= 192) ? 6 : scores_only && d <= 128 ? 3 : 4) << 20) return false;
     if (scores_only) return d <= 64 || d > 128 || N % 2 != 0 || x <= 9 || N <= 4096;
     if (d > 192 || (d > 128 && N <= 1280)) return true;
     if (d == 144 || d == 192) return x <= (N <= 2048 ? 25 : N <= 8192 ? 15 : 8);
-    if (d > 128) return x <= (N > 2048 ? 6 : d == 160 ? 25 : 8);
+    if (d > 128) return x <= (N <= 2048 ? (d == 160 ? 25 : 8) : d == 176 && N > 16384 ? 2 : 6);
+    if (d > 64 && N > 8192) return x <= (d != 112 ? 5 : N % 256 == 0 ? 2 : 4) || (x > 8.2 && x <= 10);
     if (N % 8 != 0 || N % 256 == 0) return true;  // (bounded below)
     if (d <= 64) return x * (double)d <= 1280 || (d <= 32 && N <= 2048);
     return x <= (N <= 2048 ? 24 : N <= 3072 ? 18.2 : 10);
@@ -952,7 +953,7 @@ bool prefers_stream(bool scores_only, int64_t BH, int64_t N, int64_t d)
     if (d > 128) {
         if (scores_only) return within(0, d <= 192 ? 2 : N <= 896 ? 1 : 1.4) || (odd && (within(0, 2.2) || within(4, 6)));
         const int64_t rounds = (BH * ((N + 127) / 128) + compute_units() - 1) / compute_units();
-        if (d > 192 && N > 2048) return rounds == 1 ? x <= 2.1 : rounds == 2 && d == 256 && within(4, 6);
+        if (d > 192 && N > 2048) return rounds == 1 ? x <= 2 : rounds == 2 && d == 256 && within(4, 6);
         if (d > 192) return rounds == 1 ? x <= 2.8 : rounds == 2 ? x <= 6 : rounds == 3 && N <= 1280 && x <= 10;
         if (N > 2048 && rounds <= 2) return x <= 3 * rounds;
         return x <= (N <= 640 ? 16 : N <= 896 ? 20 : 25);

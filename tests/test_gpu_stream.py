@@ -118,7 +118,8 @@ def test_exponents_of_a_million(N, d, monkeypatch):
 
 # K of a head beyond 8 MiB (scores 6), more strips per compute unit than the heads' K in L2 bears, and the last shape in front of each line
 @pytest.mark.parametrize("BH,N,d,taken", [(1, 32776, 128, False), (128, 1544, 64, False), (104, 1544, 64, True), (34, 4104, 128, False), (19, 4104, 128, True), (30, 3080, 176, False),
-                                          (300, 2056, 32, False)])
+                                          (300, 2056, 32, False),
+                                          (1, 17152, 112, False), (1, 17160, 128, True), (1, 16640, 224, False), (1, 16384, 224, True), (1, 20000, 176, False)])
 def test_where_the_other_kernels_are_faster(BH, N, d, taken, monkeypatch):
     """Weights of these are those of one kernel, bit for bit, and not of the other (2.1 to 1.05 times as fast here)."""
     out = {}
