@@ -214,33 +214,13 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 float p[16];
-                auto weigh = [&](float mb) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[qb][r], c, -mb));
-                    if constexpr (MASK) {
-                        // keys past the end were read as key N-1 (their scores change no maximum): no weight
-                        const int kbase = t * BN + u * 32 + 4 * half;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            if (kbase + 8 * (r / 4) + (r % 4) >= N) p[r] = 0.0f;
-                    }
-                };
                 // The exponent the weights are taken against (mb_run) follows the running maximum lazily: it moves only when some query
                 // of the wave exceeds it by more than kLazy binades (SUMS: when the weights' sums say so).  Until then weights up to
                 // 2^kLazy appear, which costs nothing (fp32 sums, and bf16 has the same relative precision at every magnitude),
                 // and the 16 * DVB multiplies of the output accumulator - needed at every new maximum otherwise, i.e. in most of
                 // the early sub-tiles of a row - become rare.  Lanes whose exponent stands get the factor 2^0 = 1 exactly.
-                auto move = [&](float to) __attribute__((always_inline)) {
-                    const float alpha = fast_exp2(mb_run[qb] - to);
-                    l_run[qb] *= alpha;
-#pragma unroll
-                    for (int b = 0; b < DVB; ++b)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) oacc[qb][b][r] *= alpha;
-                    mb_run[qb] = to;
-                };
                 if constexpr (!SUMS) {
-                    // (the lambdas above, written out: the compiler schedules this form in 92 registers where it takes 100 with them, 36 -> 33.7 us
+                    // (written out: the compiler schedules this form in 92 registers where it takes 100 with the lambdas of the other branch, 36 -> 33.7 us
                     // for 198 heads of N = 613, d = 32)
                     const float mbn = half_wave_max(max16(s[qb])) * c;   // shared by the two lanes of a query
                     if (__builtin_amdgcn_ballot_w64(mbn > mb_run[qb] + kLazy) != 0) {
@@ -257,6 +237,7 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
 #pragma unroll
                     for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[qb][r], c, -mb));
                     if constexpr (MASK) {
+                        // keys past the end were read as key N-1 (their scores change no maximum): no weight
                         const int kbase = t * BN + u * 32 + 4 * half;
 #pragma unroll
                         for (int r = 0; r < 16; ++r)
@@ -267,6 +248,25 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                     for (int r = 1; r < 16; ++r) sum += p[r];
                     l_run[qb] += sum;
                 } else {
+                    auto weigh = [&](float mb) __attribute__((always_inline)) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) p[r] = fast_exp2(__builtin_fmaf(s[qb][r], c, -mb));
+                        if constexpr (MASK) {
+                            const int kbase = t * BN + u * 32 + 4 * half;
+#pragma unroll
+                            for (int r = 0; r < 16; ++r)
+                                if (kbase + 8 * (r / 4) + (r % 4) >= N) p[r] = 0.0f;
+                        }
+                    };
+                    auto move = [&](float to) __attribute__((always_inline)) {
+                        const float alpha = fast_exp2(mb_run[qb] - to);
+                        l_run[qb] *= alpha;
+#pragma unroll
+                        for (int b = 0; b < DVB; ++b)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) oacc[qb][b][r] *= alpha;
+                        mb_run[qb] = to;
+                    };
                     auto maximum = [&]() __attribute__((always_inline)) { return half_wave_max(max16(s[qb])) * c; };
                     auto total = [&]() __attribute__((always_inline)) {
                         float part[4] = {p[0], p[1], p[2], p[3]};
