@@ -923,24 +923,30 @@ bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 //     from 3.1 to 4.6 and 9 to 12, other even lengths 0.65 to 0.98 from 3.2 to 4; else 0.95 to 1.5.  Whole blocks of 513 to 1280 tokens, d > 64, 1.6 to
 //     4.5: 0.43 to 0.95.  d > 128: 0.26 to 0.95 up to 2 (d > 192: 1.4, up to 896 tokens 1), odd lengths up to 2.2 and 4 to 6.
 // All that ends where K no longer comes from an XCD's L2 (4 MiB): the strips read K again for every 32 queries, once or twice, the other kernels for
-// every 128 or 256.  Measured to 148000 tokens and 250 strips per compute unit (15000 random shapes above 8192 tokens or 13 strips per unit):
-//   K of one head: weights up to 8 MiB 0.73 to 1.0, beyond 1.0 to 1.5 (d of 144 to 192 up to 12 MiB 0.76 to 0.9, beyond 1.2 to 1.4); scores, d up to
-//     128, up to 6 MiB 0.72 to 0.95, beyond 1.0 to 1.3; d above 128 up to 12 MiB 0.63 to 0.9.
-//   Weights, K of the heads that 32 workgroups are in at a time, which goes as x d: rows on 16-byte boundaries, d up to 64, x d up to 1280 0.64 to 1.0, then 1.05 to
-//     2.1 (128 heads of 1544, d = 64 2.0; d = 32 up to 2048 tokens never above 1.0); d of 80 to 128 up to 2048 tokens 0.75 to 1.0 up to x of 24, up to 3072 0.85 to
-//     1.0 up to 18, others 0.7 to 0.95 up to 10, then 1.05 to 1.9.  d of 144 to 192 beyond 1280 tokens 0.5 to 0.95, then 1.0 to 1.3: the lines below lie
-//     earlier where pieces of K overlap (112, 160, 176): d = 112 beyond 8192 tokens 1.05 to 1.3 from x of 4, whole tiles 2.  Whole blocks, scores, d above 64, beyond 4096 tokens and x of 9: 1.0 to 1.3.
+// every 128 or 256.  Measured to 148000 tokens and 250 strips per compute unit (32000 random shapes above 8192 tokens or 13 strips per unit), time there /
+// time on the other kernel:
+//   K of one head: weights up to 8 MiB 0.73 to 1.0, beyond 1.0 to 1.5 (d of 144, 160 and 192 up to 12 MiB 0.76 to 0.95, beyond 1.2 to 1.4); scores, d up to
+//     128, up to 6 MiB 0.72 to 0.95, beyond 1.0 to 1.3; d of 144 to 192 up to 12 MiB 0.63 to 0.9.
+//   Weights, K of the heads that an XCD's 32 workgroups are in at a time, which goes as x d.  Rows on 16-byte boundaries, d up to 64: x d up to 1280 0.64 to 1.0,
+//     beyond 1.05 to 2.1 (128 heads of 1544, d = 64 2.0; d of 16 and 32 up to 2048 tokens never above 1.0); d of 80 to 128 up to 2048 tokens 0.75 to 1.0 up to x of 24, to
+//     3072 0.85 to 1.0 up to 19, beyond 0.7 to 0.95 up to 10 (d of 80 and 96 later), then 1.05 to 1.9.  d = 144, 160, 176 and 192, the lines below: on this side
+//     0.5 to 0.97, on the other 1.0 to 1.5, earlier where the pieces of K overlap (112, 160, 176); d = 112 beyond 8192 tokens in whole tiles 1.05 to 1.3 from
+//     x of 2 to 4, then 0.4 to 0.55 to 5.  Whole blocks, scores, d above 64, beyond 4096 tokens and x of 9: 1.0 to 1.3.
 bool stream_keeps_k(bool scores_only, int64_t N, int64_t d, double x)
 {
     if (N * d > (d > 128 && (scores_only ? d <= 192 : d != 176 && d <= 192) ? 6 : scores_only && d <= 128 ? 3 : 4) << 20) return false;
     if (scores_only) return d <= 64 || d > 128 || N % 2 != 0 || x <= 9 || N <= 4096;
     if (d > 192 || (d > 128 && N <= 1280)) return true;
-    if (d == 144 || d == 192) return x <= (N <= 2048 ? 25 : N <= 8192 ? 15 : 8);
-    if (d > 128) return x <= (N <= 2048 ? (d == 160 ? 25 : 8) : d == 176 && N > 16384 ? 2 : 6);
-    if (d > 64 && N > 8192) return x <= (d != 112 ? 5 : N % 256 == 0 ? 2 : 4) || (x > 8.2 && x <= 10);
+    if (d == 144) return x <= (N <= 4096 ? 25 : N <= 16384 ? 15 : 9);
+    if (d == 160) return x <= (N <= 2048 ? 25 : N <= 4096 ? 14 : N <= 16384 ? 10 : 5);
+    if (d == 176) return N > 16384 ? x <= 2 || (x > 4 && x <= 5) : x <= (N <= 2048 ? 14 : N <= 4096 ? 10 : 9);
+    if (d == 192) return x <= (N <= 8192 ? 20 : N <= 16384 ? 15 : 5);
+    if (d == 112 && N > 8192 && N % 256 == 0) return x <= 2 || x > 4;
+    if (d > 64 && N > 8192) return x <= (d == 112 ? 4 : 5) || (x > 8.2 && x <= 10);
     if (N % 8 != 0 || N % 256 == 0) return true;  // (bounded below)
     if (d <= 64) return x * (double)d <= 1280 || (d <= 32 && N <= 2048);
-    return x <= (N <= 2048 ? 24 : N <= 3072 ? 18.2 : 10);
+    if (N <= 3072 || (d <= 96 && N <= 4096)) return x <= (d != 112 && N <= 2048 ? 24 : 19);
+    return x <= (d <= 96 ? 12 : 10);
 }
 
 bool prefers_stream(bool scores_only, int64_t BH, int64_t N, int64_t d)
@@ -953,7 +959,7 @@ bool prefers_stream(bool scores_only, int64_t BH, int64_t N, int64_t d)
     if (d > 128) {
         if (scores_only) return within(0, d <= 192 ? 2 : N <= 896 ? 1 : 1.4) || (odd && (within(0, 2.2) || within(4, 6)));
         const int64_t rounds = (BH * ((N + 127) / 128) + compute_units() - 1) / compute_units();
-        if (d > 192 && N > 2048) return rounds == 1 ? x <= 2 : rounds == 2 && d == 256 && within(4, 6);
+        if (d > 192 && N > 2048) return rounds == 1 ? x <= (d == 256 && N <= 8192 ? 2.1 : 2) : rounds == 2 && d == 256 && within(4, 6);
         if (d > 192) return rounds == 1 ? x <= 2.8 : rounds == 2 ? x <= 6 : rounds == 3 && N <= 1280 && x <= 10;
         if (N > 2048 && rounds <= 2) return x <= 3 * rounds;
         return x <= (N <= 640 ? 16 : N <= 896 ? 20 : 25);
