@@ -67,8 +67,9 @@ bool qk_strip_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_qk_strip(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d, float scale,
                            hipStream_t stream);
 
-// Fused attention weights or scaled scores, bf16, any N up to 2^22, d a multiple of 16 up to 256: persistent workgroups, strips of 32
-// queries whose keys are shared between the waves, scores of up to some 2500 keys in their registers, the rest computed twice.
+// Fused attention weights or scaled scores, bf16, any N from 513 to 2^22, d a multiple of 16 up to 256: persistent workgroups, strips of 32
+// queries whose keys are shared between the waves, the exponentials of up to 1792 keys (768 at d = 256 off the 16-byte boundaries, none up to d = 64) in
+// their registers, the rest computed twice.
 bool qk_stream_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_qk_stream(bool scores_only, const void* Q, const void* K, void* out, int64_t BH, int64_t N, int64_t d, float scale,
                             hipStream_t stream);

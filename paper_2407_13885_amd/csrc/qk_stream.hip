@@ -14,10 +14,10 @@
 // aligned chunks, the elements of the chunks at a window's ends following one by one.  One barrier per step.
 //
 // Measured, us, kernel before -> this one: 8 heads of N = 1659, d = 128 76 -> 37, 6 of 1833, d = 64 61 -> 30, 2 of 7066, d = 32 220 -> 76, one of 8078,
-// d = 128 112 -> 70, of 7381, d = 208 317 -> 122, 24 of 1312, d = 256 90 -> 62; over 24000 random shapes of 513 to 8192 tokens 0.74 of the time (scores
-// 0.86).  What bounds it: the vector ALU, 54 to 63 % busy (2 heads of 7072, d = 32: 149 issue slots per block of 32 x 32, of which 128 are Eq. 1 and
-// its second pass), with 2 or 4 waves per SIMD that a step's barrier keeps together; at d = 128 also K, which every strip reads again (a
-// quarter of the time goes with its transfers left out).
+// d = 128 112 -> 70, of 7381, d = 208 317 -> 122, 24 of 1312, d = 256 90 -> 62; over 3190 random shapes of 513 to 30000 tokens that come here 0.58 of the time
+// (1950 of scores 0.53).  What bounds it: waits, 38 to 46 % of a wave's life, of the 2 or 4 waves per SIMD that a step's barrier keeps together, and the
+// vector ALU, 53 % busy at d = 32, 28 to 47 % at d of 64 to 256 (2 heads of 7072, d = 32: 149 issue slots per block of 32 x 32, of which 128 are Eq. 1
+// and its second pass); at d = 128 also K, which every strip reads again (a quarter of the time goes with its transfers left out).
 #include "launchers.h"
 #include "attention_common.h"
 
