@@ -358,9 +358,14 @@ void qk_stream_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
             const float to = ref + fmaxf(m, 0.0f);
             m = to - ref;
             ref = to;
-            const float a = fast_exp2(-m);
-            l *= a;
-            rescale(a);
+            // (in two factors: v_exp_f32 gives 0 below 2^-126, and the weights before these may be as large as 2^16)
+            const float m1 = fminf(m, 64.0f);
+#pragma unroll 1
+            for (int i = 0; i < 2; ++i) {
+                const float a = fast_exp2(i == 0 ? -m1 : m1 - m);
+                l *= a;
+                rescale(a);
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) arg[r] -= m;
             static_for<16>([&](auto rc) __attribute__((always_inline)) { weigh(e, rc); });

@@ -134,3 +134,20 @@ def test_where_the_other_kernels_are_faster(BH, N, d, taken, monkeypatch):
     torch.cuda.synchronize()
     same = {kernel: torch.equal(out[None].view(torch.int16), out[kernel].view(torch.int16)) for kernel in ("stream", "rounds")}
     assert same == {"stream": taken, "rounds": not taken}
+
+
+# one wave's blocks in three windows held in registers: 1, 2^14.9 and 2^134.9 against the first
+@pytest.mark.parametrize("N,d", [(1100, 128), (1536, 96), (1280, 208)])
+def test_weights_far_below_a_later_key(N, d, monkeypatch):
+    """Weights of 2^-120, whose block was taken against a reference that then moves by 135 binades (a factor of 2^-127 and less is 0)."""
+    x = wl.fused_inputs("t", "bf16", 1, 2, N, d, seed=6810 + N + d, scale=0.125)
+    x.Q[...] = 0
+    x.Q[..., d - 1] = 0x3f80
+    x.K[..., d - 1] = 0
+    for window, units in ((1, 82.5), (2, 748.0)):
+        x.K[0, :, (window * 8 + 3) * 32, d - 1] = wl.store(np.float32(units), "bf16")
+    monkeypatch.setenv("ATTNW_FUSED_KERNEL", "stream")
+    got = gu.to_f64(gu.run_fused(x))[0]
+    for h in range(2):
+        ref = oracle.attention_weights(x.Q[0, h], x.K[0, h], "bf16", x.scale)
+        gu.check_weights(got[h], ref, "bf16", f"N={N} d={d} head {h}")
