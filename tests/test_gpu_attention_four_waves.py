@@ -1,5 +1,5 @@
 """GPU parity of attnw_attention (bf16, d of 80 and more) on both sides of the choice between workgroups of 128 and of 256 queries: one and two rounds
-of either, ragged last strips, partial strips in a launch of their own, lengths of one strip."""
+of either, three and four with the last one less and more than half full, ragged last strips, partial strips in a launch of their own, lengths of one strip."""
 import pytest
 
 from paper_2407_13885_amd import workloads as wl
@@ -16,7 +16,8 @@ def _gpu():
 
 
 @pytest.mark.parametrize("heads,N,d", [(128, 256, 128), (129, 256, 128), (300, 129, 96), (40, 600, 128), (24, 1377, 144), (64, 1024, 144), (65, 1025, 144),
-                                       (130, 1025, 80), (61, 1057, 256), (70, 1100, 256), (130, 900, 240), (90, 700, 176), (600, 130, 208)])
+                                       (130, 1025, 80), (61, 1057, 256), (70, 1100, 256), (130, 900, 240), (90, 700, 176), (600, 130, 208),
+                                       (110, 1100, 96), (150, 1100, 96), (200, 1100, 96), (100, 1300, 224), (120, 1300, 224), (46, 4200, 256)])
 def test_workgroups_of_four_waves(heads, N, d):
     x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=4300 + N + heads)
     V = wl.value_inputs(x, seed=4301 + N)
