@@ -923,7 +923,7 @@ bool prefers_strip(bool scores_only, int64_t BH, int64_t N, int64_t d)
 //     from 3.1 to 4.6 and 9 to 12, other even lengths 0.65 to 0.98 from 3.2 to 4; else 0.95 to 1.5.  Whole blocks of 513 to 1280 tokens, d > 64, 1.6 to
 //     4.5: 0.43 to 0.95.  d > 128: 0.26 to 0.95 up to 2 (d > 192: 1.4, up to 896 tokens 1), odd lengths up to 2.2 and 4 to 6.
 // All that ends where K no longer comes from an XCD's L2 (4 MiB): the strips read K again for every 32 queries, once or twice, the other kernels for
-// every 128 or 256.  Measured to 148000 tokens and 250 strips per compute unit (32000 random shapes above 8192 tokens or 13 strips per unit), time there /
+// every 128 or 256.  Measured to 148000 tokens and 250 strips per compute unit (17000 random shapes above 8192 tokens or 13 strips per unit), time there /
 // time on the other kernel:
 //   K of one head: weights up to 8 MiB 0.73 to 1.0, beyond 1.0 to 1.5 (d of 144, 160 and 192 up to 12 MiB 0.76 to 0.95, beyond 1.2 to 1.4); scores, d up to
 //     128, up to 6 MiB 0.72 to 0.95, beyond 1.0 to 1.3; d of 144 to 192 up to 12 MiB 0.63 to 0.9.
