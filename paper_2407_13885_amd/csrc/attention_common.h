@@ -26,6 +26,26 @@ __device__ __forceinline__ float half_wave_sum(float x)
 #endif
 }
 
+// the same over the four lanes l, l ^ 16, l ^ 32, l ^ 48
+__device__ __forceinline__ float quarter_wave_max(float x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return half_wave_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+#else
+    return x;
+#endif
+}
+__device__ __forceinline__ float quarter_wave_sum(float x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return half_wave_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+#else
+    return x;
+#endif
+}
+
 // The exponent that a query's weights are taken against follows its running maximum only when the 16 weights that a lane makes of
 // a sub-tile sum to more than this: a look at the sum that is needed anyway instead of at the maximum of the scores in front of the
 // exponentials (7 v_max3, an exchange between the half-waves and a branch per 32 keys, all of it in the way).  No weight is larger: fp32
@@ -63,6 +83,9 @@ template <int DVB> struct RowLayout {
         return DVB % 4 == 0 ? key & 15 : DVB % 4 == 2 ? (key >> 1) & 7 : (key >> 2) & 3;
     }
     static __device__ __forceinline__ int v_block(int key) { return DVB % 4 == 0 ? key & 3 : DVB % 4 == 2 ? (key >> 1) & 1 : 0; }
+    // Blocks of 16 columns (16 x 16 matrix instruction): half of a wave reads 32 bytes of eight consecutive rows.
+    static constexpr int V16PERIOD = DVB % 4 == 0 ? 8 : DVB % 4 == 2 ? 4 : 2;
+    static __device__ __forceinline__ int v16_block(int key) { return DVB % 4 == 0 ? key & 7 : DVB % 4 == 2 ? (key >> 1) & 3 : (key >> 2) & 1; }
 };
 
 }  // namespace attnw

@@ -233,9 +233,13 @@ hipError_t launch_wide(const void* Q, const void* K, const void* V, void* O, int
     // others as they are, 2 to 30 % faster over 2000 random shapes, at d = 144 and 160 those too, 14 %.)
     const bool one_round = DVB != 5 && BH * full <= cus && 10 * BH * full > 9 * cus;
     if (full >= 1 && tail_rows >= 1 && tail_rows <= 64 && (BH * full + cus - 1) / cus < eights && (DVB <= 2 || one_round)) {
-        const hipError_t e = launch_wide_t<DVB, HALF, 8, SUBS>(Q, K, V, O, BH, N, scale, stream, (int)full * 256);
+        constexpr int d = DVB * 32 - (HALF ? 16 : 0);
+        const hipError_t e = attention_pipe_supported(N, d) ? launch_attention_pipe(8, Q, K, V, O, BH, N, d, scale, (int)full * 256, stream)
+                                                            : launch_wide_t<DVB, HALF, 8, SUBS>(Q, K, V, O, BH, N, scale, stream, (int)full * 256);
         return e != hipSuccess ? e : launch_attention_ranges(Q, K, V, O, BH, N, DVB * 32 - (HALF ? 16 : 0), scale, (int)full * 256, stream);
     }
+    if (const int waves = attention_pipe_waves(BH, N, DVB * 32 - (HALF ? 16 : 0)))
+        return launch_attention_pipe(waves, Q, K, V, O, BH, N, DVB * 32 - (HALF ? 16 : 0), scale, N, stream);
     // d of 80 and more: workgroups of four waves (128 queries), two to a compute unit.  They move K and V twice as often, and where one
     // waits at a tile's barrier the other computes; the rounds of workgroups end in smaller steps.  Workgroups of eight stay where the second 128 queries
     // are few (N of at most 192: 2018 heads of N = 133, d = 96 50 us with four, 43 with eight), and where those of four fill the last round of theirs more than

@@ -35,6 +35,21 @@ template <> struct Mma<float> {
     static constexpr uint32_t kSignMask = 0x80000000u;
 };
 
+// The same contraction in blocks of 16 x 16: 32 elements of the contraction per instruction, lane l carries chunk l / 16 (8 elements) of
+// row l % 16 of either operand and accumulator r is element (4 (l / 16) + r, l % 16).  Half the accumulator traffic per product of the
+// 32 x 32 shape: under the board's power cap normal operands run at 2.07 instead of 1.76 PFLOP/s (both sustained for 0.1 s, one wave after
+// the other changing one operand only; changing both 1.95 and 1.73).
+__device__ __forceinline__ void mma16(f32x4& acc, const u32x4& a, const u32x4& b)
+{
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+// 16 elements of the contraction, lane l with elements 4 (l / 16) .. + 3.
+__device__ __forceinline__ void mma16(f32x4& acc, const u32x2& a, const u32x2& b)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), acc, 0, 0, 0);
+}
+
 // vmcnt(0) with the other counters left alone (gfx9 encoding of s_waitcnt)
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // lgkmcnt(0): the LDS reads issued so far have returned their data

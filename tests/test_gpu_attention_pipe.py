@@ -1,0 +1,51 @@
+"""GPU parity of attnw_attention (bf16, d = 96 to 160, more than 128 tokens) where the scores, weights and outputs of three neighbouring tiles of 32
+keys are under way at once: five tiles and few more, rests of the ring of four and of the pairs of tiles, ragged last tiles, strips with waves
+without queries, scores that climb from tile to tile."""
+import numpy as np
+import pytest
+
+from paper_2407_13885_amd import workloads as wl
+
+import gpu_util as gu
+from test_gpu_attention import _check_rows, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu(monkeypatch_module):
+    gu.require_gpu()
+    monkeypatch_module.setenv("ATTNW_ATTENTION_KERNEL", "tiled")
+
+
+@pytest.fixture(scope="module")
+def monkeypatch_module():
+    with pytest.MonkeyPatch.context() as m:
+        yield m
+
+
+# 130 heads: workgroups of eight waves; 80 and 60: of four
+@pytest.mark.parametrize("d", [96, 112, 128, 144, 160])
+@pytest.mark.parametrize("heads,N", [(130, 129), (130, 160), (130, 161), (130, 192), (130, 193), (130, 225), (130, 256), (80, 257), (80, 288), (80, 320),
+                                     (60, 353), (16, 2050)])
+def test_tiles(heads, N, d):
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=5100 + N + heads)
+    V = wl.value_inputs(x, seed=5101 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads // 2, heads - 1):
+        _check_rows(O[0, h], x, V, 0, h, [(0, 33), (max(N - 40, 0), N)], f"{heads} heads of {N} x {d}, head {h}")
+
+
+@pytest.mark.parametrize("heads,N,d", [(60, 330, 112), (130, 250, 128), (40, 1100, 96), (60, 384, 160)])
+@pytest.mark.parametrize("step", [0.05, 0.7, 9.0, 200.0])
+def test_scores_climb(heads, N, d, step):
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=5200 + N + d)
+    # the last column of K climbs every 32 keys, that of Q is one: the logits of a tile lie `step` above those of the last
+    h = heads - 1
+    climb = step / float(x.scale) * (np.arange(N) // 32)
+    x.Q[0, h, :, d - 1] = 0x3f80
+    x.K[0, h, :, d - 1] = (climb.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    V = wl.value_inputs(x, seed=5201 + N)
+    O = gu.to_f64(_run(x, V))
+    _check_rows(O[0, h], x, V, 0, h, [(0, 96), (N - 96, N)], f"{heads} heads of {N} x {d}, step {step}")
+    _check_rows(O[0, 0], x, V, 0, 0, [(0, 64)], f"{heads} heads of {N} x {d}, head 0")
