@@ -13,7 +13,7 @@
 // A workgroup is WQ query blocks of 32; a tile is SUBS x 32 keys.  K and V lie in LDS as they lie in memory, chunks
 // swizzled: V is turned by the transposing LDS read (ds_read_b64_tr_b16: 4 keys x 16 columns, a lane gets the four keys of
 // its column), so both tiles travel global -> LDS directly, without registers or a scatter.  Double buffered (4 tiles, 64 KiB at
-// d = 256), one barrier per tile.  (Problems of a few heads: attention_ranges.hip; of at most 32 keys, d > 128: attention_short.hip.)  Measured, 16 heads of N = 4096: d = 256 928 -> 238 us (1157 TFLOP/s), 192 700 -> 185, 144 633 -> 157
+// d = 256), one barrier per tile.  (Problems of a few heads: attention_ranges.hip; of at most 32 keys, d > 128: attention_short.hip.)  (Enough strips of d from 96 on: attention_pipe.hip, attention_turns.hip.)  Measured, 16 heads of N = 4096: d = 256 928 -> 238 us (1157 TFLOP/s), 192 700 -> 185, 144 633 -> 157
 // against one wave per workgroup with operands straight from the caches; d = 96 132 -> 106, d = 128 134 -> 130.5, forty
 // heads of N = 600, d = 128 26.7 -> 23.6 against 128-key tiles, V scattered transposed and rows padded to 128 columns.
 #include "launchers.h"
@@ -234,12 +234,15 @@ hipError_t launch_wide(const void* Q, const void* K, const void* V, void* O, int
     const bool one_round = DVB != 5 && BH * full <= cus && 10 * BH * full > 9 * cus;
     if (full >= 1 && tail_rows >= 1 && tail_rows <= 64 && (BH * full + cus - 1) / cus < eights && (DVB <= 2 || one_round)) {
         constexpr int d = DVB * 32 - (HALF ? 16 : 0);
-        const hipError_t e = attention_pipe_supported(N, d) ? launch_attention_pipe(8, Q, K, V, O, BH, N, d, scale, (int)full * 256, stream)
-                                                            : launch_wide_t<DVB, HALF, 8, SUBS>(Q, K, V, O, BH, N, scale, stream, (int)full * 256);
+        const hipError_t e = DVB >= 6                         ? launch_attention_turns(Q, K, V, O, BH, N, d, scale, (int)full * 256, stream)
+                             : attention_pipe_supported(N, d) ? launch_attention_pipe(8, Q, K, V, O, BH, N, d, scale, (int)full * 256, stream)
+                                                              : launch_wide_t<DVB, HALF, 8, SUBS>(Q, K, V, O, BH, N, scale, stream, (int)full * 256);
         return e != hipSuccess ? e : launch_attention_ranges(Q, K, V, O, BH, N, DVB * 32 - (HALF ? 16 : 0), scale, (int)full * 256, stream);
     }
     if (const int waves = attention_pipe_waves(BH, N, DVB * 32 - (HALF ? 16 : 0)))
         return launch_attention_pipe(waves, Q, K, V, O, BH, N, DVB * 32 - (HALF ? 16 : 0), scale, N, stream);
+    if (prefers_attention_turns(BH, N, DVB * 32 - (HALF ? 16 : 0)))
+        return launch_attention_turns(Q, K, V, O, BH, N, DVB * 32 - (HALF ? 16 : 0), scale, N, stream);
     // d of 80 and more: workgroups of four waves (128 queries), two to a compute unit.  They move K and V twice as often, and where one
     // waits at a tile's barrier the other computes; the rounds of workgroups end in smaller steps.  Workgroups of eight stay where the second 128 queries
     // are few (N of at most 192: 2018 heads of N = 133, d = 96 50 us with four, 43 with eight), and where those of four fill the last round of theirs more than

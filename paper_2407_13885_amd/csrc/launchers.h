@@ -121,6 +121,11 @@ int attention_pipe_waves(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_attention_pipe(int waves, const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d, float scale,
                                  int q_end, hipStream_t stream);
 
+// The same for d a multiple of 16 from 176 to 256, queries 0 .. q_end - 1 of every head: the two waves of a SIMD take turns at the matrix unit.
+bool prefers_attention_turns(int64_t BH, int64_t N, int64_t d);
+hipError_t launch_attention_turns(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d, float scale,
+                                  int q_end, hipStream_t stream);
+
 // The same for a few heads (bf16, d a multiple of 16 up to 256), queries q_base .. N - 1 of every head: the keys of a query
 // block shared between the waves of a workgroup.
 bool prefers_attention_ranges(int64_t BH, int64_t N, int64_t d);

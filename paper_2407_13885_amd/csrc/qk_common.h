@@ -43,12 +43,6 @@ __device__ __forceinline__ void mma16(f32x4& acc, const u32x4& a, const u32x4& b
 {
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
 }
-// 16 elements of the contraction, lane l with elements 4 (l / 16) .. + 3.
-__device__ __forceinline__ void mma16(f32x4& acc, const u32x2& a, const u32x2& b)
-{
-    typedef short s16x4 __attribute__((ext_vector_type(4)));
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), acc, 0, 0, 0);
-}
 
 // vmcnt(0) with the other counters left alone (gfx9 encoding of s_waitcnt)
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
