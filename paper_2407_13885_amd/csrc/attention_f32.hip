@@ -10,7 +10,7 @@
 // while the other contraction of the tile is under way, and the softmax of one wave is covered by the matrix
 // instructions of the other wave on its SIMD (two workgroups per compute unit up to d = 128).  Measured, N = 4096, against
 // one wave per workgroup with operands straight from the caches: 16 heads of d = 256 3.97 -> 2.11 ms (130 TFLOP/s), one head of
-// d = 128 1.03 -> 0.16.  (Many heads with d <= 128: attention_f32_split.hip; at most 32 keys with d > 128: attention_short.hip.)
+// d = 128 1.03 -> 0.16.  (Many heads with d <= 128: attention_f32_split.hip, attention_f32_turns.hip; at most 32 keys with d > 128: attention_short.hip.)
 //
 // A workgroup of (usually) four waves: WQ query blocks of 32 x WK key ranges.  A tile is 32 keys per key range; K and V have one
 // buffer each, and every tile has two phases:
@@ -318,12 +318,12 @@ hipError_t launch_f32_ranges(const void* Q, const void* K, const void* V, void* 
     constexpr int most = DVB <= 4 ? 4 : 2;
     const int wk = key_ranges_f32(BH, N, most);
     // No keys to share, and 256-query strips whose waves are more than half busy: the bf16 instruction on operands in three
-    // parts (16 heads of N = 4096, d = 128: 998 -> 609 us, eight, exactly half: 519 either way; 300 heads of N = 197, d = 64
+    // parts (16 heads of N = 4096, d = 128: 998 -> 527 us, eight, exactly half: 519 either way; 300 heads of N = 197, d = 64
     // 52 -> 42; forty of 700, d = 32, 43 % busy: 31 -> 32).
     if constexpr (DVB <= 4) {
         const int64_t cus = compute_units(), rounds = (BH * ((N + 255) / 256) + cus - 1) / cus;
         if (wk == 1 && BH * ((N + 31) / 32) * 2 > rounds * cus * 8 && split_takes_scale(scale))
-            return launch_attention_f32_split(Q, K, V, O, BH, N, d, scale, stream);
+            return DVB == 1 ? launch_attention_f32_split(Q, K, V, O, BH, N, d, scale, stream) : launch_attention_f32_turns(Q, K, V, O, BH, N, d, scale, stream);
     }
     if constexpr (most == 4)
         if (wk == 4) {

@@ -1,19 +1,16 @@
-// Attention output  O = softmax(scale * Q K^T) V  in fp32 for many heads (d a multiple of 4 up to 128, any N): both
+// Attention output  O = softmax(scale * Q K^T) V  in fp32 for many heads (d a multiple of 4 up to 32, any N): both
 // contractions on the bf16 matrix instruction, every operand as three bf16 parts (split_f32.h).
 //
 // (Paper: Multi-Head Self-Attention section, Attention(Q, K, V) = softmax(Q K^T / sqrt(d_k)) V; the product
 // with V is what the section "Limitations and future Directions" names as the next thing to fuse.  The
 // max-subtracted softmax of the Softmax section, Eq. 1, is applied incrementally as in the other kernels.)
 //
-// What bounds it: the matrix instruction (12 x 32 cycles per 32 queries, 32 keys and 16 columns of d, where the fp32
-// instruction takes 16 x 64), under the board's power cap: busy 63 % of SIMD cycles at d = 128, vector ALU 34 %, both 8 % (14 registers
-// spilled there: 4 of them are read back twice per tile, the others belong to the restart).  Eight waves of 32 queries share a tile of 32 keys: splitting a
+// What bounds it: the vector ALU (weights and their parts) beside the matrix instruction (12 x 32 cycles per 32 queries, 32 keys and 16 columns of d, where the
+// fp32 instruction takes 16 x 64).  Eight waves of 32 queries share a tile of 32 keys: splitting a
 // K or V element costs six vector instructions, spread over 256 queries.  A thread loads 8 elements of a row, splits them
 // and writes a 16-byte chunk to each of the three planes of the tile; planes lie as rows in memory do, chunks
-// swizzled, and V is turned by the transposing LDS read.  Double buffered, one barrier per tile.
-// Measured, 16 heads of N = 4096, against the fp32 instruction: d = 32 / 64 / 96 / 128 290 / 523 / 761 / 998 -> 192 / 328 / 473 /
-// 632 us (1.30 PFLOP/s of bf16 products; the weights' factor of 2^24 costs 1 to 2 % of it); error of the output against 64 bits
-// 1.24e-6 -> 1.05e-6 (d = 128).
+// swizzled, and V is turned by the transposing LDS read.  Double buffered, one barrier per tile.  (From d = 36 on: attention_f32_turns.hip.)
+// Measured, 16 heads of N = 4096, d = 32, against the fp32 instruction: 290 -> 186 us.
 #include "attention_common.h"
 #include "launchers.h"
 #include "split_f32.h"
@@ -71,9 +68,8 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
     // From 2^80 on, either way, a score in parts is infinite also where fp32 holds it, and one of -infinity leaves no trace in the sums.
     // No score of 128 products gets there while |Q| and |K| stay within 2^20 and 2^52, either of them the larger one; waves whose
     // operands do not start again on the fp32 instruction.  (Six instructions per 32 keys, before
-    // the split, and nothing kept but scalar masks: without / with, us: 16 heads of N = 4096, d = 128 652 / 656, 64 330 / 333, 32 192.5 both, 300 of
-    // 197, d = 64 39.5 / 40.6.  The smallest score beside the sums, a vector register and eight instructions: 672 / 333 / 199 / 39.8; a limit for
-    // |K| from the largest |Q| of the workgroup, one more barrier: 653 / 336 / 192 / 41.9.)
+    // the split, and nothing kept but scalar masks: 16 heads of N = 4096, d = 32 192.5 us with and without.  The smallest score beside the sums, a vector
+    // register and eight instructions: 199.)
     constexpr float kLarge = 0x1p20f, kHuge = 0x1p52f;
     const uint64_t q_large = __builtin_amdgcn_ballot_w64(q_max > kLarge), q_huge = __builtin_amdgcn_ballot_w64(q_max > kHuge);
     uint64_t large = 0, huge = 0;                 // of K
@@ -289,13 +285,7 @@ hipError_t launch_split_t(const void* Q, const void* K, const void* V, void* O, 
 hipError_t launch_attention_f32_split(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                       float scale, hipStream_t stream)
 {
-    switch ((int)((d + 31) / 32)) {
-    case 1: return launch_split_t<1>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
-    case 2: return launch_split_t<2>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
-    case 3: return launch_split_t<3>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
-    case 4: return launch_split_t<4>(Q, K, V, O, BH, (int)N, (int)d, scale, stream);
-    default: return hipErrorInvalidValue;
-    }
+    return d <= 32 ? launch_split_t<1>(Q, K, V, O, BH, (int)N, (int)d, scale, stream) : hipErrorInvalidValue;
 }
 
 }  // namespace attnw

@@ -105,7 +105,9 @@ bool attention_f32_supported(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_attention_f32(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                 float scale, hipStream_t stream);
 
-// The same for many heads (d a multiple of 4 up to 128): both contractions on the bf16 instruction, operands in three parts.
+// The same for many heads (d a multiple of 4, 36 to 128 and up to 32): both contractions on the bf16 instruction, operands in three parts.
+hipError_t launch_attention_f32_turns(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
+                                      float scale, hipStream_t stream);
 hipError_t launch_attention_f32_split(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                       float scale, hipStream_t stream);
 

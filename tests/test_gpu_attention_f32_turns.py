@@ -1,0 +1,68 @@
+"""GPU parity of attnw_attention (fp32, d = 36 to 128, many heads) on operands in three bf16 parts where the two waves of a SIMD take turns at the matrix
+unit: few tiles of 32 keys, ragged last tiles, waves without queries, scores that climb from tile to tile, waves that start again in fp32."""
+import numpy as np
+import pytest
+
+from paper_2407_13885_amd import workloads as wl
+
+import gpu_util as gu
+from test_gpu_attention_general import _check, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    gu.require_gpu()
+
+
+@pytest.mark.parametrize("d", [36, 64, 68, 96, 128])
+@pytest.mark.parametrize("N", [129, 160, 161, 191, 193, 224, 256, 257])
+def test_tiles(N, d):
+    heads = 256
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5500 + N + d)
+    V = wl.value_inputs(x, seed=5501 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads // 2 + 1, heads - 1):
+        _check(O[0, h], x, V, 0, h, (0, N), f"{heads} heads of {N} x {d}, head {h}")
+
+
+@pytest.mark.parametrize("N,d", [(161, 64), (250, 100), (200, 128)])
+@pytest.mark.parametrize("step", [0.7, 9.0, 200.0])
+def test_scores_climb(N, d, step):
+    heads = 256
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5600 + N + d)
+    # the last column of K climbs every 32 keys, that of Q is one: the logits of a tile lie `step` above those of the last
+    h = heads - 1
+    x.Q[0, h, :, d - 1] = 1.0
+    x.K[0, h, :, d - 1] = step / float(x.scale) * (np.arange(N) // 32)
+    V = wl.value_inputs(x, seed=5601 + N)
+    O = gu.to_f64(_run(x, V))
+    for g in (0, h):
+        _check(O[0, g], x, V, 0, g, (0, N), f"{heads} heads of {N} x {d}, step {step}, head {g}")
+
+
+@pytest.mark.parametrize("N,d", [(161, 64), (257, 128)])
+def test_not_finite(N, d):
+    """Infinities, NaN and values that bf16 rounds to infinity give what fp32 arithmetic gives."""
+    heads = 256
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5700 + N)
+    V = wl.value_inputs(x, seed=5701)
+    x.Q[0, 0, :, 0] = np.where(np.arange(N) % 2 == 0, 1.0, -1.0)
+    x.K[0, 0, 5, 0] = -np.inf                     # weight 0 for even queries, NaN rows for odd ones
+    V[0, 1, 3, 2] = np.inf                        # a column of infinities
+    x.Q[0, 2, 7, 1] = np.nan                      # one NaN row
+    # From 2^104 on an operand in parts is NaN.  (A weight is at most 2^8 before it is divided by the row's sum, the exponent following the maximum
+    # that far behind: 2^8 x 1e36 is below the largest fp32 number, 3.4e38 in a row this late is not.)
+    V[0, 3, N - 1, d - 1] = 1e36
+    O = gu.to_f64(_run(x, V))
+    for h in range(5):
+        with np.errstate(all="ignore"):
+            S = float(x.scale) * (x.Q[0, h].astype(np.float64) @ x.K[0, h].astype(np.float64).T)
+            E = np.exp(S - S.max(axis=1, keepdims=True))
+            ref = (E / E.sum(axis=1, keepdims=True)) @ V[0, h].astype(np.float64)
+        assert (np.isnan(O[0, h]) == np.isnan(ref)).all() and (np.isinf(O[0, h]) == np.isinf(ref)).all(), f"head {h}"
+        ok = np.isfinite(ref)
+        size = np.abs(V[0, h][np.isfinite(V[0, h])]).max()
+        # (weights and sums good to a few 2^-24 of sum_j P_ij |V_jt| <= the largest value; scores below 10)
+        assert np.abs(O[0, h][ok] - ref[ok]).max() <= 2.0 ** -16 * size, f"head {h}"
