@@ -984,6 +984,7 @@ bool prefers_stream(bool scores_only, int64_t BH, int64_t N, int64_t d)
 hipError_t launch_qk(DType dt, bool scores_only, const void* Q, const void* K, void* out,
                      int64_t BH, int64_t N, int64_t d, float scale, hipStream_t stream)
 {
+    if (dt == DType::F32 && !scores_only && prefers_f32_small(BH, N, d)) return launch_qk_f32_small(Q, K, out, BH, N, d, scale, stream);
     if (dt == DType::F32 && !scores_only && prefers_f32_split(BH, N, d) && split_takes_scale(scale))
         return launch_qk_f32_split(Q, K, out, BH, N, d, scale, stream);
     if (dt == DType::F32 && prefers_f32_strip(scores_only, BH, N, d) && split_takes_scale(scale))
