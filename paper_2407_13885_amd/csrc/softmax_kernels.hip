@@ -291,6 +291,82 @@ void softmax_rows_shifted_kernel(const T* S, T* P, int64_t rows, int cols)   // 
     }
 }
 
+// The same for rows of a few elements more than R * TPR chunks, where the kernel above needs another chunk per lane, most of them empty: whole chunks that are the row's own, and its ends -- the elements in front of the first of them and behind the
+// last, or behind the R * TPR that registers hold -- one to a lane, loaded and stored together.  cols <= (R * V + 1) * TPR.  Bound: HBM (130731 x 1025 bf16 5.4 ->
+// 5.7 TB/s, 65397 x 2049 5.2 -> 5.7).
+template <typename T, int R, int TPR>
+__global__ __launch_bounds__(TPR <= 64 ? 256 : TPR)
+void softmax_rows_ends_kernel(const T* S, T* P, int64_t rows, int cols)   // S == P (in place) is allowed
+{
+    static_assert(TPR >= 64, "the ends of a row are up to 2 V - 2 elements");
+    constexpr int V = Elem<T>::VEC;
+    constexpr int WAVES = TPR / 64;
+    constexpr int RPB = TPR == 64 ? 4 : 1;
+    const int tid = TPR == 64 ? (int)(threadIdx.x % 64) : (int)threadIdx.x;
+    const int64_t row = TPR == 64 ? (int64_t)blockIdx.x * RPB + (threadIdx.x >> 6) : (int64_t)blockIdx.x;
+    if (row >= rows) return;                      // (whole waves, none of them at a barrier)
+
+    const int64_t e0 = row * cols;
+    const int head = (int)(-e0 & (V - 1));        // elements in front of the first whole chunk (S and P are 16-byte aligned)
+    const int n_chunks = min((cols - head) / V, R * TPR);
+    const T* const src = S + e0 + head;
+    T* const dst = P + e0 + head;
+    const int end = tid < head ? tid : tid + n_chunks * V;            // the lane's element of the ends
+
+    float x[R][V], y = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int c = tid + k * TPR;
+        if (c < n_chunks) Elem<T>::unpack(__builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src) + c), x[k]);
+        else {
+#pragma unroll
+            for (int i = 0; i < V; ++i) x[k][i] = -INFINITY;
+        }
+    }
+    if (end < cols) y = Elem<T>::load1(S + e0 + end);
+    float m = y;
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+#pragma unroll
+        for (int i = 0; i < V; ++i) m = fmaxf(m, x[k][i]);
+
+    __shared__ float red[2][WAVES];
+    m = lanes_reduce_max<64>(m);
+    if constexpr (WAVES > 1) {
+        if ((threadIdx.x & 63) == 0) red[0][threadIdx.x >> 6] = m;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) m = fmaxf(m, red[0][w]);
+    }
+    y = fast_exp2((y - m) * kLog2e);              // no element: 2^-inf = 0
+    float l = y;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            x[k][i] = fast_exp2((x[k][i] - m) * kLog2e);
+            l += x[k][i];
+        }
+    }
+    l = lanes_reduce_sum<64>(l);
+    if constexpr (WAVES > 1) {
+        if ((threadIdx.x & 63) == 0) red[1][threadIdx.x >> 6] = l;
+        __syncthreads();
+        l = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) l += red[1][w];
+    }
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int c = tid + k * TPR;
+#pragma unroll
+        for (int i = 0; i < V; ++i) x[k][i] *= inv;
+        if (c < n_chunks) __builtin_nontemporal_store(Elem<T>::pack(x[k]), reinterpret_cast<u32x4*>(dst) + c);
+    }
+    if (end < cols) Elem<T>::store1(P + e0 + end, y * inv);
+}
+
 // EG consecutive elements of type T (EG * sizeof(T) bytes, naturally aligned) <-> floats
 template <typename T, int EG> __device__ __forceinline__ void load_group(const T* p, float* x)
 {
@@ -708,6 +784,18 @@ hipError_t launch_rows_shifted(const void* S, void* P, int64_t rows, int64_t col
     });
 }
 
+template <typename T, int R, int TPR>
+hipError_t launch_rows_ends(const void* S, void* P, int64_t rows, int64_t cols, hipStream_t stream)
+{
+    constexpr int RPB = TPR == 64 ? 4 : 1;
+    return launch_by_heads((rows + RPB - 1) / RPB, 1, TPR == 64 ? 256 : TPR, [&](int64_t first, int64_t blocks) {
+        const int64_t row = first * RPB;
+        hipLaunchKernelGGL((softmax_rows_ends_kernel<T, R, TPR>), dim3((uint32_t)blocks), dim3(TPR == 64 ? 256 : TPR), 0, stream,
+                           static_cast<const T*>(S) + row * cols, static_cast<T*>(P) + row * cols, rows_of(rows - row, blocks, RPB), (int)cols);
+        return hipGetLastError();
+    });
+}
+
 template <typename TI, typename TO>
 hipError_t launch_softmax_t(const void* S, void* P, int64_t rows, int64_t cols, hipStream_t stream)
 {
@@ -775,19 +863,36 @@ hipError_t launch_softmax_t(const void* S, void* P, int64_t rows, int64_t cols, 
             if (chunks <= 48) return launch_rows_shifted<TI, 3, 16>(S, P, rows, cols, stream);
             if (chunks <= 64) return launch_rows_shifted<TI, 2, 32>(S, P, rows, cols, stream);
             if (chunks <= 96) return launch_rows_shifted<TI, 3, 32>(S, P, rows, cols, stream);
+            // A few elements more than the chunks of a shape hold (2^k + 1): that shape with the ends of a row one to a lane, against the next shape, 134 M bf16
+            // elements, us: rows of 1025 99.1 -> 94.4, 2049 103.4 -> 93.3, 4097 96.3 -> 92.0, 8193 104.6 -> 93.6, 16385 99 -> 91, 24569 0.68 of the time; fp32 0.85
+            // to 1.0.  Not where the shape after it is as narrow: 1009 98.9 -> 106.6, 1601 96.6 -> 103.1, 4089 90.0 -> 93.6 (six or more below the whole chunks); 2570
+            // 94.3 -> 101.1 (five chunks).
+            const auto holds = [&](int r, int tpr) { return cols + 5 >= (int64_t)r * E * tpr && cols <= (int64_t)(r * E + 1) * tpr; };
             if (chunks <= 128) return launch_rows_shifted<TI, 2, 64>(S, P, rows, cols, stream);
+            if (holds(2, 64)) return launch_rows_ends<TI, 2, 64>(S, P, rows, cols, stream);
             if (chunks <= 192) return launch_rows_shifted<TI, 3, 64>(S, P, rows, cols, stream);
+            if (holds(3, 64)) return launch_rows_ends<TI, 3, 64>(S, P, rows, cols, stream);
             if (chunks <= 256) return launch_rows_shifted<TI, 2, 128>(S, P, rows, cols, stream);
+            if (holds(2, 128)) return launch_rows_ends<TI, 2, 128>(S, P, rows, cols, stream);
             if (chunks <= 320) return launch_rows_shifted<TI, 5, 64>(S, P, rows, cols, stream);
             if (chunks <= 384) return launch_rows_shifted<TI, 3, 128>(S, P, rows, cols, stream);
+            if (holds(3, 128)) return launch_rows_ends<TI, 3, 128>(S, P, rows, cols, stream);
             if (chunks <= 512) return launch_rows_shifted<TI, 2, 256>(S, P, rows, cols, stream);
+            if (holds(2, 256)) return launch_rows_ends<TI, 2, 256>(S, P, rows, cols, stream);
             if (chunks <= 768) return launch_rows_shifted<TI, 3, 256>(S, P, rows, cols, stream);
+            if (holds(3, 256)) return launch_rows_ends<TI, 3, 256>(S, P, rows, cols, stream);
             if (chunks <= 1024) return launch_rows_shifted<TI, 4, 256>(S, P, rows, cols, stream);
+            if (holds(4, 256)) return launch_rows_ends<TI, 4, 256>(S, P, rows, cols, stream);
             if (chunks <= 1536) return launch_rows_shifted<TI, 6, 256>(S, P, rows, cols, stream);
+            if (holds(6, 256)) return launch_rows_ends<TI, 6, 256>(S, P, rows, cols, stream);
             if (chunks <= 2048) return launch_rows_shifted<TI, 2, 1024>(S, P, rows, cols, stream);
+            if (holds(2, 1024)) return launch_rows_ends<TI, 2, 1024>(S, P, rows, cols, stream);
             if (chunks <= 3072) return launch_rows_shifted<TI, 3, 1024>(S, P, rows, cols, stream);
+            if (holds(3, 1024)) return launch_rows_ends<TI, 3, 1024>(S, P, rows, cols, stream);
             if (chunks <= 4096) return launch_rows_shifted<TI, 4, 1024>(S, P, rows, cols, stream);
+            if (holds(4, 1024)) return launch_rows_ends<TI, 4, 1024>(S, P, rows, cols, stream);
             if (chunks <= 6144) return launch_rows_shifted<TI, 6, 1024>(S, P, rows, cols, stream);
+            if (holds(6, 1024)) return launch_rows_ends<TI, 6, 1024>(S, P, rows, cols, stream);
             return launch_rows_shifted<TI, 8, 1024>(S, P, rows, cols, stream);
         }
     }
