@@ -27,6 +27,18 @@ def test_tiles(N, d):
         _check(O[0, h], x, V, 0, h, (0, N), f"{heads} heads of {N} x {d}, head {h}")
 
 
+# on both sides of the lines that the share of busy waves draws: d up to 32 half, up to 64 0.385, beyond a quarter
+@pytest.mark.parametrize("heads,N,d", [(27, 1187, 20), (26, 1187, 20), (130, 235, 32), (21, 1187, 40), (20, 1187, 64), (64, 257, 100), (56, 257, 100), (14, 1187, 128),
+                                       (13, 1187, 68), (9, 2084, 96)])
+def test_few_strips(heads, N, d):
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5800 + N + d)
+    V = wl.value_inputs(x, seed=5801 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads - 1):
+        for rows in ((0, 40), (max(0, N - 40), N)):
+            _check(O[0, h], x, V, 0, h, rows, f"{heads} heads of {N} x {d}, head {h}")
+
+
 @pytest.mark.parametrize("N,d", [(161, 64), (250, 100), (200, 128)])
 @pytest.mark.parametrize("step", [0.7, 9.0, 200.0])
 def test_scores_climb(N, d, step):
