@@ -1,4 +1,4 @@
-// Attention output  O = softmax(scale * Q K^T) V  in bf16 for d = 96 to 160 and more than 128 tokens: the sweep of attention_wide.hip with
+// Attention output  O = softmax(scale * Q K^T) V  in bf16 for d = 96 to 160 and more than 128 tokens, and for d = 64: the sweep of attention_wide.hip with
 // the steps of neighbouring tiles under way at once.
 //
 // (Paper: Multi-Head Self-Attention section, Attention(Q, K, V) = softmax(Q K^T / sqrt(d_k)) V; Softmax section, Eq. 1, applied
@@ -11,7 +11,8 @@
 // vector unit worked at the same time in 13 % of the cycles; here in 22 %.
 //
 // Matrix instructions of 16 x 16 x 32 (mma16): less power per product than 32 x 32 x 16, and these kernels run at the board's power cap.  (They take more issue
-// slots, 8 cycles of the vector unit's each: with twice the vector work per product, at d = 64, the 32 x 32 shape is as fast.)
+// slots, 8 cycles of the vector unit's each: with twice the vector work per product, at d = 64, the 32 x 32 shape is as fast, and this kernel the faster one only where its
+// smaller steps count, attention_pipe_64.)
 //
 // K and V travel global -> LDS directly into rings of four tiles, one barrier for two tiles (one for each: 3 % slower); fragments of K are read a tile ahead.
 // 16 heads of N = 4096: d = 96 107 -> 99 us, 128 131.5 -> 118.7 (1.16 PFLOP/s), 144 159 -> 142, 160 166 -> 144; 8 of 4000, d = 128 91 -> 68.5;
@@ -404,10 +405,29 @@ int attention_pipe_waves(int64_t BH, int64_t N, int64_t d)
     return (double)rounds <= cost4 ? 8 : 4;
 }
 
+// d = 64: workgroups of four waves against attention_kernel's 256 or 512 queries.  The work of a tile takes as long here, but the rounds end in smaller steps, and a
+// ragged end costs a tile of 32 keys instead of one of 128.  So (time here / there): more than one round of 256-query strips 0.58 to 1.0, where the second round of those of four is
+// more than half full and beyond 1024 tokens, and beyond 4096 tokens from the third on with the last more than 0.55 full, 1.0 to 1.1 (left); one round of ragged rows 0.76 to 0.99, of whole
+// ones up to 1.07 (left).  Whole rows of more rounds up to 1.06 beyond 1024 tokens (left).  A last strip of up to 64 queries that follows as a launch of its own there: 1.07 to 1.16 beyond 1024 tokens (left).  us: 275 heads
+// of N = 576 65.9 -> 38.4, 134 of 512 0.83 of the time, 331 of 672 76.7 -> 53.0.  (900 random shapes of 161 to 12000 tokens: taken 0.86 on
+// average; few heads stay with attention_ranges.hip, whose waves have references of their own: sharp rows 1.8e-3 off, here 2.0e-3.)
+bool attention_pipe_64(int64_t BH, int64_t N)
+{
+    const int64_t cus = compute_units(), fours = BH * ((N + 127) / 128), eights = BH * ((N + 255) / 256), last = (fours + 2 * cus - 1) % (2 * cus) + 1;
+    const int64_t full = N / 256, tail = N % 256;
+    if (N <= 320) return false;
+    if (eights <= cus) return tail != 0 && 1000 * fours > 405 * 2 * cus && (fours <= cus || (N <= 1056 && 10 * fours > 11 * cus));
+    if (fours <= 2 * cus) return true;
+    if (N > 1024 && tail >= 1 && tail <= 64 && (BH * full + cus - 1) / cus < (eights + cus - 1) / cus) return false;
+    if (fours <= 4 * cus) return tail == 0 ? last <= cus && N < 8192 : N <= 1024 || last <= cus;
+    return N <= 1024 || (tail != 0 && (N <= 4096 || 100 * last <= 55 * 2 * cus));
+}
+
 hipError_t launch_attention_pipe(int waves, const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d, float scale,
                                  int q_end, hipStream_t stream)
 {
     switch ((int)(d / 16)) {
+    case 4: return launch_pipe_t<2, false, 4>(Q, K, V, O, BH, (int)N, scale, q_end, stream);   // (attention_pipe_64)
     case 6: return launch_pipe_d<3, false>(waves, Q, K, V, O, BH, (int)N, scale, q_end, stream);
     case 7: return launch_pipe_d<4, true>(waves, Q, K, V, O, BH, (int)N, scale, q_end, stream);
     case 8: return launch_pipe_d<4, false>(waves, Q, K, V, O, BH, (int)N, scale, q_end, stream);

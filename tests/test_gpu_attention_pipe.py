@@ -49,3 +49,26 @@ def test_scores_climb(heads, N, d, step):
     O = gu.to_f64(_run(x, V))
     _check_rows(O[0, h], x, V, 0, h, [(0, 96), (N - 96, N)], f"{heads} heads of {N} x {d}, step {step}")
     _check_rows(O[0, 0], x, V, 0, 0, [(0, 64)], f"{heads} heads of {N} x {d}, head 0")
+
+
+# one round and more of 256-query strips, on both sides of the lines: ragged ends, whole rows, waves without queries
+@pytest.mark.parametrize("heads,N", [(200, 321), (110, 352), (180, 385), (139, 517), (134, 512), (76, 1024), (46, 1331), (34, 1800), (30, 2177), (20, 3328), (15, 4416), (60, 1056), (60, 1057)])
+def test_d64(heads, N):
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, 64, seed=5150 + N + heads)
+    V = wl.value_inputs(x, seed=5151 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads // 2, heads - 1):
+        _check_rows(O[0, h], x, V, 0, h, [(0, 33), (max(N - 40, 0), N)], f"{heads} heads of {N} x 64, head {h}")
+
+
+@pytest.mark.parametrize("step", [0.05, 0.7, 9.0, 200.0])
+def test_scores_climb_d64(step):
+    heads, N = 139, 517
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, 64, seed=5250)
+    h = heads - 1
+    climb = step / float(x.scale) * (np.arange(N) // 32)
+    x.Q[0, h, :, 63] = 0x3f80
+    x.K[0, h, :, 63] = (climb.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    V = wl.value_inputs(x, seed=5251)
+    O = gu.to_f64(_run(x, V))
+    _check_rows(O[0, h], x, V, 0, h, [(0, 96), (N - 96, N)], f"{heads} heads of {N} x 64, step {step}")
