@@ -7,7 +7,7 @@
 // A tile of 32 keys is two phases of a wave with a barrier after each: the output of the tile before and the scores of this one (192 matrix
 // instructions of 16 cycles at d = 128), then the weights and their parts, and the wave's share of a coming tile of K and V, split into LDS
 // (some 400 vector instructions).  Waves 4 to 7, the other wave of each SIMD, are one phase behind waves 0 to 3.  With one after the other in all
-// waves at once the matrix unit was busy 63 % and both units 8 % of the cycles.
+// waves at once the matrix unit was busy 63 % and both units 8 % of the SIMD cycles; here 82 and 28 %.
 //
 // What bounds it: the board's power (order of the phases, depth of the fragment ring and priority change the time by less than 1 %; the same code with all
 // waves in step is 10 % slower).  Hence mma16, and the operand from LDS stays for two to six instructions.  16 heads of N = 4096, all waves in step on 32 x 32
