@@ -405,12 +405,13 @@ int attention_pipe_waves(int64_t BH, int64_t N, int64_t d)
     return (double)rounds <= cost4 ? 8 : 4;
 }
 
-// d = 64: workgroups of four waves against attention_kernel's 256 or 512 queries.  The work of a tile takes as long here, but the rounds end in smaller steps, and a
-// ragged end costs a tile of 32 keys instead of one of 128.  So (time here / there): more than one round of 256-query strips 0.58 to 1.0, where the second round of those of four is
-// more than half full and beyond 1024 tokens, and beyond 4096 tokens from the third on with the last more than 0.55 full, 1.0 to 1.1 (left); one round of ragged rows 0.76 to 0.99, of whole
-// ones up to 1.07 (left).  Whole rows of more rounds up to 1.06 beyond 1024 tokens (left).  A last strip of up to 64 queries that follows as a launch of its own there: 1.07 to 1.16 beyond 1024 tokens (left).  us: 275 heads
-// of N = 576 65.9 -> 38.4, 134 of 512 0.83 of the time, 331 of 672 76.7 -> 53.0.  (900 random shapes of 161 to 12000 tokens: taken 0.86 on
-// average; few heads stay with attention_ranges.hip, whose waves have references of their own: sharp rows 1.8e-3 off, here 2.0e-3.)
+// d = 64: workgroups of four waves against attention_kernel's 256 or 512 queries.  The work of a tile takes as long here, but the rounds end in smaller steps,
+// and a ragged end costs a tile of 32 keys instead of one of 128.  So (time here / there): more than one round of 256-query strips 0.58 to 1.0; where the
+// second round of those of four is more than half full and beyond 1024 tokens, and beyond 4096 tokens from the third on with the last more than 0.55 full, 1.0
+// to 1.1 (left); one round of ragged rows 0.76 to 0.99, of whole ones up to 1.07 (left).  Whole rows of more rounds up to 1.06 beyond 1024 tokens (left).  A last
+// strip of up to 64 queries that follows as a launch of its own there: 1.07 to 1.16 beyond 1024 tokens (left).  us: 275 heads of N = 576 65.9 -> 38.4, 331 of 672
+// 76.7 -> 53.0, 134 of 512 0.83 of the time.  (900 random shapes of 161 to 12000 tokens: taken 0.86 on average; few heads stay with attention_ranges.hip, whose
+// waves have references of their own: sharp rows 1.8e-3 off, here 2.0e-3.)
 bool attention_pipe_64(int64_t BH, int64_t N)
 {
     const int64_t cus = compute_units(), fours = BH * ((N + 127) / 128), eights = BH * ((N + 255) / 256), last = (fours + 2 * cus - 1) % (2 * cus) + 1;
