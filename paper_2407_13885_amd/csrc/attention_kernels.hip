@@ -439,7 +439,7 @@ hipError_t launch_attention(const void* Q, const void* K, const void* V, void* O
                             float scale, hipStream_t stream)
 {
     if (prefers_attention_ranges(BH, N, d)) return launch_attention_ranges(Q, K, V, O, BH, N, d, scale, 0, stream);
-    if (d == 64 && attention_pipe_64(BH, N)) return launch_attention_pipe(4, Q, K, V, O, BH, N, d, scale, (int)N, stream);
+    if (d == 64 ? attention_pipe_64(BH, N) : attention_pipe_32(BH, N)) return launch_attention_pipe(4, Q, K, V, O, BH, N, d, scale, (int)N, stream);
     bool taken;
     if (d == 32) {
         if ((N % 256) == 0) return launch_attention_t<64, 1, false>(Q, K, V, O, BH, (int)N, scale, stream);

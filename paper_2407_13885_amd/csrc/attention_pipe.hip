@@ -1,4 +1,4 @@
-// Attention output  O = softmax(scale * Q K^T) V  in bf16 for d = 96 to 160 and more than 128 tokens, and for d = 64: the sweep of attention_wide.hip with
+// Attention output  O = softmax(scale * Q K^T) V  in bf16 for d = 96 to 160 and more than 128 tokens, and for d = 32 and 64: the sweep of attention_wide.hip with
 // the steps of neighbouring tiles under way at once.
 //
 // (Paper: Multi-Head Self-Attention section, Attention(Q, K, V) = softmax(Q K^T / sqrt(d_k)) V; Softmax section, Eq. 1, applied
@@ -137,7 +137,7 @@ void attention_pipe_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
 
     struct Scores { f32x4 s[2][2]; };             // keys 16 k + 4 quarter .. + 3, queries 16 x + l16
     struct Weights { u32x4 w[2]; };               // of a lane, as the operand of the second contraction
-    constexpr int KF = 2 * G, RV = 4;             // fragments of K of a tile; those of V held at a time
+    constexpr int KF = 2 * G, RV = G == 1 ? 2 : 4;   // fragments of K of a tile; those of V held at a time
     // (From one instruction to the next one operand stays: registers that change cost power.)
     auto scores = [&](int buf) __attribute__((always_inline)) {
         Scores r;
@@ -424,10 +424,18 @@ bool attention_pipe_64(int64_t BH, int64_t N)
     return N <= 1024 || (tail != 0 && (N <= 4096 || 100 * last <= 55 * 2 * cus));
 }
 
+// d = 32 (three times the vector work per product): ragged rows of 321 to 1024 tokens alone, from 0.6 of a round of workgroups of four on, 0.67 to 0.99 of the time in
+// 17 random shapes (285 heads of N = 340 20.1 -> 13.4 us, 119 of 704 23.2 -> 18.0); whole ones 0.86 to 1.2, longer ones 0.85 to 1.23.
+bool attention_pipe_32(int64_t BH, int64_t N)
+{
+    return N > 320 && N <= 1024 && N % 256 != 0 && 10 * BH * ((N + 127) / 128) > 6 * 2 * (int64_t)compute_units();
+}
+
 hipError_t launch_attention_pipe(int waves, const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d, float scale,
                                  int q_end, hipStream_t stream)
 {
     switch ((int)(d / 16)) {
+    case 2: return launch_pipe_t<1, false, 4>(Q, K, V, O, BH, (int)N, scale, q_end, stream);   // (attention_pipe_32)
     case 4: return launch_pipe_t<2, false, 4>(Q, K, V, O, BH, (int)N, scale, q_end, stream);   // (attention_pipe_64)
     case 6: return launch_pipe_d<3, false>(waves, Q, K, V, O, BH, (int)N, scale, q_end, stream);
     case 7: return launch_pipe_d<4, true>(waves, Q, K, V, O, BH, (int)N, scale, q_end, stream);

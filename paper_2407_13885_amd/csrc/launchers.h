@@ -122,9 +122,10 @@ hipError_t launch_attention_wide(const void* Q, const void* K, const void* V, vo
 
 // The same for d a multiple of 16 from 96 to 160 and N > 128, queries 0 .. q_end - 1 of every head, workgroups of four or eight waves: matrix and
 // vector work of neighbouring tiles under way at once.  attention_pipe_waves: of how many where it is the faster one, else 0.
-// attention_pipe_64: whether four waves there are the faster ones at d = 64 (workgroups of four only).
+// attention_pipe_64, attention_pipe_32: whether four waves there are the faster ones at d = 64, 32 (workgroups of four only).
 bool attention_pipe_supported(int64_t N, int64_t d);
 bool attention_pipe_64(int64_t BH, int64_t N);
+bool attention_pipe_32(int64_t BH, int64_t N);
 int attention_pipe_waves(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_attention_pipe(int waves, const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d, float scale,
                                  int q_end, hipStream_t stream);

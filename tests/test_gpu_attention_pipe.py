@@ -72,3 +72,25 @@ def test_scores_climb_d64(step):
     V = wl.value_inputs(x, seed=5251)
     O = gu.to_f64(_run(x, V))
     _check_rows(O[0, h], x, V, 0, h, [(0, 96), (N - 96, N)], f"{heads} heads of {N} x 64, step {step}")
+
+
+@pytest.mark.parametrize("heads,N", [(110, 321), (285, 340), (97, 399), (180, 385), (139, 517), (119, 704), (95, 813), (60, 1023), (60, 993)])
+def test_d32(heads, N):
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, 32, seed=5170 + N + heads)
+    V = wl.value_inputs(x, seed=5171 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads // 2, heads - 1):
+        _check_rows(O[0, h], x, V, 0, h, [(0, 33), (max(N - 40, 0), N)], f"{heads} heads of {N} x 32, head {h}")
+
+
+@pytest.mark.parametrize("step", [0.05, 0.7, 9.0, 200.0])
+def test_scores_climb_d32(step):
+    heads, N = 139, 517
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, 32, seed=5270)
+    h = heads - 1
+    climb = step / float(x.scale) * (np.arange(N) // 32)
+    x.Q[0, h, :, 31] = 0x3f80
+    x.K[0, h, :, 31] = (climb.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    V = wl.value_inputs(x, seed=5271)
+    O = gu.to_f64(_run(x, V))
+    _check_rows(O[0, h], x, V, 0, h, [(0, 96), (N - 96, N)], f"{heads} heads of {N} x 32, step {step}")
