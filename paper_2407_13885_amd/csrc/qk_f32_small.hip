@@ -6,7 +6,7 @@
 //
 // A workgroup owns 16 queries of a head, its eight waves blocks of 16 keys.  K comes straight from memory in the layout of the fp32 matrix instruction
 // (16 x 16 x 4: lane l has chunk l / 16 of 16 columns of row l % 16, instruction e of a group takes element e), all of a block requested at once; Q
-// through LDS (every wave for itself is 0.5 us more: the loads of a compute unit leave one after the other); one exchange of (exponent, sum); a lane
+// through LDS (every wave for itself is 0.5 us more: the loads of a compute unit leave one after the other); one exchange of (maximum, sum); a lane
 // stores runs of four keys.  Nothing is split into parts: of the some 400 instructions that a wave of qk_f32_strip.hip needs for a block, at 7 cycles
 // each where it has the SIMD for itself, 200 do that.  Scores are four sums (one for each element of a chunk), up to d = 48 eight, added at the end: error
 // against 64 bits 0.96 (d = 20) to 0.52 (256) of that of the strips; up to d = 16 it would be up to 1.1.
@@ -94,14 +94,17 @@ void qk_f32_small_kernel(const float* __restrict__ Q, const float* __restrict__ 
     }
     m = fmaxf(m, __shfl_xor(m, 16, 64));
     m = fmaxf(m, __shfl_xor(m, 32, 64));
-    const float e_wave = m * c;                   // (rounded: sums and factors refer to it alike)
+    // Exponents are products of differences: against fl(m c) the keys of a wave whose scores are all far below the others' (a mask through a column of K)
+    // weigh 2 to the rounding of that product, infinity from |m c| of 2^32 on, and infinity times 2^(m - the row's) is NaN in every weight of the row.
+    // (Halves: the difference of two scores may leave fp32's range.)
+    auto weight = [&](float x, float largest) __attribute__((always_inline)) { return fast_exp2(__builtin_fmaf(x, 0.5f, -0.5f * largest) * c * 2.0f); };
     float l = 0.0f;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         if (i >= nb) break;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            s[i][r] = fast_exp2(__builtin_fmaf(s[i][r], c, -e_wave));
+            s[i][r] = weight(s[i][r], m);
             if ((wave + NW * i) * 16 + 4 * quarter + r >= N) s[i][r] = 0.0f;
         }
         l += (s[i][0] + s[i][1]) + (s[i][2] + s[i][3]);
@@ -109,15 +112,15 @@ void qk_f32_small_kernel(const float* __restrict__ Q, const float* __restrict__ 
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     if (quarter == 0) {
-        stat_lds[wave * 32 + l16] = e_wave;
+        stat_lds[wave * 32 + l16] = m;
         stat_lds[wave * 32 + 16 + l16] = l;
     }
     __syncthreads();
     const int waves = min(NW, all_blocks);        // those with keys
-    float e_row = stat_lds[l16], l_row = 0.0f;
-    for (int w = 1; w < waves; ++w) e_row = fmaxf(e_row, stat_lds[w * 32 + l16]);
-    for (int w = 0; w < waves; ++w) l_row += stat_lds[w * 32 + 16 + l16] * fast_exp2(stat_lds[w * 32 + l16] - e_row);
-    const float f = fast_exp2(e_wave - e_row) * (1.0f / l_row);
+    float m_row = stat_lds[l16], l_row = 0.0f;
+    for (int w = 1; w < waves; ++w) m_row = fmaxf(m_row, stat_lds[w * 32 + l16]);
+    for (int w = 0; w < waves; ++w) l_row += stat_lds[w * 32 + 16 + l16] * weight(stat_lds[w * 32 + l16], m_row);
+    const float f = weight(m, m_row) * (1.0f / l_row);
 
     // ---- weights ----------------------------------------------------------------------------------------------------------------------------
     const int q = q0 + l16;

@@ -45,3 +45,31 @@ def test_not_finite(N, d):
         assert (np.isnan(P[0, h]) == np.isnan(ref)).all(), f"head {h}"
         ok = np.isfinite(ref)
         assert np.abs(P[0, h][ok] - ref[ok]).max() <= gu.ABS_F32, f"head {h}"
+
+
+def _masks(N):
+    """Whole blocks of 16 keys, and with them all keys of a wave: one block up to 128 tokens, two beyond."""
+    j = np.arange(N)
+    masks = {"last": j >= N - 1, "last block": j // 16 == (N - 1) // 16, "front": j < 16, "all but the first": j > 0, "all but the last": j < N - 1}
+    if N > 16:
+        masks["second block"] = j // 16 == 1
+    if N > 128:
+        masks["blocks of wave 3"] = j // 16 % 8 == 3
+    return masks
+
+
+# finite masks through one column of K: from the smallest whose rounded exponent alone is beyond fp32's range of exponentials to the largest
+@pytest.mark.parametrize("N,d", [(17, 64), (64, 20), (128, 64), (128, 32), (128, 128), (200, 256)])
+@pytest.mark.parametrize("scale", [None, 1.0, -1.0])
+def test_masked_blocks(N, d, scale):
+    scale = d ** -0.5 if scale is None else scale
+    x = wl.fused_inputs("t", "f32", 1, 1, N, d, seed=7800 + N + d, scale=scale)
+    if abs(scale) == 1.0:
+        x.Q[...] *= d ** -0.5
+    x.Q[..., d - 1] = 1.0
+    for name, mask in _masks(N).items():
+        for value in (-1e12, -1e20, -1e30, -3e38, -np.finfo(np.float32).max):
+            x.K[0, 0, :, d - 1] = np.where(mask, np.float32(value), np.float32(0.0)) * np.sign(scale)
+            P = gu.to_f64(gu.run_fused(x, guard=4096))
+            ref = oracle.attention_weights(x.Q[0, 0], x.K[0, 0], "f32", x.scale)
+            gu.check_weights(P[0, 0], ref, "f32", f"N={N} d={d} scale {scale}, {name} at {value:.1e}")
