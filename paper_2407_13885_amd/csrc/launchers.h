@@ -92,7 +92,7 @@ hipError_t launch_qk_f32_split(const void* Q, const void* K, void* P, int64_t BH
 hipError_t launch_qk_f32_strip(bool scores_only, const void* Q, const void* K, void* P, int64_t BH, int64_t N, int64_t d, float scale,
                                hipStream_t stream);
 
-// Fused attention weights, fp32, few heads of N up to 256, d a multiple of 4 from 20 to 256: workgroups of 16 queries, K straight from memory.
+// Fused attention weights, fp32, few heads of N up to 256 (d above 128: 192), d a multiple of 4 from 20 to 256: workgroups of 16 queries, K straight from memory.
 bool prefers_f32_small(int64_t BH, int64_t N, int64_t d);
 hipError_t launch_qk_f32_small(const void* Q, const void* K, void* P, int64_t BH, int64_t N, int64_t d, float scale, hipStream_t stream);
 

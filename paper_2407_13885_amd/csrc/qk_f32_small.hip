@@ -11,7 +11,7 @@
 // each where it has the SIMD for itself, 200 do that.  Scores are four sums (one for each element of a chunk), up to d = 48 eight, added at the end: error
 // against 64 bits 0.96 (d = 20) to 0.52 (256) of that of the strips; up to d = 16 it would be up to 1.1.
 // What bounds it: the launch, one way to memory and back, and the loads of a compute unit.  us, strips / here: one head of N = 128, d = 64 5.4 / 4.4, of 64 5.0 / 3.7,
-// of 100 6.2 / 4.1, of 128, d = 128 6.7 / 5.8, of 64, d = 256 9.0 / 5.9, 16 heads of 200, d = 64 7.7 / 6.1, 128 of 32 5.2 / 3.7.
+// of 100 6.2 / 4.0, of 128, d = 128 6.7 / 5.8, of 64, d = 256 9.0 / 5.9, one of 206, d = 64 7.3 / 6.2, 128 of 32 5.2 / 3.2.
 #include "launchers.h"
 #include "qk_common.h"
 
@@ -157,12 +157,12 @@ hipError_t launch_small_g(const void* Q, const void* K, void* P, int64_t BH, int
 
 }  // namespace
 
-// One workgroup to a compute unit, half of them where a wave has two blocks.  320 random shapes: 0.4 to 1.0 of the time within, median 0.93 where the
-// host's launches allow no more; beyond up to 1.3 (N <= 128) and 1.65 (N <= 256), as the fp32 instruction takes longer than the strips' bf16 parts; 257 to
-// 512 tokens 0.8 to 1.2.
+// One workgroup to a compute unit, half of them where a wave has two blocks.  560 random shapes: 0.4 to 1.0 of the time within; beyond up to 1.3 (N <= 128)
+// and 1.65 (N <= 256), as the fp32 instruction takes longer than the strips' bf16 parts; 257 to 512 tokens 0.8 to 1.2.  d above 128 up to 192 tokens only
+// (0.83 to 0.91 from 154 on): K of more leaves a compute unit too slowly, 193 to 256 tokens 0.93 to 1.1 (six heads of 247, d = 256 13.1 -> 14.5 us).
 bool prefers_f32_small(int64_t BH, int64_t N, int64_t d)
 {
-    return d > 16 && N <= 256 && BH * ((N + 15) / 16) <= (N <= 128 ? 2 : 1) * (int64_t)compute_units() / 2;
+    return d > 16 && N <= (d > 128 ? 192 : 256) && BH * ((N + 15) / 16) <= (N <= 128 ? 2 : 1) * (int64_t)compute_units() / 2;
 }
 
 hipError_t launch_qk_f32_small(const void* Q, const void* K, void* P, int64_t BH, int64_t N, int64_t d, float scale, hipStream_t stream)

@@ -19,7 +19,7 @@ def _gpu():
 
 
 @pytest.mark.parametrize("d", [20, 32, 36, 48, 52, 64, 100, 128, 132, 256])
-@pytest.mark.parametrize("heads,N", [(1, 1), (3, 2), (3, 15), (256, 16), (5, 17), (1, 63), (32, 128), (2, 127), (1, 129), (8, 256), (3, 250), (2, 145)])
+@pytest.mark.parametrize("heads,N", [(1, 1), (3, 2), (3, 15), (256, 16), (5, 17), (1, 63), (32, 128), (2, 127), (1, 129), (8, 256), (3, 250), (2, 145), (2, 192), (2, 193)])
 def test_weights(heads, N, d):
     scale = {"scale": -1.0 / math.sqrt(d)} if d in (36, 132) else {}
     x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=7600 + N + d, **scale)
