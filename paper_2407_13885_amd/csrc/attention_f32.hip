@@ -316,17 +316,15 @@ hipError_t launch_f32_ranges(const void* Q, const void* K, const void* V, void* 
     }
     // (d > 128: the K and V tiles of four ranges do not fit the LDS)
     constexpr int most = DVB <= 4 ? 4 : 2;
-    // The bf16 instruction on operands in three parts, whose strips of 256 queries keep all waves busy or not: d up to 32 from half busy on, up to 64 from 0.385,
-    // beyond from a quarter (rows of up to 96 tokens 0.31).  Random shapes, time there / on the fp32 instruction: more than half busy d up to 32 0.57 to 0.85, beyond
-    // 0.42 to 0.73 (28 heads of N = 4192, d = 68 1862 -> 776 us, 16 of 2084, d = 120 430 -> 214), 0.4 to 0.5 0.55 to 0.93, 0.25 to 0.4 and d > 64 0.73 to 0.98; below the
-    // lines up to 1.05 (d = 36 to 64), 1.36 (d up to 32) and 1.57 (a quarter).  (16 heads of N = 4096, d = 128: 998 -> 527, eight 591 -> 460.)
+    const int wk = key_ranges_f32(BH, N, most);
+    // No keys to share, and 256-query strips whose waves are more than half busy: the bf16 instruction on operands in three
+    // parts (16 heads of N = 4096, d = 128: 998 -> 527 us, eight, exactly half: 519 either way; 300 heads of N = 197, d = 64
+    // 52 -> 42; forty of 700, d = 32, 43 % busy: 31 -> 32).
     if constexpr (DVB <= 4) {
         const int64_t cus = compute_units(), rounds = (BH * ((N + 255) / 256) + cus - 1) / cus;
-        const int64_t busy = BH * ((N + 31) / 32), waves = rounds * cus * 8;
-        if ((DVB == 1 ? 2 * busy > waves : DVB == 2 ? 13 * busy > 5 * waves : 100 * busy > (N <= 96 ? 31 : 25) * waves) && split_takes_scale(scale))
+        if (wk == 1 && BH * ((N + 31) / 32) * 2 > rounds * cus * 8 && split_takes_scale(scale))
             return DVB == 1 ? launch_attention_f32_split(Q, K, V, O, BH, N, d, scale, stream) : launch_attention_f32_turns(Q, K, V, O, BH, N, d, scale, stream);
     }
-    const int wk = key_ranges_f32(BH, N, most);
     if constexpr (most == 4)
         if (wk == 4) {
             // One-block workgroups for less than half, a third or a quarter of the compute units: the others share the columns.  us, one head of

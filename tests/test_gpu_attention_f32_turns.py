@@ -3,6 +3,7 @@ unit: few tiles of 32 keys, ragged last tiles, waves without queries, scores tha
 import numpy as np
 import pytest
 
+import oracle
 from paper_2407_13885_amd import workloads as wl
 
 import gpu_util as gu
@@ -27,7 +28,7 @@ def test_tiles(N, d):
         _check(O[0, h], x, V, 0, h, (0, N), f"{heads} heads of {N} x {d}, head {h}")
 
 
-# on both sides of the lines that the share of busy waves draws: d up to 32 half, up to 64 0.385, beyond a quarter
+# on both sides of the line between this instruction and the fp32 one: more than half of the waves busy and no keys to share, or not
 @pytest.mark.parametrize("heads,N,d", [(27, 1187, 20), (26, 1187, 20), (130, 235, 32), (21, 1187, 40), (20, 1187, 64), (64, 257, 100), (56, 257, 100), (14, 1187, 128),
                                        (13, 1187, 68), (9, 2084, 96)])
 def test_few_strips(heads, N, d):
@@ -37,6 +38,26 @@ def test_few_strips(heads, N, d):
     for h in (0, heads - 1):
         for rows in ((0, 40), (max(0, N - 40), N)):
             _check(O[0, h], x, V, 0, h, rows, f"{heads} heads of {N} x {d}, head {h}")
+
+
+# Keys shared between waves make sums of a quarter of the terms, and every product of the fp32 instruction is whole: 2-norm error 3.7e-7, 4.3e-7 and 6.7e-7 (seven of
+# eight values zero: 2.4e-7, 3.0e-7, 3.8e-7) where operands in parts, one sum per output, have 5.6e-7, 5.6e-7 and 1.05e-6 (4.2e-7, 4.0e-7, 7.1e-7).  The bounds lie
+# between (geometric mean).
+@pytest.mark.parametrize("heads,N,d,dense,sparse", [(27, 1187, 20, 4.6e-7, 3.2e-7), (32, 1111, 56, 4.9e-7, 3.5e-7), (28, 4192, 68, 8.4e-7, 5.2e-7)])
+def test_shared_keys_keep_their_precision(heads, N, d, dense, sparse):
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5900 + N)
+    V = wl.value_inputs(x, seed=5901 + N)
+    for bound in (dense, sparse):
+        if bound == sparse:
+            V = V * (np.random.default_rng(N).random(V.shape) < 0.125).astype(np.float32)
+        O = gu.to_f64(_run(x, V))
+        off = size = 0.0
+        for h in (0, heads // 2, heads - 1):
+            for rows in ((0, 64), (N - 64, N)):
+                ref = oracle.attention_output(x.Q[0, h], x.K[0, h], V[0, h], "f32", x.scale, rows=rows)
+                off += np.square(O[0, h, rows[0]:rows[1]] - ref).sum()
+                size += np.square(ref).sum()
+        assert np.sqrt(off / size) <= bound, f"{heads} heads of {N} x {d}: {np.sqrt(off / size):.2e}"
 
 
 @pytest.mark.parametrize("N,d", [(161, 64), (250, 100), (200, 128)])
