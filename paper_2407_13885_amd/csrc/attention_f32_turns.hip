@@ -299,11 +299,12 @@ void attention_f32_turns_kernel(const float* __restrict__ Q, const float* __rest
     steps(n_tiles, IC<0>{}, IC<3 * CB>{});
 
     // ---- infinities, NaN and overflows (rare): what the parts make of them is not what fp32 does.  The wave starts again on
-    // the fp32 instruction, operands straight from memory ---------------------------------------------------------------------
+    // the fp32 instruction, operands straight from memory, as many bytes to a lane as the instruction's layouts allow (what bounds it are these
+    // loads) ------------------------------------------------------------------------------------------------------------------
     int k_most = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) k_most = max(k_most, k_large[w]);
-    float worst = (k_most == 0 ? q_huge : q_large) != 0 || k_most == 2 ? __builtin_inff() : l_run[0], down = kSplitDown;
+    float worst = (k_most == 0 ? q_huge : q_large) != 0 || k_most == 2 ? __builtin_inff() : l_run[0];
     worst = __builtin_fmaf(l_run[1], 0.0f, worst);
 #pragma unroll
     for (int b = 0; b < CB; ++b)
@@ -313,40 +314,67 @@ void attention_f32_turns_kernel(const float* __restrict__ Q, const float* __rest
             for (int r = 0; r < 4; ++r) worst = __builtin_fmaf(oacc[b][x][r], 0.0f, worst);   // NaN if any of them is not finite
     if (__builtin_amdgcn_ballot_w64(!(fabsf(worst) < __builtin_inff())) != 0) {
         reset();
-        down = 1.0f;
         for (int key0 = 0; key0 < N; key0 += 32) {
             zero_scores();
-            for (int col = quarter; col < d; col += 4) {
-                float a[2], b[2];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    a[i] = Kh[(int64_t)min(key0 + 16 * i + l16, N - 1) * d + col];
-                    b[i] = Qh[(int64_t)min(q0 + 16 * i + l16, N - 1) * d + col] * q_sign;
-                }
+            for (int g = 0; g < G; ++g) {         // 32 columns: of a lane chunks of four, element e of each to instruction e
+                f32x4 a[2][2], b[2][2];           // [half of them][keys, queries 16 i + l16]
 #pragma unroll
-                for (int k = 0; k < 2; ++k)
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int x = 0; x < 2; ++x) s[k][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], b[x], s[k][x], 0, 0, 0);
+                    for (int i = 0; i < 2; ++i) {
+                        const int col = g * 32 + h * 16 + quarter * 4;
+                        a[h][i] = *reinterpret_cast<const f32x4*>(Kh + (int64_t)min(key0 + 16 * i + l16, N - 1) * d + (col < d ? col : 0));
+                        b[h][i] = *reinterpret_cast<const f32x4*>(Qh + (int64_t)min(q0 + 16 * i + l16, N - 1) * d + (col < d ? col : 0));
+                        a[h][i] = col < d ? a[h][i] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                        b[h][i] = col < d ? b[h][i] * q_sign : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    }
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int k = 0; k < 2; ++k)
+#pragma unroll
+                            for (int x = 0; x < 2; ++x) s[k][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][k][e], b[h][x][e], s[k][x], 0, 0, 0);
             }
             weights(c, key0, key0 + 32 > N);
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
+            for (int r = 0; r < 8; ++r) {         // (columns 32 b + 2 l16, + 1 to the first and the second block of the 32)
                 const int key = key0 + 16 * (r / 4) + 4 * quarter + r % 4;
                 const float* vr = Vh + (int64_t)min(key, N - 1) * d;
 #pragma unroll
-                for (int b = 0; b < CB; ++b) {
-                    const float v = key < N ? vr[min(b * 16 + l16, d - 1)] : 0.0f;
+                for (int b = 0; b < DVB; ++b) {
+                    const f32x2 v = *reinterpret_cast<const f32x2*>(vr + min(b * 32 + 2 * l16, d - 2));
 #pragma unroll
-                    for (int x = 0; x < 2; ++x) oacc[b][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, p[x][r], oacc[b][x], 0, 0, 0);
+                    for (int e = 0; e < 2; ++e)
+#pragma unroll
+                        for (int x = 0; x < 2; ++x)
+                            oacc[2 * b + e][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(key < N ? v[e] : 0.0f, p[x][r], oacc[2 * b + e][x], 0, 0, 0);
                 }
             }
         }
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const float inv = 1.0f / quarter_wave_sum(l_run[x]);
+            const int q = q0 + 16 * x + l16;
+            float* const orow = Oh + (int64_t)q * d + quarter * 8;
+            if (q < N)
+#pragma unroll
+                for (int b = 0; b < DVB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; r += 2)
+                        if (b * 32 + quarter * 8 + 2 * r < d)
+                            *reinterpret_cast<f32x4*>(orow + b * 32 + 2 * r) =
+                                f32x4{oacc[2 * b][x][r], oacc[2 * b + 1][x][r], oacc[2 * b][x][r + 1], oacc[2 * b + 1][x][r + 1]} * inv;
+        }
+        return;
     }
 
     // ---- normalise and store: a lane owns runs of 4 consecutive output columns of its queries ----------------------
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-        const float inv = 1.0f / quarter_wave_sum(l_run[x]) * down;
+        const float inv = 1.0f / quarter_wave_sum(l_run[x]) * kSplitDown;
         const int q = q0 + 16 * x + l16;
         float* const orow = Oh + (int64_t)q * d + quarter * 4;
         if (q < N)

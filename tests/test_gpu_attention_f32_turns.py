@@ -99,3 +99,19 @@ def test_not_finite(N, d):
         size = np.abs(V[0, h][np.isfinite(V[0, h])]).max()
         # (weights and sums good to a few 2^-24 of sum_j P_ij |V_jt| <= the largest value; scores below 10)
         assert np.abs(O[0, h][ok] - ref[ok]).max() <= 2.0 ** -16 * size, f"head {h}"
+
+
+@pytest.mark.parametrize("N,d", [(161, 36), (129, 64), (200, 68), (250, 96), (161, 100), (257, 128)])
+def test_masked_tail(N, d):
+    """A mask through a column of K that operands in parts cannot hold: every wave starts again on the fp32 instruction."""
+    heads = 256
+    scale = {"scale": -1.0 / np.sqrt(d)} if d == 68 else {}
+    x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5950 + N + d, **scale)
+    V = wl.value_inputs(x, seed=5951)
+    x.Q[..., d - 1] = 1.0
+    x.K[..., d - 1] = np.where(np.arange(N) >= N - 40, np.float32(-1e20), np.float32(0.0)) * np.sign(x.scale)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads // 2, heads - 1):
+        ref = oracle.attention_output(x.Q[0, h], x.K[0, h], V[0, h], "f32", x.scale)
+        # (weights and sums good to a few 2^-24 of sum_j P_ij |V_jt| <= the largest value; scores of the keys left below 10)
+        assert np.abs(O[0, h] - ref).max() <= 2.0 ** -16 * np.abs(V[0, h]).max(), f"head {h}"
