@@ -157,9 +157,9 @@ void attention_f32_kernel(const float* __restrict__ Q, const float* __restrict__
             float tm = max3(s[0], s[1], s[2]);
 #pragma unroll
             for (int r = 3; r < 15; r += 2) tm = max3(tm, s[r], s[r + 1]);
-            const float mbn = half_wave_max(fmaxf(tm, s[15])) * c;   // (keys past the end are copies of key N-1: no new maximum)
-            if (__builtin_amdgcn_ballot_w64(mbn > mb_run + kLazy) != 0) {
-                const float mb_new = fmaxf(mb_run, mbn);
+            const float m = half_wave_max(fmaxf(tm, s[15]));   // (keys past the end are copies of key N-1: no new maximum)
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(m * c > mb_run + kLazy) != 0, 0)) {
+                const float mb_new = fmaxf(mb_run, reference_exponent(m, c));
                 const float alpha = fast_exp2(mb_run - mb_new);   // exactly 1 for lanes whose exponent stands
                 l_run *= alpha;
 #pragma unroll

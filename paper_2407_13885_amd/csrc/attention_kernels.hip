@@ -222,9 +222,9 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                 if constexpr (!SUMS) {
                     // (written out: the compiler schedules this form in 92 registers where it takes 100 with the lambdas of the other branch, 36 -> 33.7 us
                     // for 198 heads of N = 613, d = 32)
-                    const float mbn = half_wave_max(max16(s[qb])) * c;   // shared by the two lanes of a query
-                    if (__builtin_amdgcn_ballot_w64(mbn > mb_run[qb] + kLazy) != 0) {
-                        const float mb_new = fmaxf(mb_run[qb], mbn);
+                    const float m = half_wave_max(max16(s[qb]));   // shared by the two lanes of a query
+                    if (__builtin_expect(__builtin_amdgcn_ballot_w64(m * c > mb_run[qb] + kLazy) != 0, 0)) {
+                        const float mb_new = fmaxf(mb_run[qb], reference_exponent(m, c));
                         const float alpha = fast_exp2(mb_run[qb] - mb_new);
                         l_run[qb] *= alpha;
 #pragma unroll
@@ -267,7 +267,7 @@ void attention_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                             for (int r = 0; r < 16; ++r) oacc[qb][b][r] *= alpha;
                         mb_run[qb] = to;
                     };
-                    auto maximum = [&]() __attribute__((always_inline)) { return half_wave_max(max16(s[qb])) * c; };
+                    auto maximum = [&]() __attribute__((always_inline)) { return reference_exponent(half_wave_max(max16(s[qb])), c); };
                     auto total = [&]() __attribute__((always_inline)) {
                         float part[4] = {p[0], p[1], p[2], p[3]};
 #pragma unroll

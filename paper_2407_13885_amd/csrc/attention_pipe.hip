@@ -181,7 +181,7 @@ void attention_pipe_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
         if (__builtin_amdgcn_ballot_w64(fmaxf(__builtin_fmaf(top[0], c, -mb_run[0]), __builtin_fmaf(top[1], c, -mb_run[1])) > kLazy) == 0) return;
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
-            const float mb_new = fmaxf(mb_run[x], quarter_wave_max(top[x]) * c);
+            const float mb_new = fmaxf(mb_run[x], reference_exponent(quarter_wave_max(top[x]), c));
             const float alpha = fast_exp2(mb_run[x] - mb_new);       // exactly 1 for lanes whose exponent stands
             l_run[x] *= alpha;
 #pragma unroll
@@ -231,7 +231,7 @@ void attention_pipe_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
         float top[2];
 #pragma unroll
         for (int x = 0; x < 2; ++x) {             // the weights of tile 0
-            mb_run[x] = fmaxf(kNegBig, quarter_wave_max(largest(s, x)) * c);
+            mb_run[x] = fmaxf(kNegBig, reference_exponent(quarter_wave_max(largest(s, x)), c));
 #pragma unroll
             for (int r = 0; r < 8; ++r) p[x][r] = fast_exp2(__builtin_fmaf(s.s[r / 4][x][r % 4], c, -mb_run[x]));
             l_run[x] = p[x][0];

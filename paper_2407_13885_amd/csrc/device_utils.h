@@ -50,6 +50,15 @@ __device__ __forceinline__ float wave_reduce_sum(float v)
     return v;
 }
 
+// The exponent that weights exp2(s c - e) are taken against, m the largest of their scores s: m c, rounded.  A wave or a tile may have nothing but keys that a mask
+// through a column of K puts far below the others: the weights it makes of them are 2 to what the rounding left, from |m c| of 2^32 on
+// perhaps infinite, and infinity times the factor of 0 to the exponent of the others is NaN.  Where that is near, an exponent above all of them, which then weigh nothing.
+__device__ __forceinline__ float reference_exponent(float m, float c)
+{
+    const float e = m * c;
+    return __builtin_fmaf(m, c, -e) > 100.0f ? __builtin_fmaf(fabsf(e), 0x1p-20f, e) : e;   // (beyond the range: NaN, of which fmaxf with a sentinel leaves that)
+}
+
 // Blocks are dealt round-robin to the 8 XCDs (each with its own L2).  Remap the
 // hardware block index so that every XCD works on one contiguous range of
 // logical tiles (the same heads, hence the same K in its L2).  `padded` is the

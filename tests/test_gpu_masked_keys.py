@@ -1,0 +1,68 @@
+"""GPU parity where keys are masked through one column of K (that of Q is one): a leading tile, every other block, all but one key, with finite values down to the
+least of the type.  Reference exponents of masked keys alone are so large that their rounding exceeds fp32's range of exponentials."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2407_13885_amd as attnw
+from paper_2407_13885_amd import workloads as wl
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+VALUES = [-1e6, -1e9, -1e12, -3e15, -1e20, -3e38]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    gu.require_gpu()
+
+
+def _masks(N):
+    j = np.arange(N)
+    masks = {"front 16": j < 16, "front 32": j < 32, "front half": j < N // 2, "back half": j >= N // 2, "all but the first": j > 0, "all but the last": j < N - 1,
+             "every other 32": j // 32 % 2 == 0, "every eighth 32": j // 32 % 8 == 3, "three of four 32": j // 32 % 4 != 1, "runs of 4": j // 4 % 2 == 0}
+    return {name: m for name, m in masks.items() if m.any() and not m.all()}
+
+
+def _masked(dtype, heads, N, d, seed):
+    """Q, K on the device, the host's copies, and what sets the column of K for a mask."""
+    x = wl.fused_inputs("t", dtype, 1, heads, N, d, seed=seed)
+    one = np.float32(1.0) if dtype == "f32" else np.uint16(0x3f80)
+    x.Q[..., d - 1] = one
+    Q, K = gu.to_dev(x.Q, dtype), gu.to_dev(x.K, dtype)
+
+    def apply(mask, value):
+        column = np.where(mask, np.float32(value), np.float32(0.0)).astype(np.float32)
+        x.K[..., d - 1] = column if dtype == "f32" else (column.view(np.uint32) >> 16).astype(np.uint16)
+        K[..., d - 1] = gu.to_dev(np.ascontiguousarray(x.K[0, 0, :, d - 1]), dtype)
+    return x, Q, K, apply
+
+
+# one shape for each kernel behind attnw_attention
+@pytest.mark.parametrize("dtype,heads,N,d", [
+    ("bf16", 1, 64, 64), ("bf16", 500, 64, 64), ("bf16", 500, 200, 32), ("bf16", 400, 200, 64), ("bf16", 1, 1024, 64), ("bf16", 1, 2048, 128), ("bf16", 80, 512, 64),
+    ("bf16", 275, 576, 64), ("bf16", 45, 1343, 64), ("bf16", 64, 1280, 64), ("bf16", 285, 340, 32), ("bf16", 64, 1024, 32), ("bf16", 40, 600, 128), ("bf16", 100, 400, 96),
+    ("bf16", 400, 300, 80), ("bf16", 300, 100, 16), ("bf16", 64, 1024, 256), ("bf16", 32, 2000, 192), ("bf16", 300, 64, 192), ("bf16", 500, 30, 256),
+    ("f32", 1, 64, 64), ("f32", 500, 20, 64), ("f32", 500, 64, 128), ("f32", 1, 1024, 64), ("f32", 1, 1024, 256), ("f32", 300, 197, 64), ("f32", 256, 200, 128),
+    ("f32", 300, 197, 32), ("f32", 28, 1111, 68), ("f32", 500, 30, 256), ("f32", 100, 300, 256)])
+def test_attention(dtype, heads, N, d):
+    x, Q, K, apply = _masked(dtype, heads, N, d, seed=8100 + N + d)
+    V = wl.value_inputs(x, seed=8101)
+    Vd, O = gu.to_dev(V, dtype), torch.empty_like(Q)
+    for name, mask in _masks(N).items():
+        for value in VALUES:
+            apply(mask, value)
+            O.fill_(7.0)
+            attnw.attnw_attention(Q, K, Vd, O, 1, heads, N, d, float(x.scale), gu.DT[dtype])
+            for h, rows in ((0, (0, 4)), (heads - 1, (N - 4, N))):
+                ref, P = oracle.attention_output(x.Q[0, h], x.K[0, h], V[0, h], dtype, x.scale, rows=rows, return_weights=True)
+                got = gu.to_f64(O[0, h, rows[0]:rows[1]])
+                if dtype == "bf16":               # weights and output rounded once each
+                    A = P @ np.abs(wl.widen(V[0, h], dtype))
+                    tol = 2.0 ** -8 * (A + np.abs(ref)) * 1.02 + 1e-6 * A
+                else:                             # weights and sums good to a few 2^-24 of sum_j P_ij |V_jt| <= the largest value; scores of the keys left below 10
+                    tol = 2.0 ** -16 * np.abs(V[0, h]).max()
+                assert (np.abs(got - ref) <= tol).all(), f"{name} at {value:.0e}, head {h}: {np.abs(got - ref).max():.2e}"
