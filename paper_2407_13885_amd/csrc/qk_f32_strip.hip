@@ -290,7 +290,8 @@ void qk_f32_strip_kernel(const float* __restrict__ Q, const float* __restrict__ 
 #pragma unroll
         for (int r = 3; r < 15; r += 2) tm = max3(tm, s[r], s[r + 1]);
         m_run = fmaxf(m_run, fmaxf(tm, s[15]));                // (keys past the end are copies of key N - 1: no new maximum)
-        const float en = m_run * c;
+        // (In parts as it is: where the keys of a lane are all masked and the rounding makes their weights infinite, the strip starts again.)
+        const float en = decltype(partsc)::value != 0 ? m_run * c : fmaxf(e_run, reference_exponent(m_run, c));
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = fast_exp2(__builtin_fmaf(s[r], c, -en));
         if (key0 + 32 > N) {

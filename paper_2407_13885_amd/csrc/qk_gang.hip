@@ -411,7 +411,7 @@ void qk_gang_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
                     for (int x = 0; x < 16; x += 2) m = max3(m, X[t][x], X[t][x + 1]);
                 }
                 m = fmaxf(m, __shfl_xor(m, 32, 64));
-                mb = m * c;
+                mb = reference_exponent(m, c);
                 // ---- exponentials in place of the scores, local sum; the next strip's sweep rides along
                 constexpr int EPC = 16 * NT / NMMA;
                 constexpr int LEAD = 2;
@@ -455,6 +455,7 @@ void qk_gang_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__
                 for (int v = 0; v < NW; ++v) mw = fmaxf(mw, st[(0 * NW + v) * 32 + l32]);
 #pragma unroll
                 for (int v = 0; v < NW; ++v) lw += st[(1 * NW + v) * 32 + l32] * fast_exp2(st[(0 * NW + v) * 32 + l32] - mw);
+                lw = lw == 0.0f ? 0x1p-126f : lw; // (0 is a pair that has not come: keys that weigh nothing have this sum against their own exponent)
                 if (wave == 0 && half == 0)
                     store_slot(reinterpret_cast<uint64_t*>(out_h + table_off(i, r)) + l32, pack_pair(mw, lw));
             }

@@ -384,7 +384,7 @@ void qk_kernel(const T* __restrict__ Q, const T* __restrict__ K, T* __restrict__
             const float mn = fmaxf(m_run[qb], tm);
             l_run[qb] *= fast_exp2((m_run[qb] - mn) * c);
             m_run[qb] = mn;
-            const float mb = mn * c;
+            const float mb = reference_exponent(mn, c);   // (bf16)
             float sum = 0.0f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {

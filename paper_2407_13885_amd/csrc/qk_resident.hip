@@ -180,7 +180,7 @@ void qk_resident_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restri
         m = fmaxf(m, __shfl_xor(m, 32, 64));      // lanes l and l + 32 hold the two halves of a query's keys
 
         // ---- exponentials in place of the scores and their local sum; the next strip's sweep rides along ----
-        const float mb = m * c;
+        const float mb = reference_exponent(m, c);
         float l = 0.0f;
         constexpr int EPC = 16 * NT / NMMA;       // scores per chunk: one MFMA each
         if (ahead) {

@@ -276,7 +276,7 @@ void qk_rounds_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                         // the sum is kept relative to 2^mb with mb = fl(c * max): rescale by the difference of
                         // the ROUNDED exponents, which is exactly 0 while the maximum stands (a factor built
                         // from the unrounded product would drift the sum by an ulp per step, always the same way)
-                        mbl = m_run * c;
+                        mbl = fmaxf(mb_run, reference_exponent(m_run, c));
                         l_run *= fast_exp2(mb_run - mbl);
                         mb_run = mbl;
                     } else {

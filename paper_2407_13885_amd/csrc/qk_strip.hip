@@ -123,7 +123,7 @@ void qk_strip_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict_
             }
         }
         m = fmaxf(m, __shfl_xor(m, 32, 64));      // lanes l and l + 32 hold the two halves of a query's keys
-        const float mb = m * c;
+        const float mb = reference_exponent(m, c);
         float ls[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // four chains of additions instead of one
 #pragma unroll
         for (int t = 0; t < NT; ++t) {

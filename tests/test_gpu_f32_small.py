@@ -59,7 +59,7 @@ def _masks(N):
 
 
 # finite masks through one column of K: from the smallest whose rounded exponent alone is beyond fp32's range of exponentials to the largest
-@pytest.mark.parametrize("N,d", [(17, 64), (64, 20), (128, 64), (128, 32), (128, 128), (190, 256)])
+@pytest.mark.parametrize("N,d", [(17, 64), (64, 20), (128, 64), (128, 32), (128, 128), (190, 256), (200, 256)])
 @pytest.mark.parametrize("scale", [None, 1.0, -1.0])
 def test_masked_blocks(N, d, scale):
     scale = d ** -0.5 if scale is None else scale

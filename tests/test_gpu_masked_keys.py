@@ -66,3 +66,25 @@ def test_attention(dtype, heads, N, d):
                 else:                             # weights and sums good to a few 2^-24 of sum_j P_ij |V_jt| <= the largest value; scores of the keys left below 10
                     tol = 2.0 ** -16 * np.abs(V[0, h]).max()
                 assert (np.abs(got - ref) <= tol).all(), f"{name} at {value:.0e}, head {h}: {np.abs(got - ref).max():.2e}"
+
+
+# one shape for each kernel behind attnw_fused, by the dispatch or by name
+@pytest.mark.parametrize("dtype,heads,N,d,kernel", [
+    ("bf16", 300, 48, 16, "tiny"), ("bf16", 300, 200, 64, "heads"), ("bf16", 4, 197, 64, None), ("bf16", 8, 640, 80, None), ("bf16", 8, 640, 128, "strip"),
+    ("bf16", 16, 512, 64, None), ("bf16", 16, 1024, 64, None), ("bf16", 1, 2048, 64, "gang"), ("bf16", 2, 4096, 128, "gang"), ("bf16", 8, 1024, 128, "rounds"),
+    ("bf16", 8, 2048, 64, "rounds"), ("bf16", 2, 1024, 128, "twopass"), ("bf16", 40, 333, 64, "twopass"), ("bf16", 8, 1000, 64, "twopass"), ("bf16", 2, 1500, 256, "twopass"),
+    ("f32", 1, 128, 64, None), ("f32", 2, 200, 256, None), ("f32", 8, 512, 64, None), ("f32", 4, 1000, 100, None), ("f32", 1, 4096, 32, None), ("f32", 300, 128, 64, None),
+    ("f32", 600, 40, 16, None), ("f32", 2, 2304, 160, None)])
+def test_weights(monkeypatch, dtype, heads, N, d, kernel):
+    if kernel is not None:
+        monkeypatch.setenv("ATTNW_FUSED_KERNEL", kernel)
+    x, Q, K, apply = _masked(dtype, heads, N, d, seed=8200 + N + d)
+    P = torch.empty((1, heads, N, N), device="cuda", dtype=gu.TORCH_DT[dtype])
+    for name, mask in _masks(N).items():
+        for value in VALUES:
+            apply(mask, value)
+            P.fill_(7.0)
+            attnw.attnw_fused(Q, K, P, 1, heads, N, d, float(x.scale), gu.DT[dtype])
+            for h, rows in ((0, (0, 4)), (heads - 1, (N - 4, N))):
+                ref = oracle.attention_weights(x.Q[0, h], x.K[0, h], dtype, x.scale, rows=rows)
+                gu.check_weights(gu.to_f64(P[0, h, rows[0]:rows[1]]), ref, dtype, f"{name} at {value:.0e}, head {h}")
