@@ -329,11 +329,28 @@ void qk_stream_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
         float m = max3(acc[0], acc[1], acc[2]);
 #pragma unroll
         for (int r = 3; r < 15; r += 2) m = max3(m, acc[r], acc[r + 1]);
-        return fmaxf(fmaxf(m, acc[15]) * c, kNegBig);
+        return fmaxf(reference_exponent(fmaxf(m, acc[15]), c), kNegBig);
     };
-    // exponents of the block's weights against the reference; the first block sets it
-    auto arguments = [&](int key0) __attribute__((always_inline)) {
-        if (__builtin_amdgcn_ballot_w64(ref <= kNegBig) != 0) ref = ref <= kNegBig ? acc_max() : ref;
+    // the reference moves by m; rescale(a): the strip's exponentials so far take the factor a
+    // (in two factors: v_exp_f32 gives 0 below 2^-126, and these may be as large as 2^16)
+    auto lower = [&](float m, auto&& rescale) __attribute__((always_inline)) {
+        const float m1 = fminf(m, 64.0f);
+#pragma unroll 1
+        for (int i = 0; i < 2; ++i) {
+            const float a = fast_exp2(i == 0 ? -m1 : m1 - m);
+            l *= a;
+            rescale(a);
+        }
+    };
+    // Exponents of the block's weights against the reference; the first block sets it.  While it lies far below 0 it follows the maximum itself: exponents against
+    // that of masked keys (-1e9 through a column of K) keep too few bits to move it by them.
+    constexpr float kLow = -1024.0f;
+    auto arguments = [&](int key0, auto&& rescale) __attribute__((always_inline)) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(ref < kLow) != 0, 0)) {
+            const float to = ref < kLow ? fmaxf(ref, acc_max()) : ref;
+            if (__builtin_amdgcn_ballot_w64(to > ref) != 0) lower(to - ref, rescale);
+            ref = to;
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) arg[r] = __builtin_fmaf(acc[r], c, -ref);
         if (key0 + 32 > N) {                      // keys past N do not count
@@ -358,14 +375,7 @@ void qk_stream_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
             const float to = ref + fmaxf(m, 0.0f);
             m = to - ref;
             ref = to;
-            // (in two factors: v_exp_f32 gives 0 below 2^-126, and the weights before these may be as large as 2^16)
-            const float m1 = fminf(m, 64.0f);
-#pragma unroll 1
-            for (int i = 0; i < 2; ++i) {
-                const float a = fast_exp2(i == 0 ? -m1 : m1 - m);
-                l *= a;
-                rescale(a);
-            }
+            lower(m, rescale);
 #pragma unroll
             for (int r = 0; r < 16; ++r) arg[r] -= m;
             static_for<16>([&](auto rc) __attribute__((always_inline)) { weigh(e, rc); });
@@ -452,7 +462,7 @@ void qk_stream_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
             if (strip + 1 < s_end) bring_q(strip + 1);   // (behind a barrier that every wave reached after it took the last one)
             int wi = window(opaque(held));
             for (int j = 0; j < twice; ++j, wi = next_window(wi)) {
-                arguments((wi * kWaves + wave) * 32);
+                arguments((wi * kWaves + wave) * 32, [](float) __attribute__((always_inline)) {});
                 float e[16];
                 contract(spread(IC<16>{}, [&](auto ic) __attribute__((always_inline)) { weigh(e, ic); }));
                 count(e, [](float) __attribute__((always_inline)) {});
@@ -469,7 +479,13 @@ void qk_stream_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                 }
                 if (cur) {
                     if (twice == 0 && t + 1 == held && strip + 1 < s_end) take_q();
-                    arguments((wi * kWaves + wave) * 32);
+                    const auto rescale = [&](float a) __attribute__((always_inline)) {
+#pragma unroll
+                        for (int u = 0; u < t; ++u)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) X[u][r] *= a;
+                    };
+                    arguments((wi * kWaves + wave) * 32, rescale);
                     uint32_t pk[8];
                     contract(spread(IC<24>{}, [&](auto ic) __attribute__((always_inline)) {
                         constexpr int i = decltype(ic)::value;
@@ -481,12 +497,7 @@ void qk_stream_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict
                             weigh(X[t], IC<i - 8>{});
                         }
                     }));
-                    count(X[t], [&](float a) __attribute__((always_inline)) {
-#pragma unroll
-                        for (int u = 0; u < t; ++u)
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) X[u][r] *= a;
-                    });
+                    count(X[t], rescale);
                 } else {
                     flush_store();
 #pragma unroll
