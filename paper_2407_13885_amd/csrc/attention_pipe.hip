@@ -133,7 +133,7 @@ void attention_pipe_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
 #pragma unroll
         for (int x = 0; x < 2; ++x) oacc[b][x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     float mb_run[2], l_run[2];
-    constexpr float kLazy = 8.0f;                 // binades the maximum may run ahead of the reference exponent
+    constexpr float kLazy = 6.0f;                 // binades the maximum may run ahead of the reference exponent (8: sharp rows 3 % further off)
 
     struct Scores { f32x4 s[2][2]; };             // keys 16 k + 4 quarter .. + 3, queries 16 x + l16
     struct Weights { u32x4 w[2]; };               // of a lane, as the operand of the second contraction
@@ -176,11 +176,13 @@ void attention_pipe_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
         return fmaxf(max3(max3(max3(r.s[0][x][0], r.s[0][x][1], r.s[0][x][2]), r.s[0][x][3], r.s[1][x][0]), r.s[1][x][1], r.s[1][x][2]), r.s[1][x][3]);
     };
     // The exponents move where the largest score of some query is far above (some lane's own is if and only if its query's is); the weights p and
-    // all before them follow.
+    // all before them follow, of the 16 queries that it is among.
     auto follow = [&](const float (&top)[2]) __attribute__((always_inline)) {
-        if (__builtin_amdgcn_ballot_w64(fmaxf(__builtin_fmaf(top[0], c, -mb_run[0]), __builtin_fmaf(top[1], c, -mb_run[1])) > kLazy) == 0) return;
+        const float ahead[2] = {__builtin_fmaf(top[0], c, -mb_run[0]), __builtin_fmaf(top[1], c, -mb_run[1])};
+        if (__builtin_amdgcn_ballot_w64(fmaxf(ahead[0], ahead[1]) > kLazy) == 0) return;
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
+            if (__builtin_amdgcn_ballot_w64(ahead[x] > kLazy) == 0) continue;
             const float mb_new = fmaxf(mb_run[x], reference_exponent(quarter_wave_max(top[x]), c));
             const float alpha = fast_exp2(mb_run[x] - mb_new);       // exactly 1 for lanes whose exponent stands
             l_run[x] *= alpha;
@@ -227,21 +229,18 @@ void attention_pipe_kernel(const uint16_t* __restrict__ Q, const uint16_t* __res
     Scores s = scores(0), sn = scores(1);
     __syncthreads();
     request_pair(0);
-    {
-        float top[2];
+    // The weights of tile 0.  Their exponent is of the largest score of tiles 0 and 1: what a row's largest weight is taken against exactly is not rounded, and
+    // in sharp rows that is most of the error.
 #pragma unroll
-        for (int x = 0; x < 2; ++x) {             // the weights of tile 0
-            mb_run[x] = fmaxf(kNegBig, reference_exponent(quarter_wave_max(largest(s, x)), c));
+    for (int x = 0; x < 2; ++x) {
+        mb_run[x] = fmaxf(kNegBig, reference_exponent(quarter_wave_max(fmaxf(largest(s, x), largest(sn, x))), c));
 #pragma unroll
-            for (int r = 0; r < 8; ++r) p[x][r] = fast_exp2(__builtin_fmaf(s.s[r / 4][x][r % 4], c, -mb_run[x]));
-            l_run[x] = p[x][0];
+        for (int r = 0; r < 8; ++r) p[x][r] = fast_exp2(__builtin_fmaf(s.s[r / 4][x][r % 4], c, -mb_run[x]));
+        l_run[x] = p[x][0];
 #pragma unroll
-            for (int r = 1; r < 8; ++r) l_run[x] += p[x][r];
-            top[x] = largest(sn, x);
-        }
-        follow(top);
-        s = sn;
+        for (int r = 1; r < 8; ++r) l_run[x] += p[x][r];
     }
+    s = sn;
     u32x4 kf[KF], vf[RV];
 #pragma unroll
     for (int f = 0; f < KF; ++f) kf[f] = k_frag(2, f);
