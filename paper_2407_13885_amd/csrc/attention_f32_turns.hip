@@ -170,9 +170,11 @@ void attention_f32_turns_kernel(const float* __restrict__ Q, const float* __rest
 #pragma unroll
         for (int x = 0; x < 2; ++x)
             top[x] = fmaxf(max3(max3(max3(s[0][x][0], s[0][x][1], s[0][x][2]), s[0][x][3], s[1][x][0]), s[1][x][1], s[1][x][2]), s[1][x][3]);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(fmaxf(__builtin_fmaf(top[0], c, -mb_run[0]), __builtin_fmaf(top[1], c, -mb_run[1])) > kLazy) != 0, 0)) {
+        const float ahead[2] = {__builtin_fmaf(top[0], c, -mb_run[0]), __builtin_fmaf(top[1], c, -mb_run[1])};
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(fmaxf(ahead[0], ahead[1]) > kLazy) != 0, 0)) {
 #pragma unroll
             for (int x = 0; x < 2; ++x) {
+                if (__builtin_amdgcn_ballot_w64(ahead[x] > kLazy) == 0) continue;
                 const float mb_new = fmaxf(mb_run[x], reference_exponent(quarter_wave_max(top[x]), c));
                 const float alpha = fast_exp2(mb_run[x] - mb_new);       // exactly 1 for lanes whose exponent stands
                 l_run[x] *= alpha;

@@ -113,7 +113,7 @@ void attention_turns_kernel(const uint16_t* __restrict__ Q, const uint16_t* __re
 #pragma unroll
         for (int x = 0; x < 2; ++x) oacc[b][x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     float mb_run[2], l_run[2];
-    constexpr float kLazy = 8.0f;                 // binades the maximum may run ahead of the reference exponent
+    constexpr float kLazy = 7.0f;                 // binades the maximum may run ahead of the reference exponent
 
     // ---- the two halves of a tile's work ---------------------------------------------------------------------------------------
     f32x4 s[2][2];                                // scores of a tile: keys 16 k + 4 quarter .. + 3, queries 16 x + l16
@@ -162,9 +162,11 @@ void attention_turns_kernel(const uint16_t* __restrict__ Q, const uint16_t* __re
         for (int x = 0; x < 2; ++x) {
             top[x] = fmaxf(max3(max3(max3(s[0][x][0], s[0][x][1], s[0][x][2]), s[0][x][3], s[1][x][0]), s[1][x][1], s[1][x][2]), s[1][x][3]);
         }
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(fmaxf(__builtin_fmaf(top[0], c, -mb_run[0]), __builtin_fmaf(top[1], c, -mb_run[1])) > kLazy) != 0, 0)) {
+        const float ahead[2] = {__builtin_fmaf(top[0], c, -mb_run[0]), __builtin_fmaf(top[1], c, -mb_run[1])};
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(fmaxf(ahead[0], ahead[1]) > kLazy) != 0, 0)) {
 #pragma unroll
             for (int x = 0; x < 2; ++x) {
+                if (__builtin_amdgcn_ballot_w64(ahead[x] > kLazy) == 0) continue;
                 const float mb_new = fmaxf(mb_run[x], reference_exponent(quarter_wave_max(top[x]), c));
                 const float alpha = fast_exp2(mb_run[x] - mb_new);       // exactly 1 for lanes whose exponent stands
                 l_run[x] *= alpha;
@@ -298,10 +300,12 @@ hipError_t launch_turns_t(const void* Q, const void* K, const void* V, void* O, 
 // Whether the waves take turns for this shape.  A round of 256-query strips here takes 0.85 (d of 240 and 256) to 0.92 of one of the workgroups of four
 // waves in attention_wide.hip, two of which share a compute unit and whose rounds end in smaller steps; a last round of theirs with one to a
 // compute unit takes 0.7 of a full one.  Of 227 random shapes of 129 to 9000 tokens the rule takes 103: 0.865 to 1.06 of the time before, mean 0.93, six above
-// 1.015; the ones it leaves would take 0.9 to 1.58.  Up to 384 tokens (twelve tiles: the first and the last of a strip count) 0.98 to 1.2.
+// 1.015; the ones it leaves would take 0.9 to 1.58.  Up to 384 tokens (twelve tiles: the first and the last of a strip count) 0.98 to 1.2.  Where every row is of
+// another sharpness exponents move in more of the tiles, which costs the wave whose turn at the matrix unit comes after as well: 0.87 to 1.03 of the time before, d of
+// 176 and 192 up to 448 tokens 1.0 to 1.08 (others 0.94 to 0.99; left).
 bool prefers_attention_turns(int64_t BH, int64_t N, int64_t d)
 {
-    if (d < 176 || d > 256 || d % 16 != 0 || N <= 384) return false;
+    if (d < 176 || d > 256 || d % 16 != 0 || N <= (d <= 192 ? 448 : 384)) return false;
     const int64_t cus = compute_units(), fours = BH * ((N + 127) / 128), eights = BH * ((N + 255) / 256);
     const int64_t last = (fours + 2 * cus - 1) % (2 * cus) + 1;
     return (d >= 240 ? 0.85 : 0.92) * (double)((eights + cus - 1) / cus) <= (double)((fours - last) / (2 * cus)) + (last <= cus ? 0.71 : 1.0);
