@@ -867,7 +867,8 @@ hipError_t launch_softmax_t(const void* S, void* P, int64_t rows, int64_t cols, 
             // elements, us: rows of 1025 99.1 -> 94.4, 2049 103.4 -> 93.3, 4097 96.3 -> 92.0, 8193 104.6 -> 93.6, 16385 99 -> 91, 24569 0.68 of the time; fp32 0.85
             // to 1.0.  Not where the shape after it is as narrow: 1009 98.9 -> 106.6, 1601 96.6 -> 103.1, 4089 90.0 -> 93.6 (six or more below the whole chunks); 2570
             // 94.3 -> 101.1 (five chunks).
-            const auto holds = [&](int r, int tpr) { return cols + 5 >= (int64_t)r * E * tpr && cols <= (int64_t)(r * E + 1) * tpr; };
+            // (chunks counts two that rows share: five elements below in bf16 and three in fp32 are the first beyond the shape before)
+            const auto holds = [&](int r, int tpr) { return cols + (E == 8 ? 5 : 3) >= (int64_t)r * E * tpr && cols <= (int64_t)(r * E + 1) * tpr; };
             if (chunks <= 128) return launch_rows_shifted<TI, 2, 64>(S, P, rows, cols, stream);
             if (holds(2, 64)) return launch_rows_ends<TI, 2, 64>(S, P, rows, cols, stream);
             if (chunks <= 192) return launch_rows_shifted<TI, 3, 64>(S, P, rows, cols, stream);

@@ -1,5 +1,6 @@
 """Helpers for the GPU parity tests: host <-> device marshalling and the
 tolerances the attention-weight path is held to."""
+import ctypes
 import os
 
 import numpy as np
@@ -139,3 +140,40 @@ def large_scores(what: str, heads: int, N: int, d: int):
 
 
 LARGE_SCORES = ["straddling -2^80", "straddling -2^80, logits of -1000", "from -2^80 to 2^80", "all near -2^60"]
+
+
+class _KernelNode(ctypes.Structure):              # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p),
+                ("shared", ctypes.c_uint)]
+
+
+def kernels(call) -> list:
+    """Names of the kernels that ``call(stream)`` launches, in order, as mangled: recorded into a graph that is never run."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    stream, graph, count = torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_size_t()
+
+    def ok(status):
+        assert status == 0, f"HIP status {status}"
+    ok(hip.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 1))   # (of this thread's launches alone)
+    try:
+        call(stream)
+    finally:
+        ok(hip.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)))
+    ok(hip.hipGraphGetNodes(graph, None, ctypes.byref(count)))
+    nodes = (ctypes.c_void_p * count.value)()
+    ok(hip.hipGraphGetNodes(graph, nodes, ctypes.byref(count)))
+    names = []
+    for node in nodes:
+        params = _KernelNode()
+        ok(hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(params)))
+        names.append(hip.hipKernelNameRefByPtr(ctypes.c_void_p(params.func), None).decode())
+    ok(hip.hipGraphDestroy(graph))
+    return names
+
+
+def attention_kernels(dtype: str, heads: int, N: int, d: int) -> list:
+    """Which kernels attnw_attention launches for this shape, by what their names hold."""
+    x = torch.empty((1, heads, N, d), device="cuda", dtype=TORCH_DT[dtype])
+    o = torch.empty_like(x)
+    return kernels(lambda stream: attnw.attnw_attention(x, x, x, o, 1, heads, N, d, d ** -0.5, DT[dtype], stream))

@@ -21,6 +21,7 @@ def _gpu():
 @pytest.mark.parametrize("N", [129, 160, 161, 191, 193, 224, 256, 257])
 def test_tiles(N, d):
     heads = 256
+    assert "attention_f32_turns_kernel" in gu.attention_kernels("f32", heads, N, d)[0]
     x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5500 + N + d)
     V = wl.value_inputs(x, seed=5501 + N)
     O = gu.to_f64(_run(x, V))
@@ -45,6 +46,7 @@ def test_few_strips(heads, N, d):
 # between (geometric mean).
 @pytest.mark.parametrize("heads,N,d,dense,sparse", [(27, 1187, 20, 4.6e-7, 3.2e-7), (32, 1111, 56, 4.9e-7, 3.5e-7), (28, 4192, 68, 8.4e-7, 5.2e-7)])
 def test_shared_keys_keep_their_precision(heads, N, d, dense, sparse):
+    assert "attention_f32_kernel" in gu.attention_kernels("f32", heads, N, d)[0]
     x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5900 + N)
     V = wl.value_inputs(x, seed=5901 + N)
     for bound in (dense, sparse):
@@ -64,6 +66,7 @@ def test_shared_keys_keep_their_precision(heads, N, d, dense, sparse):
 @pytest.mark.parametrize("step", [0.7, 9.0, 200.0])
 def test_scores_climb(N, d, step):
     heads = 256
+    assert "attention_f32_turns_kernel" in gu.attention_kernels("f32", heads, N, d)[0]
     x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5600 + N + d)
     # the last column of K climbs every 32 keys, that of Q is one: the logits of a tile lie `step` above those of the last
     h = heads - 1
@@ -79,6 +82,7 @@ def test_scores_climb(N, d, step):
 def test_not_finite(N, d):
     """Infinities, NaN and values that bf16 rounds to infinity give what fp32 arithmetic gives."""
     heads = 256
+    assert "attention_f32_turns_kernel" in gu.attention_kernels("f32", heads, N, d)[0]
     x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5700 + N)
     V = wl.value_inputs(x, seed=5701)
     x.Q[0, 0, :, 0] = np.where(np.arange(N) % 2 == 0, 1.0, -1.0)
@@ -105,6 +109,7 @@ def test_not_finite(N, d):
 def test_masked_tail(N, d):
     """A mask through a column of K that operands in parts cannot hold: every wave starts again on the fp32 instruction."""
     heads = 256
+    assert "attention_f32_turns_kernel" in gu.attention_kernels("f32", heads, N, d)[0]
     scale = {"scale": -1.0 / np.sqrt(d)} if d == 68 else {}
     x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=5950 + N + d, **scale)
     V = wl.value_inputs(x, seed=5951)

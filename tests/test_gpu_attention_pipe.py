@@ -1,4 +1,4 @@
-"""GPU parity of attnw_attention (bf16, d = 96 to 160, more than 128 tokens) where the scores, weights and outputs of three neighbouring tiles of 32
+"""GPU parity of attnw_attention (bf16, d = 96 to 160, more than 128 tokens, and d = 32 and 64) where the scores, weights and outputs of three neighbouring tiles of 32
 keys are under way at once: five tiles and few more, rests of the ring of four and of the pairs of tiles, ragged last tiles, strips with waves
 without queries, scores that climb from tile to tile."""
 import numpy as np
@@ -25,11 +25,18 @@ def monkeypatch_module():
         yield m
 
 
-# 130 heads: workgroups of eight waves; 80 and 60: of four
+def _reached(heads, N, d, waves=None):
+    names = gu.attention_kernels("bf16", heads, N, d)
+    return any("attention_pipe_kernel" in n and (waves is None or f"Li{waves}EEEv" in n) for n in names)
+
+
+# 130 heads and more: workgroups of eight waves; 80 and 60: of four
 @pytest.mark.parametrize("d", [96, 112, 128, 144, 160])
-@pytest.mark.parametrize("heads,N", [(130, 129), (130, 160), (130, 161), (130, 192), (130, 193), (130, 225), (130, 256), (80, 257), (80, 288), (80, 320),
+@pytest.mark.parametrize("heads,N", [(130, 129), (130, 160), (200, 129), (200, 160), (130, 161), (130, 192), (130, 193), (130, 225), (130, 256), (80, 257), (80, 288), (80, 320),
                                      (60, 353), (16, 2050)])
 def test_tiles(heads, N, d):
+    # (of five tiles and d = 96 130 heads are few: their keys are shared between waves)
+    assert _reached(heads, N, d, 8 if heads >= 130 or heads == 16 else 4) == (not (d == 96 and heads == 130 and N <= 160))
     x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=5100 + N + heads)
     V = wl.value_inputs(x, seed=5101 + N)
     O = gu.to_f64(_run(x, V))
@@ -52,9 +59,37 @@ def test_scores_climb(heads, N, d, step):
     _check_rows(O[0, 0], x, V, 0, 0, [(0, 64)], f"{heads} heads of {N} x {d}, head 0")
 
 
+# a negative scale negates Q as it is loaded (of d = 112 and 144 the last group is half of a row's), one of 0 leaves weights of 1 / N
+@pytest.mark.parametrize("heads,N,d", [(130, 161, 112), (80, 257, 144), (130, 200, 128), (134, 512, 64), (285, 340, 32)])
+@pytest.mark.parametrize("scale", [-1.0, 0.0])
+def test_scales(heads, N, d, scale):
+    assert _reached(heads, N, d)
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=5160 + N + heads, scale=scale * d ** -0.5)
+    V = wl.value_inputs(x, seed=5161 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads - 1):
+        _check_rows(O[0, h], x, V, 0, h, [(0, 33), (max(N - 40, 0), N)], f"{heads} heads of {N} x {d}, scale {scale}, head {h}")
+
+
+# the strips of 256 queries where a head's last queries are a launch of their own
+@pytest.mark.parametrize("heads,N,d", [(240, 257, 96), (250, 320, 128), (250, 300, 112)])
+def test_own_last_strip(heads, N, d):
+    assert _reached(heads, N, d, 8) and len(gu.attention_kernels("bf16", heads, N, d)) == 2
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=5180 + N)
+    V = wl.value_inputs(x, seed=5181 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads - 1):
+        _check_rows(O[0, h], x, V, 0, h, [(0, 33), (230, N)], f"{heads} heads of {N} x {d}, head {h}")
+
+
 # one round and more of 256-query strips, on both sides of the lines: ragged ends, whole rows, waves without queries
-@pytest.mark.parametrize("heads,N", [(200, 321), (110, 352), (180, 385), (139, 517), (134, 512), (76, 1024), (46, 1331), (34, 1800), (30, 2177), (20, 3328), (15, 4416), (60, 1056), (60, 1057)])
+@pytest.mark.parametrize("heads,N", [(200, 321), (110, 352), (180, 385), (139, 517), (134, 512), (76, 1024), (46, 1331), (34, 1800), (30, 2177), (20, 3328), (15, 4416), (60, 1056), (60, 1057),
+                                     (51, 1056), (51, 1057), (54, 1200), (200, 320)])
 def test_d64(heads, N):
+    elsewhere = {(46, 1331), (34, 1800), (60, 1056), (60, 1057),   # few heads: their keys are shared between waves
+                 (15, 4416),                      # the last queries of a head in a launch of their own
+                 (51, 1057), (200, 320)}          # beyond the lines
+    assert _reached(heads, N, 64, 4) == ((heads, N) not in elsewhere)
     x = wl.fused_inputs("t", "bf16", 1, heads, N, 64, seed=5150 + N + heads)
     V = wl.value_inputs(x, seed=5151 + N)
     O = gu.to_f64(_run(x, V))
@@ -77,6 +112,7 @@ def test_scores_climb_d64(step):
 
 @pytest.mark.parametrize("heads,N", [(110, 321), (285, 340), (97, 399), (180, 385), (139, 517), (119, 704), (95, 813), (60, 1023), (60, 993)])
 def test_d32(heads, N):
+    assert _reached(heads, N, 32, 4)
     x = wl.fused_inputs("t", "bf16", 1, heads, N, 32, seed=5170 + N + heads)
     V = wl.value_inputs(x, seed=5171 + N)
     O = gu.to_f64(_run(x, V))

@@ -1,4 +1,4 @@
-"""GPU parity of attnw_attention (bf16, d = 176 to 256, more than 384 tokens) where the two waves of a SIMD take turns at the matrix unit: rests of the
+"""GPU parity of attnw_attention (bf16, d = 176 to 256, more than 384 tokens, d up to 192 more than 448) where the two waves of a SIMD take turns at the matrix unit: rests of the
 ring of four tiles, ragged last tiles, strips with waves without queries, a last strip that another kernel takes, scores that climb from tile to
 tile."""
 import numpy as np
@@ -19,13 +19,27 @@ def _gpu():
 
 # one full round of 256-query strips, (120, 520): 240 strips and eight queries of every head left over
 @pytest.mark.parametrize("d", [176, 192, 208, 224, 240, 256])
-@pytest.mark.parametrize("heads,N", [(128, 385), (128, 416), (128, 417), (128, 448), (128, 479), (128, 481), (128, 512), (120, 520), (16, 4066)])
+@pytest.mark.parametrize("heads,N", [(128, 385), (128, 416), (128, 417), (128, 448), (128, 449), (128, 479), (128, 481), (128, 512), (120, 520), (16, 4066)])
 def test_tiles(heads, N, d):
+    names = gu.attention_kernels("bf16", heads, N, d)
+    assert ("attention_turns_kernel" in names[0]) == (d > 192 or N > 448) and len(names) == (2 if heads == 120 else 1)
     x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=5300 + N + heads)
     V = wl.value_inputs(x, seed=5301 + N)
     O = gu.to_f64(_run(x, V))
     for h in (0, heads // 2, heads - 1):
         _check_rows(O[0, h], x, V, 0, h, [(0, 33), (max(N - 40, 0), N)], f"{heads} heads of {N} x {d}, head {h}")
+
+
+# rows of nine and ten tiles: the strips of 256 queries where a head's last ones are a launch of their own
+@pytest.mark.parametrize("heads,N,d", [(240, 257, 176), (250, 320, 208), (256, 288, 256)])
+def test_own_last_strip(heads, N, d):
+    names = gu.attention_kernels("bf16", heads, N, d)
+    assert "attention_turns_kernel" in names[0] and len(names) == 2
+    x = wl.fused_inputs("t", "bf16", 1, heads, N, d, seed=5350 + N)
+    V = wl.value_inputs(x, seed=5351 + N)
+    O = gu.to_f64(_run(x, V))
+    for h in (0, heads - 1):
+        _check_rows(O[0, h], x, V, 0, h, [(0, 33), (230, N)], f"{heads} heads of {N} x {d}, head {h}")
 
 
 @pytest.mark.parametrize("heads,N,d", [(128, 449, 176), (128, 500, 208), (120, 520, 240), (128, 400, 256)])

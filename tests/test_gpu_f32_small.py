@@ -4,8 +4,10 @@ import math
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
+import paper_2407_13885_amd as attnw
 from paper_2407_13885_amd import workloads as wl
 
 import gpu_util as gu
@@ -18,9 +20,17 @@ def _gpu():
     gu.require_gpu()
 
 
+def _kernel(heads, N, d):
+    Q = torch.empty((1, heads, N, d), device="cuda")
+    P = torch.empty((1, heads, N, N), device="cuda")
+    name, = gu.kernels(lambda stream: attnw.attnw_fused(Q, Q, P, 1, heads, N, d, d ** -0.5, attnw.ATTNW_F32, stream))
+    return name
+
+
 @pytest.mark.parametrize("d", [20, 32, 36, 48, 52, 64, 100, 128, 132, 256])
 @pytest.mark.parametrize("heads,N", [(1, 1), (3, 2), (3, 15), (256, 16), (5, 17), (1, 63), (32, 128), (2, 127), (1, 129), (8, 256), (3, 250), (2, 145), (2, 192), (2, 193)])
 def test_weights(heads, N, d):
+    assert ("qk_f32_small_kernel" in _kernel(heads, N, d)) == (d <= 128 or N <= 192)
     scale = {"scale": -1.0 / math.sqrt(d)} if d in (36, 132) else {}
     x = wl.fused_inputs("t", "f32", 1, heads, N, d, seed=7600 + N + d, **scale)
     P = gu.to_f64(gu.run_fused(x, guard=4096))
