@@ -18,23 +18,18 @@
 namespace attnw {
 namespace {
 
-// DVB: 32-column blocks of a row, ceil(d / 32); columns past d are zeros on chip.  Rows past N are read as row N - 1, weigh
-// nothing and are not stored.
-template <int DVB>
+// Columns past d are zeros on chip.  Rows past N are read as row N - 1, weigh nothing and are not stored.
 __global__ __launch_bounds__(512)
 void attention_f32_split_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
                                 float* __restrict__ O, int N, int d, float c, float q_sign, uint32_t strips, uint32_t total)
 {
-    using L = RowLayout<DVB>;
+    using L = RowLayout<1>;
     constexpr int NW = 8, BN = 32;
-    constexpr int DB = DVB * 64;                  // bytes of a row of a plane
-    constexpr int CPR = DVB * 4;                  // 16-byte chunks of it
+    constexpr int DB = 64;                        // bytes of a row of a plane: 32 columns
+    constexpr int CPR = 4;                        // 16-byte chunks of it
     constexpr int PLANE = BN * DB;
     constexpr int BUF_BYTES = 6 * PLANE;          // K hi, mid, lo, V hi, mid, lo
-    constexpr int G = DVB * 2;                    // 16-column contraction groups
-    constexpr int CHUNKS = BN * CPR;              // chunks of a plane: the first CHUNKS slots are K's, as many follow of V
-    constexpr int SLOTS = (2 * CHUNKS + NW * 64 - 1) / (NW * 64);
-    static_assert(CHUNKS % 64 == 0, "a wave's slots are of one tensor");
+    constexpr int G = 2;                          // 16-column contraction groups
 
     __shared__ __align__(1024) char lds[2 * BUF_BYTES];
     __shared__ int k_large[NW];                   // a wave has brought a |K| beyond kLarge, beyond kHuge (1, 2)
@@ -74,62 +69,39 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
     const uint64_t q_large = __builtin_amdgcn_ballot_w64(q_max > kLarge), q_huge = __builtin_amdgcn_ballot_w64(q_max > kHuge);
     uint64_t large = 0, huge = 0;                 // of K
 
-    // ---- tiles: slot s of a tile is chunk s of K or chunk s - CHUNKS of V --------------------------------------------------
-    static_assert(CHUNKS <= NW * 64, "all of K in the first slots");
-    Row8 reg[SLOTS];
+    // ---- tiles: waves 0 and 1 bring the 128 chunks of K, 2 and 3 those of V -------------------------------------------------
+    const bool v = wave >= 2;
+    const int at = (wave & 1) * 64 + lane, key = at / CPR, ch = at % CPR;
+    Row8 reg;
     auto load = [&](int t) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < SLOTS; ++j) {
-            const int w = wave + NW * j;          // (wave-uniform: which tensor, and whether there is such a slot)
-            if ((SLOTS * NW * 64 == 2 * CHUNKS || w * 64 < 2 * CHUNKS)) {
-                const bool v = w * 64 >= CHUNKS;
-                const int s = (v ? w * 64 - CHUNKS : w * 64) + lane;
-                const int key = s / CPR;
-                reg[j] = load_row8((v ? Vh : Kh) + (int64_t)min(t * BN + key, N - 1) * d, (s - key * CPR) * 8, d);
-            }
-        }
+        if (wave < 4) reg = load_row8((v ? Vh : Kh) + (int64_t)min(t * BN + key, N - 1) * d, ch * 8, d);
     };
     auto store = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < SLOTS; ++j) {
-            const int w = wave + NW * j;
-            if ((SLOTS * NW * 64 == 2 * CHUNKS || w * 64 < 2 * CHUNKS)) {
-                const bool v = w * 64 >= CHUNKS;
-                const int s = (v ? w * 64 - CHUNKS : w * 64) + lane;
-                const int key = s / CPR, ch = s - key * CPR;
-                if (j == 0) {
-                    const float k_max = largest(reg[j]);
-                    large |= __builtin_amdgcn_ballot_w64(k_max > kLarge);
-                    huge |= __builtin_amdgcn_ballot_w64(k_max > kHuge);
-                }
-                const Split8 x = split_row8(reg[j], ch * 8, d);
-                char* to = lds + buf * BUF_BYTES + (v ? 3 * PLANE : 0) + key * DB + (ch ^ (v ? L::v_block(key) * 4 : L::k_chunk(key))) * 16;
-                *reinterpret_cast<u32x4*>(to) = x.hi;
-                *reinterpret_cast<u32x4*>(to + PLANE) = x.mid;
-                *reinterpret_cast<u32x4*>(to + 2 * PLANE) = x.lo;
-            }
-        }
+        if (wave >= 4) return;
+        const float k_max = largest(reg);
+        large |= __builtin_amdgcn_ballot_w64(k_max > kLarge);
+        huge |= __builtin_amdgcn_ballot_w64(k_max > kHuge);
+        const Split8 x = split_row8(reg, ch * 8, d);
+        char* to = lds + buf * BUF_BYTES + (v ? 3 * PLANE : 0) + key * DB + (ch ^ (v ? L::v_block(key) * 4 : L::k_chunk(key))) * 16;
+        *reinterpret_cast<u32x4*>(to) = x.hi;
+        *reinterpret_cast<u32x4*>(to + PLANE) = x.mid;
+        *reinterpret_cast<u32x4*>(to + 2 * PLANE) = x.lo;
     };
 
     // ---- per-lane places of the operand fragments ------------------------------------------------------------------------
     const char* const krow = lds + l32 * DB;
-    constexpr int KPERIOD = L::KPERIOD, VPERIOD = L::VPERIOD;
-    int koff[KPERIOD];
+    int koff[G];
 #pragma unroll
-    for (int g = 0; g < KPERIOD; ++g) koff[g] = ((2 * g + half) ^ L::k_chunk(l32)) * 16;
+    for (int g = 0; g < G; ++g) koff[g] = ((2 * g + half) ^ L::k_chunk(l32)) * 16;
     const int vkey = 4 * half + ((lane & 15) >> 2);            // a lane's row of the 8-key group that it reads
     const char* const vrow = lds + 3 * PLANE + vkey * DB + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
-    int voff[VPERIOD];
-#pragma unroll
-    for (int b = 0; b < VPERIOD; ++b) voff[b] = (b ^ L::v_block(vkey)) * 64;
+    static_assert(L::KPERIOD == G && L::VPERIOD == 1, "rows of one block: those of V are not swizzled");
 
-    f32x16 oacc[DVB];
+    f32x16 oacc;
     float mb_run, l_run;
     auto reset = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int b = 0; b < DVB; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[b][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) oacc[r] = 0.0f;
         mb_run = kNegBig;
         l_run = 0.0f;
     };
@@ -146,9 +118,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
             const float alpha = fast_exp2(mb_run - mb_new);    // exactly 1 for lanes whose exponent stands
             l_run *= alpha;
 #pragma unroll
-            for (int b = 0; b < DVB; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[b][r] *= alpha;
+            for (int r = 0; r < 16; ++r) oacc[r] *= alpha;
             mb_run = mb_new;
         }
 #pragma unroll
@@ -170,7 +140,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
         for (int r = 0; r < 16; ++r) s[r] = 0.0f;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const char* k = krow + buf * BUF_BYTES + (g / KPERIOD) * KPERIOD * 32 + koff[g % KPERIOD];
+            const char* k = krow + buf * BUF_BYTES + koff[g];
             const Split8 kf = {*reinterpret_cast<const u32x4*>(k), *reinterpret_cast<const u32x4*>(k + PLANE),
                                *reinterpret_cast<const u32x4*>(k + 2 * PLANE)};
             mma_split(s, kf, qf[g]);
@@ -183,14 +153,10 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
 #pragma unroll
             for (int e = 0; e < 8; ++e) x[e] = p[8 * m + e] * kSplitUp;
             const Split8 pw = split8(x);          // a lane's weights of group m are its operand of the second contraction
-#pragma unroll
-            for (int b = 0; b < DVB; ++b) {
-                const char* v = vrow + buf * BUF_BYTES + 16 * m * DB + (b / VPERIOD) * VPERIOD * 64 + voff[b % VPERIOD];
-                const Split8 vf = {u32x4_of(lds_read_tr16(v), lds_read_tr16(v + 8 * DB)),
-                                   u32x4_of(lds_read_tr16(v + PLANE), lds_read_tr16(v + PLANE + 8 * DB)),
-                                   u32x4_of(lds_read_tr16(v + 2 * PLANE), lds_read_tr16(v + 2 * PLANE + 8 * DB))};
-                mma_split(oacc[b], vf, pw);
-            }
+            const char* v = vrow + buf * BUF_BYTES + 16 * m * DB;
+            const Split8 vf = {u32x4_of(lds_read_tr16(v), lds_read_tr16(v + 8 * DB)), u32x4_of(lds_read_tr16(v + PLANE), lds_read_tr16(v + PLANE + 8 * DB)),
+                               u32x4_of(lds_read_tr16(v + 2 * PLANE), lds_read_tr16(v + 2 * PLANE + 8 * DB))};
+            mma_split(oacc, vf, pw);
         }
     };
 
@@ -207,7 +173,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
             store(BUF ^ 1);
             if (t + 2 < n_tiles) load(t + 2);
         } else if (lane == 0) {
-            k_large[wave] = wave * 64 < CHUNKS ? (large != 0) + (huge != 0) : 0;   // (else its first slots are of V)
+            k_large[wave] = wave < 2 ? (large != 0) + (huge != 0) : 0;   // (else of V)
         }
         if (q0 < N) compute(t, BUF);              // (a wave without queries only moves tiles)
         __syncthreads();
@@ -221,9 +187,7 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
     for (int w = 0; w < NW; ++w) k_most = max(k_most, k_large[w]);
     float worst = (k_most == 0 ? q_huge : q_large) != 0 || k_most == 2 ? __builtin_inff() : l_run, down = kSplitDown;
 #pragma unroll
-    for (int b = 0; b < DVB; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) worst = __builtin_fmaf(oacc[b][r], 0.0f, worst);   // NaN if any of them is not finite
+    for (int r = 0; r < 16; ++r) worst = __builtin_fmaf(oacc[r], 0.0f, worst);   // NaN if any of them is not finite
     if (__builtin_amdgcn_ballot_w64(!(fabsf(worst) < __builtin_inff())) != 0) {
         reset();
         down = 1.0f;
@@ -243,12 +207,8 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int key = key0 + 4 * half + 8 * (r / 4) + (r % 4);
-                const float* vr = Vh + (int64_t)min(key, N - 1) * d;
-#pragma unroll
-                for (int b = 0; b < DVB; ++b) {
-                    const float v = vr[min(b * 32 + l32, d - 1)];
-                    oacc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(key < N ? v : 0.0f, p[r], oacc[b], 0, 0, 0);
-                }
+                const float v = Vh[(int64_t)min(key, N - 1) * d + min(l32, d - 1)];
+                oacc = __builtin_amdgcn_mfma_f32_32x32x2f32(key < N ? v : 0.0f, p[r], oacc, 0, 0, 0);
             }
         }
     }
@@ -258,26 +218,10 @@ void attention_f32_split_kernel(const float* __restrict__ Q, const float* __rest
     if (q0 + l32 >= N) return;
     float* const orow = Oh + (int64_t)(q0 + l32) * d + half * 4;
 #pragma unroll
-    for (int b = 0; b < DVB; ++b)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const f32x4 o = {oacc[b][4 * i], oacc[b][4 * i + 1], oacc[b][4 * i + 2], oacc[b][4 * i + 3]};
-            if (b * 32 + 8 * i + 4 * half < d) *reinterpret_cast<f32x4*>(orow + b * 32 + 8 * i) = o * inv;
-        }
-}
-
-template <int DVB>
-hipError_t launch_split_t(const void* Q, const void* K, const void* V, void* O, int64_t BH, int N, int d, float scale, hipStream_t stream)
-{
-    const uint32_t strips = (uint32_t)((N + 255) / 256);
-    return launch_by_heads(BH, strips, 512, [&](int64_t first, int64_t heads) {
-        const int64_t at = first * N * d;
-        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
-        hipLaunchKernelGGL((attention_f32_split_kernel<DVB>), dim3(grid), dim3(512), 0, stream, static_cast<const float*>(Q) + at,
-                           static_cast<const float*>(K) + at, static_cast<const float*>(V) + at, static_cast<float*>(O) + at, N, d,
-                           fabsf(scale) * kLog2e, scale < 0.0f ? -1.0f : 1.0f, strips, total);
-        return hipGetLastError();
-    });
+    for (int i = 0; i < 4; ++i) {
+        const f32x4 o = {oacc[4 * i], oacc[4 * i + 1], oacc[4 * i + 2], oacc[4 * i + 3]};
+        if (8 * i + 4 * half < d) *reinterpret_cast<f32x4*>(orow + 8 * i) = o * inv;
+    }
 }
 
 }  // namespace
@@ -285,7 +229,16 @@ hipError_t launch_split_t(const void* Q, const void* K, const void* V, void* O, 
 hipError_t launch_attention_f32_split(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d,
                                       float scale, hipStream_t stream)
 {
-    return d <= 32 ? launch_split_t<1>(Q, K, V, O, BH, (int)N, (int)d, scale, stream) : hipErrorInvalidValue;
+    if (d > 32) return hipErrorInvalidValue;
+    const uint32_t strips = (uint32_t)((N + 255) / 256);
+    return launch_by_heads(BH, strips, 512, [&](int64_t first, int64_t heads) {
+        const int64_t at = first * N * d;
+        const uint32_t total = (uint32_t)heads * strips, grid = (total + 7) / 8 * 8;
+        hipLaunchKernelGGL(attention_f32_split_kernel, dim3(grid), dim3(512), 0, stream, static_cast<const float*>(Q) + at,
+                           static_cast<const float*>(K) + at, static_cast<const float*>(V) + at, static_cast<float*>(O) + at, (int)N, (int)d,
+                           fabsf(scale) * kLog2e, scale < 0.0f ? -1.0f : 1.0f, strips, total);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace attnw

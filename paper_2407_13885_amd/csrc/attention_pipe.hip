@@ -23,14 +23,6 @@
 namespace attnw {
 namespace {
 
-// What computes x stands in front of this (the compiler moves it to its first use otherwise, out from under the matrix instructions).
-template <typename T> __device__ __forceinline__ void stays(T& x)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" : "+v"(x));
-#endif
-}
-
 // DVB: 32-column blocks of a row, ceil(d / 32).  HALF: d is an odd multiple of 16 -- the last 16 columns on chip are zeros in Q and K
 // (written once: no transfer touches them) and left out of the second contraction.  WQ: waves of a workgroup, 32
 // queries each.  At least five tiles of 32 keys.  Rows past N are read as row N - 1, weigh nothing and are not stored.
