@@ -8,14 +8,14 @@
 // of tile t - 1 and the scores of tile t + 1: one matrix instruction, then its share of the exponentials, sums, packs and maxima, so that neither unit
 // waits for the other.  A wave alone issues a vector instruction every 7.6 cycles (two waves 3.8): what stands one after the other in a wave is slow even where
 // the SIMD's other wave fills the gaps, and with the scores, the softmax and the output of one tile after the other (attention_wide.hip) matrix and
-// vector unit worked at the same time in 13 % of the cycles; here in 22 %.
+// vector unit worked at the same time in 13 % of the cycles; here in 24 %.
 //
 // Matrix instructions of 16 x 16 x 32 (mma16): less power per product than 32 x 32 x 16, and these kernels run at the board's power cap.  (They take more issue
 // slots, 8 cycles of the vector unit's each: with twice the vector work per product, at d = 64, the 32 x 32 shape is as fast, and this kernel the faster one only where its
 // smaller steps count, attention_pipe_64.)
 //
 // K and V travel global -> LDS directly into rings of four tiles, one barrier for two tiles (one for each: 3 % slower); fragments of K are read a tile ahead.
-// 16 heads of N = 4096: d = 96 107 -> 99 us, 128 131.5 -> 118.7 (1.16 PFLOP/s), 144 159 -> 142, 160 166 -> 144; 8 of 4000, d = 128 91 -> 68.5;
+// 16 heads of N = 4096: d = 96 107 -> 99 us, 128 131.5 -> 117 (1.17 PFLOP/s), 144 159 -> 142, 160 166 -> 144; 8 of 4000, d = 128 91 -> 68.5;
 // two of 32768 980 -> 876 (1.25 PFLOP/s); 40 of 600 18.7 -> 15.6.  Wider heads have no registers for the scores of two tiles.
 #include "launchers.h"
 #include "attention_common.h"
@@ -397,30 +397,33 @@ int attention_pipe_waves(int64_t BH, int64_t N, int64_t d)
 }
 
 // d = 64: workgroups of four waves against attention_kernel's 256 or 512 queries.  The work of a tile takes as long here, but the rounds end in smaller steps,
-// and a ragged end costs a tile of 32 keys instead of one of 128.  So (time here / there): more than one round of 256-query strips 0.58 to 1.0; where the
-// second round of those of four is more than half full and beyond 1024 tokens, and beyond 4096 tokens from the third on with the last more than 0.55 full, 1.0
-// to 1.1 (left); one round of ragged rows 0.76 to 0.99, of whole ones up to 1.07 (left).  Whole rows of more rounds up to 1.06 beyond 1024 tokens (left).  A last
-// strip of up to 64 queries that follows as a launch of its own there: 1.07 to 1.16 beyond 1024 tokens (left).  us: 275 heads of N = 576 65.9 -> 38.4, 331 of 672
-// 76.7 -> 53.0, 134 of 512 0.83 of the time.  (900 random shapes of 161 to 12000 tokens: taken 0.86 on average; few heads stay with attention_ranges.hip, whose
-// waves have references of their own: sharp rows 1.8e-3 off, here 2.0e-3.)
+// and a ragged end costs a tile of 32 keys instead of one of 128.  So (time here / there; fewer workgroups than half of a round are attention_ranges'
+// before this is asked; 323 shapes on both sides of the lines):
+//   one round of 256-query strips: ragged rows up to 1056 tokens 0.76 to 0.93, from 1100 on, where the first tiles no longer count, 0.995 to 1.04; whole rows
+//     up to 1.07;
+//   up to one round of those of four, the strips of 256 queries in a second: 0.72 to 0.93;
+//   the second round of those of four at most half full, where two rounds here are as many strips as one there: 0.77 to 0.88; whole rows 0.84 to 1.01, from 8192 on
+//     0.97 to 1.03 (left); more than half full: ragged rows up to 1024 tokens 0.7 to 0.93, longer ones 0.91 to 1.09 (left);
+//   three rounds and more: ragged rows 0.75 to 0.99, beyond 4096 tokens with the last round more than 0.55 full 0.98 to 1.0 (left); whole ones up to 1.06 beyond 1024
+//     tokens (left).
+// A last strip of up to 64 queries that follows as a launch of its own there: 1.07 to 1.16 beyond 1024 tokens (left).  us: 275 heads of N = 576 65.9 -> 38.4, 331 of 672
+// 76.7 -> 53.0, 134 of 512 0.83 of the time.  (Few heads stay with attention_ranges.hip also because of its waves' references of their own: sharp rows 1.8e-3
+// off, here 1.9e-3 to 2.0e-3.)
 bool attention_pipe_64(int64_t BH, int64_t N)
 {
     const int64_t cus = compute_units(), fours = BH * ((N + 127) / 128), eights = BH * ((N + 255) / 256), last = (fours + 2 * cus - 1) % (2 * cus) + 1;
     const int64_t full = N / 256, tail = N % 256;
     if (N <= 320) return false;
-    if (eights <= cus) return tail != 0 && 1000 * fours > 405 * 2 * cus && (fours <= cus || (N <= 1056 && 10 * fours > 11 * cus));
+    if (eights <= cus) return tail != 0 && N <= 1056;
     if (fours <= 2 * cus) return true;
     if (N > 1024 && tail >= 1 && tail <= 64 && (BH * full + cus - 1) / cus < (eights + cus - 1) / cus) return false;
     if (fours <= 4 * cus) return tail == 0 ? last <= cus && N < 8192 : N <= 1024 || last <= cus;
     return N <= 1024 || (tail != 0 && (N <= 4096 || 100 * last <= 55 * 2 * cus));
 }
 
-// d = 32 (three times the vector work per product): ragged rows of 321 to 1024 tokens alone, from 0.6 of a round of workgroups of four on, 0.67 to 0.99 of the time in
-// 17 random shapes (285 heads of N = 340 20.1 -> 13.4 us, 119 of 704 23.2 -> 18.0); whole ones 0.86 to 1.2, longer ones 0.85 to 1.23.
-bool attention_pipe_32(int64_t BH, int64_t N)
-{
-    return N > 320 && N <= 1024 && N % 256 != 0 && 10 * BH * ((N + 127) / 128) > 6 * 2 * (int64_t)compute_units();
-}
+// d = 32 (three times the vector work per product): ragged rows of 321 to 1024 tokens alone, 0.64 (285 heads of N = 340 20.1 -> 13.0 us) to 0.94, of 1000 tokens 1.0 to
+// 1.02; from 1100 on 1.06 to 1.23, whole rows 0.86 to 1.2.
+bool attention_pipe_32(int64_t, int64_t N) { return N > 320 && N <= 1024 && N % 256 != 0; }
 
 hipError_t launch_attention_pipe(int waves, const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d, float scale,
                                  int q_end, hipStream_t stream)

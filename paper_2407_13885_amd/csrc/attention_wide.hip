@@ -231,6 +231,9 @@ hipError_t launch_wide(const void* Q, const void* K, const void* V, void* O, int
     // a full strip: it follows as a launch of the kernel for few heads (16 heads of N = 4097, d = 128: 209 -> 170 us).  (From d = 80 only where
     // the full strips are nine tenths of one round or more: 19 heads of N = 3360, d = 256 350 -> 237 us; workgroups of four waves take the
     // others as they are, 2 to 30 % faster over 2000 random shapes, at d = 144 and 160 those too, 14 %.)
+    // (The full strips go to attention_turns.hip and attention_pipe.hip here whatever their own rules say: those weigh them against four waves that would take the tail
+    // too.  231 to 256 heads of 257 to 320 tokens 0.90 to 0.99 of the time on eight waves here at d of 176 and more, at 96 to 128 0.99 to 1.015; 64 to 128 heads of 513 to
+    // 1088 tokens 0.89 to 0.95.)
     const bool one_round = DVB != 5 && BH * full <= cus && 10 * BH * full > 9 * cus;
     if (full >= 1 && tail_rows >= 1 && tail_rows <= 64 && (BH * full + cus - 1) / cus < eights && (DVB <= 2 || one_round)) {
         constexpr int d = DVB * 32 - (HALF ? 16 : 0);
