@@ -304,7 +304,7 @@ def bench_fused(cfg, steps, warmup, with_unfused=True, with_attention=True, samp
         rec["attention_output"] = {
             "call": "attnw_attention", "ms_per_step": round(wall_a, 5), "kernel_ms": round(ev_a, 5),
             "steps": k_a, "warmup": w_a, "mfma_TFLOPs": round(tf, 1),
-            "roofline": {"bound": "mfma", "kernel": "attention_kernel" if x.d in (32, 64) else "attention_wide_kernel", "achieved": round(tf, 1),
+            "roofline": {"bound": "mfma", "kernel": "attention_kernel" if x.d in (32, 64) else "attention_pipe_kernel", "achieved": round(tf, 1),
                          "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4)},
             "elements_per_s": x.elements / (wall_a * 1e-3),
         }

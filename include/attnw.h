@@ -19,7 +19,7 @@
  *     arithmetic between load and store is fp32, but for contractions in parts:
  *     bf16 inputs are multiplied on the matrix cores with fp32 accumulation; most fp32
  *     calls (attnw_fused at any number of heads and head size unless rows are
- *     short and heads small; attnw_gemm_scores with d above 32, but for few
+ *     short and heads small, or rows short and heads few; attnw_gemm_scores with d above 32, but for few
  *     long or short odd rows, and many with d of 8 to 32; attnw_attention with d <= 128 and enough
  *     heads) go to the bf16 matrix instruction too, operands as three bf16 parts
  *     each, which hold all 24 bits of every fp32 number, six of the nine
@@ -48,7 +48,11 @@
  *     count of 0: returns ATTNW_OK, launches nothing, pointers not looked at),
  *     null pointers, size overflow, supported sizes, 16-byte alignment of each
  *     base pointer, overlap of output with inputs.
- *   - Inputs must be finite.  A NaN poisons its own row only.
+ *   - Inputs must be finite.  A NaN poisons its own row only.  Keys may be masked
+ *     through a column of K (that of Q one, their scores down to the least finite
+ *     number): they weigh nothing, wherever they stand; a row all of whose scores
+ *     times log2(e) lie below about -2^31 has no weights to speak of (NaN, or what the rounding
+ *     of such numbers leaves).
  *   - The library keeps no mutable global state apart from a per-device cache
  *     of the compute-unit count and, per kernel for short sequences, of the
  *     number of its workgroups that a compute unit holds (queried once, at the

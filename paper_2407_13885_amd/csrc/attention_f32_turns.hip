@@ -7,11 +7,11 @@
 // A tile of 32 keys is two phases of a wave with a barrier after each: the output of the tile before and the scores of this one (192 matrix
 // instructions of 16 cycles at d = 128), then the weights and their parts, and the wave's share of a coming tile of K and V, split into LDS
 // (some 400 vector instructions).  Waves 4 to 7, the other wave of each SIMD, are one phase behind waves 0 to 3.  With one after the other in all
-// waves at once the matrix unit was busy 63 % and both units 8 % of the SIMD cycles; here 82 and 28 %.
+// waves at once the matrix unit was busy 63 % and both units 8 % of the SIMD cycles; here 82 and 27 %.
 //
 // What bounds it: the board's power (order of the phases, depth of the fragment ring and priority change the time by less than 1 %; the same code with all
 // waves in step is 10 % slower).  Hence mma16, and the operand from LDS stays for two to six instructions.  16 heads of N = 4096, all waves in step on 32 x 32
-// x 16 / here: d = 64 322 / 287 us, 96 462 / 407, 128 622 / 527 (1.56 PFLOP/s of bf16 products); error against 64 bits 1.06e-6 / 1.05e-6.  Random
+// x 16 / here: d = 64 320 / 284 us, 96 458 / 397, 128 612 / 508 (1.62 PFLOP/s of bf16 products); error against 64 bits 1.06e-6 / 1.05e-6.  Random
 // shapes of d = 36 to 128: 52 of 195 come here, 0.82 to 0.965 of the time.  Up to d = 32 the weights are most of the work: 0.98 on long rows, 1.1 on short ones,
 // and attention_f32_split.hip stays.
 #include "attention_common.h"

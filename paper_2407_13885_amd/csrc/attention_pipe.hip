@@ -15,8 +15,8 @@
 // smaller steps count, attention_pipe_64.)
 //
 // K and V travel global -> LDS directly into rings of four tiles, one barrier for two tiles (one for each: 3 % slower); fragments of K are read a tile ahead.
-// 16 heads of N = 4096: d = 96 107 -> 99 us, 128 131.5 -> 117 (1.17 PFLOP/s), 144 159 -> 142, 160 166 -> 144; 8 of 4000, d = 128 91 -> 68.5;
-// two of 32768 980 -> 876 (1.25 PFLOP/s); 40 of 600 18.7 -> 15.6.  Wider heads have no registers for the scores of two tiles.
+// 16 heads of N = 4096: d = 96 105 -> 96 us, 128 129 -> 115.5 (1.19 PFLOP/s), 144 154 -> 134, 160 161 -> 140; 8 of 4000, d = 128 91 -> 67;
+// two of 32768 965 -> 861 (1.28 PFLOP/s); 40 of 600 18.5 -> 15.1.  Wider heads have no registers for the scores of two tiles.
 #include "launchers.h"
 #include "attention_common.h"
 

@@ -10,11 +10,11 @@
 // waves 0 to 3, so that one multiplies while the other makes its weights.  In step (both in the same phase) the same code takes 221 us where it takes
 // 207.5 (16 heads of N = 4096, d = 256); without the matrix phase's priority 212.
 //
-// What bounds it: the matrix phase under the board's power cap (matrix unit busy 69 % of SIMD cycles, both units 24 %, waves waiting 18 %; attention_wide.hip
+// What bounds it: the matrix phase under the board's power cap (matrix unit busy 68 % of SIMD cycles, both units 23 %, waves waiting 19 %; attention_wide.hip
 // 59, 8 and 52 %).  Its fragments come from LDS four instruction pairs ahead (six ahead: 2 % slower at d = 176, spilled at 256).  mma16 for less power per
 // product, as in attention_pipe.hip.  Below d = 176 a vector phase is longer than a matrix phase (a wave alone issues a vector instruction every 7.6
 // cycles) and attention_pipe.hip is the faster one (d = 128 116.6 / 122.7 us, 160 146.9 / 147.9).
-// 16 heads of N = 4096, attention_wide.hip / here: d = 176 177 / 158 us, 192 184 / 167, 240 231 / 203, 256 238 / 207.5 (1.32 PFLOP/s).
+// 16 heads of N = 4096, attention_wide.hip / here: d = 176 172 / 153 us, 192 179 / 161, 240 225 / 197, 256 232 / 204 (1.35 PFLOP/s).
 #include "launchers.h"
 #include "attention_common.h"
 

@@ -37,8 +37,8 @@ template <> struct Mma<float> {
 
 // The same contraction in blocks of 16 x 16: 32 elements of the contraction per instruction, lane l carries chunk l / 16 (8 elements) of
 // row l % 16 of either operand and accumulator r is element (4 (l / 16) + r, l % 16).  Half the accumulator traffic per product of the
-// 32 x 32 shape: under the board's power cap normal operands run at 2.07 instead of 1.76 PFLOP/s (both sustained for 0.1 s, one wave after
-// the other changing one operand only; changing both 1.95 and 1.73).
+// 32 x 32 shape: under the board's power cap normal operands run at 2.09 instead of 1.82 PFLOP/s (both sustained for 0.1 s, from one instruction to the
+// next changing one operand only; changing both 2.02 and 1.80; zeros 2.46 either way).
 __device__ __forceinline__ void mma16(f32x4& acc, const u32x4& a, const u32x4& b)
 {
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
