@@ -373,11 +373,11 @@ bool attention_pipe_supported(int64_t N, int64_t d) { return d >= 96 && d <= 160
 
 // Waves of a workgroup for this shape, 0 where attention_wide_kernel is the faster one.  That one takes 120 to 170 registers: with workgroups of four
 // waves three or four of them share a SIMD, which hides as much as the order here does, and one workgroup's first and last tiles hide under another's
-// middle.  So it keeps (time here / there) d = 80 (1.0 to 1.14), d = 96 from the second round of 256-query strips on (1.02 to 1.16), short rows of few
-// heads (up to 1.1), and of more rounds those of up to 384, 512, then 1024 tokens at d = 128 (1.02 to
-// 1.16), of up to 1024, then 1536 at the others (1.02 to 1.07).  A second round that is less than half
+// middle.  So it keeps (time here / there, rows alike; rows of every sharpness 0.01 to 0.05 more) d = 80 (1.0 to 1.14), d = 96 from the second round of 256-query strips on
+// (1.02 to 1.16), d = 112 from the third (1.0 to 1.07), short rows of few heads (up to 1.1), and of more rounds those of up to 256, 512, 768, then 1024 tokens at d = 128
+// (0.99 to 1.16), of up to 1024, then 1536 at 144 and 160 (1.02 to 1.07).  A second round that is less than half
 // full is the faster one there too (1.05 to 1.15; d = 128 0.93 to 0.98).  One round: d = 96 0.93 to 0.98, 112 0.92 to 0.97, 128 0.86 to 0.97, 144 0.82 to
-// 0.95, 160 0.78 to 0.92; more rounds of long rows 0.90 to 0.98.  (4200 random shapes of 129 to 12000 tokens.)
+// 0.95, 160 0.78 to 0.92; more rounds of long rows 0.90 to 0.99.  (6700 random shapes of 129 to 12000 tokens.)
 int attention_pipe_waves(int64_t BH, int64_t N, int64_t d)
 {
     if (!attention_pipe_supported(N, d)) return 0;
@@ -386,9 +386,9 @@ int attention_pipe_waves(int64_t BH, int64_t N, int64_t d)
     bool take;
     if (rounds == 1) take = N > 352 || 2 * fours > cus;
     else if (d == 96) take = false;
-    else if (d == 128) take = rounds == 2 || N > (rounds == 3 ? 384 : rounds <= 6 ? 512 : 1024);
+    else if (d == 128) take = N > (rounds == 2 ? 256 : rounds == 3 ? 512 : rounds <= 6 ? 768 : 1024);
     else if (rounds == 2) take = last > cus;
-    else take = N > (rounds == 3 ? 1024 : 1536) && rounds <= 12;
+    else take = d != 112 && N > (rounds == 3 ? 1024 : 1536) && rounds <= 12;
     if (!take) return 0;
     // Workgroups of four, two to a compute unit, move K and V twice as often: three hundredths more time a round; a last round of one to a
     // compute unit takes two thirds of that.

@@ -297,18 +297,19 @@ hipError_t launch_turns_t(const void* Q, const void* K, const void* V, void* O, 
 
 }  // namespace
 
-// Whether the waves take turns for this shape.  A round of 256-query strips here takes 0.85 (d of 240 and 256) to 0.92 of one of the workgroups of four
-// waves in attention_wide.hip, two of which share a compute unit and whose rounds end in smaller steps; a last round of theirs with one to a
-// compute unit takes 0.7 of a full one.  Of 227 random shapes of 129 to 9000 tokens the rule takes 103: 0.865 to 1.06 of the time before, mean 0.93, six above
-// 1.015; the ones it leaves would take 0.9 to 1.58.  Up to 384 tokens (twelve tiles: the first and the last of a strip count) 0.98 to 1.2.  Where every row is of
-// another sharpness exponents move in more of the tiles, which costs the wave whose turn at the matrix unit comes after as well: 0.87 to 1.03 of the time before, d of
-// 176 and 192 up to 448 tokens 1.0 to 1.08 (others 0.94 to 0.99; left).
+// Whether the waves take turns for this shape.  A round of 256-query strips here against one of the workgroups of four waves in attention_wide.hip, two of which share
+// a compute unit and whose rounds end in smaller steps; a last round of theirs with one to a compute unit takes 0.7 of a full one.  What a round takes here (theirs is 1):
+// rows alike 0.85 (d of 240 and 256) to 0.94, of 512 tokens and fewer 0.01 to 0.05 more (the first and the last of twelve to sixteen tiles count), rows of every
+// sharpness 0.02 to 0.07 more (exponents move in more of the tiles, and the wave whose turn at the matrix unit comes after waits), d = 192 0.02 more than its neighbours, whose
+// rows have zeros to multiply there and here.  The lines leave what is then the slower one for rows of both kinds together: of 2100 random shapes of 385 to 3500 tokens those
+// taken are rows alike 0.91 (d of 240 and 256) to 0.94 of the time, 1.012 at most, of every sharpness 0.94 to 0.99, 30 of 445 above 1.04 (to 1.09).
 bool prefers_attention_turns(int64_t BH, int64_t N, int64_t d)
 {
-    if (d < 176 || d > 256 || d % 16 != 0 || N <= (d <= 192 ? 448 : 384)) return false;
+    if (d < 176 || d > 256 || d % 16 != 0 || N <= 384) return false;
     const int64_t cus = compute_units(), fours = BH * ((N + 127) / 128), eights = BH * ((N + 255) / 256);
     const int64_t last = (fours + 2 * cus - 1) % (2 * cus) + 1;
-    return (d >= 240 ? 0.85 : 0.92) * (double)((eights + cus - 1) / cus) <= (double)((fours - last) / (2 * cus)) + (last <= cus ? 0.71 : 1.0);
+    const double round = d >= 240 ? (N > 512 ? 0.85 : 0.88) : d == 192 ? 0.94 + 48.0 / (double)N : 0.917 + 38.0 / (double)N;
+    return round * (double)((eights + cus - 1) / cus) <= (double)((fours - last) / (2 * cus)) + (last <= cus ? 0.71 : 1.0);
 }
 
 hipError_t launch_attention_turns(const void* Q, const void* K, const void* V, void* O, int64_t BH, int64_t N, int64_t d, float scale,
