@@ -358,9 +358,12 @@ void qk_kernel(const T* __restrict__ Q, const T* __restrict__ K, T* __restrict__
         }
     };
 
+    // bf16: no exponent is taken against less than about -2^31.  A lane's keys may all be masked through a column of K, and the rounding of their own exponent alone would make their
+    // weights infinite (reference_exponent, which two to four more instructions per block would be: 1.04 of the time at d above 128).
+    const float least = ES == 2 ? fmaxf(-0x1p31f * __builtin_amdgcn_rcpf(c), kNegBig) : kNegBig;
     float m_run[QB], l_run[QB], bias[QB];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) { m_run[qb] = kNegBig; l_run[qb] = 0.0f; bias[qb] = 0.0f; }
+    for (int qb = 0; qb < QB; ++qb) { m_run[qb] = least; l_run[qb] = 0.0f; bias[qb] = 0.0f; }
 
     // pass one on the scores of one 32-key sub-tile: running maximum and sum of
     // exponentials (Eq. 1), kept per lane; kbase = first key of this lane's first run
@@ -384,7 +387,7 @@ void qk_kernel(const T* __restrict__ Q, const T* __restrict__ K, T* __restrict__
             const float mn = fmaxf(m_run[qb], tm);
             l_run[qb] *= fast_exp2((m_run[qb] - mn) * c);
             m_run[qb] = mn;
-            const float mb = reference_exponent(mn, c);   // (bf16)
+            const float mb = mn * c;
             float sum = 0.0f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
