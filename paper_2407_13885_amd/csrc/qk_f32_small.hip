@@ -159,10 +159,12 @@ hipError_t launch_small_g(const void* Q, const void* K, void* P, int64_t BH, int
 
 // One workgroup to a compute unit, half of them where a wave has two blocks.  560 random shapes: 0.4 to 1.0 of the time within; beyond up to 1.3 (N <= 128)
 // and 1.65 (N <= 256), as the fp32 instruction takes longer than the strips' bf16 parts; 257 to 512 tokens 0.8 to 1.2.  d above 128 up to 192 tokens only
-// (0.83 to 0.91 from 154 on): K of more leaves a compute unit too slowly, 193 to 256 tokens 0.93 to 1.1 (six heads of 247, d = 256 13.1 -> 14.5 us).
+// (0.83 to 0.91 from 154 on): K of more leaves a compute unit too slowly, 193 to 256 tokens 0.93 to 1.1 (six heads of 247, d = 256 13.1 -> 14.5 us); of those d of 97 to
+// 128 but 224 and 256, whole blocks for the strips (1.02 and 1.06; others 0.9 to 0.97).
 bool prefers_f32_small(int64_t BH, int64_t N, int64_t d)
 {
-    return d > 16 && N <= (d > 128 ? 192 : 256) && BH * ((N + 15) / 16) <= (N <= 128 ? 2 : 1) * (int64_t)compute_units() / 2;
+    if (d <= 16 || N > 256 || (N > 192 && (d > 128 || (d > 96 && N % 32 == 0)))) return false;
+    return BH * ((N + 15) / 16) <= (N <= 128 ? 2 : 1) * (int64_t)compute_units() / 2;
 }
 
 hipError_t launch_qk_f32_small(const void* Q, const void* K, void* P, int64_t BH, int64_t N, int64_t d, float scale, hipStream_t stream)
