@@ -300,8 +300,8 @@ hipError_t launch_turns_t(const void* Q, const void* K, const void* V, void* O, 
 // Whether the waves take turns for this shape.  A round of 256-query strips here against one of the workgroups of four waves in attention_wide.hip, two of which share
 // a compute unit and whose rounds end in smaller steps; a last round of theirs with one to a compute unit takes 0.7 of a full one.  What a round takes here (theirs is 1):
 // rows alike 0.85 (d of 240 and 256) to 0.94, of 512 tokens and fewer 0.01 to 0.05 more (the first and the last of twelve to sixteen tiles count), rows of every
-// sharpness 0.02 to 0.07 more (exponents move in more of the tiles, and the wave whose turn at the matrix unit comes after waits), d = 192 0.02 more than its neighbours, whose
-// rows have zeros to multiply there and here.  The lines leave what is then the slower one for rows of both kinds together: of 2100 random shapes of 385 to 3500 tokens those
+// sharpness 0.02 to 0.07 more (exponents move in more of the tiles, and the wave whose turn at the matrix unit comes after waits), d = 192 0.02 more than its neighbours
+// (measured, the reason is not known).  The lines leave what is then the slower one for rows of both kinds together: of 2100 random shapes of 385 to 3500 tokens those
 // taken are rows alike 0.91 (d of 240 and 256) to 0.94 of the time, 1.012 at most, of every sharpness 0.94 to 0.99, 30 of 445 above 1.04 (to 1.09).
 bool prefers_attention_turns(int64_t BH, int64_t N, int64_t d)
 {
